@@ -636,6 +636,13 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
                 }
             }
         };
+        // The weights' cache policy (2 = non-temporal).  Below 33 rows per expert every weight byte is used by one
+        // tile and never again, and a non-temporal stream gets 6.3 TB/s out of HBM where the plain one gets 5.7 (64
+        // tokens over 128 experts of 2048 -> 8192: layer 0.986 -> 0.898 ms, e4m3 0.536 -> 0.496; 4099 tokens over 512
+        // experts of 1024 -> 4096, the popular ones with several tiles: 1.645 -> 1.612).  Taller tiles belong to
+        // experts with several of them, which share the weights through the caches: 64-row tiles of 4-bit weights over
+        // 256 rows per expert 0.402 -> 0.412 with it.
+        constexpr int B_CPOL = GROUPED && BM <= 32 ? 2 : 0;
         auto issue = [&](int kt, int buf) {
 #pragma unroll
             for (int i = 0; i < A_IT; ++i)
@@ -644,7 +651,7 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
 #pragma unroll
             for (int i = 0; i < B_IT; ++i)
                 __builtin_amdgcn_global_load_lds((const glb_void *)(b_base + (b_off[i] + kt * (BQ != 0 ? 512 : BK))),
-                                                 (lds_void *)(sB + buf * BTILE + (wave * B_IT + i) * 8 * BK), 16, 0, 0);
+                                                 (lds_void *)(sB + buf * BTILE + (wave * B_IT + i) * 8 * BK), 16, 0, B_CPOL);
         };
         // The loads run STAGES-1 K tiles ahead of the MFMAs along the block's whole sequence of
         // (tile, K tile) pairs, so the pipeline never drains between tiles and an epilogue's stores
