@@ -53,75 +53,15 @@
 // one: the pipeline never drains between tiles and the epilogue's stores overlap the next tile.
 #include <mutex>
 
+#include "gemm_bf16_dev.h"
 #include "moe_internal.h"
 
 namespace moe355 {
-
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
-// Types for reading operand fragments out of LDS.  The compiler orders an LDS read that carries type-based
-// alias information after EVERY direct-to-LDS load in flight (s_waitcnt vmcnt(0) in front of the read), which
-// drains the load pipeline once per K tile; reads through vector types and may_alias types carry none, and
-// the explicit vmcnt before each stage barrier is what orders them.
-typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
-typedef uint32_t __attribute__((may_alias)) u32_lds;
-typedef uint16_t __attribute__((may_alias)) u16_lds;
-typedef __attribute__((ext_vector_type(16))) float f32x16;
-typedef __attribute__((address_space(3))) void lds_void;
-typedef __attribute__((address_space(1))) void glb_void;
-
-// One 32-bit word at an address that is the same for every lane of the wave, through the scalar data path
-// (read only).  The compiler issues such loads as vector loads here (it cannot prove that the kernel's own
-// stores leave the tile map alone), and a vector load's result can only be waited for together with every
-// vector load issued before it -- at a tile switch that drains the whole operand pipeline.  The scalar path
-// has its own counter.  The words read were written by an earlier kernel.
-__device__ __forceinline__ int32_t uniform_load(const int32_t *ptr)
-{
-    int32_t v;
-    asm volatile("s_load_dword %0, %1, 0x0\n\ts_waitcnt lgkmcnt(0)" : "=s"(v) : "s"(ptr) : "memory");
-    return v;
-}
-// two independent words with one wait
-__device__ __forceinline__ void uniform_load2(const int32_t *pa, const int32_t *pb, int32_t &a, int32_t &b)
-{
-    asm volatile("s_load_dword %0, %2, 0x0\n\ts_load_dword %1, %3, 0x0\n\ts_waitcnt lgkmcnt(0)"
-                 : "=&s"(a), "=&s"(b)
-                 : "s"(pa), "s"(pb)
-                 : "memory");
-}
 
 static constexpr int BK = 64;
 static constexpr int GROUP_M = 4;
 static constexpr int REG_STAGED = 0;  // value of the STAGES template argument that selects the register-staged pipeline
 static constexpr int DTL16 = -1;      // ... and the one that selects 16x16x32 MFMAs out of a ring of K-step slots filled by direct-to-LDS loads
-typedef __attribute__((ext_vector_type(4))) float f32x4;
-
-__device__ __forceinline__ uint32_t to_bf16(float f)
-{
-    uint32_t u = __float_as_uint(f);
-    u += 0x7fffu + ((u >> 16) & 1u);
-    return u >> 16;
-}
-__device__ __forceinline__ float from_bf16(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
-// two fp32 -> packed bf16, round to nearest even (one v_cvt_pk_bf16_f32)
-typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
-typedef __attribute__((ext_vector_type(2))) float f32x2;
-__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi)
-{
-    const f32x2 v = {lo, hi};
-    const bf16x2 b = __builtin_convertvector(v, bf16x2);
-    return *reinterpret_cast<const uint32_t *>(&b);
-}
-
-// max(x, 0) on two packed bf16: a bf16 is negative exactly when its bit pattern is negative as a 16-bit integer,
-// so one packed integer max replaces two fp32 compares (and the canonicalisation the compiler puts in front of
-// them); rounding is monotonic and keeps zero, so ReLU after the conversion equals ReLU before it.
-typedef __attribute__((ext_vector_type(2))) short i16x2;
-__device__ __forceinline__ uint32_t relu_bf16x2(uint32_t packed)
-{
-    const i16x2 zero = {0, 0};
-    const i16x2 r = __builtin_elementwise_max(*reinterpret_cast<const i16x2 *>(&packed), zero);
-    return *reinterpret_cast<const uint32_t *>(&r);
-}
 
 struct TileInfo {
     int row0, row_end, expert, n0;
@@ -1339,6 +1279,8 @@ int gemm_bf16_variant(int64_t n_rows, int E, int N, int num_cus)
     return 3;
 }
 
+int launch_gemm_stream(const GemmParams &p, int wbits, bool relu, int num_cus, hipStream_t s, bool *taken);
+
 template <int BM, int BN, int WM, int WN, int MINB, int STAGES = 2>
 static int launch_grouped(const GemmParams &p, bool relu, int num_cus, hipStream_t s, int *main_grid = nullptr)
 {
@@ -1374,6 +1316,11 @@ int launch_gemm_bf16(const GemmParams &p, bool grouped, int variant, bool out_f3
     if (out_f32) {
         set_error("grouped bf16 GEMM is only instantiated for bf16 output");
         return MOE_ERR_UNSUPPORTED;
+    }
+    if (variant == 3 || variant == 23 || variant == 43) {
+        bool taken = false;
+        const int rc = launch_gemm_stream(p, variant == 23 ? 8 : variant == 43 ? 4 : 0, relu, num_cus, s, &taken);
+        if (taken || rc != MOE_OK) return rc;
     }
     switch (variant) {
     case 8: {

@@ -357,6 +357,7 @@ static int run_expert_ffn(moe_handle_t *h, const void *xp, const FfnExtra &ex, c
     GemmParams p;
     memset(&p, 0, sizeof(p));
     p.offsets = offsets;
+    p.n_experts = c.E;
     p.tile_expert = tile_expert;
     p.tile_row = tile_row;
     p.num_tiles = num_tiles;

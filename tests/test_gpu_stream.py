@@ -1,0 +1,65 @@
+"""The weight-streaming expert GEMM (a few rows per expert) against the fp64 oracle: row counts at the edges of its 16-
+and 32-row tiles, idle experts, the cuts of K it is instantiated for, and every storage of the weights."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import moe_oracle as orc
+from oracle import quant_e4m3 as o8
+from oracle import quant_mxfp4 as o4
+from paper_2303_06182_amd import binding, workloads as wl
+from helpers import TOL, norm_max_err, to_np, worst_row_rms_rel_err
+
+pytestmark = pytest.mark.gpu
+
+EDGES = [1, 15, 0, 16, 17, 31, 0, 32, 33, 48]
+SPARSE = [1, 0, 3, 17, 0, 2, 16, 1] * 4 + [33, 0, 1, 1]
+CASES = [
+    # counts, D, F, bias
+    (EDGES, 512, 1024, True),       # few tiles: eight and four waves share K
+    ([1], 2048, 1024, False),       # the smallest call
+    ([2, 0, 1], 1024, 4096, True),
+    (EDGES, 256, 192, False),       # K the kernel does not serve (some formats): the tiled one takes over
+    (SPARSE, 512, 2048, True),      # mxfp4: one and four waves with 64 columns each
+    (SPARSE, 1024, 512, False),     # ... two waves and one
+    ([2] * 64, 2048, 512, True),    # more tiles than resident blocks
+]
+
+
+@pytest.mark.parametrize("weights", ["bf16", "e4m3", "mxfp4"])
+@pytest.mark.parametrize("case", range(len(CASES)))
+def test_expert_ffn_stream(case, weights):
+    counts, D, F, bias = CASES[case]
+    print("stream ffn", weights, counts, D, F, bias, flush=True)
+    E, N = len(counts), int(sum(counts))
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    bf = torch.bfloat16
+    xp = wl.normal(61, 0, (N, D), 1.0, bf)
+    w1 = wl.normal(61, 1, (E, F, D), 1.0 / np.sqrt(D), bf)
+    w2 = wl.normal(61, 2, (E, D, F), 1.0 / np.sqrt(F), bf)
+    b1 = wl.normal(61, 3, (E, F), 0.5, bf) if bias else None
+    b2 = wl.normal(61, 4, (E, D), 0.5, bf) if bias else None
+    m = binding.MoeLayer(N, D, F, E, 1, "bf16")
+    xg, og = xp.cuda(), torch.from_numpy(offsets).cuda()
+    bg1, bg2 = (None if b is None else b.cuda() for b in (b1, b2))
+    idle = [e for e, c in enumerate(counts) if c == 0]
+    if weights == "bf16":
+        g1, g2 = w1.cuda(), w2.cuda()
+        g1[idle], g2[idle] = float("nan"), float("nan")
+        yp = m.moe_expert_ffn(xg, og, g1, g2, bg1, bg2)
+    else:
+        quantise = m.moe_quantize_e4m3 if weights == "e4m3" else m.moe_quantize_mxfp4
+        (q1, s1), (q2, s2) = quantise(w1.cuda()), quantise(w2.cuda())
+        q1[idle], q2[idle] = 0x77, 0x77
+        ffn = m.moe_expert_ffn_w8 if weights == "e4m3" else m.moe_expert_ffn_w4
+        yp = ffn(xg, og, q1, q2, s1, s2, bg1, bg2)
+        oq = o8 if weights == "e4m3" else o4
+        w1, w2 = (torch.from_numpy(oq.dequantize(*oq.quantize(w.float().numpy().astype(np.float64))).astype(np.float32)).to(bf)
+                  for w in (w1, w2))
+    torch.cuda.synchronize()
+    ref = orc.expert_ffn(xp, offsets, w1, w2, b1, b2)
+    got = to_np(yp)
+    assert np.all(np.isfinite(got))
+    # the bf16 bar of the tiled kernels; in norm, H and Yp are each rounded once (2^-9 relative at most, 2^-9.8 on average)
+    assert norm_max_err(got, ref) <= TOL["bf16"]
+    assert worst_row_rms_rel_err(got, ref) <= 2.0 ** -7
