@@ -96,21 +96,22 @@ int launch_gemm_bf16(const GemmParams &p, bool grouped, int variant, bool out_f3
                      hipStream_t s);
 int gemm_bf16_variant(int64_t n_rows, int E, int N, int num_cus);
 int gemm_bf16_variant_block_m(int variant);
-int launch_gemm_f32(const GemmParams &p, bool grouped, bool relu, hipStream_t s);
-int gemm_f32_block_m();
+int launch_gemm_f32(const GemmParams &p, bool grouped, int variant, bool relu, int num_cus, hipStream_t s);
+int gemm_f32_variant(int64_t n_rows, int E, int N, int K, int num_cus);
+int gemm_f32_block_m(int variant);
 bool gemm_bf16_variant_gathers(int variant, int K);
 int gemm_bf16_variant_w8(int64_t n_rows, int E);
 int gemm_bf16_variant_w4(int64_t n_rows, int E);
 int gemm_bf16_gate_split(int M, int N, int K, int num_cus);
 
-int gemm_variant(int dtype, int64_t n_rows, int E, int N, int num_cus)
+int gemm_variant(int dtype, int64_t n_rows, int E, int N, int K, int num_cus)
 {
-    return dtype == MOE_DTYPE_BF16 ? gemm_bf16_variant(n_rows, E, N, num_cus) : 0;
+    return dtype == MOE_DTYPE_BF16 ? gemm_bf16_variant(n_rows, E, N, num_cus) : gemm_f32_variant(n_rows, E, N, K, num_cus);
 }
 
 int gemm_variant_block_m(int dtype, int variant)
 {
-    return dtype == MOE_DTYPE_BF16 ? gemm_bf16_variant_block_m(variant) : gemm_f32_block_m();
+    return dtype == MOE_DTYPE_BF16 ? gemm_bf16_variant_block_m(variant) : gemm_f32_block_m(variant);
 }
 
 int launch_gemm(int dtype, const GemmParams &p, bool grouped, int variant, bool out_f32, bool relu, int num_cus,
@@ -118,7 +119,7 @@ int launch_gemm(int dtype, const GemmParams &p, bool grouped, int variant, bool 
 {
     ProfScope ps(p.name ? p.name : (!grouped ? "gate_gemm" : (relu ? "expert_gemm1" : "expert_gemm2")), s);
     if (dtype == MOE_DTYPE_BF16) return launch_gemm_bf16(p, grouped, variant, out_f32, relu, num_cus, s);
-    return launch_gemm_f32(p, grouped, relu, s);  // fp32 storage: C is fp32 either way
+    return launch_gemm_f32(p, grouped, variant, relu, num_cus, s);  // fp32 storage: C is fp32 either way
 }
 
 // ---- workspace ---------------------------------------------------------------------------------
@@ -344,8 +345,8 @@ static int run_expert_ffn(moe_handle_t *h, const void *xp, const FfnExtra &ex, c
     // each GEMM picks its own tile shape (N differs: F for the first, D for the second); the tile
     // map is rebuilt between them only when the M tile height differs
     const int wbits = ex.w1_blk ? 4 : ex.w1_scale ? 8 : 0;
-    const int v1 = wbits ? quant_variant(wbits, n_rows, c.E) : gemm_variant(c.dtype, n_rows, c.E, c.F, h->num_cus);
-    const int v2 = wbits ? v1 : gemm_variant(c.dtype, n_rows, c.E, c.D, h->num_cus);
+    const int v1 = wbits ? quant_variant(wbits, n_rows, c.E) : gemm_variant(c.dtype, n_rows, c.E, c.F, c.D, h->num_cus);
+    const int v2 = wbits ? v1 : gemm_variant(c.dtype, n_rows, c.E, c.D, c.F, h->num_cus);
     const int bm1 = gemm_variant_block_m(c.dtype, v1), bm2 = gemm_variant_block_m(c.dtype, v2);
     int max_tiles = (int)(n_rows / bm1) + c.E + 1;
     int rc = MOE_OK;
@@ -418,8 +419,9 @@ static int run_expert_ffn(moe_handle_t *h, const void *xp, const FfnExtra &ex, c
 static bool fused_dispatch_ok(const moe_handle_t *h, int64_t T, int wbits = 0)
 {
     const moe_config_t &c = h->cfg;
-    if (c.dtype != MOE_DTYPE_BF16 || T * c.D >= ((int64_t)1 << 31)) return false;
-    const int v = wbits ? quant_variant(wbits, T * c.k, c.E) : gemm_variant(c.dtype, T * c.k, c.E, c.F, h->num_cus);
+    if (c.dtype == MOE_DTYPE_F32) return true;  // 64-bit row pointers
+    if (T * c.D >= ((int64_t)1 << 31)) return false;
+    const int v = wbits ? quant_variant(wbits, T * c.k, c.E) : gemm_variant(c.dtype, T * c.k, c.E, c.F, c.D, h->num_cus);
     return gemm_bf16_variant_gathers(v, c.D);
 }
 
@@ -803,7 +805,7 @@ static int layer_forward_impl(moe_handle_t *h, moe_expert_cache_t *cache, const 
     const int wbits = cache ? cache->wbits : (w1_blk ? 4 : w1_scale ? 8 : 0);
     const int bm1 = cache ? 0
                           : gemm_variant_block_m(c.dtype, wbits ? quant_variant(wbits, n_rows, c.E)
-                                                                : gemm_variant(c.dtype, n_rows, c.E, c.F, h->num_cus));
+                                                                : gemm_variant(c.dtype, n_rows, c.E, c.F, c.D, h->num_cus));
     rc = launch_route(idx, T, c.E, c.k, counts, offsets, dst_row, src_tok, block_hist, s, bm1,
                       at<int32_t>(workspace, L.tile_expert), at<int32_t>(workspace, L.tile_row),
                       at<int32_t>(workspace, L.num_tiles), bm1 > 0 ? (int)(n_rows / bm1) + c.E + 1 : 0, hist_tokens);

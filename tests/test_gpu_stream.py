@@ -63,3 +63,37 @@ def test_expert_ffn_stream(case, weights):
     # the bf16 bar of the tiled kernels; in norm, H and Yp are each rounded once (2^-9 relative at most, 2^-9.8 on average)
     assert norm_max_err(got, ref) <= TOL["bf16"]
     assert worst_row_rms_rel_err(got, ref) <= 2.0 ** -7
+
+
+F32_CASES = [
+    # counts, D, F, bias: the fp32 kernels' tiles (32 rows, K cut between waves; 64 rows) and K that ends inside a step
+    ([1], 8, 16, True),
+    ([31, 0, 33, 1, 64, 65], 40, 72, True),
+    ([31, 0, 33, 1, 64, 65], 520, 1560, False),
+    ([130, 5, 0, 97], 256, 1024, True),
+    ([1500, 0, 1, 1700], 64, 2048, True),   # 64-row tiles in the first GEMM, 32-row ones in the second
+]
+
+
+@pytest.mark.parametrize("case", range(len(F32_CASES)))
+def test_expert_ffn_f32(case):
+    counts, D, F, bias = F32_CASES[case]
+    print("f32 ffn", counts, D, F, bias, flush=True)
+    E, N = len(counts), int(sum(counts))
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    f32 = torch.float32
+    xp = wl.normal(62, 0, (N, D), 1.0, f32)
+    w1 = wl.normal(62, 1, (E, F, D), 1.0 / np.sqrt(D), f32)
+    w2 = wl.normal(62, 2, (E, D, F), 1.0 / np.sqrt(F), f32)
+    b1 = wl.normal(62, 3, (E, F), 0.5, f32) if bias else None
+    b2 = wl.normal(62, 4, (E, D), 0.5, f32) if bias else None
+    g1, g2 = w1.cuda(), w2.cuda()
+    idle = [e for e, c in enumerate(counts) if c == 0]
+    g1[idle], g2[idle] = float("nan"), float("nan")
+    m = binding.MoeLayer(N, D, F, E, 1, "f32")
+    yp = m.moe_expert_ffn(xp.cuda(), torch.from_numpy(offsets).cuda(), g1, g2, *(None if b is None else b.cuda() for b in (b1, b2)))
+    torch.cuda.synchronize()
+    ref = orc.expert_ffn(xp, offsets, w1, w2, b1, b2)
+    got = to_np(yp)
+    assert np.all(np.isfinite(got))
+    assert norm_max_err(got, ref) <= TOL["f32"]
