@@ -100,8 +100,8 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
     uint16_t *sA = reinterpret_cast<uint16_t *>(smem_raw);  // [NSTAGE][BM*64]
     uint16_t *sB = sA + NSTAGE * BM * BK;                   // [NSTAGE][BN*64]
     static_assert(NSTAGE >= 2, "at least two LDS stages");
-    static_assert(!RSTAGE || KFULL, "the register-staged pipeline needs K to be a multiple of the K tile");
     static_assert(!D16 || (KFULL && BQ == 0 && !OUT_F32), "the 16x16x32 pipeline: bf16 in and out, K a multiple of the K tile");
+    static_assert(KFULL || RSTAGE || STAGES == 2, "K that ends inside a K tile: register-staged, or the plain two-stage loop");
     static_assert(BQ == 0 || (KFULL && !RSTAGE && GROUPED), "8- and 4-bit weights: grouped direct-to-LDS pipeline, K a multiple of the K tile");
 
     const int tid = threadIdx.x;
@@ -422,7 +422,7 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
     constexpr int STRIP_BYTES = 32 * STRIP_ROW_BYTES;
     constexpr bool STRIP_IN_A = A_IT * 1024 >= STRIP_BYTES;
     constexpr bool STRIP_IN_B = !STRIP_IN_A && B_IT * 1024 >= STRIP_BYTES;
-    constexpr bool LDS_EPILOGUE = !OUT_F32 && KFULL && (STRIP_IN_A || STRIP_IN_B);
+    constexpr bool LDS_EPILOGUE = !OUT_F32 && (KFULL || RSTAGE) && (STRIP_IN_A || STRIP_IN_B);
     auto epilogue_lds = [&](const TileInfo &t, int free_stage) {
         constexpr int CPRW = STRIP_ROW_BYTES / 16;  // chunks per strip row
         constexpr int RPI = 64 / CPRW;              // strip rows one 64-lane access covers
@@ -493,7 +493,7 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
 
     TileInfo t = tile_info(seq);
 
-    if constexpr (KFULL) {
+    if constexpr (KFULL || RSTAGE) {
         // ---- global -> LDS without registers: one global_load_lds_dwordx4 moves 64 lanes x 16 B =
         // 1 KB = 8 tile rows into LDS, lane L landing at byte 16*L of the instruction's LDS base.
         // The base is fixed per instruction, so the swizzle is applied on the global side: the lane
@@ -882,16 +882,29 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
             bool l_more = true;
             set_ptrs(t);
             uint4 R[LPS];
+            // K that ends inside the last K tile (KFULL false; K is a multiple of 8): there a lane whose chunk lies past the
+            // end loads the K tile's first chunk instead and writes zeros, for both operands, so that not even a NaN of
+            // the neighbouring row can reach a sum.
+            const int tail_chunks = (K & (BK - 1)) / 8;  // valid chunks of the last K tile
+            bool put_tail = false;                       // R holds the last K tile
+            auto chunk_of = [&](int i) {                 // the K chunk this lane fetches with load i (see set_ptrs)
+                const int g = i < A_IT ? wave * A_IT + i : wave * B_IT + (i - A_IT);
+                return (lane & 7) ^ ((g * 4 + (lane >> 4)) & 7);
+            };
             auto gload = [&](int i) -> uint4 {
-                const uint16_t *g = i < A_IT ? a_base + (a_off[i] + l_kt * BK) : b_base + (b_off[i - A_IT] + l_kt * BK);
+                int ko = l_kt * BK;
+                if (!KFULL && l_kt == KT - 1 && chunk_of(i) >= tail_chunks) ko -= chunk_of(i) * 8;
+                const uint16_t *g = i < A_IT ? a_base + (a_off[i] + ko) : b_base + (b_off[i - A_IT] + ko);
                 return *reinterpret_cast<const uint4 *>(g);
             };
-            auto lds_put = [&](int buf, int i, const uint4 &v) {
+            auto lds_put = [&](int buf, int i, uint4 v) {
+                if (!KFULL && put_tail && chunk_of(i) >= tail_chunks) v = make_uint4(0, 0, 0, 0);
                 uint16_t *d = i < A_IT ? sA + buf * BM * BK + (wave * A_IT + i) * 8 * BK
                                        : sB + buf * BTILE + (wave * B_IT + (i - A_IT)) * 8 * BK;
                 *reinterpret_cast<uint4 *>(d + lane * 8) = v;
             };
             auto advance = [&]() {
+                if (!KFULL) put_tail = l_kt == KT - 1;
                 if (l_more && ++l_kt == KT) {
                     if (seq_ok(l_seq + slots)) {
                         l_seq += slots;
@@ -1105,7 +1118,7 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
             }
             uint4 a_reg[A_IT], b_reg[B_IT];
             auto load_global = [&](int kt) {
-                const int k0 = kt * BK;
+                const int k0 = (t.kt0 + kt) * BK;
                 const bool ok = k0 + kc * 8 < K;
 #pragma unroll
                 for (int i = 0; i < A_IT; ++i)
@@ -1167,8 +1180,8 @@ static int launch_k(const GemmParams &p_in, int num_cus, hipStream_t s, int *mai
     int64_t grid = (int64_t)num_cus * blocks_per_cu;
     int64_t tiles = (int64_t)m_tiles * n_tiles;
     if (!GROUPED && p.k_split > 1) {
-        if (!KFULL || (p.K / BK) % p.k_split != 0) {
-            set_error("split K: %d does not divide the %d K tiles", p.k_split, p.K / BK);
+        if (ceil_div(p.K, BK) % p.k_split != 0) {
+            set_error("split K: %d does not divide the %d K tiles", p.k_split, ceil_div(p.K, BK));
             return MOE_ERR_INVALID_ARG;
         }
         tiles *= p.k_split;
@@ -1195,11 +1208,11 @@ static int launch_k(const GemmParams &p_in, int num_cus, hipStream_t s, int *mai
 template <int BM, int BN, int WM, int WN, bool OUT_F32, bool RELU, bool GROUPED, int MINB, int STAGES = 2>
 static int launch_one(const GemmParams &p, int num_cus, hipStream_t s, int *main_grid = nullptr)
 {
-    // K a multiple of the K tile: pipelined main loop without a tail predicate; the K-tail path
-    // always uses two LDS stages
+    // K a multiple of the K tile: pipelined main loop without a tail predicate; else the register-staged
+    // pipeline zero-fills the last K tile, and the other shapes run a plain two-stage loop
     return (p.K % BK == 0)
                ? launch_k<BM, BN, WM, WN, OUT_F32, RELU, GROUPED, true, MINB, STAGES>(p, num_cus, s, main_grid)
-               : launch_k<BM, BN, WM, WN, OUT_F32, RELU, GROUPED, false, MINB, 2>(p, num_cus, s, main_grid);
+               : launch_k<BM, BN, WM, WN, OUT_F32, RELU, GROUPED, false, MINB, STAGES == REG_STAGED || STAGES == DTL16 ? REG_STAGED : 2>(p, num_cus, s, main_grid);
 }
 
 // grouped GEMM with 8-bit (BQ = 8) or 4-bit (BQ = 4) weights (K a multiple of the K tile: checked by the caller)
@@ -1216,9 +1229,6 @@ static int launch_grouped_w8(const GemmParams &p, bool relu, int num_cus, hipStr
 // The choice goes by the average number of rows per expert.  (Direct-to-LDS forms of the two large shapes
 // measured 7-8 % slower than the register-staged ones; a 128x256 shape, meant to quantise better over the
 // CUs when a GEMM has only one or two 256x256 tiles per CU, measured 16 % slower per flop and lost even there.)
-// every grouped bf16 shape reads A through per-lane row pointers when K is a multiple of the K tile
-bool gemm_bf16_variant_gathers(int variant, int K) { return variant != 0 && K % BK == 0; }
-
 // 8-bit weights are for the weight-streaming regime: always the small tiles (three / four LDS
 // stages deep, the stages cost half the LDS), whatever the row count.  (Measured on 128 experts of
 // 2048 x 8192 with 1 to 64 rows each: 2 to 6 stages, 32x64 and 32x256 tiles and up to 6 blocks per
@@ -1248,11 +1258,10 @@ int gemm_bf16_variant_w4(int64_t n_rows, int E)
 // range and does not make more tiles than CUs.
 int gemm_bf16_gate_split(int M, int N, int K, int num_cus)
 {
-    if (K % BK != 0) return 1;
     const int bn = N <= 32 ? 32 : (N <= 64 ? 64 : 128);
     const int64_t tiles = (int64_t)ceil_div(M, 32) * ceil_div(N, bn);
     if ((int64_t)ceil_div(M, 128) * ceil_div(N, 128) >= 2 * (int64_t)num_cus) return 1;  // the 128-row shape runs
-    const int kt = K / BK;
+    const int kt = ceil_div(K, BK);
     int s = 1;
     while (s * 2 <= 16 && kt % (s * 2) == 0 && kt / (s * 2) >= 2 && tiles * s * 2 <= num_cus) s *= 2;
     return s;
@@ -1325,13 +1334,12 @@ int launch_gemm_bf16(const GemmParams &p, bool grouped, int variant, bool out_f3
     switch (variant) {
     case 8: {
         // whole rounds as 256x256 tiles, the partly filled last round as 128x128 sub-tiles
-        if (p.K % BK != 0) return launch_grouped<256, 256, 2, 4, 1, REG_STAGED>(p, relu, num_cus, s);
         GemmParams q = p;
         int main_grid = 0;
         q.tail_mode = 1;
         // the ring pipeline addresses both operands with 32-bit byte offsets from one base
         const int64_t a_rows_max = (int64_t)(p.a_zero_row >= p.M ? p.a_zero_row + 1 : p.M);
-        const bool ring_ok = a_rows_max * p.lda * 2 < (1ll << 32) && (int64_t)p.N * p.ldb * 2 < (1ll << 32) &&
+        const bool ring_ok = p.K % BK == 0 && a_rows_max * p.lda * 2 < (1ll << 32) && (int64_t)p.N * p.ldb * 2 < (1ll << 32) &&
                              ((int64_t)(p.c_zero_row >= p.M ? p.c_zero_row + 1 : p.M) + 256) * p.ldc * 2 < (1ll << 32);
         int rc = ring_ok ? launch_grouped<256, 256, 2, 4, 1, DTL16>(q, relu, num_cus, s, &main_grid)
                          : launch_grouped<256, 256, 2, 4, 1, REG_STAGED>(q, relu, num_cus, s, &main_grid);
@@ -1344,8 +1352,18 @@ int launch_gemm_bf16(const GemmParams &p, bool grouped, int variant, bool out_f3
     case 23: return launch_grouped_w8<32, 128, 1, 4, 2, 4>(p, relu, num_cus, s);
     case 43: return launch_grouped_w8<32, 256, 1, 4, 2, 3, 4>(p, relu, num_cus, s);
     case 48: return launch_grouped_w8<64, 256, 1, 4, 2, 3, 4>(p, relu, num_cus, s);
-    case 2: return launch_grouped<64, 128, 1, 4, 2>(p, relu, num_cus, s);
-    case 3: return launch_grouped<32, 128, 1, 4, 2>(p, relu, num_cus, s);
+    case 2:
+        if (p.K % BK != 0)
+            return relu ? launch_k<64, 128, 1, 4, false, true, true, false, 2, REG_STAGED>(p, num_cus, s, nullptr)
+                        : launch_k<64, 128, 1, 4, false, false, true, false, 2, REG_STAGED>(p, num_cus, s, nullptr);
+        return relu ? launch_k<64, 128, 1, 4, false, true, true, true, 2, 2>(p, num_cus, s, nullptr)
+                    : launch_k<64, 128, 1, 4, false, false, true, true, 2, 2>(p, num_cus, s, nullptr);
+    case 3:
+        if (p.K % BK != 0)
+            return relu ? launch_k<32, 128, 1, 4, false, true, true, false, 2, REG_STAGED>(p, num_cus, s, nullptr)
+                        : launch_k<32, 128, 1, 4, false, false, true, false, 2, REG_STAGED>(p, num_cus, s, nullptr);
+        return relu ? launch_k<32, 128, 1, 4, false, true, true, true, 2, 2>(p, num_cus, s, nullptr)
+                    : launch_k<32, 128, 1, 4, false, false, true, true, 2, 2>(p, num_cus, s, nullptr);
     default:
         set_error("unsupported grouped GEMM variant %d", variant);
         return MOE_ERR_UNSUPPORTED;

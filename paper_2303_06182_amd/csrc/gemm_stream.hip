@@ -36,11 +36,14 @@ __device__ __forceinline__ const uint8_t *scalar_base(const uint8_t *ptr)
 }
 
 // BQ: weight storage as in gemm_bf16.hip (0 bf16, 8 e4m3, 4 mxfp4).  DP1 / DP2: K steps in flight per wave for tiles
-// of up to 16 / 32 rows (the step count of a wave is a multiple of both).
-template <int BQ, bool RELU, int NC, int W, int DP1, int DP2>
+// of up to 16 / 32 rows (the step count of a wave is a multiple of both).  RAGGED (bf16): any K and N that are
+// multiples of 8: the waves' shares of K differ by a step, both operands are zero past the end of K (their loads
+// repeat the row's last 16 bytes), columns past N repeat the last weight row and are not stored.
+template <int BQ, bool RELU, int NC, int W, int DP1, int DP2, bool RAGGED = false>
 __global__ __launch_bounds__(W * 64, W == 8 ? 4 : 3) void gemm_stream_kernel(GemmParams p)
 {
     constexpr bool B8 = BQ == 8, B4 = BQ == 4;
+    static_assert(!RAGGED || BQ == 0, "8- and 4-bit weights come in whole blocks");
     constexpr int KSTEP = B4 ? 128 : 64;       // K elements of one step
     constexpr int NF = KSTEP / 32;             // MFMA operands along K per step
     constexpr int NB = BQ == 0 ? 2 : 1;        // 16-byte weight loads per step and 16 columns
@@ -54,8 +57,11 @@ __global__ __launch_bounds__(W * 64, W == 8 ? 4 : 3) void gemm_stream_kernel(Gem
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r16 = lane & 15, kq = lane >> 4;
-    const int K = p.K, KW = K / W, n_steps = KW / KSTEP;
-    const int n_tiles = p.N / COLS;
+    const int K = p.K;
+    const int all_steps = (K + KSTEP - 1) / KSTEP;
+    const int s_begin = all_steps * wave / W, n_steps = all_steps * (wave + 1) / W - s_begin;  // not RAGGED: K / W each
+    const int KW = RAGGED ? 0 : K / W;
+    const int n_tiles = (p.N + COLS - 1) / COLS;
     const int m_tiles = uniform_load(p.num_tiles);
     const int live = m_tiles * n_tiles, chunk = (live + 7) >> 3, xcd = blockIdx.x & 7, slots = gridDim.x >> 3;
 
@@ -82,7 +88,7 @@ __global__ __launch_bounds__(W * 64, W == 8 ? 4 : 3) void gemm_stream_kernel(Gem
         const uint8_t *sbase = nullptr;
         uint32_t soff = 0;
         if constexpr (BQ == 0) {
-            bbase = static_cast<const uint8_t *>(p.B) + ((int64_t)slot * p.strideB + (int64_t)n0 * p.ldb + wave * KW) * 2;
+            bbase = static_cast<const uint8_t *>(p.B) + ((int64_t)slot * p.strideB + (int64_t)n0 * p.ldb + s_begin * KSTEP) * 2;
             boff = (uint32_t)r16 * (uint32_t)p.ldb * 2u + kq * 16;
             bcol = 16u * (uint32_t)p.ldb * 2u;
         } else if constexpr (B8) {  // [16 rows][64 bytes] blocks, along K inside a 16-row group
@@ -105,13 +111,21 @@ __global__ __launch_bounds__(W * 64, W == 8 ? 4 : 3) void gemm_stream_kernel(Gem
         auto tile = [&](auto rc, auto dpc) {
             constexpr int R = decltype(rc)::value, DP = decltype(dpc)::value;
             uint32_t aoff[R];
+            const uint8_t *aptr[R], *bptr[NC];  // RAGGED: the lane's rows at its first k of the wave's first step
 #pragma unroll
             for (int r = 0; r < R; ++r) {
                 int gr = min(row0 + r * 16 + r16, row_end - 1);  // rows past the end repeat the last one, their results are not stored
                 if (p.a_rows) gr = p.a_rows[gr];
+                if constexpr (RAGGED) aptr[r] = static_cast<const uint8_t *>(p.A) + (int64_t)gr * p.lda * 2;
                 aoff[r] = (uint32_t)gr * (uint32_t)p.lda * 2u + kq * (B4 ? 64 : B8 ? 32 : 16);
             }
-            const uint8_t *abase = static_cast<const uint8_t *>(p.A) + wave * KW * 2;
+            if constexpr (RAGGED) {
+#pragma unroll
+                for (int c = 0; c < NC; ++c)
+                    bptr[c] = static_cast<const uint8_t *>(p.B) + ((int64_t)slot * p.strideB + (int64_t)min(n0 + c * 16 + r16, p.N - 1) * p.ldb) * 2;
+            }
+            (void)aptr, (void)bptr;
+            const uint8_t *abase = static_cast<const uint8_t *>(p.A) + s_begin * (KSTEP * 2);
             u32x4 bq[DP][NC][NB], aq[DP][R][NF];
             uint32_t sc[DP][NC];
             u32x4 sc_now[NC], sc_next[NC];  // mxfp4: the scale bytes of a 512-element group of the lane's rows
@@ -124,6 +138,18 @@ __global__ __launch_bounds__(W * 64, W == 8 ? 4 : 3) void gemm_stream_kernel(Gem
 #pragma unroll
                     for (int i = 0; i < 4; ++i) acc[r][c][i] = 0.f;
             auto load = [&](int d, int s) {
+                if constexpr (RAGGED) {
+#pragma unroll
+                    for (int f = 0; f < NF; ++f) {
+                        const int k = min((s_begin + s) * KSTEP + f * 32 + kq * 8, K - 8);
+#pragma unroll
+                        for (int c = 0; c < NC; ++c) bq[d][c][f] = *reinterpret_cast<const u32x4 *>(bptr[c] + (int64_t)k * 2);
+#pragma unroll
+                        for (int r = 0; r < R; ++r) aq[d][r][f] = *reinterpret_cast<const u32x4 *>(aptr[r] + (int64_t)k * 2);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    return;
+                }
                 const uint8_t *as = scalar_base(abase + s * (KSTEP * 2));
 #pragma unroll
                 for (int c = 0; c < NC; ++c) {
@@ -157,6 +183,16 @@ __global__ __launch_bounds__(W * 64, W == 8 ? 4 : 3) void gemm_stream_kernel(Gem
                     sc_next[c] = *reinterpret_cast<const u32x4 *>(scalar_base(ss + (c >> 1) * sgroup + (c & 1) * 256) + soff);
             };
             auto compute = [&](int d, int quarter) {
+                if constexpr (RAGGED) {  // quarter: the step
+#pragma unroll
+                    for (int f = 0; f < NF; ++f)
+                        if ((s_begin + quarter) * KSTEP + f * 32 + kq * 8 >= K) {
+#pragma unroll
+                            for (int c = 0; c < NC; ++c) bq[d][c][f] = u32x4{0, 0, 0, 0};
+#pragma unroll
+                            for (int r = 0; r < R; ++r) aq[d][r][f] = u32x4{0, 0, 0, 0};
+                        }
+                }
 #pragma unroll
                 for (int f = 0; f < NF; ++f)
 #pragma unroll
@@ -194,7 +230,26 @@ __global__ __launch_bounds__(W * 64, W == 8 ? 4 : 3) void gemm_stream_kernel(Gem
                     }
                 __builtin_amdgcn_sched_barrier(0);
             };
-            if constexpr (SC4) {  // the loop below goes four steps at a time, the scales one such group ahead
+            if constexpr (RAGGED) {
+                // whole rounds with the next round's loads behind each step, then the last one to two rounds
+#pragma unroll
+                for (int d = 0; d < DP; ++d) load(d, d);
+                int s = 0;
+                for (; s + 2 * DP <= n_steps; s += DP)
+#pragma unroll
+                    for (int d = 0; d < DP; ++d) {
+                        compute(d, s + d);
+                        load(d, s + DP + d);
+                    }
+#pragma unroll
+                for (int d = 0; d < DP; ++d) {
+                    if (s + d < n_steps) compute(d, s + d);
+                    if (s + DP + d < n_steps) load(d, s + DP + d);
+                }
+#pragma unroll
+                for (int d = 0; d < DP; ++d)
+                    if (s + DP + d < n_steps) compute(d, s + DP + d);
+            } else if constexpr (SC4) {  // the loop below goes four steps at a time, the scales one such group ahead
                 static_assert(4 % DP == 0, "a group of four steps is whole rounds of the load ring");
                 load_scales(0);
 #pragma unroll
@@ -247,6 +302,7 @@ __global__ __launch_bounds__(W * 64, W == 8 ? 4 : 3) void gemm_stream_kernel(Gem
         const uint16_t *bias = static_cast<const uint16_t *>(p.bias);
         for (int i = tid; i < (row_end - row0) * (COLS / 2); i += W * 64) {
             const int r = i / (COLS / 2), c = (i % (COLS / 2)) * 2;
+            if (RAGGED && n0 + c >= p.N) continue;  // N is even
             float v0 = red[buf][0][r][c], v1 = red[buf][0][r][c + 1];
 #pragma unroll
             for (int w = 1; w < W; ++w) {
@@ -273,10 +329,10 @@ __global__ __launch_bounds__(W * 64, W == 8 ? 4 : 3) void gemm_stream_kernel(Gem
     }
 }
 
-template <int BQ, bool RELU, int NC, int W, int DP1, int DP2>
+template <int BQ, bool RELU, int NC, int W, int DP1, int DP2, bool RAGGED = false>
 static int launch_stream_t(const GemmParams &p, int num_cus, hipStream_t s)
 {
-    auto kern = gemm_stream_kernel<BQ, RELU, NC, W, DP1, DP2>;
+    auto kern = gemm_stream_kernel<BQ, RELU, NC, W, DP1, DP2, RAGGED>;
     static std::once_flag once;
     static int blocks_per_cu = 1;
     static hipError_t setup_rc = hipSuccess;
@@ -286,7 +342,7 @@ static int launch_stream_t(const GemmParams &p, int num_cus, hipStream_t s)
         blocks_per_cu = occ < 1 ? 1 : (occ > 16 ? 16 : occ);
     });
     MOE_HIP_CHECK(setup_rc);
-    const int64_t tiles = (int64_t)(p.max_m_tiles < p.M ? p.max_m_tiles : p.M) * (p.N / (16 * NC));  // every tile has a row
+    const int64_t tiles = (int64_t)(p.max_m_tiles < p.M ? p.max_m_tiles : p.M) * ceil_div(p.N, 16 * NC);  // every tile has a row
     int64_t grid = (int64_t)num_cus * blocks_per_cu;
     if (grid > tiles) grid = tiles;
     grid = align_up(grid, 8);
@@ -327,7 +383,15 @@ template <int BQ, bool RELU>
 static int launch_stream_q(const GemmParams &p, int num_cus, hipStream_t s, bool *taken)
 {
     const int64_t m_up = p.max_m_tiles < p.M ? p.max_m_tiles : p.M;  // every tile has a row
-    if (p.N % 32 != 0 || !stream_pays<BQ>(p, num_cus, m_up)) return MOE_OK;
+    const bool pays = stream_pays<BQ>(p, num_cus, m_up);
+    if constexpr (BQ == 0) {
+        if (pays && (p.N % 32 != 0 || stream_steps<BQ>(p.K, 4) == 0 || stream_steps<BQ>(p.K, 4) % 2 != 0)) {
+            *taken = true;
+            return m_up * ceil_div(p.N, 32) < num_cus ? launch_stream_t<BQ, RELU, 1, 8, 2, 2, true>(p, num_cus, s)
+                                                      : launch_stream_t<BQ, RELU, 2, 4, 2, 2, true>(p, num_cus, s);
+        }
+    }
+    if (p.N % 32 != 0 || !pays) return MOE_OK;
     *taken = true;
     const int n8 = stream_steps<BQ>(p.K, 8), n4 = stream_steps<BQ>(p.K, 4);
     // fewer than one 32-column tile per CU: 16 columns and eight waves each (1 token, bf16 21.2 -> 14.5 us; with more
@@ -363,7 +427,6 @@ int launch_gemm_stream(const GemmParams &p, int wbits, bool relu, int num_cus, h
     *taken = false;
     // 32-bit lane offsets into A (a gathered A is the token array: its caller checked that it fits)
     if (!p.a_rows && (int64_t)p.M * p.lda * 2 >= (1ll << 32)) return MOE_OK;
-    if ((int64_t)32 * p.ldb * 2 >= (1ll << 32)) return MOE_OK;
     if (wbits == 8) return relu ? launch_stream_q<8, true>(p, num_cus, s, taken) : launch_stream_q<8, false>(p, num_cus, s, taken);
     if (wbits == 4) return relu ? launch_stream_q<4, true>(p, num_cus, s, taken) : launch_stream_q<4, false>(p, num_cus, s, taken);
     return relu ? launch_stream_q<0, true>(p, num_cus, s, taken) : launch_stream_q<0, false>(p, num_cus, s, taken);

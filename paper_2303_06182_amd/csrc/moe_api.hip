@@ -99,7 +99,6 @@ int gemm_bf16_variant_block_m(int variant);
 int launch_gemm_f32(const GemmParams &p, bool grouped, int variant, bool relu, int num_cus, hipStream_t s);
 int gemm_f32_variant(int64_t n_rows, int E, int N, int K, int num_cus);
 int gemm_f32_block_m(int variant);
-bool gemm_bf16_variant_gathers(int variant, int K);
 int gemm_bf16_variant_w8(int64_t n_rows, int E);
 int gemm_bf16_variant_w4(int64_t n_rows, int E);
 int gemm_bf16_gate_split(int M, int N, int K, int num_cus);
@@ -415,14 +414,12 @@ static int run_expert_ffn(moe_handle_t *h, const void *xp, const FfnExtra &ex, c
     return launch_gemm(c.dtype, p, true, v2, false, false, h->num_cus, s);
 }
 
-// Can the first expert GEMM gather its rows from the token array (T tokens) itself?
-static bool fused_dispatch_ok(const moe_handle_t *h, int64_t T, int wbits = 0)
+// Can the first expert GEMM gather its rows from the token array (T tokens) itself?  The bf16 kernels address it with
+// 32-bit element offsets, the fp32 ones with 64-bit row pointers.
+static bool fused_dispatch_ok(const moe_handle_t *h, int64_t T)
 {
     const moe_config_t &c = h->cfg;
-    if (c.dtype == MOE_DTYPE_F32) return true;  // 64-bit row pointers
-    if (T * c.D >= ((int64_t)1 << 31)) return false;
-    const int v = wbits ? quant_variant(wbits, T * c.k, c.E) : gemm_variant(c.dtype, T * c.k, c.E, c.F, c.D, h->num_cus);
-    return gemm_bf16_variant_gathers(v, c.D);
+    return c.dtype == MOE_DTYPE_F32 || T * c.D < ((int64_t)1 << 31);
 }
 
 // 8- and 4-bit weights need bf16 activations and K dimensions that are whole K tiles
@@ -811,7 +808,7 @@ static int layer_forward_impl(moe_handle_t *h, moe_expert_cache_t *cache, const 
                       at<int32_t>(workspace, L.num_tiles), bm1 > 0 ? (int)(n_rows / bm1) + c.E + 1 : 0, hist_tokens);
     if (rc != MOE_OK) return rc;
     // dispatch: a scatter of its own, or folded into the first GEMM's row addressing (then Xp is never written)
-    const bool fused = fused_dispatch_ok(h, T, wbits);
+    const bool fused = fused_dispatch_ok(h, T);
     if (!fused) {
         rc = launch_dispatch(c.dtype, x, dst_row, T, c.D, c.k, xp, s);
         if (rc != MOE_OK) return rc;

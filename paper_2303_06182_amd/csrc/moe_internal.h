@@ -138,9 +138,6 @@ struct GemmParams {
 // and a contraction of K, and the M tile height of a variant; the tile map must be built with that height.
 int gemm_variant(int dtype, int64_t n_rows, int E, int N, int K, int num_cus);
 int gemm_variant_block_m(int dtype, int variant);
-// true when the variant's kernel can read its A rows through GemmParams::a_rows
-bool gemm_variant_gathers(int dtype, int variant);
-
 // variant: from gemm_variant (grouped) or 0 (plain).  out_f32: C is fp32 (else elem); relu:
 // max(.,0) before the store.
 int launch_gemm(int dtype, const GemmParams &p, bool grouped, int variant, bool out_f32, bool relu,

@@ -432,7 +432,7 @@ __global__ __launch_bounds__(kThreads) void route_rank_kernel(const int32_t *__r
 // below it in its wave with the same expert); waves add their counts to the running per-expert
 // totals one after the other, so the order is that of a, as in the kernels above.
 // ------------------------------------------------------------------------------------------------
-static constexpr int kSmallRouteMax = 4096;  // assignments
+static constexpr int kSmallRouteMax = 1024;  // assignments
 
 __global__ __launch_bounds__(1024) void route_small_kernel(const int32_t *__restrict__ idx, int n_assign, int E, int k,
                                                            int32_t *__restrict__ counts,

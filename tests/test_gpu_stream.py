@@ -25,11 +25,37 @@ CASES = [
     ([2] * 64, 2048, 512, True),    # more tiles than resident blocks
 ]
 
+# bf16 with K that ends inside a K tile, for every tile height; the neighbouring rows hold NaN (idle experts)
+RAGGED = [
+    ([1, 0, 17, 33], 8, 72, True),                  # K below one step
+    ([3, 0, 20] * 100, 72, 1032, False),            # 32-row tiles, more of them than the streaming form takes
+    ([64, 0, 130, 50], 200, 328, True),             # 64-row tiles
+    ([100, 257, 0, 60, 128], 1000, 136, False),     # 128-row tiles
+    ([300, 0, 513, 1], 264, 456, True),             # 256-row tiles and their tail launch
+]
+
+
+@pytest.mark.parametrize("case", range(len(RAGGED)))
+def test_expert_ffn_ragged_k(case):
+    run_ffn("bf16", *RAGGED[case])
+
 
 @pytest.mark.parametrize("weights", ["bf16", "e4m3", "mxfp4"])
 @pytest.mark.parametrize("case", range(len(CASES)))
 def test_expert_ffn_stream(case, weights):
-    counts, D, F, bias = CASES[case]
+    run_ffn(weights, *CASES[case])
+
+
+@pytest.mark.parametrize("T,k,E", [(512, 2, 7), (1025, 1, 7), (513, 2, 300)])   # around the single-block routing kernel's limit
+def test_route_small_limit(T, k, E):
+    g = torch.Generator().manual_seed(T)
+    idx = torch.stack([torch.randperm(E, generator=g)[:k] for _ in range(T)]).to(torch.int32)
+    out = binding.MoeLayer(T, 64, 64, E, k, "bf16").moe_route_counts(idx.cuda())
+    for got, ref in zip(out, orc.route(idx.numpy(), E)):
+        assert np.array_equal(to_np(got), ref)
+
+
+def run_ffn(weights, counts, D, F, bias):
     print("stream ffn", weights, counts, D, F, bias, flush=True)
     E, N = len(counts), int(sum(counts))
     offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
