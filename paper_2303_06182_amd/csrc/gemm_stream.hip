@@ -365,18 +365,19 @@ static int stream_steps(int K, int W)
 //  * bf16: only while the tiled kernel's 32 x 128 tiles are fewer than 1.5 per CU (1 token 14.5 / 98.6, 8 tokens
 //    94 / 121 on the 2048 layer's second GEMM); from there on that kernel reads whole lines with the non-temporal
 //    policy (6.3 TB/s) and this one cannot (1.9 tiles per CU 94 / 80, 64 tokens 494 / 447).
-//  * e4m3: up to 4 rows per expert on average (64 tokens 221 / 244, 256 tokens 341 / 363; at 16 rows 488 / 383: the
-//    activations, read once per 32 columns, weigh too much), or while the tiled kernel has less than one tile per CU.
-//  * mxfp4: below 8 rows per expert (64 tokens 124 / 141, 256 tokens 200 / 224, 8 rows 443 / 438 for both GEMMs), or
-//    while the tiled kernel's 256-column tiles number at most one per CU (32 rows, 2048 -> 512: 21.6 / 25.2).
+//  * e4m3 and mxfp4: up to 64 / 128 rows in all, or while the tiled kernel has at most one 128-column / two 256-column
+//    tiles per CU (rows 1 token: 11 / 54 and 10 / 82 on the 2048 layer's second GEMM; 16 tokens 84 / 90 and 51 / 75 on
+//    its first).  With more rows it is a matter of their spread: a tile of 17 ... 32 rows reads its activations 16 rows at a
+//    time, four times slower per byte than whole lines, so that evenly spread rows still gain (256 tokens over
+//    128 experts, mxfp4: 200 / 224) but a few hot experts cost more than that (same layer, skewed, 128 tokens: e4m3 304 / 185,
+//    mxfp4 162 / 111).  The host does not know the spread.
 template <int BQ>
 static bool stream_pays(const GemmParams &p, int num_cus, int64_t m_up)
 {
-    const int64_t E = p.n_experts;
     const int64_t tiles = m_up * ceil_div(p.N, BQ == 4 ? 256 : 128);
     if (BQ == 0) return 2 * tiles < 3 * (int64_t)num_cus;
-    if (BQ == 8) return (int64_t)p.M <= 4 * E || tiles < num_cus;
-    return (int64_t)p.M < 8 * E || tiles <= num_cus;
+    if (BQ == 8) return p.M <= 64 || tiles <= num_cus;
+    return p.M <= 128 || tiles <= 2 * (int64_t)num_cus;
 }
 
 template <int BQ, bool RELU>
