@@ -1194,12 +1194,12 @@ static int launch_k(const GemmParams &p_in, int num_cus, hipStream_t s, int *mai
         tiles = (parents < left_max ? parents : left_max) * ((256 / BM) * (256 / BN));
         if (tiles <= 0) return MOE_OK;
     }
-    if (grid > tiles) grid = tiles;
-    grid = align_up(grid, 8);
-    if (p.tail_mode == 1) {
+    if (p.tail_mode == 1) {  // a round is the whole chip, also where the grid is smaller
         p.main_slots = (int)grid;
         *main_grid = (int)grid;
     }
+    if (grid > tiles) grid = tiles;
+    grid = align_up(grid, 8);
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(WM * WN * 64), smem, s, p);
     MOE_LAUNCH_CHECK("gemm_bf16_kernel");
     return MOE_OK;
@@ -1223,12 +1223,6 @@ static int launch_grouped_w8(const GemmParams &p, bool relu, int num_cus, hipStr
                 : launch_k<BM, BN, WM, WN, false, false, true, true, MINB, STAGES, BQ>(p, num_cus, s, nullptr);
 }
 
-// Tile shapes of the grouped GEMM.  variant -> (BM, BN, waves, pipeline)
-//   8: 256x256, 8 waves, register-staged    10: 128x128, 4 waves, register-staged
-//   2: 64x128, 4 waves, direct-to-LDS        3: 32x128, 4 waves, direct-to-LDS
-// The choice goes by the average number of rows per expert.  (Direct-to-LDS forms of the two large shapes
-// measured 7-8 % slower than the register-staged ones; a 128x256 shape, meant to quantise better over the
-// CUs when a GEMM has only one or two 256x256 tiles per CU, measured 16 % slower per flop and lost even there.)
 // 8-bit weights are for the weight-streaming regime: always the small tiles (three / four LDS
 // stages deep, the stages cost half the LDS), whatever the row count.  (Measured on 128 experts of
 // 2048 x 8192 with 1 to 64 rows each: 2 to 6 stages, 32x64 and 32x256 tiles and up to 6 blocks per
@@ -1236,7 +1230,9 @@ static int launch_grouped_w8(const GemmParams &p, bool relu, int num_cus, hipStr
 int gemm_bf16_variant_w8(int64_t n_rows, int E)
 {
     const int64_t avg = E > 0 ? n_rows / E : n_rows;
-    return avg >= 48 ? 22 : 23;
+    // 64-row tiles, us against 32-row ones (128 experts 2048 -> 8192 / 64 experts 1024 -> 4096): 24 rows 942 / 993 and
+    // 165 / 151, 36 rows 998 / 1250 and 171 / 203
+    return avg >= 28 ? 22 : 23;
 }
 
 // 4-bit weights: 43 = 32x256, 48 = 64x256, three LDS stages each plus the two scale buffers (32x256: 44 KB,
@@ -1247,10 +1243,13 @@ int gemm_bf16_variant_w8(int64_t n_rows, int E)
 // With 8 or 16 tokens the second GEMM has fewer tiles than CUs and its time is the K loop of one tile,
 // 128 K tiles at about 0.65 us each, whatever the tile width or pipeline depth: only a split along K
 // would shorten it.)
-int gemm_bf16_variant_w4(int64_t n_rows, int E)
+// 64-row tiles, us against 32-row ones: 128 experts 2048 -> 8192: 36 rows per expert 774 / 726, 64 rows 939 / 1113; 16
+// experts 1024 -> 4096, whose 64 weight panels leave the chip to few tiles: 64 rows 95 / 80, 100 rows 97 / 99.
+int gemm_bf16_variant_w4(int64_t n_rows, int E, int N, int K, int num_cus)
 {
     const int64_t avg = E > 0 ? n_rows / E : n_rows;
-    return avg >= 96 ? 48 : 43;
+    const int64_t panels = (int64_t)E * (N < K ? N : K) / 256;
+    return avg >= (4 * panels > num_cus ? 44 : 96) ? 48 : 43;
 }
 
 // K ranges for the fp32-output plain GEMM (the gate): 1 unless the 32-row tiles would leave most of the
@@ -1270,22 +1269,40 @@ int gemm_bf16_gate_split(int M, int N, int K, int num_cus)
 int gemm_bf16_variant_block_m(int v)
 {
     switch (v) {
-    case 10: return 128;
-    case 2: case 22: case 48: return 64;
+    case 10: case 11: return 128;
+    case 22: case 48: return 64;
     case 3: case 23: case 43: return 32;
     default: return 256;
     }
 }
 
-int gemm_bf16_variant(int64_t n_rows, int E, int N, int num_cus)
+// Tile shapes of the grouped GEMM.  variant -> (BM, BN, waves, pipeline)
+//   8: 256x256, 8 waves, ring    11: 128x256, 8 waves, ring    10: 128x128, 4 waves, register-staged
+//   3: 32x128, 4 waves, direct-to-LDS
+// By the average number of rows per expert and by how many 256-column weight panels there are (E * min(D, F) / 256,
+// the same for both GEMMs of a layer).  Where the panels alone fill the chip, one tall tile per expert beats two
+// of half its height as soon as most experts need two of those (from about 112 rows on), and with fewer rows the
+// 128-row ring streams the weights faster than any other shape.  With few panels, the smaller tiles' even spread wins.
+// Layer times in us, top-2:
+//   128 experts 2048 -> 8192, skewed, rows per expert     18     36     64    100    140    170
+//     32x128                                             1589   2159   3431
+//     64x128 (no longer used)                                   1749   2060   2665   3248   3342
+//     128x128                                            1594   1744   1934   2099   2426   2866
+//     128x256 ring                                       1486   1692   1825   1906   2188   2573
+//     256x256 ring                                       1775   1822   1940   2010   2187   2298
+//   64 experts 1024 -> 4096, even, rows per expert         18     36     64    100    140    170
+//     32x128                                              230    335
+//     128x128                                             244    262    269    315    381    367
+//     256x256 ring                                        277    292    301    301    313    313
+// K that is no multiple of the K tile has no ring: there 256 rows pay from 192 on.
+int gemm_bf16_variant(int64_t n_rows, int E, int N, int K, int num_cus)
 {
-    (void)N;
-    (void)num_cus;
     const int64_t avg = E > 0 ? n_rows / E : n_rows;
-    if (avg >= 192) return 8;
-    if (avg >= 96) return 10;
-    if (avg >= 48) return 2;
-    return 3;
+    const int64_t panels = (int64_t)E * (N < K ? N : K) / 256;
+    const bool ring = N % BK == 0 && K % BK == 0;
+    if (avg >= 192 || (ring && avg >= 112 && 4 * panels >= num_cus)) return 8;
+    if (ring && panels >= 2 * (int64_t)num_cus) return avg >= 18 ? 11 : 3;
+    return avg >= (4 * panels > num_cus ? 30 : 48) ? 10 : 3;
 }
 
 int launch_gemm_stream(const GemmParams &p, int wbits, bool relu, int num_cus, hipStream_t s, bool *taken);
@@ -1347,17 +1364,18 @@ int launch_gemm_bf16(const GemmParams &p, bool grouped, int variant, bool out_f3
         q.tail_mode = 2;
         return launch_grouped<128, 128, 2, 2, 2, REG_STAGED>(q, relu, num_cus, s, &main_grid);
     }
+    case 11:
+        // the ring pipeline's 32-bit byte offsets, as above
+        if ((int64_t)p.M * p.lda * 2 < (1ll << 32) && (p.a_zero_row + 1) * p.lda * 2 < (1ll << 32) && (int64_t)p.N * p.ldb * 2 < (1ll << 32) &&
+            ((int64_t)(p.c_zero_row >= p.M ? p.c_zero_row + 1 : p.M) + 256) * p.ldc * 2 < (1ll << 32))
+            return relu ? launch_k<128, 256, 2, 4, false, true, true, true, 1, DTL16>(p, num_cus, s, nullptr)
+                        : launch_k<128, 256, 2, 4, false, false, true, true, 1, DTL16>(p, num_cus, s, nullptr);
+        return launch_grouped<128, 128, 2, 2, 2, REG_STAGED>(p, relu, num_cus, s);
     case 10: return launch_grouped<128, 128, 2, 2, 2, REG_STAGED>(p, relu, num_cus, s);
     case 22: return launch_grouped_w8<64, 128, 1, 4, 2, 3>(p, relu, num_cus, s);
     case 23: return launch_grouped_w8<32, 128, 1, 4, 2, 4>(p, relu, num_cus, s);
     case 43: return launch_grouped_w8<32, 256, 1, 4, 2, 3, 4>(p, relu, num_cus, s);
     case 48: return launch_grouped_w8<64, 256, 1, 4, 2, 3, 4>(p, relu, num_cus, s);
-    case 2:
-        if (p.K % BK != 0)
-            return relu ? launch_k<64, 128, 1, 4, false, true, true, false, 2, REG_STAGED>(p, num_cus, s, nullptr)
-                        : launch_k<64, 128, 1, 4, false, false, true, false, 2, REG_STAGED>(p, num_cus, s, nullptr);
-        return relu ? launch_k<64, 128, 1, 4, false, true, true, true, 2, 2>(p, num_cus, s, nullptr)
-                    : launch_k<64, 128, 1, 4, false, false, true, true, 2, 2>(p, num_cus, s, nullptr);
     case 3:
         if (p.K % BK != 0)
             return relu ? launch_k<32, 128, 1, 4, false, true, true, false, 2, REG_STAGED>(p, num_cus, s, nullptr)

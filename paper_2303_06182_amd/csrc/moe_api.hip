@@ -94,18 +94,18 @@ ProfScope::~ProfScope()
 
 int launch_gemm_bf16(const GemmParams &p, bool grouped, int variant, bool out_f32, bool relu, int num_cus,
                      hipStream_t s);
-int gemm_bf16_variant(int64_t n_rows, int E, int N, int num_cus);
+int gemm_bf16_variant(int64_t n_rows, int E, int N, int K, int num_cus);
 int gemm_bf16_variant_block_m(int variant);
 int launch_gemm_f32(const GemmParams &p, bool grouped, int variant, bool relu, int num_cus, hipStream_t s);
 int gemm_f32_variant(int64_t n_rows, int E, int N, int K, int num_cus);
 int gemm_f32_block_m(int variant);
 int gemm_bf16_variant_w8(int64_t n_rows, int E);
-int gemm_bf16_variant_w4(int64_t n_rows, int E);
+int gemm_bf16_variant_w4(int64_t n_rows, int E, int N, int K, int num_cus);
 int gemm_bf16_gate_split(int M, int N, int K, int num_cus);
 
 int gemm_variant(int dtype, int64_t n_rows, int E, int N, int K, int num_cus)
 {
-    return dtype == MOE_DTYPE_BF16 ? gemm_bf16_variant(n_rows, E, N, num_cus) : gemm_f32_variant(n_rows, E, N, K, num_cus);
+    return dtype == MOE_DTYPE_BF16 ? gemm_bf16_variant(n_rows, E, N, K, num_cus) : gemm_f32_variant(n_rows, E, N, K, num_cus);
 }
 
 int gemm_variant_block_m(int dtype, int variant)
@@ -308,10 +308,11 @@ static int do_gate_topk(moe_handle_t *h, const void *x, const void *wg, const fl
 // scale bytes of one expert's [rows, cols] matrix in the 4-bit layout: 16 per row and 512 columns
 static int64_t mxfp4_scale_bytes(int64_t rows, int64_t cols) { return (rows / 32) * ((cols + 511) / 512) * 512; }
 
-// tile shape of the grouped GEMM for quantised weights
-static int quant_variant(int wbits, int64_t n_rows, int E)
+// tile shape of the grouped GEMM for quantised weights (both GEMMs of the layer)
+static int quant_variant(const moe_handle_t *h, int wbits, int64_t n_rows)
 {
-    return wbits == 4 ? gemm_bf16_variant_w4(n_rows, E) : gemm_bf16_variant_w8(n_rows, E);
+    const moe_config_t &c = h->cfg;
+    return wbits == 4 ? gemm_bf16_variant_w4(n_rows, c.E, c.F, c.D, h->num_cus) : gemm_bf16_variant_w8(n_rows, c.E);
 }
 
 // Options of the grouped FFN beyond the plain call.
@@ -344,7 +345,7 @@ static int run_expert_ffn(moe_handle_t *h, const void *xp, const FfnExtra &ex, c
     // each GEMM picks its own tile shape (N differs: F for the first, D for the second); the tile
     // map is rebuilt between them only when the M tile height differs
     const int wbits = ex.w1_blk ? 4 : ex.w1_scale ? 8 : 0;
-    const int v1 = wbits ? quant_variant(wbits, n_rows, c.E) : gemm_variant(c.dtype, n_rows, c.E, c.F, c.D, h->num_cus);
+    const int v1 = wbits ? quant_variant(h, wbits, n_rows) : gemm_variant(c.dtype, n_rows, c.E, c.F, c.D, h->num_cus);
     const int v2 = wbits ? v1 : gemm_variant(c.dtype, n_rows, c.E, c.D, c.F, h->num_cus);
     const int bm1 = gemm_variant_block_m(c.dtype, v1), bm2 = gemm_variant_block_m(c.dtype, v2);
     int max_tiles = (int)(n_rows / bm1) + c.E + 1;
@@ -357,7 +358,6 @@ static int run_expert_ffn(moe_handle_t *h, const void *xp, const FfnExtra &ex, c
     GemmParams p;
     memset(&p, 0, sizeof(p));
     p.offsets = offsets;
-    p.n_experts = c.E;
     p.tile_expert = tile_expert;
     p.tile_row = tile_row;
     p.num_tiles = num_tiles;
@@ -801,7 +801,7 @@ static int layer_forward_impl(moe_handle_t *h, moe_expert_cache_t *cache, const 
     const int64_t n_rows = (int64_t)T * c.k;
     const int wbits = cache ? cache->wbits : (w1_blk ? 4 : w1_scale ? 8 : 0);
     const int bm1 = cache ? 0
-                          : gemm_variant_block_m(c.dtype, wbits ? quant_variant(wbits, n_rows, c.E)
+                          : gemm_variant_block_m(c.dtype, wbits ? quant_variant(h, wbits, n_rows)
                                                                 : gemm_variant(c.dtype, n_rows, c.E, c.F, c.D, h->num_cus));
     rc = launch_route(idx, T, c.E, c.k, counts, offsets, dst_row, src_tok, block_hist, s, bm1,
                       at<int32_t>(workspace, L.tile_expert), at<int32_t>(workspace, L.tile_row),

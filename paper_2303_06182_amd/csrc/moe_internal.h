@@ -115,7 +115,6 @@ struct GemmParams {
     float *c_parts;
     // grouped mode
     const int32_t *offsets;      // [E+1]
-    int n_experts;               // E
     const int32_t *tile_expert;  // [max_m_tiles]
     const int32_t *tile_row;     // [max_m_tiles] first row of the tile
     const int32_t *num_tiles;    // [1]
