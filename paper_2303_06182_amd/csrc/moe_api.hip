@@ -261,12 +261,16 @@ static int validate_config(const moe_config_t *c)
 // hist != NULL: a kernel that decides the routing in the gate GEMM's epilogue may also leave the per-tile expert
 // histogram there (room for ceil(T / 32) * E int32); *hist_tokens then says how many tokens one row covers (0 =
 // no histogram was written and the routing step makes its own).
+// route != NULL (with routed): the routing step's outputs; *routed then says that a decoder step's top-k launch has
+// already written them.
 static int do_gate_topk(moe_handle_t *h, const void *x, const void *wg, const float *gate_bias, int T,
                         float *logits_req, float *logits_ws, int32_t *idx, float *w, hipStream_t s,
-                        float *parts = nullptr, int32_t *hist = nullptr, int *hist_tokens = nullptr)
+                        float *parts = nullptr, int32_t *hist = nullptr, int *hist_tokens = nullptr,
+                        const RouteOut *route = nullptr, bool *routed = nullptr)
 {
     const moe_config_t &c = h->cfg;
     if (hist_tokens) *hist_tokens = 0;
+    if (routed) *routed = false;
     if (T == 0) return MOE_OK;
     // Batches beyond a decoder step, bf16, at most 128 experts: one kernel streams x, keeps the logits in
     // registers and writes the decision (and the logits only where the caller asked for them).
@@ -302,6 +306,10 @@ static int do_gate_topk(moe_handle_t *h, const void *x, const void *wg, const fl
     }
     int rc = launch_gemm(c.dtype, p, false, 0, true, false, h->num_cus, s);
     if (rc != MOE_OK) return rc;
+    if (route) {
+        rc = launch_route_topk(logits, T, c.E, c.k, c.renormalize, idx, w, s, split, parts, p.split_stride, *route, routed);
+        if (rc != MOE_OK || *routed) return rc;
+    }
     return launch_topk(logits, T, c.E, c.k, c.renormalize, idx, w, s, split, parts, p.split_stride);
 }
 
@@ -690,8 +698,8 @@ int moe_route_counts(moe_handle_t *h, const int32_t *topk_idx, int32_t T, int32_
         return MOE_ERR_INVALID_ARG;
     rc = check_ws(h, workspace, workspace_bytes);
     if (rc != MOE_OK) return rc;
-    return launch_route(topk_idx, T, h->cfg.E, h->cfg.k, counts, offsets, dst_row, src_tok,
-                        at<int32_t>(workspace, ws_layout(h->cfg).block_hist), (hipStream_t)stream);
+    const RouteOut out = {counts, offsets, dst_row, src_tok, 0, nullptr, nullptr, nullptr, 0};
+    return launch_route(topk_idx, T, h->cfg.E, h->cfg.k, out, at<int32_t>(workspace, ws_layout(h->cfg).block_hist), (hipStream_t)stream);
 }
 
 int moe_dispatch(moe_handle_t *h, const void *x, const int32_t *dst_row, int32_t T, void *xp, void *stream)
@@ -787,26 +795,30 @@ static int layer_forward_impl(moe_handle_t *h, moe_expert_cache_t *cache, const 
     void *xp = at<void>(workspace, L.xp);
     void *yp = at<void>(workspace, L.yp);
 
-    if (empty) return launch_route(idx, 0, c.E, c.k, counts, offsets, dst_row, src_tok, block_hist, s);
+    // the routing step's ranking kernel also writes the first expert GEMM's tile map (not when the
+    // experts are buffered: their tile maps are per stage)
+    const int64_t n_rows = (int64_t)T * c.k;
+    const int wbits = cache ? cache->wbits : (w1_blk ? 4 : w1_scale ? 8 : 0);
+    const int bm1 = cache || empty ? 0
+                                   : gemm_variant_block_m(c.dtype, wbits ? quant_variant(h, wbits, n_rows)
+                                                                         : gemm_variant(c.dtype, n_rows, c.E, c.F, c.D, h->num_cus));
+    const RouteOut route = {counts, offsets, dst_row, src_tok, bm1, at<int32_t>(workspace, L.tile_expert),
+                            at<int32_t>(workspace, L.tile_row), at<int32_t>(workspace, L.num_tiles),
+                            bm1 > 0 ? (int)(n_rows / bm1) + c.E + 1 : 0};
+    if (empty) return launch_route(idx, 0, c.E, c.k, route, block_hist, s);
     {
         // an event pair around nothing: what the bracketing itself adds to every record of this call
         ProfScope nothing("event_pair_overhead", s);
     }
     int hist_tokens = 0;  // > 0: the gate kernel has already left the expert histogram in block_hist
+    bool routed = false;
     rc = do_gate_topk(h, x, wg, gate_bias, T, r.logits, at<float>(workspace, L.logits), idx, w, s,
-                      at<float>(workspace, L.gate_parts), block_hist, &hist_tokens);
+                      at<float>(workspace, L.gate_parts), block_hist, &hist_tokens, &route, &routed);
     if (rc != MOE_OK) return rc;
-    // the routing step's ranking kernel also writes the first expert GEMM's tile map (not when the
-    // experts are buffered: their tile maps are per stage)
-    const int64_t n_rows = (int64_t)T * c.k;
-    const int wbits = cache ? cache->wbits : (w1_blk ? 4 : w1_scale ? 8 : 0);
-    const int bm1 = cache ? 0
-                          : gemm_variant_block_m(c.dtype, wbits ? quant_variant(h, wbits, n_rows)
-                                                                : gemm_variant(c.dtype, n_rows, c.E, c.F, c.D, h->num_cus));
-    rc = launch_route(idx, T, c.E, c.k, counts, offsets, dst_row, src_tok, block_hist, s, bm1,
-                      at<int32_t>(workspace, L.tile_expert), at<int32_t>(workspace, L.tile_row),
-                      at<int32_t>(workspace, L.num_tiles), bm1 > 0 ? (int)(n_rows / bm1) + c.E + 1 : 0, hist_tokens);
-    if (rc != MOE_OK) return rc;
+    if (!routed) {
+        rc = launch_route(idx, T, c.E, c.k, route, block_hist, s, hist_tokens);
+        if (rc != MOE_OK) return rc;
+    }
     // dispatch: a scatter of its own, or folded into the first GEMM's row addressing (then Xp is never written)
     const bool fused = fused_dispatch_ok(h, T);
     if (!fused) {
@@ -1331,8 +1343,8 @@ int moe_layer_forward_static(moe_handle_t *h, const void *x, const void *wg, con
     // slot of every assignment = its rank inside its expert in slot-major order
     rc = launch_transpose_idx(idx, T, c.k, idx_t, dropped, s);
     if (rc != MOE_OK) return rc;
-    rc = launch_route(idx_t, T * c.k, c.E, 1, counts_s, offsets_s, pos, at<int32_t>(ws, L.src_s),
-                      at<int32_t>(ws, L.block_hist), s);
+    const RouteOut out_s = {counts_s, offsets_s, pos, at<int32_t>(ws, L.src_s), 0, nullptr, nullptr, nullptr, 0};
+    rc = launch_route(idx_t, T * c.k, c.E, 1, out_s, at<int32_t>(ws, L.block_hist), s);
     if (rc != MOE_OK) return rc;
     rc = launch_static_rows(idx_t, pos, offsets_s, T, c.k, c.E, capacity, slot_row, dropped, s);
     if (rc != MOE_OK) return rc;

@@ -163,9 +163,17 @@ int route_blocks(int T);
 // ones are routed by one block that needs none
 bool route_uses_hist(int T, int k);
 // hist_tokens > 0: block_hist already holds one histogram row per hist_tokens tokens (a divisor of 256)
-int launch_route(const int32_t *idx, int T, int E, int k, int32_t *counts, int32_t *offsets, int32_t *dst_row,
-                 int32_t *src_tok, int32_t *block_hist, hipStream_t s, int tile_bm = 0, int32_t *tile_expert = nullptr,
-                 int32_t *tile_row = nullptr, int32_t *num_tiles = nullptr, int max_m_tiles = 0, int hist_tokens = 0);
+// what the routing step writes; the tile map only with tile_bm > 0
+struct RouteOut {
+    int32_t *counts, *offsets, *dst_row, *src_tok;
+    int tile_bm;
+    int32_t *tile_expert, *tile_row, *num_tiles;
+    int max_m_tiles;
+};
+int launch_route(const int32_t *idx, int T, int E, int k, const RouteOut &o, int32_t *block_hist, hipStream_t s, int hist_tokens = 0);
+// top-k and routing in one launch, for a decoder step
+int launch_route_topk(float *logits, int T, int E, int k, int renorm, int32_t *idx, float *w, hipStream_t s, int n_parts,
+                      const float *parts, int64_t part_stride, const RouteOut &o, bool *taken);
 
 // Gate GEMM with softmax / top-k and the per-tile expert histogram in its epilogue (gate_topk.hip); bf16, E <= 128,
 // K a multiple of 64.  logits and hist may be NULL.  hist gets one row per gate_topk_tile_tokens() tokens.

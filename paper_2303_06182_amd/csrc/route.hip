@@ -22,19 +22,15 @@ static constexpr int kMaxLogitParts = 16;  // slices the top-k kernel can add up
 // VEC: lane `sub` instead holds the 16-byte groups sub, sub+G, ... of the row (4 logits each, E a
 // multiple of 4), so every lane has V/4 float4 loads in flight; slot i of the lane is expert
 // (i/4)*4G + 4*sub + i%4, still ascending with i.
-template <int G, int V, bool VEC>
 // n_parts > 1: the logits arrive as n_parts partial sums (the gate GEMM's split K): slice 0 at `logits`,
 // slice i > 0 at parts + (i - 1) * part_stride; they are added in slice order and the sum is written
 // back to `logits`.
-__global__ __launch_bounds__(kThreads) void topk_kernel(float *logits, int T, int E, int k, int renorm,
-                                                        int32_t *__restrict__ idx, float *__restrict__ w,
-                                                        int n_parts, const float *__restrict__ parts,
-                                                        int64_t part_stride)
+// One token per group of G lanes: token t, lane sub of the group.  s_idx (may be NULL): the selection goes there too.
+template <int G, int V, bool VEC>
+__device__ __forceinline__ void topk_token(int t, bool live, int sub, float *logits, int E, int k, int renorm,
+                                           int32_t *__restrict__ idx, float *__restrict__ w, int n_parts,
+                                           const float *__restrict__ parts, int64_t part_stride, int *s_idx)
 {
-    constexpr int TOK_PER_BLOCK = kThreads / G;
-    const int sub = threadIdx.x % G;
-    const int t = blockIdx.x * TOK_PER_BLOCK + threadIdx.x / G;
-    const bool live = t < T;
     const float NEG_INF = -__builtin_huge_valf();
     auto expert_of = [&](int i) { return VEC ? (i >> 2) * (4 * G) + 4 * sub + (i & 3) : sub + i * G; };
 
@@ -160,10 +156,21 @@ __global__ __launch_bounds__(kThreads) void topk_kernel(float *logits, int T, in
         for (int j = 0; j < MOE_MAX_K; ++j) {
             if (j < k) {
                 idx[(int64_t)t * k + j] = sel_e[j];
+                if (s_idx) s_idx[t * k + j] = sel_e[j];
                 w[(int64_t)t * k + j] = expf(sel_v[j] - m) / denom;
             }
         }
     }
+}
+
+template <int G, int V, bool VEC>
+__global__ __launch_bounds__(kThreads) void topk_kernel(float *logits, int T, int E, int k, int renorm,
+                                                        int32_t *__restrict__ idx, float *__restrict__ w,
+                                                        int n_parts, const float *__restrict__ parts,
+                                                        int64_t part_stride)
+{
+    const int t = blockIdx.x * (kThreads / G) + threadIdx.x / G;
+    topk_token<G, V, VEC>(t, t < T, threadIdx.x % G, logits, E, k, renorm, idx, w, n_parts, parts, part_stride, nullptr);
 }
 
 template <int G, int V, bool VEC>
@@ -434,14 +441,10 @@ __global__ __launch_bounds__(kThreads) void route_rank_kernel(const int32_t *__r
 // ------------------------------------------------------------------------------------------------
 static constexpr int kSmallRouteMax = 1024;  // assignments
 
-__global__ __launch_bounds__(1024) void route_small_kernel(const int32_t *__restrict__ idx, int n_assign, int E, int k,
-                                                           int32_t *__restrict__ counts,
-                                                           int32_t *__restrict__ offsets,
-                                                           int32_t *__restrict__ dst_row,
-                                                           int32_t *__restrict__ src_tok, int tile_bm,
-                                                           int32_t *__restrict__ tile_expert,
-                                                           int32_t *__restrict__ tile_row,
-                                                           int32_t *__restrict__ num_tiles, int max_m_tiles)
+__device__ __forceinline__ void route_small(const int32_t *idx, int n_assign, int E, int k, int32_t *__restrict__ counts,
+                                            int32_t *__restrict__ offsets, int32_t *__restrict__ dst_row,
+                                            int32_t *__restrict__ src_tok, int tile_bm, int32_t *__restrict__ tile_expert,
+                                            int32_t *__restrict__ tile_row, int32_t *__restrict__ num_tiles, int max_m_tiles)
 {
     __shared__ int hist[MOE_MAX_E];   // counts, then the running totals of the ranking pass
     __shared__ int start[MOE_MAX_E];  // first row of every expert
@@ -548,16 +551,66 @@ __global__ __launch_bounds__(1024) void route_small_kernel(const int32_t *__rest
     }
 }
 
+__global__ __launch_bounds__(1024) void route_small_kernel(const int32_t *__restrict__ idx, int n_assign, int E, int k, RouteOut o)
+{
+    route_small(idx, n_assign, E, k, o.counts, o.offsets, o.dst_row, o.src_tok, o.tile_bm, o.tile_expert, o.tile_row, o.num_tiles,
+                o.max_m_tiles);
+}
+
+// Top-k of a decoder step and its routing in one launch: 1024 / G tokens fit the block, their selection stays in LDS.
+// Bound by launch latency: a dependent launch costs about 4.5 us here whatever it does.
+template <int G, int V, bool VEC>
+__global__ __launch_bounds__(1024) void route_topk_kernel(float *logits, int T, int E, int k, int renorm, int32_t *__restrict__ idx,
+                                                          float *__restrict__ w, int n_parts, const float *__restrict__ parts,
+                                                          int64_t part_stride, RouteOut o)
+{
+    __shared__ int s_idx[kSmallRouteMax];
+    const int t = threadIdx.x / G;
+    topk_token<G, V, VEC>(t, t < T, threadIdx.x % G, logits, E, k, renorm, idx, w, n_parts, parts, part_stride, s_idx);
+    __syncthreads();
+    route_small(s_idx, T * k, E, k, o.counts, o.offsets, o.dst_row, o.src_tok, o.tile_bm, o.tile_expert, o.tile_row, o.num_tiles,
+                o.max_m_tiles);
+}
+
+template <int G, int V, bool VEC>
+static int launch_route_topk_t(float *logits, int T, int E, int k, int renorm, int32_t *idx, float *w, hipStream_t s, int n_parts,
+                               const float *parts, int64_t part_stride, const RouteOut &o, bool *taken)
+{
+    if (T > 1024 / G) return MOE_OK;
+    *taken = true;
+    ProfScope ps("route", s);
+    hipLaunchKernelGGL((route_topk_kernel<G, V, VEC>), dim3(1), dim3(1024), 0, s, logits, T, E, k, renorm, idx, w, n_parts, parts,
+                       part_stride, o);
+    MOE_LAUNCH_CHECK("route_topk_kernel");
+    return MOE_OK;
+}
+
+// *taken = false: not a batch for the single block (nothing was launched).  Few tokens only, so that the block's one
+// compute unit is no slower than the top-k kernel's blocks; the lane groups are the top-k kernel's.
+int launch_route_topk(float *logits, int T, int E, int k, int renorm, int32_t *idx, float *w, hipStream_t s, int n_parts,
+                      const float *parts, int64_t part_stride, const RouteOut &o, bool *taken)
+{
+    *taken = false;
+    if (T < 1 || T > 64 || (int64_t)T * k > kSmallRouteMax || E % 4 != 0 || n_parts > kMaxLogitParts) return MOE_OK;
+#define MOE_ROUTE_TOPK(G, V) launch_route_topk_t<G, V, true>(logits, T, E, k, renorm, idx, w, s, n_parts, parts, part_stride, o, taken)
+    if (E <= 8) return MOE_ROUTE_TOPK(2, 4);
+    if (E <= 16) return MOE_ROUTE_TOPK(4, 4);
+    if (E <= 32) return MOE_ROUTE_TOPK(8, 4);
+    if (E <= 64) return MOE_ROUTE_TOPK(16, 4);
+    if (E <= 128) return MOE_ROUTE_TOPK(16, 8);
+    if (E <= 256) return MOE_ROUTE_TOPK(16, 16);
+    if (E <= 512) return MOE_ROUTE_TOPK(32, 16);
+    return MOE_ROUTE_TOPK(64, 16);
+#undef MOE_ROUTE_TOPK
+}
+
 bool route_uses_hist(int T, int k) { return (int64_t)T * k > kSmallRouteMax; }
 
-int launch_route(const int32_t *idx, int T, int E, int k, int32_t *counts, int32_t *offsets, int32_t *dst_row,
-                 int32_t *src_tok, int32_t *block_hist, hipStream_t s, int tile_bm, int32_t *tile_expert,
-                 int32_t *tile_row, int32_t *num_tiles, int max_m_tiles, int hist_tokens)
+int launch_route(const int32_t *idx, int T, int E, int k, const RouteOut &o, int32_t *block_hist, hipStream_t s, int hist_tokens)
 {
     ProfScope ps("route", s);  // histogram + prefix + rank together
     if ((int64_t)T * k <= kSmallRouteMax) {
-        hipLaunchKernelGGL(route_small_kernel, dim3(1), dim3(1024), 0, s, idx, T * k, E, k, counts, offsets, dst_row,
-                           src_tok, tile_bm, tile_expert, tile_row, num_tiles, max_m_tiles);
+        hipLaunchKernelGGL(route_small_kernel, dim3(1), dim3(1024), 0, s, idx, T * k, E, k, o);
         MOE_LAUNCH_CHECK("route_small_kernel");
         return MOE_OK;
     }
@@ -577,14 +630,14 @@ int launch_route(const int32_t *idx, int T, int E, int k, int32_t *counts, int32
         MOE_LAUNCH_CHECK("route_hist_kernel");
     }
     hipLaunchKernelGGL(route_prefix_kernel, dim3(ceil_div(E, kThreads / kWave)), dim3(kThreads), 0, s, block_hist,
-                       nrows, E, counts);
+                       nrows, E, o.counts);
     MOE_LAUNCH_CHECK("route_prefix_kernel");
     int nbits = 0;
     while ((1 << nbits) < E) ++nbits;
 #define MOE_RANK(KM)                                                                                              \
-    hipLaunchKernelGGL(route_rank_kernel<KM>, dim3(nblk), dim3(kThreads), 0, s, idx, T, E, k, nbits, counts,      \
-                       block_hist, row_step, offsets, dst_row, src_tok, tile_bm, tile_expert, tile_row, num_tiles, \
-                       max_m_tiles)
+    hipLaunchKernelGGL(route_rank_kernel<KM>, dim3(nblk), dim3(kThreads), 0, s, idx, T, E, k, nbits, o.counts, \
+                       block_hist, row_step, o.offsets, o.dst_row, o.src_tok, o.tile_bm, o.tile_expert, o.tile_row, \
+                       o.num_tiles, o.max_m_tiles)
     // KMAX = slots a lane holds: the smallest instantiation that holds k
     if (k <= 1) MOE_RANK(1);
     else if (k <= 2) MOE_RANK(2);

@@ -123,3 +123,19 @@ def test_expert_ffn_f32(case):
     got = to_np(yp)
     assert np.all(np.isfinite(got))
     assert norm_max_err(got, ref) <= TOL["f32"]
+
+
+@pytest.mark.parametrize("T", [1, 16, 64, 65])
+@pytest.mark.parametrize("E,k,dtype", [(8, 2, "bf16"), (12, 3, "f32"), (64, 8, "bf16"), (130, 1, "bf16"), (512, 2, "f32"), (1024, 4, "bf16")])
+def test_decoder_step_topk_and_routing_in_one_launch(T, E, k, dtype):
+    w = wl.Workload("route", dtype, T=T, D=64, F=64, E=E, k=k, seed=5)
+    m = binding.MoeLayer(T, 64, 64, E, k, dtype)
+    inp = {n: (None if v is None else v.cuda()) for n, v in wl.make_inputs(w).items()}
+    r = m.empty_routing(T)
+    m.moe_layer_forward(inp["x"], inp["wg"], inp["w1"], inp["w2"], inp["gate_bias"], routing_out=r)
+    torch.cuda.synchronize()
+    idx, gw = orc.topk(to_np(r["logits"]), k)
+    assert np.array_equal(to_np(r["topk_idx"]), idx)
+    assert np.abs(to_np(r["topk_w"]) - gw).max() <= 2e-6
+    for got, ref in zip((r["counts"], r["offsets"], r["dst_row"], r["src_tok"]), orc.route(idx, E)):
+        assert np.array_equal(to_np(got), ref)
