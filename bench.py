@@ -50,11 +50,16 @@ def profile_kernel_name(kernel: str):
             out_f32, relu, grouped = args[4] == "true", args[5] == "true", args[6] == "true"
             if len(args) > 10 and args[10] != "0":
                 return None  # quantised weights (the weight_formats runs), not the bf16 layer
-        else:  # gemm_f32_*<RELU, GROUPED, ...>
+        else:  # gemm_f32_*<[waves,] RELU, GROUPED, ...>
+            if k.startswith("gemm_f32_wave_kernel<"):
+                args = args[1:]
             out_f32, relu, grouped = False, args[0] == "true", args[1] == "true"
         if not grouped:
             return "gate_gemm" if (out_f32 or k.startswith("gemm_f32")) else None
         return "expert_gemm1" if relu else "expert_gemm2"
+    if k.startswith("gemm_stream_kernel<"):  # <weight storage, RELU, ...>
+        args = [a.strip() for a in k[k.index("<") + 1:].rstrip(">").split(",")]
+        return None if args[0] != "0" else "expert_gemm1" if args[1] == "true" else "expert_gemm2"
     for prefix, name in (("gate_topk_kernel", "gate_topk"), ("topk_kernel", "topk"), ("route_", "route"),
                          ("dispatch_kernel", "dispatch"), ("combine_kernel", "combine"), ("tile_map_kernel", "tile_map")):
         if k.startswith(prefix):

@@ -16,29 +16,31 @@ namespace moe355 {
 static constexpr int kThreads = 256;
 static constexpr int kUnroll = 4;
 
-// vpr = 16-byte vectors per row (D*2/16 for bf16, D*4/16 for fp32)
+// vpr = 16-byte vectors per row (D*2/16 for bf16, D*4/16 for fp32).  Index: 32 bits where the flat index space fits them
+// (a 64-bit division per vector costs more than its memory access).  Lanes past the end repeat the last vector and
+// store nothing: with a predicate on the loads the compiler kept the four values in LDS.
+template <typename Index>
 __global__ __launch_bounds__(kThreads) void dispatch_kernel(const uint4 *__restrict__ x,
-                                                            const int32_t *__restrict__ dst_row, int64_t total,
-                                                            int vpr, int k, uint4 *__restrict__ xp)
+                                                            const int32_t *__restrict__ dst_row, Index total,
+                                                            Index vpr, int k, uint4 *__restrict__ xp)
 {
-    const int64_t base = (int64_t)blockIdx.x * (kThreads * kUnroll) + threadIdx.x;
+    const Index base = (Index)blockIdx.x * (kThreads * kUnroll) + threadIdx.x;
     uint4 val[kUnroll];
+    Index tok[kUnroll], col[kUnroll];
 #pragma unroll
     for (int u = 0; u < kUnroll; ++u) {
-        const int64_t v = base + (int64_t)u * kThreads;
-        if (v < total) val[u] = x[v];
+        const Index v = base + u * kThreads < total ? base + u * kThreads : total - 1;
+        val[u] = x[v];
+        tok[u] = v / vpr;
+        col[u] = v - tok[u] * vpr;
     }
+    for (int j = 0; j < k; ++j) {
+        int64_t row[kUnroll];
 #pragma unroll
-    for (int u = 0; u < kUnroll; ++u) {
-        const int64_t v = base + (int64_t)u * kThreads;
-        if (v < total) {
-            const int64_t t = v / vpr;
-            const int c = (int)(v - t * vpr);
-            for (int j = 0; j < k; ++j) {
-                const int64_t r = dst_row[t * k + j];
-                xp[r * vpr + c] = val[u];
-            }
-        }
+        for (int u = 0; u < kUnroll; ++u) row[u] = dst_row[(int64_t)tok[u] * k + j];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u)
+            if (base + u * kThreads < total) xp[row[u] * vpr + col[u]] = val[u];
     }
 }
 
@@ -141,8 +143,12 @@ int launch_dispatch(int dtype, const void *x, const int32_t *dst_row, int T, int
     const int64_t total = (int64_t)T * vpr;
     const int64_t blocks = (total + kThreads * kUnroll - 1) / (kThreads * kUnroll);
     ProfScope ps("dispatch", s);
-    hipLaunchKernelGGL(dispatch_kernel, dim3((unsigned)blocks), dim3(kThreads), 0, s, (const uint4 *)x, dst_row, total,
-                       vpr, k, (uint4 *)xp);
+    if (blocks * (kThreads * kUnroll) < (1ll << 31))
+        hipLaunchKernelGGL(dispatch_kernel<uint32_t>, dim3((unsigned)blocks), dim3(kThreads), 0, s, (const uint4 *)x, dst_row,
+                           (uint32_t)total, (uint32_t)vpr, k, (uint4 *)xp);
+    else
+        hipLaunchKernelGGL(dispatch_kernel<int64_t>, dim3((unsigned)blocks), dim3(kThreads), 0, s, (const uint4 *)x, dst_row,
+                           total, (int64_t)vpr, k, (uint4 *)xp);
     MOE_LAUNCH_CHECK("dispatch_kernel");
     return MOE_OK;
 }
