@@ -1223,10 +1223,10 @@ static int launch_grouped_w8(const GemmParams &p, bool relu, int num_cus, hipStr
                 : launch_k<BM, BN, WM, WN, false, false, true, true, MINB, STAGES, BQ>(p, num_cus, s, nullptr);
 }
 
-// 8-bit weights are for the weight-streaming regime: always the small tiles (three / four LDS
-// stages deep, the stages cost half the LDS), whatever the row count.  (Measured on 128 experts of
-// 2048 x 8192 with 1 to 64 rows each: 2 to 6 stages, 32x64 and 32x256 tiles and up to 6 blocks per
-// CU all land within +-8 % of these two; deeper pipelines lose blocks per CU and are slower.)
+// 8-bit weights are for the weight-streaming regime: always the small tiles, three LDS stages deep (36 KB with 32 rows:
+// four blocks per CU; a fourth stage leaves room for three: 16 experts 2048 -> 8192, 100 tokens 129 -> 137 us, 128 experts,
+// 512 tokens 786 -> 797), whatever the row count.  (Measured on 128 experts of 2048 x 8192 with 1 to 64 rows each: 2 to 6
+// stages, 32x64 and 32x256 tiles and up to 6 blocks per CU all land within +-8 % of these two.)
 int gemm_bf16_variant_w8(int64_t n_rows, int E)
 {
     const int64_t avg = E > 0 ? n_rows / E : n_rows;
@@ -1373,7 +1373,7 @@ int launch_gemm_bf16(const GemmParams &p, bool grouped, int variant, bool out_f3
         return launch_grouped<128, 128, 2, 2, 2, REG_STAGED>(p, relu, num_cus, s);
     case 10: return launch_grouped<128, 128, 2, 2, 2, REG_STAGED>(p, relu, num_cus, s);
     case 22: return launch_grouped_w8<64, 128, 1, 4, 2, 3>(p, relu, num_cus, s);
-    case 23: return launch_grouped_w8<32, 128, 1, 4, 2, 4>(p, relu, num_cus, s);
+    case 23: return launch_grouped_w8<32, 128, 1, 4, 2, 3>(p, relu, num_cus, s);
     case 43: return launch_grouped_w8<32, 256, 1, 4, 2, 3, 4>(p, relu, num_cus, s);
     case 48: return launch_grouped_w8<64, 256, 1, 4, 2, 3, 4>(p, relu, num_cus, s);
     case 3:
