@@ -48,7 +48,7 @@ def profile_kernel_name(kernel: str):
         args = [a.strip() for a in k[k.index("<") + 1:].rstrip(">").split(",")]
         if k.startswith("gemm_bf16_kernel<"):
             out_f32, relu, grouped = args[4] == "true", args[5] == "true", args[6] == "true"
-            if len(args) > 10 and args[10] != "0":
+            if len(args) > 10 and args[-1] != "0":
                 return None  # quantised weights (the weight_formats runs), not the bf16 layer
         else:  # gemm_f32_*<[waves,] RELU, GROUPED, ...>
             if k.startswith("gemm_f32_wave_kernel<"):

@@ -76,7 +76,7 @@ struct TileInfo {
 // elements along K; the scale is applied while widening (v_cvt_scalef32_pk_bf16_fp4), the result is
 // again exactly a bf16 value.  8 and 4: direct-to-LDS pipeline only.
 template <int BM, int BN, int WM, int WN, bool OUT_F32, bool RELU, bool GROUPED, bool KFULL, int MINB, int STAGES,
-          int BQ = 0>
+          bool NT = false, int BQ = 0>
 __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams p)
 {
     constexpr int THREADS = WM * WN * 64;
@@ -576,13 +576,8 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
                 }
             }
         };
-        // The weights' cache policy (2 = non-temporal).  Below 33 rows per expert every weight byte is used by one
-        // tile and never again, and a non-temporal stream gets 6.3 TB/s out of HBM where the plain one gets 5.7 (64
-        // tokens over 128 experts of 2048 -> 8192: layer 0.986 -> 0.898 ms, e4m3 0.536 -> 0.496; 4099 tokens over 512
-        // experts of 1024 -> 4096, the popular ones with several tiles: 1.645 -> 1.612).  Taller tiles belong to
-        // experts with several of them, which share the weights through the caches: 64-row tiles of 4-bit weights over
-        // 256 rows per expert 0.402 -> 0.412 with it.
-        constexpr int B_CPOL = GROUPED && BM <= 32 ? 2 : 0;
+        // The weights' cache policy (2 = non-temporal; chosen by the variant).
+        constexpr int B_CPOL = NT ? 2 : 0;
         auto issue = [&](int kt, int buf) {
 #pragma unroll
             for (int i = 0; i < A_IT; ++i)
@@ -1153,7 +1148,7 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
 }
 
 template <int BM, int BN, int WM, int WN, bool OUT_F32, bool RELU, bool GROUPED, bool KFULL, int MINB, int STAGES,
-          int BQ = 0>
+          bool NT = false, int BQ = 0>
 static int launch_k(const GemmParams &p_in, int num_cus, hipStream_t s, int *main_grid)
 {
     GemmParams p = p_in;
@@ -1163,7 +1158,7 @@ static int launch_k(const GemmParams &p_in, int num_cus, hipStream_t s, int *mai
     const size_t smem = STAGES == DTL16 ? (size_t)5 * (BM + BN) * 64  // five slots of one 32-wide K step
                                         : (size_t)(STAGES == REG_STAGED ? 2 : STAGES) * (BM + (BQ == 8 ? BN / 2 : BQ == 4 ? BN / 4 : BN)) * BK * sizeof(uint16_t) +
                                               (BQ == 4 ? 2 * BN * 16 : 0);  // 4-bit weights: two buffers of block scales
-    auto kern = gemm_bf16_kernel<BM, BN, WM, WN, OUT_F32, RELU, GROUPED, KFULL, MINB, STAGES, BQ>;
+    auto kern = gemm_bf16_kernel<BM, BN, WM, WN, OUT_F32, RELU, GROUPED, KFULL, MINB, STAGES, NT, BQ>;
     // per instantiation, once, whichever host thread comes first: the LDS size attribute and the occupancy
     static std::once_flag once;
     static int blocks_per_cu = 0;
@@ -1215,13 +1210,22 @@ static int launch_one(const GemmParams &p, int num_cus, hipStream_t s, int *main
                : launch_k<BM, BN, WM, WN, OUT_F32, RELU, GROUPED, false, MINB, STAGES == REG_STAGED || STAGES == DTL16 ? REG_STAGED : 2>(p, num_cus, s, main_grid);
 }
 
-// grouped GEMM with 8-bit (BQ = 8) or 4-bit (BQ = 4) weights (K a multiple of the K tile: checked by the caller)
-template <int BM, int BN, int WM, int WN, int MINB, int STAGES, int BQ = 8>
-static int launch_grouped_w8(const GemmParams &p, bool relu, int num_cus, hipStream_t s)
+// grouped GEMM on the direct-to-LDS pipeline, bf16 (BQ = 0), 8-bit (8) or 4-bit (4) weights (K a multiple of the K tile:
+// checked by the caller)
+template <int BM, int BN, int WM, int WN, int MINB, int STAGES, bool NT, int BQ>
+static int launch_grouped_dtl(const GemmParams &p, bool relu, int num_cus, hipStream_t s)
 {
-    return relu ? launch_k<BM, BN, WM, WN, false, true, true, true, MINB, STAGES, BQ>(p, num_cus, s, nullptr)
-                : launch_k<BM, BN, WM, WN, false, false, true, true, MINB, STAGES, BQ>(p, num_cus, s, nullptr);
+    return relu ? launch_k<BM, BN, WM, WN, false, true, true, true, MINB, STAGES, NT, BQ>(p, num_cus, s, nullptr)
+                : launch_k<BM, BN, WM, WN, false, false, true, true, MINB, STAGES, NT, BQ>(p, num_cus, s, nullptr);
 }
+
+// Below this many rows per expert the 32-row tiles read the weights with the non-temporal policy (variants 3, 23, 43): an
+// expert then has one row tile, nothing is used twice, and such a stream gets 6.3 TB/s out of HBM where the plain one
+// gets 5.7 (64 tokens over 128 experts of 2048 -> 8192: layer 0.986 -> 0.898 ms, e4m3 0.536 -> 0.496).  Experts with several
+// row tiles share their weights through the caches: 4099 tokens over 512 experts of 1024 -> 4096, 16 rows each and skewed,
+// gain 2 % on repeated passes (1.645 -> 1.612) but lose 6 % on a first one (1.732 -> 1.837), and 64-row tiles of 4-bit weights
+// over 256 rows 0.402 -> 0.412; those (4, 24, 44 and the taller shapes) read plainly.
+static constexpr int kNtRows = 8;
 
 // 8-bit weights are for the weight-streaming regime: always the small tiles, three LDS stages deep (36 KB with 32 rows:
 // four blocks per CU; a fourth stage leaves room for three: 16 experts 2048 -> 8192, 100 tokens 129 -> 137 us, 128 experts,
@@ -1232,7 +1236,7 @@ int gemm_bf16_variant_w8(int64_t n_rows, int E)
     const int64_t avg = E > 0 ? n_rows / E : n_rows;
     // 64-row tiles, us against 32-row ones (128 experts 2048 -> 8192 / 64 experts 1024 -> 4096): 24 rows 942 / 993 and
     // 165 / 151, 36 rows 998 / 1250 and 171 / 203
-    return avg >= 28 ? 22 : 23;
+    return avg >= 28 ? 22 : avg >= kNtRows ? 24 : 23;
 }
 
 // 4-bit weights: 43 = 32x256, 48 = 64x256, three LDS stages each plus the two scale buffers (32x256: 44 KB,
@@ -1249,7 +1253,7 @@ int gemm_bf16_variant_w4(int64_t n_rows, int E, int N, int K, int num_cus)
 {
     const int64_t avg = E > 0 ? n_rows / E : n_rows;
     const int64_t panels = (int64_t)E * (N < K ? N : K) / 256;
-    return avg >= (4 * panels > num_cus ? 44 : 96) ? 48 : 43;
+    return avg >= (4 * panels > num_cus ? 44 : 96) ? 48 : avg >= kNtRows ? 44 : 43;
 }
 
 // K ranges for the fp32-output plain GEMM (the gate): 1 unless the 32-row tiles would leave most of the
@@ -1271,14 +1275,14 @@ int gemm_bf16_variant_block_m(int v)
     switch (v) {
     case 10: case 11: return 128;
     case 22: case 48: return 64;
-    case 3: case 23: case 43: return 32;
+    case 3: case 4: case 23: case 24: case 43: case 44: return 32;
     default: return 256;
     }
 }
 
 // Tile shapes of the grouped GEMM.  variant -> (BM, BN, waves, pipeline)
 //   8: 256x256, 8 waves, ring    11: 128x256, 8 waves, ring    10: 128x128, 4 waves, register-staged
-//   3: 32x128, 4 waves, direct-to-LDS
+//   3, 4: 32x128, 4 waves, direct-to-LDS, weights read non-temporally / plainly
 // By the average number of rows per expert and by how many 256-column weight panels there are (E * min(D, F) / 256,
 // the same for both GEMMs of a layer).  Where the panels alone fill the chip, one tall tile per expert beats two
 // of half its height as soon as most experts need two of those (from about 112 rows on), and with fewer rows the
@@ -1301,8 +1305,9 @@ int gemm_bf16_variant(int64_t n_rows, int E, int N, int K, int num_cus)
     const int64_t panels = (int64_t)E * (N < K ? N : K) / 256;
     const bool ring = N % BK == 0 && K % BK == 0;
     if (avg >= 192 || (ring && avg >= 112 && 4 * panels >= num_cus)) return 8;
-    if (ring && panels >= 2 * (int64_t)num_cus) return avg >= 18 ? 11 : 3;
-    return avg >= (4 * panels > num_cus ? 30 : 48) ? 10 : 3;
+    const int small = avg >= kNtRows ? 4 : 3;
+    if (ring && panels >= 2 * (int64_t)num_cus) return avg >= 18 ? 11 : small;
+    return avg >= (4 * panels > num_cus ? 30 : 48) ? 10 : small;
 }
 
 int launch_gemm_stream(const GemmParams &p, int wbits, bool relu, int num_cus, hipStream_t s, bool *taken);
@@ -1343,9 +1348,9 @@ int launch_gemm_bf16(const GemmParams &p, bool grouped, int variant, bool out_f3
         set_error("grouped bf16 GEMM is only instantiated for bf16 output");
         return MOE_ERR_UNSUPPORTED;
     }
-    if (variant == 3 || variant == 23 || variant == 43) {
+    if (gemm_bf16_variant_block_m(variant) == 32) {
         bool taken = false;
-        const int rc = launch_gemm_stream(p, variant == 23 ? 8 : variant == 43 ? 4 : 0, relu, num_cus, s, &taken);
+        const int rc = launch_gemm_stream(p, variant >= 43 ? 4 : variant >= 23 ? 8 : 0, relu, num_cus, s, &taken);
         if (taken || rc != MOE_OK) return rc;
     }
     switch (variant) {
@@ -1372,16 +1377,18 @@ int launch_gemm_bf16(const GemmParams &p, bool grouped, int variant, bool out_f3
                         : launch_k<128, 256, 2, 4, false, false, true, true, 1, DTL16>(p, num_cus, s, nullptr);
         return launch_grouped<128, 128, 2, 2, 2, REG_STAGED>(p, relu, num_cus, s);
     case 10: return launch_grouped<128, 128, 2, 2, 2, REG_STAGED>(p, relu, num_cus, s);
-    case 22: return launch_grouped_w8<64, 128, 1, 4, 2, 3>(p, relu, num_cus, s);
-    case 23: return launch_grouped_w8<32, 128, 1, 4, 2, 3>(p, relu, num_cus, s);
-    case 43: return launch_grouped_w8<32, 256, 1, 4, 2, 3, 4>(p, relu, num_cus, s);
-    case 48: return launch_grouped_w8<64, 256, 1, 4, 2, 3, 4>(p, relu, num_cus, s);
-    case 3:
+    case 22: return launch_grouped_dtl<64, 128, 1, 4, 2, 3, false, 8>(p, relu, num_cus, s);
+    case 23: return launch_grouped_dtl<32, 128, 1, 4, 2, 3, true, 8>(p, relu, num_cus, s);
+    case 24: return launch_grouped_dtl<32, 128, 1, 4, 2, 3, false, 8>(p, relu, num_cus, s);
+    case 43: return launch_grouped_dtl<32, 256, 1, 4, 2, 3, true, 4>(p, relu, num_cus, s);
+    case 44: return launch_grouped_dtl<32, 256, 1, 4, 2, 3, false, 4>(p, relu, num_cus, s);
+    case 48: return launch_grouped_dtl<64, 256, 1, 4, 2, 3, false, 4>(p, relu, num_cus, s);
+    case 3: case 4:
         if (p.K % BK != 0)
             return relu ? launch_k<32, 128, 1, 4, false, true, true, false, 2, REG_STAGED>(p, num_cus, s, nullptr)
                         : launch_k<32, 128, 1, 4, false, false, true, false, 2, REG_STAGED>(p, num_cus, s, nullptr);
-        return relu ? launch_k<32, 128, 1, 4, false, true, true, true, 2, 2>(p, num_cus, s, nullptr)
-                    : launch_k<32, 128, 1, 4, false, false, true, true, 2, 2>(p, num_cus, s, nullptr);
+        return variant == 3 ? launch_grouped_dtl<32, 128, 1, 4, 2, 2, true, 0>(p, relu, num_cus, s)
+                            : launch_grouped_dtl<32, 128, 1, 4, 2, 2, false, 0>(p, relu, num_cus, s);
     default:
         set_error("unsupported grouped GEMM variant %d", variant);
         return MOE_ERR_UNSUPPORTED;
