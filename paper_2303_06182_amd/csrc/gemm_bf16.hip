@@ -1226,6 +1226,8 @@ static int launch_grouped_dtl(const GemmParams &p, bool relu, int num_cus, hipSt
 // gain 2 % on repeated passes (1.645 -> 1.612) but lose 6 % on a first one (1.732 -> 1.837), and 64-row tiles of 4-bit weights
 // over 256 rows 0.402 -> 0.412; those (4, 24, 44 and the taller shapes) read plainly.
 static constexpr int kNtRows = 8;
+// Weights of one GEMM (all experts) from which on its time is that of streaming them
+static constexpr int64_t kHeavyWeights = 1ll << 29;
 
 // 8-bit weights are for the weight-streaming regime: always the small tiles, three LDS stages deep (36 KB with 32 rows:
 // four blocks per CU; a fourth stage leaves room for three: 16 experts 2048 -> 8192, 100 tokens 129 -> 137 us, 128 experts,
@@ -1283,11 +1285,11 @@ int gemm_bf16_variant_block_m(int v)
 // Tile shapes of the grouped GEMM.  variant -> (BM, BN, waves, pipeline)
 //   8: 256x256, 8 waves, ring    11: 128x256, 8 waves, ring    10: 128x128, 4 waves, register-staged
 //   3, 4: 32x128, 4 waves, direct-to-LDS, weights read non-temporally / plainly
-// By the average number of rows per expert and by how many 256-column weight panels there are (E * min(D, F) / 256,
-// the same for both GEMMs of a layer).  Where the panels alone fill the chip, one tall tile per expert beats two
-// of half its height as soon as most experts need two of those (from about 112 rows on), and with fewer rows the
-// 128-row ring streams the weights faster than any other shape.  With few panels, the smaller tiles' even spread wins.
-// Layer times in us, top-2:
+// By the average number of rows per expert, by how many 256-column weight panels there are (E * min(D, F) / 256, the
+// same for both GEMMs of a layer), and by how many weights a GEMM streams.  Where the panels alone fill the chip, one
+// tall tile per expert beats two of half its height as soon as most experts need two of those, and with fewer
+// rows the 128-row ring streams the weights faster than any other shape.  With few panels, the smaller tiles' even spread
+// wins.  Layer times in us, top-2:
 //   128 experts 2048 -> 8192, skewed, rows per expert     18     36     64    100    140    170
 //     32x128                                             1589   2159   3431
 //     64x128 (no longer used)                                   1749   2060   2665   3248   3342
@@ -1296,15 +1298,24 @@ int gemm_bf16_variant_block_m(int v)
 //     256x256 ring                                       1775   1822   1940   2010   2187   2298
 //   64 experts 1024 -> 4096, even, rows per expert         18     36     64    100    140    170
 //     32x128                                              230    335
-//     128x128                                             244    262    269    315    381    367
-//     256x256 ring                                        277    292    301    301    313    313
+//     128x128                                            244    262    269    315    381    367
+//     256x256 ring                                       277    292    301    301    313    313
+// 256 rows below 192 are for GEMMs of 2^29 weights and more (1 GB, four times the last-level cache): there one pass over
+// an expert's weights pays for the padding of an uneven batch, from 112 rows on where both dimensions are 2048 or more
+// and a tile's K loop is long, else from 128.  128x128 / 256x256 at that many rows per expert, even, skewed (exponent
+// 0.8), more skewed (1.2): 128 experts 2048 -> 8192 2054 / 1923, 2160 / 2058, 2431 / 2270; 32 experts 2048 -> 8192 565 / 504,
+// 562 / 575, 616 / 596; 128 experts 1024 -> 4096 646 / 548, 634 / 620, 662 / 680 (at 112 rows 570 / 532, 586 / 600, 634 / 658).
+// With fewer weights only an even batch gains, at 128 rows: 64 experts 1024 -> 4096 345 / 310, 338 / 372, 363 / 360; 128
+// experts 512 -> 2048 209 / 208, 208 / 239, 217 / 252; 16 experts 1024 -> 4096 122 / 114, 120 / 115, 121 / 143.
 // K that is no multiple of the K tile has no ring: there 256 rows pay from 192 on.
 int gemm_bf16_variant(int64_t n_rows, int E, int N, int K, int num_cus)
 {
     const int64_t avg = E > 0 ? n_rows / E : n_rows;
-    const int64_t panels = (int64_t)E * (N < K ? N : K) / 256;
+    const int width = N < K ? N : K;
+    const int64_t panels = (int64_t)E * width / 256;
     const bool ring = N % BK == 0 && K % BK == 0;
-    if (avg >= 192 || (ring && avg >= 112 && 4 * panels >= num_cus)) return 8;
+    const bool heavy = (int64_t)E * N * K >= kHeavyWeights;
+    if (avg >= 192 || (ring && heavy && avg >= (width >= 2048 ? 112 : 128))) return 8;
     const int small = avg >= kNtRows ? 4 : 3;
     if (ring && panels >= 2 * (int64_t)num_cus) return avg >= 18 ? 11 : small;
     return avg >= (4 * panels > num_cus ? 30 : 48) ? 10 : small;
