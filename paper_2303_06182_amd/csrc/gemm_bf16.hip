@@ -1276,7 +1276,7 @@ int gemm_bf16_variant_block_m(int v)
 {
     switch (v) {
     case 10: case 11: return 128;
-    case 22: case 48: return 64;
+    case 2: case 22: case 48: return 64;
     case 3: case 4: case 23: case 24: case 43: case 44: return 32;
     default: return 256;
     }
@@ -1284,7 +1284,7 @@ int gemm_bf16_variant_block_m(int v)
 
 // Tile shapes of the grouped GEMM.  variant -> (BM, BN, waves, pipeline)
 //   8: 256x256, 8 waves, ring    11: 128x256, 8 waves, ring    10: 128x128, 4 waves, register-staged
-//   3, 4: 32x128, 4 waves, direct-to-LDS, weights read non-temporally / plainly
+//   2: 64x128, 4 waves, direct-to-LDS    3, 4: 32x128, the same, weights read non-temporally / plainly
 // By the average number of rows per expert, by how many 256-column weight panels there are (E * min(D, F) / 256, the
 // same for both GEMMs of a layer), and by how many weights a GEMM streams.  Where the panels alone fill the chip, one
 // tall tile per expert beats two of half its height as soon as most experts need two of those, and with fewer
@@ -1292,7 +1292,7 @@ int gemm_bf16_variant_block_m(int v)
 // wins.  Layer times in us, top-2:
 //   128 experts 2048 -> 8192, skewed, rows per expert     18     36     64    100    140    170
 //     32x128                                             1589   2159   3431
-//     64x128 (no longer used)                                   1749   2060   2665   3248   3342
+//     64x128                                                    1749   2060   2665   3248   3342
 //     128x128                                            1594   1744   1934   2099   2426   2866
 //     128x256 ring                                       1486   1692   1825   1906   2188   2573
 //     256x256 ring                                       1775   1822   1940   2010   2187   2298
@@ -1307,18 +1307,27 @@ int gemm_bf16_variant_block_m(int v)
 // 562 / 575, 616 / 596; 128 experts 1024 -> 4096 646 / 548, 634 / 620, 662 / 680 (at 112 rows 570 / 532, 586 / 600, 634 / 658).
 // With fewer weights only an even batch gains, at 128 rows: 64 experts 1024 -> 4096 345 / 310, 338 / 372, 363 / 360; 128
 // experts 512 -> 2048 209 / 208, 208 / 239, 217 / 252; 16 experts 1024 -> 4096 122 / 114, 120 / 115, 121 / 143.
-// K that is no multiple of the K tile has no ring: there 256 rows pay from 192 on.
+// The 128-row ring, too, needs a GEMM of 2^29 weights: 32x128 / 128x256 ring at 24 rows per expert, even, skewed, more
+// skewed: 256 experts 512 -> 2048 281 / 272, 280 / 309, 244 / 244; 512 experts 256 -> 1024 157 / 157, 160 / 177, 135 / 133.
+// There 64x128 is the steadiest shape from 34 to 63 rows, 32x128 / 64x128 / 128x128: 128 experts 512 -> 2048, 36 rows 171 / 161 /
+// 162, 173 / 169 / 183, 170 / 164 / 176; 64 experts 1024 -> 4096, 48 rows 314 / 287 / 266, 327 / 280 / 309, 329 / 281 / 302; 16
+// experts 2048 -> 8192, 48 rows 292 / 291 / 279, 319 / 298 / 285, 310 / 297 / 323; at 64 rows 128x128 has caught up (342 / 320 /
+// 284, 332 / 311 / 309, 342 / 308 / 338).  With 64 panels or fewer it is ahead from 48 on (16 experts 1024 -> 4096 115 / 108 /
+// 101, 124 / 114 / 102, 120 / 114 / 110).
+// K that is no multiple of the K tile has neither ring nor 64x128: there 128 rows pay from 30 and 256 from 192 on.
 int gemm_bf16_variant(int64_t n_rows, int E, int N, int K, int num_cus)
 {
     const int64_t avg = E > 0 ? n_rows / E : n_rows;
     const int width = N < K ? N : K;
     const int64_t panels = (int64_t)E * width / 256;
-    const bool ring = N % BK == 0 && K % BK == 0;
-    const bool heavy = (int64_t)E * N * K >= kHeavyWeights;
-    if (avg >= 192 || (ring && heavy && avg >= (width >= 2048 ? 112 : 128))) return 8;
+    const bool whole = N % BK == 0 && K % BK == 0;
+    const bool heavy = whole && (int64_t)E * N * K >= kHeavyWeights;
+    if (avg >= 192 || (heavy && avg >= (width >= 2048 ? 112 : 128))) return 8;
     const int small = avg >= kNtRows ? 4 : 3;
-    if (ring && panels >= 2 * (int64_t)num_cus) return avg >= 18 ? 11 : small;
-    return avg >= (4 * panels > num_cus ? 30 : 48) ? 10 : small;
+    if (heavy && panels >= 2 * (int64_t)num_cus) return avg >= 18 ? 11 : small;
+    if (4 * panels <= num_cus) return avg >= 48 ? 10 : small;
+    if (whole && !heavy && avg < 64) return avg >= 34 ? 2 : small;
+    return avg >= 30 ? 10 : small;
 }
 
 int launch_gemm_stream(const GemmParams &p, int wbits, bool relu, int num_cus, hipStream_t s, bool *taken);
@@ -1388,6 +1397,12 @@ int launch_gemm_bf16(const GemmParams &p, bool grouped, int variant, bool out_f3
                         : launch_k<128, 256, 2, 4, false, false, true, true, 1, DTL16>(p, num_cus, s, nullptr);
         return launch_grouped<128, 128, 2, 2, 2, REG_STAGED>(p, relu, num_cus, s);
     case 10: return launch_grouped<128, 128, 2, 2, 2, REG_STAGED>(p, relu, num_cus, s);
+    case 2:
+        if (p.K % BK != 0) {
+            set_error("64x128 tiles need K (%d) to be a multiple of %d", p.K, BK);
+            return MOE_ERR_UNSUPPORTED;
+        }
+        return launch_grouped_dtl<64, 128, 1, 4, 2, 2, false, 0>(p, relu, num_cus, s);
     case 22: return launch_grouped_dtl<64, 128, 1, 4, 2, 3, false, 8>(p, relu, num_cus, s);
     case 23: return launch_grouped_dtl<32, 128, 1, 4, 2, 3, true, 8>(p, relu, num_cus, s);
     case 24: return launch_grouped_dtl<32, 128, 1, 4, 2, 3, false, 8>(p, relu, num_cus, s);

@@ -1,0 +1,58 @@
+"""The expert GEMM's tile shapes that only some sizes reach, against the fp64 oracle.  Each case names the shape it is
+for and is checked against a copy of the choice, so that it cannot drift to another one."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import moe_oracle as orc
+from paper_2303_06182_amd import binding, workloads as wl
+from helpers import TOL, norm_max_err, to_np, worst_row_rms_rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+def bf16_shape(n_rows, E, N, K, cus):
+    """gemm_bf16_variant (gemm_bf16.hip), N and K whole K tiles."""
+    avg, width = n_rows // E, min(N, K)
+    panels, heavy = E * width // 256, E * N * K >= 1 << 29
+    if avg >= 192 or (heavy and avg >= (112 if width >= 2048 else 128)):
+        return "256x256"
+    if heavy and panels >= 2 * cus:
+        return "128x256" if avg >= 18 else "32x128"
+    if 4 * panels <= cus:
+        return "128x128" if avg >= 48 else "32x128"
+    if not heavy and avg < 64:
+        return "64x128" if avg >= 34 else "32x128"
+    return "128x128" if avg >= 30 else "32x128"
+
+
+def ragged(E, edges, lo, hi, seed):
+    """Rows per expert: the edges first, the rest spread over lo ... hi."""
+    rng = np.random.default_rng(seed)
+    return list(edges) + [int(c) for c in rng.integers(lo, hi + 1, E - len(edges))]
+
+
+def run(shape, counts, D, F):
+    """One FFN call with biases; idle experts' weights are NaN.  The reference covers the first experts (the edges)."""
+    print("tile shape", shape, len(counts), D, F, sum(counts), flush=True)
+    E, N = len(counts), int(sum(counts))
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert bf16_shape(N, E, F, D, cus) == shape
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    g = torch.Generator(device="cuda").manual_seed(7)
+    t = lambda s, std: torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=g)
+    xp, w1, w2, b1, b2 = t((N, D), 1.0), t((E, F, D), D ** -0.5), t((E, D, F), F ** -0.5), t((E, F), 0.5), t((E, D), 0.5)
+    idle = [e for e, c in enumerate(counts) if c == 0]
+    w1[idle], w2[idle] = float("nan"), float("nan")
+    yp = to_np(binding.MoeLayer(N, D, F, E, 1, "bf16").moe_expert_ffn(xp, torch.from_numpy(offsets).cuda(), w1, w2, b1, b2))
+    assert np.all(np.isfinite(yp))
+    n = min(E, 12)
+    rows = int(offsets[n])
+    w1, w2 = (w[:n].nan_to_num().cpu() for w in (w1, w2))
+    ref = orc.expert_ffn(xp[:rows].cpu(), offsets[:n + 1], w1, w2, b1[:n].cpu(), b2[:n].cpu())
+    assert norm_max_err(yp[:rows], ref) <= TOL["bf16"]
+    assert worst_row_rms_rel_err(yp[:rows], ref) <= 2.0 ** -7
+
+
+def test_64x128():
+    run("64x128", ragged(80, [0, 1, 63, 64, 65, 33, 0, 127, 128, 129], 20, 60, 1), 256, 320)
