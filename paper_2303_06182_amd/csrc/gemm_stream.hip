@@ -364,7 +364,10 @@ static int stream_steps(int K, int W)
 // 1024 -> 4096 and 64 experts 512 -> 2048, top-2, 1 ... 6144 tokens; us, this kernel / the tiled one:
 //  * bf16: only while the tiled kernel's 32 x 128 tiles are fewer than 1.5 per CU (1 token 14.5 / 98.6, 8 tokens
 //    94 / 121 on the 2048 layer's second GEMM); from there on that kernel reads whole lines with the non-temporal
-//    policy (6.3 TB/s) and this one cannot (1.9 tiles per CU 94 / 80, 64 tokens 494 / 447).
+//    policy (6.3 TB/s) and this one cannot (1.9 tiles per CU 94 / 80, 64 tokens 494 / 447).  Between 1 and 1.5 tiles per CU
+//    only up to 8 rows per expert on average: with more, tiles of 17 ... 32 rows come up (16 experts 2048 -> 8192, second GEMM:
+//    8 rows 112 / 133, 12 rows even 117 / 132, skewed 160 / 135; 8 experts, 36 rows 123 / 108).  And not for K below 256,
+//    where a wave has a step or none (a layer of 64 experts 64 -> 64, 512 tokens: 34.9 / 31.1).
 //  * e4m3 and mxfp4: up to 64 / 128 rows in all, or while the tiled kernel has at most one 128-column / two 256-column
 //    tiles per CU (rows 1 token: 11 / 54 and 10 / 82 on the 2048 layer's second GEMM; 16 tokens 84 / 90 and 51 / 75 on
 //    its first).  With more rows it is a matter of their spread: a tile of 17 ... 32 rows reads its activations 16 rows at a
@@ -375,7 +378,8 @@ template <int BQ>
 static bool stream_pays(const GemmParams &p, int num_cus, int64_t m_up)
 {
     const int64_t tiles = m_up * ceil_div(p.N, BQ == 4 ? 256 : 128);
-    if (BQ == 0) return 2 * tiles < 3 * (int64_t)num_cus;
+    if (BQ == 0)
+        return p.K >= 256 && (tiles <= num_cus || (2 * tiles < 3 * (int64_t)num_cus && p.M <= 8 * (int64_t)p.num_experts));
     if (BQ == 8) return p.M <= 64 || tiles <= num_cus;
     return p.M <= 128 || tiles <= 2 * (int64_t)num_cus;
 }

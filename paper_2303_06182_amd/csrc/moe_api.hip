@@ -370,6 +370,7 @@ static int run_expert_ffn(moe_handle_t *h, const void *xp, const FfnExtra &ex, c
     p.tile_row = tile_row;
     p.num_tiles = num_tiles;
     p.max_m_tiles = max_tiles;
+    p.num_experts = c.E;
     p.M = (int)n_rows;
     p.a_zero_row = -1;
     // The first GEMM leaves a zero row behind H's n_rows rows (hbuf has room for it); the second reads it for the

@@ -32,6 +32,8 @@ RAGGED = [
     ([64, 0, 130, 50], 200, 328, True),             # 64-row tiles
     ([100, 257, 0, 60, 128], 1000, 136, False),     # 128-row tiles
     ([300, 0, 513, 1], 264, 456, True),             # 256-row tiles and their tail launch
+    ([1, 0, 17, 33], 264, 328, True),               # streaming form, eight waves: fewer steps of K than waves
+    ([1, 0, 17, 33, 8, 0, 2, 31] * 2, 264, 1032, True),     # ... four waves and 32 columns in the first GEMM
 ]
 
 
