@@ -1237,8 +1237,10 @@ int gemm_bf16_variant_w8(int64_t n_rows, int E)
 {
     const int64_t avg = E > 0 ? n_rows / E : n_rows;
     // 64-row tiles, us against 32-row ones (128 experts 2048 -> 8192 / 64 experts 1024 -> 4096): 24 rows 942 / 993 and
-    // 165 / 151, 36 rows 998 / 1250 and 171 / 203
-    return avg >= 28 ? 22 : avg >= kNtRows ? 24 : 23;
+    // 165 / 151, 36 rows 998 / 1250 and 171 / 203.  With fewer experts their smaller number counts for more, above all
+    // where the rows are spread unevenly: 32 experts 2048 -> 8192, skewed, 30 rows 285 / 267, 36 rows 287 / 312; 8 experts
+    // 512 -> 2048, 36 rows 44 / 41; 8 experts 2048 -> 8192, 32 rows even 112 / 108, skewed 117 / 106; 16 experts, 44 rows 188 / 176.
+    return avg >= (E >= 64 ? 28 : E >= 32 ? 34 : 48) ? 22 : avg >= kNtRows ? 24 : 23;
 }
 
 // 4-bit weights: 43 = 32x256, 48 = 64x256, three LDS stages each plus the two scale buffers (32x256: 44 KB,
