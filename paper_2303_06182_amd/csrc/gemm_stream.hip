@@ -373,14 +373,22 @@ static int stream_steps(int K, int W)
 //    its first).  With more rows it is a matter of their spread: a tile of 17 ... 32 rows reads its activations 16 rows at a
 //    time, four times slower per byte than whole lines, so that evenly spread rows still gain (256 tokens over
 //    128 experts, mxfp4: 200 / 224) but a few hot experts cost more than that (same layer, skewed, 128 tokens: e4m3 304 / 185,
-//    mxfp4 162 / 111).  The host does not know the spread.
+//    mxfp4 162 / 111).  The host does not know the spread, but the mean bounds it:
+//    e4m3, up to half a tile per CU: any (8 experts 512 -> 2048, 24 rows, second GEMM 9 / 18, skewed 13 / 18); up to
+//    one: 20 rows per expert (second GEMM, even, skewed, more skewed; 8 experts 2048 -> 8192, 20 rows
+//    39 / 55, 43 / 54, 60 / 54, 24 rows 45 / 54, 60 / 55, 60 / 54; 32 experts 512 -> 2048, 24 rows 19 / 18 for all); else up to 64
+//    rows, one per expert (32 experts 2048 -> 8192, 2 rows, second GEMM 87 / 81, 83 / 78, 79 / 63; 8 experts, 4 rows, first
+//    33 / 30), or two with less than 1.5 tiles per CU (16 experts 2048 -> 8192, second GEMM 46 / 56).
 template <int BQ>
 static bool stream_pays(const GemmParams &p, int num_cus, int64_t m_up)
 {
-    const int64_t tiles = m_up * ceil_div(p.N, BQ == 4 ? 256 : 128);
+    const int64_t tiles = m_up * ceil_div(p.N, BQ == 4 ? 256 : 128), E = p.num_experts;
     if (BQ == 0)
-        return p.K >= 256 && (tiles <= num_cus || (2 * tiles < 3 * (int64_t)num_cus && p.M <= 8 * (int64_t)p.num_experts));
-    if (BQ == 8) return p.M <= 64 || tiles <= num_cus;
+        return p.K >= 256 && (tiles <= num_cus || (2 * tiles < 3 * (int64_t)num_cus && p.M <= 8 * E));
+    if (BQ == 8) {
+        if (tiles <= num_cus) return 2 * tiles <= num_cus || p.M <= 20 * E;
+        return p.M <= 64 && p.M <= (2 * tiles < 3 * (int64_t)num_cus ? 2 * E : E);
+    }
     return p.M <= 128 || tiles <= 2 * (int64_t)num_cus;
 }
 
