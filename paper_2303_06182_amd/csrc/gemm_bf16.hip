@@ -1252,12 +1252,16 @@ int gemm_bf16_variant_w8(int64_t n_rows, int E)
 // 128 K tiles at about 0.65 us each, whatever the tile width or pipeline depth: only a split along K
 // would shorten it.)
 // 64-row tiles, us against 32-row ones: 128 experts 2048 -> 8192: 36 rows per expert 774 / 726, 64 rows 939 / 1113; 16
-// experts 1024 -> 4096, whose 64 weight panels leave the chip to few tiles: 64 rows 95 / 80, 100 rows 97 / 99.
+// experts 1024 -> 4096, whose 64 weight panels leave the chip to few tiles: 64 rows 95 / 80, 100 rows 97 / 99.  At 44 rows they
+// gain on evenly spread rows only (even, skewed, more skewed: 32 experts 2048 -> 8192 210 / 236, 251 / 232, 259 / 238; 64
+// experts 1024 -> 4096 137 / 141, 151 / 142, 157 / 145), at 56 on all (255 / 267, 265 / 281, 266 / 268; 155 / 159, 160 / 165, 168 / 164).
+// From 2^30 weights per GEMM on, reading them once instead of twice pays at 44 (64 experts 2048 -> 8192 346 / 453, 422 / 444,
+// 468 / 442; 128 experts 701 / 812, 773 / 794, 874 / 847).
 int gemm_bf16_variant_w4(int64_t n_rows, int E, int N, int K, int num_cus)
 {
     const int64_t avg = E > 0 ? n_rows / E : n_rows;
     const int64_t panels = (int64_t)E * (N < K ? N : K) / 256;
-    return avg >= (4 * panels > num_cus ? 44 : 96) ? 48 : avg >= kNtRows ? 44 : 43;
+    return avg >= (4 * panels <= num_cus ? 96 : (int64_t)E * N * K >= 2 * kHeavyWeights ? 44 : 56) ? 48 : avg >= kNtRows ? 44 : 43;
 }
 
 // K ranges for the fp32-output plain GEMM (the gate): 1 unless the 32-row tiles would leave most of the
