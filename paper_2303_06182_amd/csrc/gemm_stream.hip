@@ -379,6 +379,11 @@ static int stream_steps(int K, int W)
 //    39 / 55, 43 / 54, 60 / 54, 24 rows 45 / 54, 60 / 55, 60 / 54; 32 experts 512 -> 2048, 24 rows 19 / 18 for all); else up to 64
 //    rows, one per expert (32 experts 2048 -> 8192, 2 rows, second GEMM 87 / 81, 83 / 78, 79 / 63; 8 experts, 4 rows, first
 //    33 / 30), or two with less than 1.5 tiles per CU (16 experts 2048 -> 8192, second GEMM 46 / 56).
+//    mxfp4, up to one tile per CU: any (16 experts 2048 -> 8192, 30 rows, second GEMM 63 / 80 for every spread); up to two: 16 rows
+//    per expert (second GEMM, even, skewed, more skewed; 64 experts 1024 -> 4096, 16 rows 40 / 44, 51 / 54, 53 / 55, 30 rows
+//    63 / 57, 62 / 56, 71 / 56; 32 experts 2048 -> 8192, 24 rows 99 / 104, 100 / 103, 115 / 103); else up to 64 rows, 128 with
+//    less than six tiles per CU, two per expert (first GEMM; 64 experts 1024 -> 4096, 2 rows 25 / 35, 26 / 35, 24 / 25; 128
+//    experts 2048 -> 8192, 128 rows 119 / 131, 111 / 124, 94 / 76; 16 experts 2048 -> 8192, 8 rows 37 / 35, 38 / 35, 49 / 36).
 template <int BQ>
 static bool stream_pays(const GemmParams &p, int num_cus, int64_t m_up)
 {
@@ -389,7 +394,8 @@ static bool stream_pays(const GemmParams &p, int num_cus, int64_t m_up)
         if (tiles <= num_cus) return 2 * tiles <= num_cus || p.M <= 20 * E;
         return p.M <= 64 && p.M <= (2 * tiles < 3 * (int64_t)num_cus ? 2 * E : E);
     }
-    return p.M <= 128 || tiles <= 2 * (int64_t)num_cus;
+    if (tiles <= 2 * (int64_t)num_cus) return tiles <= num_cus || p.M <= 16 * E;
+    return p.M <= (tiles < 6 * (int64_t)num_cus ? 128 : 64) && p.M <= 2 * E;
 }
 
 template <int BQ, bool RELU>
