@@ -61,10 +61,14 @@ namespace moe355 {
 static constexpr int BK = 64;
 static constexpr int GROUP_M = 4;
 static constexpr int REG_STAGED = 0;  // value of the STAGES template argument that selects the register-staged pipeline
+// cache policy of the direct-to-LDS weight loads (template argument NT): plain, non-temporal, or non-temporal for the tiles
+// that are their expert's only one
+static constexpr int NT_NONE = 0, NT_ALL = 1, NT_SOLE = 2;
 static constexpr int DTL16 = -1;      // ... and the one that selects 16x16x32 MFMAs out of a ring of K-step slots filled by direct-to-LDS loads
 
 struct TileInfo {
     int row0, row_end, expert, n0;
+    int row_begin;  // the expert's first row (NT_SOLE only)
     int kt0, split;  // plain mode with split K: first K tile and index of this block's K range
 };
 
@@ -76,7 +80,7 @@ struct TileInfo {
 // elements along K; the scale is applied while widening (v_cvt_scalef32_pk_bf16_fp4), the result is
 // again exactly a bf16 value.  8 and 4: direct-to-LDS pipeline only.
 template <int BM, int BN, int WM, int WN, bool OUT_F32, bool RELU, bool GROUPED, bool KFULL, int MINB, int STAGES,
-          bool NT = false, int BQ = 0>
+          int NT = 0, int BQ = 0>
 __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams p)
 {
     constexpr int THREADS = WM * WN * 64;
@@ -164,7 +168,10 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
         TileInfo t;
         if (GROUPED) {
             uniform_load2(p.tile_expert + mt, p.tile_row + mt, t.expert, t.row0);
-            t.row_end = uniform_load(p.offsets + t.expert + 1);
+            if constexpr (NT == NT_SOLE)
+                uniform_load2(p.offsets + t.expert, p.offsets + t.expert + 1, t.row_begin, t.row_end);
+            else
+                t.row_end = uniform_load(p.offsets + t.expert + 1);
         } else {
             t.expert = 0;
             t.row0 = mt * BM;
@@ -504,7 +511,9 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
         // the accumulators of the largest tile.
         const uint16_t *a_base, *b_base;
         int a_off[A_IT], b_off[B_IT];
+        int b_rows = 0;  // NT_SOLE: rows of the expert the loads are at
         auto set_ptrs = [&](const TileInfo &ti) {
+            if constexpr (NT == NT_SOLE) b_rows = __builtin_amdgcn_readfirstlane(ti.row_end - ti.row_begin);
             // weights of expert e sit in slot b_slot[e] of the weight array when experts are buffered
             const uint16_t *Bg = Bg0 + (int64_t)((GROUPED && p.b_slot) ? uniform_load(p.b_slot + ti.expert) : ti.expert) * p.strideB;
             int gr0 = 0, gn0 = 0;
@@ -576,17 +585,22 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
                 }
             }
         };
-        // The weights' cache policy (2 = non-temporal; chosen by the variant).
-        constexpr int B_CPOL = NT ? 2 : 0;
         auto issue = [&](int kt, int buf) {
 #pragma unroll
             for (int i = 0; i < A_IT; ++i)
                 __builtin_amdgcn_global_load_lds((const glb_void *)(a_base + (a_off[i] + kt * BK)),
                                                  (lds_void *)(sA + buf * BM * BK + (wave * A_IT + i) * 8 * BK), 16, 0, 0);
+            if (NT == NT_ALL || (NT == NT_SOLE && b_rows <= BM)) {
 #pragma unroll
-            for (int i = 0; i < B_IT; ++i)
-                __builtin_amdgcn_global_load_lds((const glb_void *)(b_base + (b_off[i] + kt * (BQ != 0 ? 512 : BK))),
-                                                 (lds_void *)(sB + buf * BTILE + (wave * B_IT + i) * 8 * BK), 16, 0, B_CPOL);
+                for (int i = 0; i < B_IT; ++i)
+                    __builtin_amdgcn_global_load_lds((const glb_void *)(b_base + (b_off[i] + kt * (BQ != 0 ? 512 : BK))),
+                                                     (lds_void *)(sB + buf * BTILE + (wave * B_IT + i) * 8 * BK), 16, 0, 2);
+            } else {
+#pragma unroll
+                for (int i = 0; i < B_IT; ++i)
+                    __builtin_amdgcn_global_load_lds((const glb_void *)(b_base + (b_off[i] + kt * (BQ != 0 ? 512 : BK))),
+                                                     (lds_void *)(sB + buf * BTILE + (wave * B_IT + i) * 8 * BK), 16, 0, 0);
+            }
         };
         // The loads run STAGES-1 K tiles ahead of the MFMAs along the block's whole sequence of
         // (tile, K tile) pairs, so the pipeline never drains between tiles and an epilogue's stores
@@ -1148,7 +1162,7 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
 }
 
 template <int BM, int BN, int WM, int WN, bool OUT_F32, bool RELU, bool GROUPED, bool KFULL, int MINB, int STAGES,
-          bool NT = false, int BQ = 0>
+          int NT = 0, int BQ = 0>
 static int launch_k(const GemmParams &p_in, int num_cus, hipStream_t s, int *main_grid)
 {
     GemmParams p = p_in;
@@ -1212,20 +1226,23 @@ static int launch_one(const GemmParams &p, int num_cus, hipStream_t s, int *main
 
 // grouped GEMM on the direct-to-LDS pipeline, bf16 (BQ = 0), 8-bit (8) or 4-bit (4) weights (K a multiple of the K tile:
 // checked by the caller)
-template <int BM, int BN, int WM, int WN, int MINB, int STAGES, bool NT, int BQ>
+template <int BM, int BN, int WM, int WN, int MINB, int STAGES, int NT, int BQ>
 static int launch_grouped_dtl(const GemmParams &p, bool relu, int num_cus, hipStream_t s)
 {
     return relu ? launch_k<BM, BN, WM, WN, false, true, true, true, MINB, STAGES, NT, BQ>(p, num_cus, s, nullptr)
                 : launch_k<BM, BN, WM, WN, false, false, true, true, MINB, STAGES, NT, BQ>(p, num_cus, s, nullptr);
 }
 
-// Below this many rows per expert the 32-row tiles read the weights with the non-temporal policy (variants 3, 23, 43): an
-// expert then has one row tile, nothing is used twice, and such a stream gets 6.3 TB/s out of HBM where the plain one
-// gets 5.7 (64 tokens over 128 experts of 2048 -> 8192: layer 0.986 -> 0.898 ms, e4m3 0.536 -> 0.496).  Experts with several
-// row tiles share their weights through the caches: 4099 tokens over 512 experts of 1024 -> 4096, 16 rows each and skewed,
-// gain 2 % on repeated passes (1.645 -> 1.612) but lose 6 % on a first one (1.732 -> 1.837), and 64-row tiles of 4-bit weights
-// over 256 rows 0.402 -> 0.412; those (4, 24, 44 and the taller shapes) read plainly.
-static constexpr int kNtRows = 8;
+// Below kNtRows rows per expert on average the 32-row tiles read the weights with the non-temporal policy: an expert with
+// one row tile uses them once, and such a stream gets 6.3 TB/s out of HBM where the plain one gets 5.7.  128 experts
+// 2048 -> 8192, layer in ms, plain / non-temporal, 1, 2, 4, 7 rows per expert: 0.95 / 0.87, 1.28 / 1.18, 1.50 / 1.37, 1.53 / 1.41;
+// e4m3 0.50 / 0.47, 0.67 / 0.62, 0.77 / 0.71, 0.80 / 0.75.  A hot expert's row tiles share its weights through the caches; from
+// kNtSoleRows on (variants 5, 25) its tiles read plainly: 512 experts 1024 -> 4096, 1792 skewed tokens 676 us, with all tiles
+// non-temporal 788, with none 745.  Below it (3, 23) the choice costs the 0.5 % it gains.  4-bit weights (43): all, there
+// the choice costs 1 % and gains nothing.  From kNtRows on the plain variants (4, 24, 44) run: with 16 skewed rows over 512
+// experts of 1024 -> 4096 the policy, taken for all tiles, gained 2 % on repeated passes (1.645 -> 1.612) and lost 6 % on a first one
+// (1.732 -> 1.837), and 64-row tiles of 4-bit weights over 256 rows 0.402 -> 0.412.
+static constexpr int kNtRows = 8, kNtSoleRows = 2;
 // Weights of one GEMM (all experts) from which on its time is that of streaming them
 static constexpr int64_t kHeavyWeights = 1ll << 29;
 
@@ -1240,7 +1257,7 @@ int gemm_bf16_variant_w8(int64_t n_rows, int E)
     // 165 / 151, 36 rows 998 / 1250 and 171 / 203.  With fewer experts their smaller number counts for more, above all
     // where the rows are spread unevenly: 32 experts 2048 -> 8192, skewed, 30 rows 285 / 267, 36 rows 287 / 312; 8 experts
     // 512 -> 2048, 36 rows 44 / 41; 8 experts 2048 -> 8192, 32 rows even 112 / 108, skewed 117 / 106; 16 experts, 44 rows 188 / 176.
-    return avg >= (E >= 64 ? 28 : E >= 32 ? 34 : 48) ? 22 : avg >= kNtRows ? 24 : 23;
+    return avg >= (E >= 64 ? 28 : E >= 32 ? 34 : 48) ? 22 : avg >= kNtRows ? 24 : avg >= kNtSoleRows ? 25 : 23;
 }
 
 // 4-bit weights: 43 = 32x256, 48 = 64x256, three LDS stages each plus the two scale buffers (32x256: 44 KB,
@@ -1283,14 +1300,14 @@ int gemm_bf16_variant_block_m(int v)
     switch (v) {
     case 10: case 11: return 128;
     case 2: case 22: case 48: return 64;
-    case 3: case 4: case 23: case 24: case 43: case 44: return 32;
+    case 3: case 4: case 5: case 23: case 24: case 25: case 43: case 44: return 32;
     default: return 256;
     }
 }
 
 // Tile shapes of the grouped GEMM.  variant -> (BM, BN, waves, pipeline)
 //   8: 256x256, 8 waves, ring    11: 128x256, 8 waves, ring    10: 128x128, 4 waves, register-staged
-//   2: 64x128, 4 waves, direct-to-LDS    3, 4: 32x128, the same, weights read non-temporally / plainly
+//   2: 64x128, 4 waves, direct-to-LDS    3, 4, 5: 32x128, the same, weights read non-temporally, plainly, by tile (kNtRows)
 // By the average number of rows per expert, by how many 256-column weight panels there are (E * min(D, F) / 256, the
 // same for both GEMMs of a layer), and by how many weights a GEMM streams.  Where the panels alone fill the chip, one
 // tall tile per expert beats two of half its height as soon as most experts need two of those, and with fewer
@@ -1329,7 +1346,7 @@ int gemm_bf16_variant(int64_t n_rows, int E, int N, int K, int num_cus)
     const bool whole = N % BK == 0 && K % BK == 0;
     const bool heavy = whole && (int64_t)E * N * K >= kHeavyWeights;
     if (avg >= 192 || (heavy && avg >= (width >= 2048 ? 112 : 128))) return 8;
-    const int small = avg >= kNtRows ? 4 : 3;
+    const int small = avg >= kNtRows ? 4 : avg >= kNtSoleRows ? 5 : 3;
     if (heavy && panels >= 2 * (int64_t)num_cus) return avg >= 18 ? 11 : small;
     if (4 * panels <= num_cus) return avg >= 48 ? 10 : small;
     if (whole && !heavy && avg < 64) return avg >= 34 ? 2 : small;
@@ -1408,19 +1425,21 @@ int launch_gemm_bf16(const GemmParams &p, bool grouped, int variant, bool out_f3
             set_error("64x128 tiles need K (%d) to be a multiple of %d", p.K, BK);
             return MOE_ERR_UNSUPPORTED;
         }
-        return launch_grouped_dtl<64, 128, 1, 4, 2, 2, false, 0>(p, relu, num_cus, s);
-    case 22: return launch_grouped_dtl<64, 128, 1, 4, 2, 3, false, 8>(p, relu, num_cus, s);
-    case 23: return launch_grouped_dtl<32, 128, 1, 4, 2, 3, true, 8>(p, relu, num_cus, s);
-    case 24: return launch_grouped_dtl<32, 128, 1, 4, 2, 3, false, 8>(p, relu, num_cus, s);
-    case 43: return launch_grouped_dtl<32, 256, 1, 4, 2, 3, true, 4>(p, relu, num_cus, s);
-    case 44: return launch_grouped_dtl<32, 256, 1, 4, 2, 3, false, 4>(p, relu, num_cus, s);
-    case 48: return launch_grouped_dtl<64, 256, 1, 4, 2, 3, false, 4>(p, relu, num_cus, s);
-    case 3: case 4:
+        return launch_grouped_dtl<64, 128, 1, 4, 2, 2, NT_NONE, 0>(p, relu, num_cus, s);
+    case 22: return launch_grouped_dtl<64, 128, 1, 4, 2, 3, NT_NONE, 8>(p, relu, num_cus, s);
+    case 23: return launch_grouped_dtl<32, 128, 1, 4, 2, 3, NT_ALL, 8>(p, relu, num_cus, s);
+    case 24: return launch_grouped_dtl<32, 128, 1, 4, 2, 3, NT_NONE, 8>(p, relu, num_cus, s);
+    case 25: return launch_grouped_dtl<32, 128, 1, 4, 2, 3, NT_SOLE, 8>(p, relu, num_cus, s);
+    case 43: return launch_grouped_dtl<32, 256, 1, 4, 2, 3, NT_ALL, 4>(p, relu, num_cus, s);
+    case 44: return launch_grouped_dtl<32, 256, 1, 4, 2, 3, NT_NONE, 4>(p, relu, num_cus, s);
+    case 48: return launch_grouped_dtl<64, 256, 1, 4, 2, 3, NT_NONE, 4>(p, relu, num_cus, s);
+    case 3: case 4: case 5:
         if (p.K % BK != 0)
             return relu ? launch_k<32, 128, 1, 4, false, true, true, false, 2, REG_STAGED>(p, num_cus, s, nullptr)
                         : launch_k<32, 128, 1, 4, false, false, true, false, 2, REG_STAGED>(p, num_cus, s, nullptr);
-        return variant == 3 ? launch_grouped_dtl<32, 128, 1, 4, 2, 2, true, 0>(p, relu, num_cus, s)
-                            : launch_grouped_dtl<32, 128, 1, 4, 2, 2, false, 0>(p, relu, num_cus, s);
+        return variant == 3 ? launch_grouped_dtl<32, 128, 1, 4, 2, 2, NT_ALL, 0>(p, relu, num_cus, s)
+               : variant == 5 ? launch_grouped_dtl<32, 128, 1, 4, 2, 2, NT_SOLE, 0>(p, relu, num_cus, s)
+                              : launch_grouped_dtl<32, 128, 1, 4, 2, 2, NT_NONE, 0>(p, relu, num_cus, s);
     default:
         set_error("unsupported grouped GEMM variant %d", variant);
         return MOE_ERR_UNSUPPORTED;

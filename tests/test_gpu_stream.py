@@ -23,6 +23,7 @@ CASES = [
     (SPARSE, 512, 2048, True),      # mxfp4: one and four waves with 64 columns each
     (SPARSE, 1024, 512, False),     # ... two waves and one
     ([2] * 64, 2048, 512, True),    # more tiles than resident blocks
+    ([0, 1, 31, 32, 33, 64, 65, 200] + [3, 0, 1, 5] * 30, 256, 512, True),   # tiled: weights' cache policy by the expert's rows
 ]
 
 # bf16 with K that ends inside a K tile, for every tile height; the neighbouring rows hold NaN (idle experts)
