@@ -439,7 +439,16 @@ __global__ __launch_bounds__(kThreads) void route_rank_kernel(const int32_t *__r
 // below it in its wave with the same expert); waves add their counts to the running per-expert
 // totals one after the other, so the order is that of a, as in the kernels above.
 // ------------------------------------------------------------------------------------------------
-static constexpr int kSmallRouteMax = 1024;  // assignments
+static constexpr int kSmallRouteMax = 1024;  // assignments: one round of the block
+
+// Assignments up to which that block also beats the three launches.  A round costs by the distinct experts of a wave: us by 1100,
+// 2048, 3072, 4096 assignments, against 17.5 ... 19 for the three launches: 8 experts 13, 13, 13, 17; 16 experts 13, 13, 17, 22; 24 experts
+// 13, 15, 22, 28; 32 experts 14, 17, 25, 32; 48 experts 16, 20, 29, 37; 64 experts 18, 22, 32, 41.
+static int small_route_max(int E)
+{
+    const int n = 56 * kSmallRouteMax / E;
+    return n < kSmallRouteMax ? kSmallRouteMax : n > 4 * kSmallRouteMax ? 4 * kSmallRouteMax : n;
+}
 
 __device__ __forceinline__ void route_small(const int32_t *idx, int n_assign, int E, int k, int32_t *__restrict__ counts,
                                             int32_t *__restrict__ offsets, int32_t *__restrict__ dst_row,
@@ -609,7 +618,7 @@ bool route_uses_hist(int T, int k) { return (int64_t)T * k > kSmallRouteMax; }
 int launch_route(const int32_t *idx, int T, int E, int k, const RouteOut &o, int32_t *block_hist, hipStream_t s, int hist_tokens)
 {
     ProfScope ps("route", s);  // histogram + prefix + rank together
-    if ((int64_t)T * k <= kSmallRouteMax) {
+    if ((int64_t)T * k <= (hist_tokens > 0 ? kSmallRouteMax : small_route_max(E))) {  // a histogram that is there saves a launch
         hipLaunchKernelGGL(route_small_kernel, dim3(1), dim3(1024), 0, s, idx, T * k, E, k, o);
         MOE_LAUNCH_CHECK("route_small_kernel");
         return MOE_OK;

@@ -167,8 +167,11 @@ def random_idx(T, E, k, seed, skew=False):
 ROUTE_CASES = [(1, 4, 2, False), (64, 128, 2, False), (255, 8, 2, False), (256, 8, 2, True), (257, 16, 1, False),
                (1000, 128, 2, True), (5000, 64, 2, True), (777, 1000, 8, False), (4096, 3, 3, False),
                (3000, 1, 1, False), (20000, 128, 2, True),
-               # around the limit of the single-block kernel for small batches (4096 assignments)
-               (2048, 16, 2, True), (2049, 16, 2, False), (512, 1000, 8, False), (130, 1024, 8, False)]
+               # past one round of the single-block kernel for small batches (1024 assignments)
+               (2048, 16, 2, True), (2049, 16, 2, False), (512, 1000, 8, False), (130, 1024, 8, False),
+               # around that kernel's limit: 1024 assignments from 56 experts on, 56 * 1024 / E below, 4096 at most
+               (512, 64, 2, True), (513, 64, 2, True), (128, 1000, 8, False), (1792, 16, 2, True), (1793, 16, 2, True),
+               (4096, 8, 1, True), (4097, 8, 1, True), (2048, 2, 2, False)]
 
 
 @pytest.mark.parametrize("T,E,k,skew", ROUTE_CASES)
@@ -185,7 +188,7 @@ def test_route_counts_bit_exact(dev, T, E, k, skew):
     np.testing.assert_array_equal(to_np(src_tok), rs)
 
 
-@pytest.mark.parametrize("T", [700, 5000])   # below and above the single-block kernel's 4096 assignments
+@pytest.mark.parametrize("T", [300, 700, 5000])   # one and two rounds of the single-block kernel (its limit here is 3584), three launches
 def test_route_with_a_repeated_expert_inside_a_token(dev, T):
     """The k experts of a token are distinct by construction (top-k selection, Sec. 2.3); handed a token that
     names one expert twice, the routing still has to be a permutation -- both kernels rank such assignments
