@@ -263,8 +263,8 @@ FFN_CASES = [
     ("bf16", [64] * 16, 512, 1024, False),
     ("f32", [100, 0, 37, 64, 1], 64, 128, True),
     ("f32", [300], 128, 256, False),
-    # fp32: D a multiple of 32 but F not (first GEMM on the MFMA kernel, second on the vector-FMA kernel),
-    # and the other way round; many K tiles, several M tiles per expert with ragged ends
+    # fp32: K a multiple of a step's 32 k in the first GEMM and not in the second, and the other way round;
+    # many steps, several M tiles per expert with ragged ends
     ("f32", [65, 0, 130, 1], 96, 72, True),
     ("f32", [65, 0, 130, 1], 72, 96, True),
     ("f32", [200, 63, 64, 0, 129], 1024, 160, False),

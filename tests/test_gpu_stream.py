@@ -20,8 +20,8 @@ CASES = [
     ([1], 2048, 1024, False),       # the smallest call
     ([2, 0, 1], 1024, 4096, True),
     (EDGES, 256, 192, False),       # K the kernel does not serve (some formats): the tiled one takes over
-    (SPARSE, 512, 2048, True),      # mxfp4: one and four waves with 64 columns each
-    (SPARSE, 1024, 512, False),     # ... two waves and one
+    (SPARSE, 512, 2048, True),      # mxfp4: one wave with 64 columns, four with 32
+    (SPARSE, 1024, 512, False),     # ... four waves, one
     ([2] * 64, 2048, 512, True),    # more tiles than resident blocks
     ([0, 1, 31, 32, 33, 64, 65, 200] + [3, 0, 1, 5] * 30, 256, 512, True),   # tiled: weights' cache policy by the expert's rows
 ]
@@ -30,7 +30,7 @@ CASES = [
 RAGGED = [
     ([1, 0, 17, 33], 8, 72, True),                  # K below one step
     ([3, 0, 20] * 100, 72, 1032, False),            # 32-row tiles, more of them than the streaming form takes
-    ([64, 0, 130, 50], 200, 328, True),             # 64-row tiles
+    ([64, 0, 130, 50], 200, 328, True),             # 128-row tiles, few rows per expert
     ([100, 257, 0, 60, 128], 1000, 136, False),     # 128-row tiles
     ([300, 0, 513, 1], 264, 456, True),             # 256-row tiles and their tail launch
     ([1, 0, 17, 33], 264, 328, True),               # streaming form, eight waves: fewer steps of K than waves
@@ -49,7 +49,13 @@ def test_expert_ffn_stream(case, weights):
     run_ffn(weights, *CASES[case])
 
 
-@pytest.mark.parametrize("T,k,E", [(512, 2, 7), (1025, 1, 7), (513, 2, 300)])   # around the single-block routing kernel's limit
+# mxfp4 with 64 columns: four, two and one waves (K a multiple of 2048, 1024, 512), tiles below and above 16 rows
+@pytest.mark.parametrize("D", [2048, 1024, 512])
+def test_expert_ffn_stream_mxfp4_wide(D):
+    run_ffn("mxfp4", [17, 0, 31, 1, 16, 32, 0, 5], D, 4096, True)
+
+
+@pytest.mark.parametrize("T,k,E", [(512, 2, 7), (1025, 1, 7), (513, 2, 300)])   # around one round of the single-block routing kernel
 def test_route_small_limit(T, k, E):
     g = torch.Generator().manual_seed(T)
     idx = torch.stack([torch.randperm(E, generator=g)[:k] for _ in range(T)]).to(torch.int32)

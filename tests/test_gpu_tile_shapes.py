@@ -56,3 +56,39 @@ def run(shape, counts, D, F):
 
 def test_64x128():
     run("64x128", ragged(80, [0, 1, 63, 64, 65, 33, 0, 127, 128, 129], 20, 60, 1), 256, 320)
+
+
+EDGES = [0, 1, 127, 128, 129, 257, 33, 0, 64, 65, 16, 17]   # around the 128-row tile
+
+
+def test_128x256_ring():
+    run("128x256", ragged(512, EDGES, 5, 40, 2), 1088, 1088)   # 17 K tiles, a last column tile of 64
+
+
+def test_256x256_ring_below_192_rows():
+    run("256x256", ragged(512, EDGES, 120, 150, 3), 1088, 1088)
+
+
+def test_layer_on_the_128x256_ring():
+    """Rows gathered from the token array by the first GEMM; the tokens of the fullest expert (several tiles) and a sample of
+    the others against the oracle."""
+    T, D, F, E, k = 6000, 1024, 1088, 512, 2
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    assert bf16_shape(T * k, E, F, D, cus) == "128x256"
+    g = torch.Generator(device="cuda").manual_seed(8)
+    t = lambda s, std: torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=g)
+    x, wg, w1, w2 = t((T, D), 1.0), t((E, D), 10 * D ** -0.5), t((E, F, D), D ** -0.5), t((E, D, F), F ** -0.5)
+    bias = torch.zeros(E, device="cuda")
+    bias[5] = 25.0   # a hot expert
+    m = binding.MoeLayer(T, D, F, E, k, "bf16")
+    r = m.empty_routing(T)
+    y = to_np(m.moe_layer_forward(x, wg, w1, w2, bias, routing_out=r))
+    idx, gw, counts = to_np(r["topk_idx"]), to_np(r["topk_w"]), to_np(r["counts"])
+    hot = int(counts.argmax())
+    assert counts[hot] > 256
+    tok = np.unique(np.concatenate([np.flatnonzero((idx == hot).any(axis=1))[::97], np.arange(0, T, 149)]))
+    used, local = np.unique(idx[tok], return_inverse=True)
+    sel = torch.from_numpy(used).cuda().long()
+    ref = orc.layer_tokens(x[tok].cpu(), w1[sel].cpu(), w2[sel].cpu(), local.reshape(len(tok), k).astype(np.int32), gw[tok])
+    assert norm_max_err(y[tok], ref) <= TOL["bf16"]
+    assert worst_row_rms_rel_err(y[tok], ref) <= 2.0 ** -7
