@@ -112,7 +112,9 @@ def kernel_models(w, counts):
     # gate GEMM with the top-k decision (and the tile histograms) in its epilogue: x and Wg in, indices and
     # weights out; the logits stay in registers, so their 2 x 4*T*E bytes are NOT counted here
     m["gate_topk"] = dict(bytes=T * D * b + E * D * b + 8 * T * k + 4 * ((T + 31) // 32) * E, flops=2 * T * D * E)
-    m["route"] = dict(bytes=12 * N + 4 * E, flops=0)
+    # a decoder step's selection is made in the routing launch: the logits in, the weights out as well
+    fused_topk = m["topk"]["bytes"] if T <= 64 and E % 4 == 0 else 0
+    m["route"] = dict(bytes=12 * N + 4 * E + fused_topk, flops=0)
     m["dispatch"] = dict(bytes=T * D * b + N * D * b + 4 * N, flops=0)
     m["expert_gemm1"] = dict(bytes=e_active * F * D * b + N * D * b + N * F * b, flops=2 * N * D * F)
     m["expert_gemm2"] = dict(bytes=e_active * F * D * b + N * F * b + N * D * b, flops=2 * N * D * F)

@@ -19,15 +19,15 @@
 // ds_read_b128 against 6 clk with an (r & 7) swizzle).
 //
 // Three K pipelines, chosen per tile shape (template argument STAGES):
-//  * ring of K steps (the 256x256 tiles of the grouped GEMM, STAGES = DTL16): v_mfma_f32_16x16x32_bf16
+//  * ring of K steps (the 256x256 and 128x256 tiles of the grouped GEMM, STAGES = DTL16): v_mfma_f32_16x16x32_bf16
 //    instead of the 32x32 blocks, operands straight into LDS, five slots of one 32-wide K step, one
-//    load every seventh MFMA (four per step); described where it is implemented, inside the kernel.
+//    load every seventh MFMA (four per step; 128 rows: two and four); described where it is implemented, inside the kernel.
 //  * direct-to-LDS, whole K tiles (small tiles, the gate): STAGES LDS stages; K tiles go straight from global
 //    memory into LDS (global_load_lds_dwordx4, no register staging), the loads run STAGES-1 K
 //    tiles ahead of the MFMAs and are waited for (vmcnt) only at the barrier that ends an
 //    iteration.  Several such blocks share a CU, so one block's load burst and barrier hide
 //    behind another block's MFMAs.
-//  * register-staged (256- and 128-row tiles, one or two blocks per CU): measured on gfx950, a
+//  * register-staged (256- and 128-row tiles, one or two blocks per CU; every height for K that ends inside a K tile): measured on gfx950, a
 //    vector-memory instruction costs the issuing wave 20-30 clocks of MFMA issue and the CU's
 //    address unit 16 clocks, so a K tile's loads issued as one burst stall every wave while the
 //    matrix units idle, and with only two 64 KB stages in LDS they cannot be issued late either.
@@ -105,7 +105,7 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
     uint16_t *sB = sA + NSTAGE * BM * BK;                   // [NSTAGE][BN*64]
     static_assert(NSTAGE >= 2, "at least two LDS stages");
     static_assert(!D16 || (KFULL && BQ == 0 && !OUT_F32), "the 16x16x32 pipeline: bf16 in and out, K a multiple of the K tile");
-    static_assert(KFULL || RSTAGE || STAGES == 2, "K that ends inside a K tile: register-staged, or the plain two-stage loop");
+    static_assert(KFULL || RSTAGE || (STAGES == 2 && !GROUPED), "K that ends inside a K tile: register-staged, or the gate's two-stage loop");
     static_assert(BQ == 0 || (KFULL && !RSTAGE && GROUPED), "8- and 4-bit weights: grouped direct-to-LDS pipeline, K a multiple of the K tile");
 
     const int tid = threadIdx.x;
@@ -1103,11 +1103,10 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
         }
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no LDS write may outlive the block
     } else {
-        // ---- K not a multiple of the K tile: stage through registers so the tail can be zero filled.
+        // ---- the gate with K no multiple of the K tile: stage through registers so the tail can be zero filled.
         // chunk c = tid + i*THREADS; row = c >> 3, kc = c & 7
         const int kc = tid & 7;
         while (true) {
-            const uint16_t *Bg = Bg0 + (int64_t)((GROUPED && p.b_slot) ? uniform_load(p.b_slot + t.expert) : t.expert) * p.strideB;
             const uint16_t *a_ptr[A_IT];
             const uint16_t *b_ptr[B_IT];
             int a_lds[A_IT], b_lds[B_IT];
@@ -1122,7 +1121,7 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
             for (int i = 0; i < B_IT; ++i) {
                 const int r = (tid + i * THREADS) >> 3;
                 const int gn = min(t.n0 + r, p.N - 1);
-                b_ptr[i] = Bg + (int64_t)gn * p.ldb + kc * 8;
+                b_ptr[i] = Bg0 + (int64_t)gn * p.ldb + kc * 8;
                 b_lds[i] = r * BK + ((kc ^ ((r >> 1) & 7)) << 3);
             }
             uint4 a_reg[A_IT], b_reg[B_IT];
@@ -1218,7 +1217,7 @@ template <int BM, int BN, int WM, int WN, bool OUT_F32, bool RELU, bool GROUPED,
 static int launch_one(const GemmParams &p, int num_cus, hipStream_t s, int *main_grid = nullptr)
 {
     // K a multiple of the K tile: pipelined main loop without a tail predicate; else the register-staged
-    // pipeline zero-fills the last K tile, and the other shapes run a plain two-stage loop
+    // pipeline zero-fills the last K tile, and the gate's shapes run a plain two-stage loop
     return (p.K % BK == 0)
                ? launch_k<BM, BN, WM, WN, OUT_F32, RELU, GROUPED, true, MINB, STAGES>(p, num_cus, s, main_grid)
                : launch_k<BM, BN, WM, WN, OUT_F32, RELU, GROUPED, false, MINB, STAGES == REG_STAGED || STAGES == DTL16 ? REG_STAGED : 2>(p, num_cus, s, main_grid);
@@ -1264,10 +1263,8 @@ int gemm_bf16_variant_w8(int64_t n_rows, int E)
 // three blocks per CU; a fourth stage would leave room for two, 0.141 -> 0.154 ms on the decoder's first
 // GEMM; two stages 0.150).  (Measured on 128 experts of 2048 x 8192
 // with 1 to 64 rows each: 256 columns per tile beat 128 by 25-30 % -- the A tile, re-read once per column
-// tile, weighs as much as a 128-column B tile at 4 bits -- and 512 lost again.
-// With 8 or 16 tokens the second GEMM has fewer tiles than CUs and its time is the K loop of one tile,
-// 128 K tiles at about 0.65 us each, whatever the tile width or pipeline depth: only a split along K
-// would shorten it.)
+// tile, weighs as much as a 128-column B tile at 4 bits -- and 512 lost again.  Where the tiles are fewer than the CUs the
+// time is the K loop of one tile, whatever its width or the pipeline's depth; those calls are gemm_stream.hip's.)
 // 64-row tiles, us against 32-row ones: 128 experts 2048 -> 8192: 36 rows per expert 774 / 726, 64 rows 939 / 1113; 16
 // experts 1024 -> 4096, whose 64 weight panels leave the chip to few tiles: 64 rows 95 / 80, 100 rows 97 / 99.  At 44 rows they
 // gain on evenly spread rows only (even, skewed, more skewed: 32 experts 2048 -> 8192 210 / 236, 251 / 232, 259 / 238; 64

@@ -350,8 +350,8 @@ static int run_expert_ffn(moe_handle_t *h, const void *xp, const FfnExtra &ex, c
 {
     const moe_config_t &c = h->cfg;
     if (n_rows == 0) return MOE_OK;
-    // each GEMM picks its own tile shape (N differs: F for the first, D for the second); the tile
-    // map is rebuilt between them only when the M tile height differs
+    // bf16 GEMMs of a layer share the tile height; the fp32 ones may differ (N and K swap places), and then the tile map is
+    // rebuilt between them
     const int wbits = ex.w1_blk ? 4 : ex.w1_scale ? 8 : 0;
     const int v1 = wbits ? quant_variant(h, wbits, n_rows) : gemm_variant(c.dtype, n_rows, c.E, c.F, c.D, h->num_cus);
     const int v2 = wbits ? v1 : gemm_variant(c.dtype, n_rows, c.E, c.D, c.F, h->num_cus);

@@ -160,10 +160,9 @@ int launch_topk(float *logits, int T, int E, int k, int renorm, int32_t *idx, fl
                 const float *parts = nullptr, int64_t part_stride = 0);
 // block_hist: scratch of route_blocks(T)*E int32
 int route_blocks(int T);
-// true when launch_route for T tokens with k experts each reads per-block histograms (large batches); small
-// ones are routed by one block that needs none
+// true when a histogram left by the gate kernel speeds launch_route up (T tokens with k experts each); smaller
+// batches are routed by one block that needs none
 bool route_uses_hist(int T, int k);
-// hist_tokens > 0: block_hist already holds one histogram row per hist_tokens tokens (a divisor of 256)
 // what the routing step writes; the tile map only with tile_bm > 0
 struct RouteOut {
     int32_t *counts, *offsets, *dst_row, *src_tok;
@@ -171,6 +170,7 @@ struct RouteOut {
     int32_t *tile_expert, *tile_row, *num_tiles;
     int max_m_tiles;
 };
+// hist_tokens > 0: block_hist already holds one histogram row per hist_tokens tokens (a divisor of 256)
 int launch_route(const int32_t *idx, int T, int E, int k, const RouteOut &o, int32_t *block_hist, hipStream_t s, int hist_tokens = 0);
 // top-k and routing in one launch, for a decoder step
 int launch_route_topk(float *logits, int T, int E, int k, int renorm, int32_t *idx, float *w, hipStream_t s, int n_parts,
