@@ -58,6 +58,9 @@
 
 namespace moe355 {
 
+bool gemm_ring_ok(int64_t n_rows, int N, int K);
+int launch_gemm_ring(const GemmParams &p, bool relu, hipStream_t s);
+
 static constexpr int BK = 64;
 static constexpr int GROUP_M = 4;
 static constexpr int REG_STAGED = 0;  // value of the STAGES template argument that selects the register-staged pipeline
@@ -1295,6 +1298,7 @@ int gemm_bf16_gate_split(int M, int N, int K, int num_cus)
 int gemm_bf16_variant_block_m(int v)
 {
     switch (v) {
+    case 8: return kRingMap;
     case 10: case 11: return 128;
     case 2: case 22: case 48: return 64;
     case 3: case 4: case 5: case 23: case 24: case 25: case 43: case 44: return 32;
@@ -1303,38 +1307,34 @@ int gemm_bf16_variant_block_m(int v)
 }
 
 // Tile shapes of the grouped GEMM.  variant -> (BM, BN, waves, pipeline)
-//   8: 256x256, 8 waves, ring    11: 128x256, 8 waves, ring    10: 128x128, 4 waves, register-staged
+//   8: 32 .. 256 x 256, 8 waves, gemm_ring.hip    11: 128x256, 8 waves, ring    10: 128x128, 4 waves, register-staged
+//   9: 256x256, register-staged, for what gemm_ring.hip cannot address
 //   2: 64x128, 4 waves, direct-to-LDS    3, 4, 5: 32x128, the same, weights read non-temporally, plainly, by tile (kNtRows)
 // By the average number of rows per expert, by how many 256-column weight panels there are (E * min(D, F) / 256, the
-// same for both GEMMs of a layer), and by how many weights a GEMM streams.  Where the panels alone fill the chip, one
-// tall tile per expert beats two of half its height as soon as most experts need two of those, and with fewer
-// rows the 128-row ring streams the weights faster than any other shape.  With few panels, the smaller tiles' even spread
-// wins.  Layer times in us, top-2:
-//   128 experts 2048 -> 8192, skewed, rows per expert     18     36     64    100    140    170
-//     32x128                                             1589   2159   3431
-//     64x128                                                    1749   2060   2665   3248   3342
-//     128x128                                            1594   1744   1934   2099   2426   2866
-//     128x256 ring                                       1486   1692   1825   1906   2188   2573
-//     256x256 ring                                       1775   1822   1940   2010   2187   2298
-//   64 experts 1024 -> 4096, even, rows per expert         18     36     64    100    140    170
-//     32x128                                              230    335
-//     128x128                                            244    262    269    315    381    367
-//     256x256 ring                                       277    292    301    301    313    313
-// 256 rows below 192 are for GEMMs of 2^29 weights and more (1 GB, four times the last-level cache): there one pass over
-// an expert's weights pays for the padding of an uneven batch, from 112 rows on where both dimensions are 2048 or more
-// and a tile's K loop is long, else from 128.  128x128 / 256x256 at that many rows per expert, even, skewed (exponent
-// 0.8), more skewed (1.2): 128 experts 2048 -> 8192 2054 / 1923, 2160 / 2058, 2431 / 2270; 32 experts 2048 -> 8192 565 / 504,
-// 562 / 575, 616 / 596; 128 experts 1024 -> 4096 646 / 548, 634 / 620, 662 / 680 (at 112 rows 570 / 532, 586 / 600, 634 / 658).
-// With fewer weights only an even batch gains, at 128 rows: 64 experts 1024 -> 4096 345 / 310, 338 / 372, 363 / 360; 128
-// experts 512 -> 2048 209 / 208, 208 / 239, 217 / 252; 16 experts 1024 -> 4096 122 / 114, 120 / 115, 121 / 143.
-// The 128-row ring, too, needs a GEMM of 2^29 weights: 32x128 / 128x256 ring at 24 rows per expert, even, skewed, more
-// skewed: 256 experts 512 -> 2048 281 / 272, 280 / 309, 244 / 244; 512 experts 256 -> 1024 157 / 157, 160 / 177, 135 / 133.
-// There 64x128 is the steadiest shape from 34 to 63 rows, 32x128 / 64x128 / 128x128: 128 experts 512 -> 2048, 36 rows 171 / 161 /
-// 162, 173 / 169 / 183, 170 / 164 / 176; 64 experts 1024 -> 4096, 48 rows 314 / 287 / 266, 327 / 280 / 309, 329 / 281 / 302; 16
-// experts 2048 -> 8192, 48 rows 292 / 291 / 279, 319 / 298 / 285, 310 / 297 / 323; at 64 rows 128x128 has caught up (342 / 320 /
-// 284, 332 / 311 / 309, 342 / 308 / 338).  With 64 panels or fewer it is ahead from 48 on (16 experts 1024 -> 4096 115 / 108 /
-// 101, 124 / 114 / 102, 120 / 114 / 110).
-// K that is no multiple of the K tile has neither ring nor 64x128: there 128 rows pay from 30 and 256 from 192 on.
+// same for both GEMMs of a layer), and by how many weights a GEMM streams.
+//  * Tiles cut to an expert's rows (8) pay as soon as most experts need two 128-row tiles, and from 64 rows on for GEMMs of
+//    2^29 weights and more (1 GB, four times the last-level cache), whose time is that of one pass over an expert's weights.
+//    FFN in us, what ran before / 8, evenly spread, skewed (exponent 0.8), more skewed (1.2) rows:
+//      128 experts 2048 -> 8192, 64 rows per expert 1611 / 1597, 1807 / 1712, 1874 / 1731; 100 rows 1614 / 1695, 1991 / 1824,
+//      2213 / 1885; 160 rows 1972 / 1858, 2316 / 2071, 2597 / 2199; 256 rows 2844 / 2366, 2870 / 2560, 3090 / 2654; 800 rows
+//      6901 / 5767, 6612 / 5815, 6384 / 5904
+//      64 experts 1024 -> 4096, 100 rows 261 / 277, 299 / 298, 300 / 294; 160 rows 351 / 307, 349 / 327, 353 / 333; 800 rows
+//      956 / 853, 903 / 825, 904 / 873
+//      24 experts 1000 -> 4000, 128 rows 190 / 157, 179 / 161, 180 / 160
+//    They need tiles enough for the chip: with fewer than 96 in the GEMM with fewer columns 128x128 is ahead (10 / 8: 8 experts
+//    512 -> 2048, 192 rows 35 / 42; 16 experts 1024 -> 4096, 192 rows 107 / 113, 111 / 121, 113 / 121; 8 experts 2048 -> 8192, 192
+//    rows 196 / 205, 201 / 246, 198 / 227), with 96 and more behind (24 experts 1000 -> 4000, 192 rows 192 / 179; 16 experts 2048 -> 8192,
+//    256 rows 446 / 400, 478 / 377, 439 / 408).
+//  * The 128-row ring streams the weights of such a GEMM faster than any other shape from 18 rows on (128 experts
+//    2048 -> 8192, skewed, 32x128 / 128x128 / 128x256 ring: 18 rows 1589 / 1594 / 1486, 36 rows 2159 / 1744 / 1692).  With
+//    fewer weights it does not pay: 32x128 / 128x256 ring at 24 rows per expert, even, skewed, more skewed: 256 experts
+//    512 -> 2048 281 / 272, 280 / 309, 244 / 244; 512 experts 256 -> 1024 157 / 157, 160 / 177, 135 / 133.
+//  * There 64x128 is the steadiest shape from 34 to 63 rows, 32x128 / 64x128 / 128x128: 128 experts 512 -> 2048, 36 rows 171 / 161 /
+//    162, 173 / 169 / 183, 170 / 164 / 176; 64 experts 1024 -> 4096, 48 rows 314 / 287 / 266, 327 / 280 / 309, 329 / 281 / 302; 16
+//    experts 2048 -> 8192, 48 rows 292 / 291 / 279, 319 / 298 / 285, 310 / 297 / 323; at 64 rows 128x128 has caught up (342 / 320 /
+//    284, 332 / 311 / 309, 342 / 308 / 338).  With 64 panels or fewer it is ahead from 48 on (16 experts 1024 -> 4096 115 / 108 /
+//    101, 124 / 114 / 102, 120 / 114 / 110).
+//  * K that is no multiple of the K tile has neither the 128-row ring nor 64x128: there 128 rows pay from 30 on.
 int gemm_bf16_variant(int64_t n_rows, int E, int N, int K, int num_cus)
 {
     const int64_t avg = E > 0 ? n_rows / E : n_rows;
@@ -1342,7 +1342,10 @@ int gemm_bf16_variant(int64_t n_rows, int E, int N, int K, int num_cus)
     const int64_t panels = (int64_t)E * width / 256;
     const bool whole = N % BK == 0 && K % BK == 0;
     const bool heavy = whole && (int64_t)E * N * K >= kHeavyWeights;
-    if (avg >= 192 || (heavy && avg >= (width >= 2048 ? 112 : 128))) return 8;
+    const bool ring = gemm_ring_ok(n_rows, N, K);
+    const int64_t tiles = (int64_t)E * ((avg + 255) / 256) * ceil_div(width, 256);
+    if (ring && ((avg >= 116 && tiles >= 96) || (heavy && avg >= 64))) return 8;
+    if (avg >= 192) return ring ? 10 : 9;
     const int small = avg >= kNtRows ? 4 : avg >= kNtSoleRows ? 5 : 3;
     if (heavy && panels >= 2 * (int64_t)num_cus) return avg >= 18 ? 11 : small;
     if (4 * panels <= num_cus) return avg >= 48 ? 10 : small;
@@ -1394,28 +1397,24 @@ int launch_gemm_bf16(const GemmParams &p, bool grouped, int variant, bool out_f3
         if (taken || rc != MOE_OK) return rc;
     }
     switch (variant) {
-    case 8: {
-        // whole rounds as 256x256 tiles, the partly filled last round as 128x128 sub-tiles
-        GemmParams q = p;
-        int main_grid = 0;
-        q.tail_mode = 1;
-        // the ring pipeline addresses both operands with 32-bit byte offsets from one base
-        const int64_t a_rows_max = (int64_t)(p.a_zero_row >= p.M ? p.a_zero_row + 1 : p.M);
-        const bool ring_ok = p.K % BK == 0 && a_rows_max * p.lda * 2 < (1ll << 32) && (int64_t)p.N * p.ldb * 2 < (1ll << 32) &&
-                             ((int64_t)(p.c_zero_row >= p.M ? p.c_zero_row + 1 : p.M) + 256) * p.ldc * 2 < (1ll << 32);
-        int rc = ring_ok ? launch_grouped<256, 256, 2, 4, 1, DTL16>(q, relu, num_cus, s, &main_grid)
-                         : launch_grouped<256, 256, 2, 4, 1, REG_STAGED>(q, relu, num_cus, s, &main_grid);
-        if (rc != MOE_OK || main_grid == 0) return rc;
-        q.tail_mode = 2;
-        return launch_grouped<128, 128, 2, 2, 2, REG_STAGED>(q, relu, num_cus, s, &main_grid);
-    }
+    case 8: return launch_gemm_ring(p, relu, s);
     case 11:
-        // the ring pipeline's 32-bit byte offsets, as above
+        // the ring pipeline's 32-bit byte offsets
         if ((int64_t)p.M * p.lda * 2 < (1ll << 32) && (p.a_zero_row + 1) * p.lda * 2 < (1ll << 32) && (int64_t)p.N * p.ldb * 2 < (1ll << 32) &&
             ((int64_t)(p.c_zero_row >= p.M ? p.c_zero_row + 1 : p.M) + 256) * p.ldc * 2 < (1ll << 32))
             return relu ? launch_k<128, 256, 2, 4, false, true, true, true, 1, DTL16>(p, num_cus, s, nullptr)
                         : launch_k<128, 256, 2, 4, false, false, true, true, 1, DTL16>(p, num_cus, s, nullptr);
         return launch_grouped<128, 128, 2, 2, 2, REG_STAGED>(p, relu, num_cus, s);
+    case 9: {
+        // whole rounds as 256x256 tiles, the partly filled last round as 128x128 sub-tiles
+        GemmParams q = p;
+        int main_grid = 0;
+        q.tail_mode = 1;
+        const int rc = launch_grouped<256, 256, 2, 4, 1, REG_STAGED>(q, relu, num_cus, s, &main_grid);
+        if (rc != MOE_OK || main_grid == 0) return rc;
+        q.tail_mode = 2;
+        return launch_grouped<128, 128, 2, 2, 2, REG_STAGED>(q, relu, num_cus, s, &main_grid);
+    }
     case 10: return launch_grouped<128, 128, 2, 2, 2, REG_STAGED>(p, relu, num_cus, s);
     case 2:
         if (p.K % BK != 0) {

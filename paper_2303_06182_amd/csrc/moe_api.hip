@@ -126,6 +126,9 @@ static constexpr int kMinBlockM = 32;  // smallest M tile any grouped GEMM uses:
 // split K of the gate GEMM: at most this many K ranges, only for this many tokens or fewer (sizes the slices)
 static constexpr int kGateSplitMax = 16, kGateSplitTokens = 256;
 
+// Entries of the tile map at most.  (The ring kernel's schedule takes what there is of the arrays, E + 7 entries.)
+static int map_tiles_max(int64_t n_rows, int E, int block_m) { return (int)(n_rows / (block_m == kRingMap ? kMinBlockM : block_m)) + E + 1; }
+
 struct WsLayout {
     int64_t logits, topk_idx, topk_w, counts, offsets, dst_row, src_tok, block_hist;
     int64_t tile_expert, tile_row, num_tiles, gate_parts, xp, h, yp, total;
@@ -155,7 +158,7 @@ static WsLayout ws_layout(const moe_config_t &c)
     const int64_t max_tiles = N / kMinBlockM + E + 1;
     L.tile_expert = take(max_tiles * 4);
     L.tile_row = take(max_tiles * 4);
-    L.num_tiles = take(4);
+    L.num_tiles = take(256);
     L.gate_parts = take((int64_t)(kGateSplitMax - 1) * (T < kGateSplitTokens ? T : kGateSplitTokens) * E * 4);
     L.xp = take(N * c.D * es);
     L.h = take((N + 1) * c.F * es);  // one more row: zeros, read for the padded rows of the second GEMM's tiles
@@ -356,10 +359,10 @@ static int run_expert_ffn(moe_handle_t *h, const void *xp, const FfnExtra &ex, c
     const int v1 = wbits ? quant_variant(h, wbits, n_rows) : gemm_variant(c.dtype, n_rows, c.E, c.F, c.D, h->num_cus);
     const int v2 = wbits ? v1 : gemm_variant(c.dtype, n_rows, c.E, c.D, c.F, h->num_cus);
     const int bm1 = gemm_variant_block_m(c.dtype, v1), bm2 = gemm_variant_block_m(c.dtype, v2);
-    int max_tiles = (int)(n_rows / bm1) + c.E + 1;
+    int max_tiles = map_tiles_max(n_rows, c.E, bm1);
     int rc = MOE_OK;
     if (ex.stage_of || ex.tile_map_ready_bm != bm1) {
-        rc = launch_tile_map(offsets, c.E, bm1, tile_expert, tile_row, num_tiles, max_tiles, ex.stage_of, ex.stage, s);
+        rc = launch_tile_map(offsets, c.E, bm1, tile_expert, tile_row, num_tiles, max_tiles, ex.stage_of, ex.stage, s, ceil_div(c.F, 256), ceil_div(c.D, 256));
         if (rc != MOE_OK) return rc;
     }
 
@@ -370,6 +373,8 @@ static int run_expert_ffn(moe_handle_t *h, const void *xp, const FfnExtra &ex, c
     p.tile_row = tile_row;
     p.num_tiles = num_tiles;
     p.max_m_tiles = max_tiles;
+    p.ring_list = tile_expert;
+    p.ring_words = num_tiles;
     p.num_experts = c.E;
     p.M = (int)n_rows;
     p.a_zero_row = -1;
@@ -397,12 +402,14 @@ static int run_expert_ffn(moe_handle_t *h, const void *xp, const FfnExtra &ex, c
     rc = launch_gemm(c.dtype, p, true, v1, false, true, h->num_cus, s);
     if (rc != MOE_OK) return rc;
     if (bm2 != bm1) {
-        max_tiles = (int)(n_rows / bm2) + c.E + 1;
-        rc = launch_tile_map(offsets, c.E, bm2, tile_expert, tile_row, num_tiles, max_tiles, ex.stage_of, ex.stage, s);
+        max_tiles = map_tiles_max(n_rows, c.E, bm2);
+        rc = launch_tile_map(offsets, c.E, bm2, tile_expert, tile_row, num_tiles, max_tiles, ex.stage_of, ex.stage, s, ceil_div(c.F, 256), ceil_div(c.D, 256));
         if (rc != MOE_OK) return rc;
         p.max_m_tiles = max_tiles;
     }
     // Yp = H * W2[e]^T + b2[e]
+    p.ring_list = tile_row;
+    p.ring_cap_shift = 8;
     p.A = hbuf;
     p.a_rows = nullptr;
     p.a_zero_row = zero_row ? (int)n_rows : -1;
@@ -486,7 +493,7 @@ static StaticLayout static_layout(const moe_config_t &c, int64_t T, int64_t cap,
     const int64_t max_tiles = R / kMinBlockM + E + 1;
     L.tile_expert = take(max_tiles * 4);
     L.tile_row = take(max_tiles * 4);
-    L.num_tiles = take(4);
+    L.num_tiles = take(256);
     L.xd = take(R * c.D * es);
     L.hd = take((R + 1) * c.F * es);
     L.yd = take(R * c.D * es);
@@ -699,7 +706,7 @@ int moe_route_counts(moe_handle_t *h, const int32_t *topk_idx, int32_t T, int32_
         return MOE_ERR_INVALID_ARG;
     rc = check_ws(h, workspace, workspace_bytes);
     if (rc != MOE_OK) return rc;
-    const RouteOut out = {counts, offsets, dst_row, src_tok, 0, nullptr, nullptr, nullptr, 0};
+    const RouteOut out = {counts, offsets, dst_row, src_tok, 0, nullptr, nullptr, nullptr, 0, 0, 0};
     return launch_route(topk_idx, T, h->cfg.E, h->cfg.k, out, at<int32_t>(workspace, ws_layout(h->cfg).block_hist), (hipStream_t)stream);
 }
 
@@ -805,7 +812,7 @@ static int layer_forward_impl(moe_handle_t *h, moe_expert_cache_t *cache, const 
                                                                          : gemm_variant(c.dtype, n_rows, c.E, c.F, c.D, h->num_cus));
     const RouteOut route = {counts, offsets, dst_row, src_tok, bm1, at<int32_t>(workspace, L.tile_expert),
                             at<int32_t>(workspace, L.tile_row), at<int32_t>(workspace, L.num_tiles),
-                            bm1 > 0 ? (int)(n_rows / bm1) + c.E + 1 : 0};
+                            bm1 > 0 ? map_tiles_max(n_rows, c.E, bm1) : 0, ceil_div(c.F, 256), ceil_div(c.D, 256)};
     if (empty) return launch_route(idx, 0, c.E, c.k, route, block_hist, s);
     {
         // an event pair around nothing: what the bracketing itself adds to every record of this call
@@ -1344,7 +1351,7 @@ int moe_layer_forward_static(moe_handle_t *h, const void *x, const void *wg, con
     // slot of every assignment = its rank inside its expert in slot-major order
     rc = launch_transpose_idx(idx, T, c.k, idx_t, dropped, s);
     if (rc != MOE_OK) return rc;
-    const RouteOut out_s = {counts_s, offsets_s, pos, at<int32_t>(ws, L.src_s), 0, nullptr, nullptr, nullptr, 0};
+    const RouteOut out_s = {counts_s, offsets_s, pos, at<int32_t>(ws, L.src_s), 0, nullptr, nullptr, nullptr, 0, 0, 0};
     rc = launch_route(idx_t, T * c.k, c.E, 1, out_s, at<int32_t>(ws, L.block_hist), s);
     if (rc != MOE_OK) return rc;
     rc = launch_static_rows(idx_t, pos, offsets_s, T, c.k, c.E, capacity, slot_row, dropped, s);

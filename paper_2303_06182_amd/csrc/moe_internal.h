@@ -119,6 +119,9 @@ struct GemmParams {
     const int32_t *tile_row;     // [max_m_tiles] first row of the tile
     const int32_t *num_tiles;    // [1]
     int max_m_tiles;             // host upper bound of *num_tiles (sizes the grid)
+    const int32_t *ring_list;    // the ring kernel (gemm_ring.hip): its schedule, see kRingMap
+    const int32_t *ring_words;
+    int ring_cap_shift;          // 0 for the layer's first GEMM, 8 for the second
     int num_experts;             // host only: E
     // tail splitting of a grouped GEMM over 256x256 tiles (0 = off): 1 = this launch runs the whole
     // rounds of 256x256 tiles, 2 = this launch runs the tiles of the last, partly filled round as
@@ -151,9 +154,17 @@ int launch_quantize_mxfp4(int dtype, const void *w, int E, int rows, int cols, u
                           hipStream_t s);
 
 // Tile map for the grouped GEMM from the device-side offsets (one block).
-// stage_of != NULL: only the experts e with stage_of[e] == stage get tiles.
+// stage_of != NULL: only the experts e with stage_of[e] == stage get tiles.  block_m = kRingMap: the ring kernel's schedule.
 int launch_tile_map(const int32_t *offsets, int E, int block_m, int32_t *tile_expert, int32_t *tile_row,
-                    int32_t *num_tiles, int max_m_tiles, const int32_t *stage_of, int stage, hipStream_t s);
+                    int32_t *num_tiles, int max_m_tiles, const int32_t *stage_of, int stage, hipStream_t s, int ring_n1 = 0, int ring_n2 = 0);
+
+// Schedule of the ring kernel, in the place of a tile map.  For each of the layer's two GEMMs a list of experts grouped by
+// XCD, the first GEMM's in tile_expert, the second's in tile_row.  Among the 64 words at num_tiles: kRingFirst + x, where XCD
+// x's part of the lists begins (x = 8: where the last ends); kRingCut + x, the expert cut between XCD x - 1 and x and the
+// 32-row unit of it that the latter begins with (expert << kRingCutShift | unit; MOE_MAX_E as expert: none); kRingCap + x, the
+// greatest tile height in units (bits 0 .. 7 first, 8 .. 15 second GEMM).
+static constexpr int kRingMap = 1 << 30;  // tile height that stands for it
+static constexpr int kRingFirst = 8, kRingCut = 17, kRingCap = 26, kRingCutShift = 20;
 
 // ---- routing -------------------------------------------------------------------------------------
 int launch_topk(float *logits, int T, int E, int k, int renorm, int32_t *idx, float *w, hipStream_t s, int n_parts = 1,
@@ -169,6 +180,7 @@ struct RouteOut {
     int tile_bm;
     int32_t *tile_expert, *tile_row, *num_tiles;
     int max_m_tiles;
+    int ring_n1, ring_n2;  // tile_bm = kRingMap: column tiles of the two GEMMs
 };
 // hist_tokens > 0: block_hist already holds one histogram row per hist_tokens tokens (a divisor of 256)
 int launch_route(const int32_t *idx, int T, int E, int k, const RouteOut &o, int32_t *block_hist, hipStream_t s, int hist_tokens = 0);

@@ -307,6 +307,107 @@ __device__ __forceinline__ void block_exclusive_scan4(int *vals, int n, int *wav
     __syncthreads();
 }
 
+// Schedule of the grouped GEMM's ring kernel (layout: moe_internal.h), by one whole block.  rows_of(e), e < E.
+// What it balances: an expert's rows come in tiles of up to eight 32-row units, and a tile costs about six units whatever
+// its height (measured: the time per K tile is 0.8 us at one unit and 1.6 at eight).  The experts' rows, in order, are cut in
+// eight parts of equal cost, one per XCD, between two tiles of an expert at most (an XCD's blocks share weights and rows in
+// its L2, so what one expert needs stays together).  Inside a part every expert's tiles get the same height, at most the
+// one that makes the part's rounds of 32 blocks cheapest, and the experts with the taller tiles come first, so that a round's
+// tiles cost about the same.  (Places among experts of one height are handed out by LDS atomics: their
+// order differs between runs, the sums do not.)
+struct RingScratch {
+    int cost[MOE_MAX_E];         // then its prefix
+    int wave_tot[16];
+    int units[8];                // of every part
+    int tiles[8][9];             // ... cut to a height of at most h
+    int cap[2][8];
+    int bin[2][64];              // experts by GEMM, part and height (8 first), then the first place of each
+};
+
+template <typename Rows>
+__device__ __forceinline__ void ring_schedule(const Rows &rows_of, int E, int n1, int n2, int32_t *__restrict__ list1,
+                                              int32_t *__restrict__ list2, int max_list, int32_t *__restrict__ words, RingScratch &sm)
+{
+    const int tid = threadIdx.x, nthreads = blockDim.x, lane = tid % kWave, wave = tid / kWave;
+    for (int e = tid; e < E; e += nthreads) {
+        const int units = (rows_of(e) + 31) >> 5;
+        sm.cost[e] = units + 6 * ((units + 7) >> 3);
+    }
+    if (tid < 8) sm.units[tid] = 0;
+    if (tid < 72) sm.tiles[tid / 9][tid % 9] = 0;
+    if (tid < 128) sm.bin[tid / 64][tid % 64] = 0;
+    if (tid < 9) words[kRingCut + tid] = MOE_MAX_E << kRingCutShift;  // no expert
+    __syncthreads();
+    int total = 0;
+    block_exclusive_scan4(sm.cost, E, sm.wave_tot, total);
+    // the pieces of expert e: fn(part, first unit, units)
+    auto pieces = [&](int e, auto fn) {
+        const int units = (rows_of(e) + 31) >> 5;
+        if (units == 0) return;
+        const int cuts = (units + 7) >> 3, height = (units + cuts - 1) / cuts, cost = units + 6 * cuts;
+        const int64_t pre = sm.cost[e];
+        int done = 0;
+        for (int x = (int)(pre * 8 / total); x < 8 && done < units; ++x) {
+            const int64_t in = (int64_t)total * (x + 1) - 8 * pre;  // 8 x cost of the expert in front of the part's end
+            int end = x == 7 ? units : (int)min((int64_t)cuts, (2 * in * cuts + 8 * cost) / (16 * (int64_t)cost)) * height;
+            end = min(end, units);
+            if (end > done) fn(x, done, end - done);
+            done = max(done, end);
+        }
+    };
+    for (int e = tid; e < E; e += nthreads)
+        pieces(e, [&](int x, int first, int units) {
+            if (first > 0) words[kRingCut + x] = e << kRingCutShift | first;  // cut in front of part x
+            atomicAdd(&sm.units[x], units);
+            for (int h = 1; h <= 8; ++h) atomicAdd(&sm.tiles[x][h], (units + h - 1) / h);
+        });
+    __syncthreads();
+    if (tid < 16) {
+        const int x = tid & 7, n = tid < 8 ? n1 : n2;
+        float best = 0.f;
+        int cap = 8;
+        for (int h = 8; h >= 1; --h) {
+            const int tiles = sm.tiles[x][h];
+            // below four units only to give every block of a single round a tile
+            if (tiles == 0 || (h < 4 && (int64_t)tiles * n > 32)) break;
+            const float c = (float)(((int64_t)tiles * n + 31) / 32) * (6.f + (float)sm.units[x] / (float)tiles);
+            if (h == 8 || c < 0.97f * best) best = c, cap = h;
+        }
+        sm.cap[tid >> 3][x] = cap;
+    }
+    __syncthreads();
+    if (tid < 8) words[kRingCap + tid] = sm.cap[0][tid] | sm.cap[1][tid] << 8;
+    auto bin_of = [&](int g, int x, int units) {
+        const int k = (units + sm.cap[g][x] - 1) / sm.cap[g][x];
+        return &sm.bin[g][8 * x + 8 - (units + k - 1) / k];
+    };
+    for (int e = tid; e < E; e += nthreads)
+        pieces(e, [&](int x, int, int units) {
+            for (int g = 0; g < 2; ++g) atomicAdd(bin_of(g, x, units), 1);
+        });
+    __syncthreads();
+    if (wave < 2) {
+        const int v = sm.bin[wave][lane];
+        int incl = v;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const int up = __shfl_up(incl, off, kWave);
+            if (lane >= off) incl += up;
+        }
+        sm.bin[wave][lane] = incl - v;
+        if (wave == 0 && (lane & 7) == 0) words[kRingFirst + (lane >> 3)] = incl - v;  // the same for both GEMMs
+        if (wave == 0 && lane == kWave - 1) words[kRingFirst + 8] = incl;
+    }
+    __syncthreads();
+    for (int e = tid; e < E; e += nthreads)
+        pieces(e, [&](int x, int, int units) {
+            for (int g = 0; g < 2; ++g) {
+                const int at = atomicAdd(bin_of(g, x, units), 1);
+                if (at < max_list) (g == 0 ? list1 : list2)[at] = e;  // at most E + 7 places are needed
+            }
+        });
+}
+
 // Stable position of every assignment.  Block b ranks its 256 tokens:
 //   row(t, j) = offsets[e] + (assignments to e in the blocks before b) + (in the waves before this one)
 //               + (in the lanes before this one, or in earlier slots of this lane)
@@ -326,7 +427,8 @@ __global__ __launch_bounds__(kThreads) void route_rank_kernel(const int32_t *__r
                                                               int32_t *__restrict__ src_tok, int tile_bm,
                                                               int32_t *__restrict__ tile_expert,
                                                               int32_t *__restrict__ tile_row,
-                                                              int32_t *__restrict__ num_tiles, int max_m_tiles)
+                                                              int32_t *__restrict__ num_tiles, int max_m_tiles,
+                                                              int ring_n1, int ring_n2)
 {
     constexpr int NW = kThreads / kWave;
     __shared__ int offs[MOE_MAX_E];
@@ -344,6 +446,12 @@ __global__ __launch_bounds__(kThreads) void route_rank_kernel(const int32_t *__r
     __syncthreads();
     int total = 0;
     block_exclusive_scan4(offs, E, wave_tot, total);  // offs[e] = first row of expert e
+    if (tile_bm == kRingMap && blockIdx.x == gridDim.x - 1) {  // a block of its own, next to the ranking ones
+        __shared__ RingScratch ring;
+        ring_schedule([&](int e) { return (e + 1 < E ? offs[e + 1] : total) - offs[e]; }, E, ring_n1, ring_n2, tile_expert, tile_row,
+                      max_m_tiles, num_tiles, ring);
+        return;
+    }
     if (blockIdx.x == 0) {
         for (int e = threadIdx.x; e < E; e += kThreads) offsets[e] = offs[e];
         if (threadIdx.x == 0) offsets[E] = total;
@@ -410,7 +518,7 @@ __global__ __launch_bounds__(kThreads) void route_rank_kernel(const int32_t *__r
             }
         }
     }
-    if (tile_bm > 0 && blockIdx.x == 0) {  // the grouped GEMM's M-tile map: expert e owns ceil(count / tile_bm) tiles
+    if (tile_bm > 0 && tile_bm != kRingMap && blockIdx.x == 0) {  // the grouped GEMM's M-tile map: expert e owns ceil(count / tile_bm) tiles
         __syncthreads();
         int *first = &wave_cnt[0][0];  // reused: first tile of every expert
         for (int e = threadIdx.x; e < E; e += kThreads) first[e] = (counts[e] + tile_bm - 1) / tile_bm;
@@ -453,7 +561,8 @@ static int small_route_max(int E)
 __device__ __forceinline__ void route_small(const int32_t *idx, int n_assign, int E, int k, int32_t *__restrict__ counts,
                                             int32_t *__restrict__ offsets, int32_t *__restrict__ dst_row,
                                             int32_t *__restrict__ src_tok, int tile_bm, int32_t *__restrict__ tile_expert,
-                                            int32_t *__restrict__ tile_row, int32_t *__restrict__ num_tiles, int max_m_tiles)
+                                            int32_t *__restrict__ tile_row, int32_t *__restrict__ num_tiles, int max_m_tiles,
+                                            int ring_n1, int ring_n2)
 {
     __shared__ int hist[MOE_MAX_E];   // counts, then the running totals of the ranking pass
     __shared__ int start[MOE_MAX_E];  // first row of every expert
@@ -483,7 +592,10 @@ __device__ __forceinline__ void route_small(const int32_t *idx, int n_assign, in
         start[threadIdx.x] = my_off;
     }
     if (threadIdx.x == 0) offsets[E] = n_assign;
-    if (tile_bm > 0) {  // uniform over the block: the grouped GEMM's M-tile map, as route_rank_kernel's block 0 writes it
+    if (tile_bm == kRingMap) {
+        __shared__ RingScratch ring;
+        ring_schedule([&](int e) { return hist[e]; }, E, ring_n1, ring_n2, tile_expert, tile_row, max_m_tiles, num_tiles, ring);
+    } else if (tile_bm > 0) {  // uniform over the block: the grouped GEMM's M-tile map, as route_rank_kernel's block 0 writes it
         const int nt = (threadIdx.x < E && cnt > 0) ? (cnt + tile_bm - 1) / tile_bm : 0;
         int incl_t = nt;
 #pragma unroll
@@ -563,7 +675,7 @@ __device__ __forceinline__ void route_small(const int32_t *idx, int n_assign, in
 __global__ __launch_bounds__(1024) void route_small_kernel(const int32_t *__restrict__ idx, int n_assign, int E, int k, RouteOut o)
 {
     route_small(idx, n_assign, E, k, o.counts, o.offsets, o.dst_row, o.src_tok, o.tile_bm, o.tile_expert, o.tile_row, o.num_tiles,
-                o.max_m_tiles);
+                o.max_m_tiles, o.ring_n1, o.ring_n2);
 }
 
 // Top-k of a decoder step and its routing in one launch: 1024 / G tokens fit the block, their selection stays in LDS.
@@ -578,7 +690,7 @@ __global__ __launch_bounds__(1024) void route_topk_kernel(float *logits, int T, 
     topk_token<G, V, VEC>(t, t < T, threadIdx.x % G, logits, E, k, renorm, idx, w, n_parts, parts, part_stride, s_idx);
     __syncthreads();
     route_small(s_idx, T * k, E, k, o.counts, o.offsets, o.dst_row, o.src_tok, o.tile_bm, o.tile_expert, o.tile_row, o.num_tiles,
-                o.max_m_tiles);
+                o.max_m_tiles, o.ring_n1, o.ring_n2);
 }
 
 template <int G, int V, bool VEC>
@@ -644,9 +756,9 @@ int launch_route(const int32_t *idx, int T, int E, int k, const RouteOut &o, int
     int nbits = 0;
     while ((1 << nbits) < E) ++nbits;
 #define MOE_RANK(KM)                                                                                              \
-    hipLaunchKernelGGL(route_rank_kernel<KM>, dim3(nblk), dim3(kThreads), 0, s, idx, T, E, k, nbits, o.counts, \
+    hipLaunchKernelGGL(route_rank_kernel<KM>, dim3(nblk + (o.tile_bm == kRingMap)), dim3(kThreads), 0, s, idx, T, E, k, nbits, o.counts, \
                        block_hist, row_step, o.offsets, o.dst_row, o.src_tok, o.tile_bm, o.tile_expert, o.tile_row, \
-                       o.num_tiles, o.max_m_tiles)
+                       o.num_tiles, o.max_m_tiles, o.ring_n1, o.ring_n2)
     // KMAX = slots a lane holds: the smallest instantiation that holds k
     if (k <= 1) MOE_RANK(1);
     else if (k <= 2) MOE_RANK(2);
@@ -667,8 +779,17 @@ __global__ __launch_bounds__(1024) void tile_map_kernel(const int32_t *__restric
                                                         int32_t *__restrict__ tile_expert,
                                                         int32_t *__restrict__ tile_row,
                                                         int32_t *__restrict__ num_tiles, int max_m_tiles,
-                                                        const int32_t *__restrict__ stage_of, int stage)
+                                                        const int32_t *__restrict__ stage_of, int stage, int ring_n1, int ring_n2)
 {
+    if (BM == kRingMap) {
+        __shared__ RingScratch ring;
+        __shared__ int rows[MOE_MAX_E];
+        if (threadIdx.x < E)
+            rows[threadIdx.x] = stage_of && stage_of[threadIdx.x] != stage ? 0 : max(0, offsets[threadIdx.x + 1] - offsets[threadIdx.x]);
+        __syncthreads();
+        ring_schedule([&](int e) { return rows[e]; }, E, ring_n1, ring_n2, tile_expert, tile_row, max_m_tiles, num_tiles, ring);
+        return;
+    }
     __shared__ int wave_tot[16];
     const int e = threadIdx.x;
     int row0 = 0, row1 = 0;
@@ -701,11 +822,11 @@ __global__ __launch_bounds__(1024) void tile_map_kernel(const int32_t *__restric
 }
 
 int launch_tile_map(const int32_t *offsets, int E, int block_m, int32_t *tile_expert, int32_t *tile_row,
-                    int32_t *num_tiles, int max_m_tiles, const int32_t *stage_of, int stage, hipStream_t s)
+                    int32_t *num_tiles, int max_m_tiles, const int32_t *stage_of, int stage, hipStream_t s, int ring_n1, int ring_n2)
 {
     ProfScope ps("tile_map", s);
     hipLaunchKernelGGL(tile_map_kernel, dim3(1), dim3(1024), 0, s, offsets, E, block_m, tile_expert, tile_row,
-                       num_tiles, max_m_tiles, stage_of, stage);
+                       num_tiles, max_m_tiles, stage_of, stage, ring_n1, ring_n2);
     MOE_LAUNCH_CHECK("tile_map_kernel");
     return MOE_OK;
 }
