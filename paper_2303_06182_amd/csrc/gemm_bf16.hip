@@ -18,10 +18,7 @@
 // different chunk positions, so fragment reads are conflict free (measured: 4 clk per
 // ds_read_b128 against 6 clk with an (r & 7) swizzle).
 //
-// Three K pipelines, chosen per tile shape (template argument STAGES):
-//  * ring of K steps (the 256x256 and 128x256 tiles of the grouped GEMM, STAGES = DTL16): v_mfma_f32_16x16x32_bf16
-//    instead of the 32x32 blocks, operands straight into LDS, five slots of one 32-wide K step, one
-//    load every seventh MFMA (four per step; 128 rows: two and four); described where it is implemented, inside the kernel.
+// Two K pipelines, chosen per tile shape (template argument STAGES); tiles cut to an expert's rows are gemm_ring.hip's:
 //  * direct-to-LDS, whole K tiles (small tiles, the gate): STAGES LDS stages; K tiles go straight from global
 //    memory into LDS (global_load_lds_dwordx4, no register staging), the loads run STAGES-1 K
 //    tiles ahead of the MFMAs and are waited for (vmcnt) only at the barrier that ends an
@@ -35,11 +32,11 @@
 //    are written to the other LDS buffer at the same slot of iteration i+1 and the register is
 //    refilled at once: every load has a full iteration to land and the address unit sees an
 //    even stream.
-// In the last two, the fragments of K-step ks+1 are read while the MFMAs of K-step ks issue (the
+// In both, the fragments of K-step ks+1 are read while the MFMAs of K-step ks issue (the
 // instruction order is pinned with sched_group_barrier / sched_barrier, otherwise the compiler
 // sinks the reads next to their use).
 //
-// Epilogue (bf16 output, last two pipelines): each wave converts a 32-row strip of its tile, parks it in the LDS rows
+// Epilogue (bf16 output): each wave converts a 32-row strip of its tile, parks it in the LDS rows
 // only this wave's loads ever fill, and writes it out with 16 bytes per lane, i.e. whole
 // contiguous row segments per store instruction; the scattered form (16 bytes per row per
 // instruction) cost up to a fifth of a tile's time.
@@ -67,7 +64,6 @@ static constexpr int REG_STAGED = 0;  // value of the STAGES template argument t
 // cache policy of the direct-to-LDS weight loads (template argument NT): plain, non-temporal, or non-temporal for the tiles
 // that are their expert's only one
 static constexpr int NT_NONE = 0, NT_ALL = 1, NT_SOLE = 2;
-static constexpr int DTL16 = -1;      // ... and the one that selects 16x16x32 MFMAs out of a ring of K-step slots filled by direct-to-LDS loads
 
 struct TileInfo {
     int row0, row_end, expert, n0;
@@ -102,12 +98,10 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem_raw[];
     // STAGES == REG_STAGED selects the register-staged pipeline (two LDS buffers)
     constexpr bool RSTAGE = STAGES == REG_STAGED;
-    constexpr bool D16 = STAGES == DTL16;
-    constexpr int NSTAGE = (RSTAGE || D16) ? 2 : STAGES;
+    constexpr int NSTAGE = RSTAGE ? 2 : STAGES;
     uint16_t *sA = reinterpret_cast<uint16_t *>(smem_raw);  // [NSTAGE][BM*64]
     uint16_t *sB = sA + NSTAGE * BM * BK;                   // [NSTAGE][BN*64]
     static_assert(NSTAGE >= 2, "at least two LDS stages");
-    static_assert(!D16 || (KFULL && BQ == 0 && !OUT_F32), "the 16x16x32 pipeline: bf16 in and out, K a multiple of the K tile");
     static_assert(KFULL || RSTAGE || (STAGES == 2 && !GROUPED), "K that ends inside a K tile: register-staged, or the gate's two-stage loop");
     static_assert(BQ == 0 || (KFULL && !RSTAGE && GROUPED), "8- and 4-bit weights: grouped direct-to-LDS pipeline, K a multiple of the K tile");
 
@@ -625,259 +619,6 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
             __builtin_amdgcn_sched_barrier(0);
         };
         constexpr int LPS = A_IT + B_IT;             // load instructions per wave per stage
-        if constexpr (D16) {
-            // ---- 16x16x32 MFMAs out of a ring of K-step slots filled by direct-to-LDS loads.
-            // Why 16x16x32: v_mfma_f32_16x16x32_bf16 contracts 32 k per accumulator read and write where
-            // v_mfma_f32_32x32x16_bf16 contracts 16; a register-only loop on live data sustains 2.14 PFLOP/s with the
-            // former against 1.93 with the latter under the chip's power limit.  Why direct-to-LDS: ds_write_b128 moves
-            // 64 bytes per clock per CU (measured) where ds_read_b128 moves 256, so writing a K tile's 64 KB from
-            // registers costs the LDS more time than reading its 192 KB of fragments.  Why a ring: a CU takes 64 KB per
-            // K tile through a 64-byte-per-clock path -- half the time the MFMAs of that tile need -- so the loads must
-            // flow evenly, not in a burst per K tile, and they come from HBM or a remote L2 slice.  With two 64 KB
-            // buffers a load can only be issued in the first half of a K tile to land by its end (measured: MFMA pipes
-            // 56 % busy; 68 % when every load hits the L2).  Five slots of ONE K step (32 k: 256 + 256 rows of 64 bytes
-            // = 32 KB; 160 KB in all) let a wave issue four loads per step, seven MFMAs apart, all the time, each with one to three
-            // steps to land: 66 - 73 % busy at a higher clock.
-            //
-            // Step u multiplies the fragments of slot u mod 5, which were read into registers during step u - 1:
-            //   1. the MFMAs of activation block 0 (their operands landed long ago);
-            //   2. wait for this wave's LDS reads (all of step u's fragments), on odd steps also for its loads of the
-            //      next K tile; barrier.  Behind it every wave's fragments of slot u are in registers, so slots u - 1
-            //      and u are free, and the next K tile has landed for everybody;
-            //   3. the other MFMAs; behind them the reads of step u + 1's fragments from slot u + 1 (the four weight
-            //      fragments into the other register set and block 0 at once, activation block mi in place behind its
-            //      last MFMA) and the loads of the K tile two ahead: both halves of a 16-row group back to back (the
-            //      second request finds the line in the L1 or merges with the first), the first half into slot u + 4,
-            //      the second into slot u + 5 = u.  Loads of a wave land in order, so "at most as many outstanding as
-            //      were issued since" is the wait of point 2.
-            // A slot row is 64 bytes: 16-byte chunk c of row r sits at position c ^ ((r >> 2) & 3), which keeps the 16
-            // lanes x 16 bytes of a fragment read on 16 different bank groups; the permutation is applied on the global
-            // side of the load, inside one 64-byte segment.
-            // Weight row (output column) permutation inside a wave's columns: LDS row 16 * ni + r holds column
-            // 32 * (ni / 2) + 8 * (r / 4) + 4 * (ni % 2) + r % 4, so that the accumulators of blocks 2p and 2p + 1 of a
-            // lane are the 8 consecutive columns 32 p + 8 * (lane / 16) ... of token row lane % 16 and leave as one
-            // 16-byte store, without a trip through LDS (all of which the ring holds).
-            static_assert(GROUPED, "the ring pipeline is instantiated for the grouped GEMM");
-            constexpr int NSLOT = 5;
-            constexpr int SLOT_BYTES = (BM + BN) * 64;
-            constexpr int MI16 = WTM / 16, NI16 = WTN / 16;
-            constexpr int NWAVE = THREADS / 64;
-            constexpr int AG = BM / 16 / NWAVE, BG = BN / 16 / NWAVE;  // 16-row groups a wave loads per K tile
-            constexpr int PAIRS = AG + BG;
-            constexpr int Q1 = PAIRS / 2;                              // pairs issued in the even step; the rest in the odd one
-            constexpr int PB = 1;                                      // activation blocks multiplied in front of the barrier
-            constexpr int PRE = PB * NI16;
-            constexpr int NM16 = MI16 * NI16;
-            constexpr bool ACC16_IN_AGPR = NM16 * 4 > 128;
-            static_assert(BM % (16 * NWAVE) == 0 && BN % (16 * NWAVE) == 0 && WTN % 32 == 0 && MI16 >= 2 && PB < MI16 - 1, "ring pipeline tile shape");
-            static_assert(BK == 64, "a K tile is two steps of 32");
-            f32x4 acc16[MI16][NI16];
-            const int wave_u = __builtin_amdgcn_readfirstlane(wave);
-            const int row16 = lane & 15, kq = lane >> 4;
-            // fragment reads: row (block base + row16), chunk position kq ^ ((row16 >> 2) & 3)
-            const int frag_off = row16 * 64 + ((kq ^ ((row16 >> 2) & 3)) << 4);
-            const uint8_t *fragA = smem_raw + (wm * WTM) * 64 + frag_off;
-            const uint8_t *fragB = smem_raw + BM * 64 + (wn * WTN) * 64 + frag_off;
-            // load stream
-            int l_seq = seq, l_kt = 0;
-            bool l_more = true;
-            int w_slot = 0;  // slot of the first half of the K tile the stream is at
-            const uint8_t *srcA, *srcB;  // same for every lane: the operand's first byte of the stream's K tile
-            uint32_t a_voff[AG][2], b_voff[BG][2];
-            const int ld_row = lane >> 2;                              // row inside the 16-row group
-            const int ld_chunk = (lane & 3) ^ ((lane >> 4) & 3);      // K chunk this lane fetches for its LDS position
-            auto set_ptrs16 = [&](const TileInfo &ti) {
-                const int slot = p.b_slot ? uniform_load(p.b_slot + ti.expert) : ti.expert;
-                srcB = reinterpret_cast<const uint8_t *>(Bg0 + (int64_t)slot * p.strideB);
-                srcA = reinterpret_cast<const uint8_t *>(Ag);
-#pragma unroll
-                for (int g = 0; g < AG; ++g) {
-                    const int r = (wave * AG + g) * 16 + ld_row;
-                    int gr = min(ti.row0 + r, ti.row_end - 1);
-                    if (p.a_zero_row >= 0 && ti.row0 + r >= ti.row_end) gr = p.a_zero_row;
-                    if (p.a_rows) gr = p.a_rows[gr];
-                    const uint32_t o = (uint32_t)gr * (uint32_t)p.lda * 2u + ld_chunk * 16;
-                    a_voff[g][0] = o;
-                    a_voff[g][1] = o + 64;
-                }
-#pragma unroll
-                for (int g = 0; g < BG; ++g) {
-                    const int rho = (wave * BG + g) * 16 + ld_row;  // LDS row of the tile
-                    const int x = rho % WTN, xi = x >> 4, xr = x & 15;
-                    const int c = (rho / WTN) * WTN + 32 * (xi >> 1) + 8 * (xr >> 2) + 4 * (xi & 1) + (xr & 3);
-                    const int gn = min(ti.n0 + c, p.N - 1);
-                    const uint32_t o = (uint32_t)gn * (uint32_t)p.ldb * 2u + ld_chunk * 16;
-                    b_voff[g][0] = o;
-                    b_voff[g][1] = o + 64;
-                }
-            };
-            auto issue_load = [&](int j) {  // load j of the stream's K tile: pair j / 2, K half j % 2
-                const int g = j >> 1, h = j & 1;
-                int slot = w_slot + h;
-                if (slot >= NSLOT) slot -= NSLOT;
-                if (g < AG)
-                    __builtin_amdgcn_global_load_lds((const glb_void *)(srcA + (size_t)l_kt * 128 + a_voff[g][h]),
-                                                     (lds_void *)(smem_raw + slot * SLOT_BYTES + (wave_u * AG + g) * 1024), 16, 0, 0);
-                else
-                    __builtin_amdgcn_global_load_lds((const glb_void *)(srcB + (size_t)l_kt * 128 + b_voff[g - AG][h]),
-                                                     (lds_void *)(smem_raw + slot * SLOT_BYTES + BM * 64 + (wave_u * BG + (g - AG)) * 1024), 16, 0, 0);
-            };
-            auto advance = [&]() {
-                w_slot += 2;
-                if (w_slot >= NSLOT) w_slot -= NSLOT;
-                if (l_more && ++l_kt == KT) {
-                    if (seq_ok(l_seq + slots)) {
-                        l_seq += slots;
-                        l_kt = 0;
-                        set_ptrs16(tile_info(l_seq));
-                    } else {
-                        l_more = false;
-                        l_kt = KT - 1;  // past the end: re-read the last K tile into slots nobody reads
-                    }
-                }
-            };
-            // a16[MI16 - 1 + P]: the last activation block has a register set per step parity, so that its read for the
-            // next step goes out with the first ones and the step's last LDS read is four MFMAs from the step's end
-            bf16x8 a16[MI16 + 1], w16[2][NI16];
-            int r_slot = 0;  // slot of the step being multiplied
-            auto read_frag = [&](const uint8_t *base, int slot, int block) {
-                return *reinterpret_cast<const bf16x8 *>(base + slot * SLOT_BYTES + block * 1024);
-            };
-            auto step = [&](auto parity) {
-                constexpr int P = decltype(parity)::value;
-                constexpr int NL = P == 0 ? 2 * Q1 : 2 * (PAIRS - Q1);  // loads issued in this step
-                constexpr int J0 = P == 0 ? 0 : 2 * Q1;
-                constexpr int GAP = NL > 0 ? ((NM16 - PRE) / NL > 8 ? 8 : (NM16 - PRE) / NL) : 1;  // MFMAs between two loads
-                static_assert(NL == 0 || GAP >= 1, "more loads than MFMA slots behind the barrier");
-                auto mfma = [&](int mi, int ni) {
-                    acc16[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w16[P][ni], a16[mi == MI16 - 1 ? mi + P : mi], acc16[mi][ni], 0, 0, 0);
-                };
-#pragma unroll
-                for (int mi = 0; mi < PB; ++mi)
-#pragma unroll
-                    for (int ni = 0; ni < NI16; ++ni) mfma(mi, ni);
-                __builtin_amdgcn_sched_barrier(0);
-                asm volatile("" ::: "memory");
-                // lgkmcnt(0); odd steps: at most the loads of the even step before may be outstanding
-                if (P == 1)
-                    __builtin_amdgcn_s_waitcnt(0x0070 | ((2 * Q1) & 15) | (((2 * Q1) >> 4) << 14));
-                else
-                    __builtin_amdgcn_s_waitcnt(0xc07f);
-                __builtin_amdgcn_s_barrier();
-                asm volatile("" ::: "memory");
-                __builtin_amdgcn_sched_barrier(0);
-                const int nslot = r_slot + 1 == NSLOT ? 0 : r_slot + 1;
-#pragma unroll
-                for (int ni = 0; ni < NI16; ++ni) w16[P ^ 1][ni] = read_frag(fragB, nslot, ni);
-#pragma unroll
-                for (int mi = 0; mi < PB; ++mi) a16[mi] = read_frag(fragA, nslot, mi);
-                a16[MI16 - 1 + (P ^ 1)] = read_frag(fragA, nslot, MI16 - 1);
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int mi = PB; mi < MI16; ++mi) {
-#pragma unroll
-                    for (int ni = 0; ni < NI16; ++ni) {
-                        const int gm = mi * NI16 + ni;
-                        mfma(mi, ni);
-                        if (ni == NI16 - 1 && mi < MI16 - 1) a16[mi] = read_frag(fragA, nslot, mi);
-                        if (NL > 0 && (gm - PRE) % GAP == 0 && (gm - PRE) / GAP < NL) issue_load(J0 + (gm - PRE) / GAP);
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                }
-                r_slot = nslot;
-                if (P == (Q1 == PAIRS ? 0 : 1)) advance();  // behind the K tile's last load
-                __builtin_amdgcn_sched_barrier(0);
-            };
-            auto epilogue16 = [&](const TileInfo &ti) {
-                const uint16_t *bias = static_cast<const uint16_t *>(p.bias);
-                if (bias) bias += (int64_t)ti.expert * p.strideBias;
-                const int col_base = ti.n0 + wn * WTN + 8 * kq;
-                uint8_t *const cbase = static_cast<uint8_t *>(p.C);
-                const uint32_t row_step = 16u * (uint32_t)p.ldc * 2u;  // bytes between two row blocks
-                auto store_all = [&](auto with_bias) {
-                    constexpr bool BIAS = decltype(with_bias)::value;
-                    uint32_t bw[NI16 / 2][4] = {};
-                    if constexpr (BIAS) {
-#pragma unroll
-                        for (int pp = 0; pp < NI16 / 2; ++pp)
-                            if (col_base + 32 * pp < p.N) {  // N is a multiple of 8
-                                const uint4 bb = *reinterpret_cast<const uint4 *>(bias + col_base + 32 * pp);
-                                bw[pp][0] = bb.x, bw[pp][1] = bb.y, bw[pp][2] = bb.z, bw[pp][3] = bb.w;
-                            }
-                    }
-                    const int row0 = ti.row0 + wm * WTM + row16;
-                    uint32_t off = (uint32_t)row0 * (uint32_t)p.ldc * 2u + (uint32_t)col_base * 2u;  // the launcher checked that C fits 32 bits
-#pragma unroll
-                    for (int mi = 0; mi < MI16; ++mi) {
-                        // the column pairs of a row block back to back: together they fill whole 128-byte lines
-#pragma unroll
-                        for (int pp = 0; pp < NI16 / 2; ++pp) {
-                            uint32_t o[4];
-#pragma unroll
-                            for (int q = 0; q < 4; ++q) {  // columns 2q, 2q + 1 of the 8: block 2pp + q / 2, registers 2 (q % 2), + 1
-                                float v0, v1;
-                                if constexpr (ACC16_IN_AGPR) {  // read in place, as in the 32x32 epilogue
-                                    asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v0) : "a"(acc16[mi][2 * pp + (q >> 1)][2 * (q & 1)]));
-                                    asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(v1) : "a"(acc16[mi][2 * pp + (q >> 1)][2 * (q & 1) + 1]));
-                                } else {
-                                    v0 = acc16[mi][2 * pp + (q >> 1)][2 * (q & 1)], v1 = acc16[mi][2 * pp + (q >> 1)][2 * (q & 1) + 1];
-                                }
-                                if constexpr (BIAS) {
-                                    v0 += __uint_as_float(bw[pp][q] << 16);
-                                    v1 += __uint_as_float(bw[pp][q] & 0xffff0000u);
-                                }
-                                o[q] = pack_bf16(v0, v1);
-                                if (RELU) o[q] = relu_bf16x2(o[q]);
-                            }
-                            if (row0 + mi * 16 < ti.row_end && col_base + 32 * pp < p.N)
-                                *reinterpret_cast<uint4 *>(cbase + off + 64 * pp) = make_uint4(o[0], o[1], o[2], o[3]);
-                        }
-                        off += row_step;
-                    }
-                };
-                if constexpr (ACC16_IN_AGPR) asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
-                if (bias)
-                    store_all(std::true_type{});
-                else
-                    store_all(std::false_type{});
-            };
-            // prologue: the first two K tiles of the stream -> slots 0..3; fragments of step 0
-            set_ptrs16(t);
-#pragma unroll
-            for (int rep = 0; rep < 2; ++rep) {
-#pragma unroll
-                for (int j = 0; j < 2 * PAIRS; ++j) issue_load(j);
-                advance();
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_s_waitcnt(0x0f70 | ((2 * PAIRS) & 15) | (((2 * PAIRS) >> 4) << 14));  // the first K tile has landed
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int ni = 0; ni < NI16; ++ni) w16[0][ni] = read_frag(fragB, 0, ni);
-#pragma unroll
-            for (int mi = 0; mi < MI16; ++mi) a16[mi] = read_frag(fragA, 0, mi);  // step 0 is even: its last block is a16[MI16 - 1]
-            while (true) {
-#pragma unroll
-                for (int mi = 0; mi < MI16; ++mi)
-#pragma unroll
-                    for (int ni = 0; ni < NI16; ++ni)
-#pragma unroll
-                        for (int r = 0; r < 4; ++r) acc16[mi][ni][r] = 0.f;
-                for (int kt = 0; kt < KT; ++kt) {
-                    step(std::integral_constant<int, 0>{});
-                    step(std::integral_constant<int, 1>{});
-                }
-                epilogue16(t);
-                seq += slots;
-                if (!seq_ok(seq)) break;
-                t = tile_info(seq);
-            }
-            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no LDS write may outlive the block
-            return;
-        }
         if constexpr (RSTAGE) {
             // ---- register-staged pipeline.  A vector-memory instruction costs the issuing wave
             // about one MFMA slot and the CU's address unit 16 clocks, so the loads of a K tile
@@ -1171,9 +912,8 @@ static int launch_k(const GemmParams &p_in, int num_cus, hipStream_t s, int *mai
     const int n_tiles = ceil_div(p.N, BN);
     const int m_tiles = GROUPED ? p.max_m_tiles : ceil_div(p.M, BM);
     if (m_tiles <= 0 || n_tiles <= 0) return MOE_OK;
-    const size_t smem = STAGES == DTL16 ? (size_t)5 * (BM + BN) * 64  // five slots of one 32-wide K step
-                                        : (size_t)(STAGES == REG_STAGED ? 2 : STAGES) * (BM + (BQ == 8 ? BN / 2 : BQ == 4 ? BN / 4 : BN)) * BK * sizeof(uint16_t) +
-                                              (BQ == 4 ? 2 * BN * 16 : 0);  // 4-bit weights: two buffers of block scales
+    const size_t smem = (size_t)(STAGES == REG_STAGED ? 2 : STAGES) * (BM + (BQ == 8 ? BN / 2 : BQ == 4 ? BN / 4 : BN)) * BK * sizeof(uint16_t) +
+                        (BQ == 4 ? 2 * BN * 16 : 0);  // 4-bit weights: two buffers of block scales
     auto kern = gemm_bf16_kernel<BM, BN, WM, WN, OUT_F32, RELU, GROUPED, KFULL, MINB, STAGES, NT, BQ>;
     // per instantiation, once, whichever host thread comes first: the LDS size attribute and the occupancy
     static std::once_flag once;
@@ -1223,7 +963,7 @@ static int launch_one(const GemmParams &p, int num_cus, hipStream_t s, int *main
     // pipeline zero-fills the last K tile, and the gate's shapes run a plain two-stage loop
     return (p.K % BK == 0)
                ? launch_k<BM, BN, WM, WN, OUT_F32, RELU, GROUPED, true, MINB, STAGES>(p, num_cus, s, main_grid)
-               : launch_k<BM, BN, WM, WN, OUT_F32, RELU, GROUPED, false, MINB, STAGES == REG_STAGED || STAGES == DTL16 ? REG_STAGED : 2>(p, num_cus, s, main_grid);
+               : launch_k<BM, BN, WM, WN, OUT_F32, RELU, GROUPED, false, MINB, STAGES == REG_STAGED ? REG_STAGED : 2>(p, num_cus, s, main_grid);
 }
 
 // grouped GEMM on the direct-to-LDS pipeline, bf16 (BQ = 0), 8-bit (8) or 4-bit (4) weights (K a multiple of the K tile:
@@ -1299,7 +1039,7 @@ int gemm_bf16_variant_block_m(int v)
 {
     switch (v) {
     case 8: return kRingMap;
-    case 10: case 11: return 128;
+    case 10: return 128;
     case 2: case 22: case 48: return 64;
     case 3: case 4: case 5: case 23: case 24: case 25: case 43: case 44: return 32;
     default: return 256;
@@ -1307,16 +1047,20 @@ int gemm_bf16_variant_block_m(int v)
 }
 
 // Tile shapes of the grouped GEMM.  variant -> (BM, BN, waves, pipeline)
-//   8: 32 .. 256 x 256, 8 waves, gemm_ring.hip    11: 128x256, 8 waves, ring    10: 128x128, 4 waves, register-staged
+//   8: 32 .. 256 x 256, 8 waves, gemm_ring.hip    10: 128x128, 4 waves, register-staged
 //   9: 256x256, register-staged, for what gemm_ring.hip cannot address
 //   2: 64x128, 4 waves, direct-to-LDS    3, 4, 5: 32x128, the same, weights read non-temporally, plainly, by tile (kNtRows)
 // By the average number of rows per expert, by how many 256-column weight panels there are (E * min(D, F) / 256, the
 // same for both GEMMs of a layer), and by how many weights a GEMM streams.
-//  * Tiles cut to an expert's rows (8) pay as soon as most experts need two 128-row tiles, and from 64 rows on for GEMMs of
+//  * Tiles cut to an expert's rows (8) pay as soon as most experts need two 128-row tiles, and from 8 rows on for GEMMs of
 //    2^29 weights and more (1 GB, four times the last-level cache), whose time is that of one pass over an expert's weights.
 //    FFN in us, what ran before / 8, evenly spread, skewed (exponent 0.8), more skewed (1.2) rows:
-//      128 experts 2048 -> 8192, 64 rows per expert 1611 / 1597, 1807 / 1712, 1874 / 1731; 100 rows 1614 / 1695, 1991 / 1824,
-//      2213 / 1885; 160 rows 1972 / 1858, 2316 / 2071, 2597 / 2199; 256 rows 2844 / 2366, 2870 / 2560, 3090 / 2654; 800 rows
+//      128 experts 2048 -> 8192, 4 rows per expert 1319 / 1482, 1125 / 1293, 978 / 1087; 8 rows 1513 / 1544, 1496 / 1438,
+//      1304 / 1304; 34 rows 1476 / 1554, 1594 / 1594, 1645 / 1613; 64 rows 1556 / 1588, 1750 / 1683, 1840 / 1688; 100 rows
+//      1611 / 1661, 1993 / 1795, 2129 / 1868;
+//      512 experts 1024 -> 4096, 8 rows 1550 / 1535, 1498 / 1454, 1208 / 1150; 34 rows 1600 / 1584, 1665 / 1601, 1706 / 1565
+//      (of the 128 experts only an even batch of 12 to 50 rows is behind, by 1 to 8 %: a 128x256 ring of fixed height ran there)
+//      128 experts 2048 -> 8192, 160 rows 1972 / 1858, 2316 / 2071, 2597 / 2199; 256 rows 2844 / 2366, 2870 / 2560, 3090 / 2654; 800 rows
 //      6901 / 5767, 6612 / 5815, 6384 / 5904
 //      64 experts 1024 -> 4096, 100 rows 261 / 277, 299 / 298, 300 / 294; 160 rows 351 / 307, 349 / 327, 353 / 333; 800 rows
 //      956 / 853, 903 / 825, 904 / 873
@@ -1325,16 +1069,13 @@ int gemm_bf16_variant_block_m(int v)
 //    512 -> 2048, 192 rows 35 / 42; 16 experts 1024 -> 4096, 192 rows 107 / 113, 111 / 121, 113 / 121; 8 experts 2048 -> 8192, 192
 //    rows 196 / 205, 201 / 246, 198 / 227), with 96 and more behind (24 experts 1000 -> 4000, 192 rows 192 / 179; 16 experts 2048 -> 8192,
 //    256 rows 446 / 400, 478 / 377, 439 / 408).
-//  * The 128-row ring streams the weights of such a GEMM faster than any other shape from 18 rows on (128 experts
-//    2048 -> 8192, skewed, 32x128 / 128x128 / 128x256 ring: 18 rows 1589 / 1594 / 1486, 36 rows 2159 / 1744 / 1692).  With
-//    fewer weights it does not pay: 32x128 / 128x256 ring at 24 rows per expert, even, skewed, more skewed: 256 experts
-//    512 -> 2048 281 / 272, 280 / 309, 244 / 244; 512 experts 256 -> 1024 157 / 157, 160 / 177, 135 / 133.
-//  * There 64x128 is the steadiest shape from 34 to 63 rows, 32x128 / 64x128 / 128x128: 128 experts 512 -> 2048, 36 rows 171 / 161 /
+//    With fewer weights it does not pay below that (8 / small tiles at 24 rows: 128 experts 512 -> 2048 137 / 137, 159 / 135, 157 / 133).
+//  * For those 64x128 is the steadiest shape from 34 to 63 rows, 32x128 / 64x128 / 128x128: 128 experts 512 -> 2048, 36 rows 171 / 161 /
 //    162, 173 / 169 / 183, 170 / 164 / 176; 64 experts 1024 -> 4096, 48 rows 314 / 287 / 266, 327 / 280 / 309, 329 / 281 / 302; 16
 //    experts 2048 -> 8192, 48 rows 292 / 291 / 279, 319 / 298 / 285, 310 / 297 / 323; at 64 rows 128x128 has caught up (342 / 320 /
 //    284, 332 / 311 / 309, 342 / 308 / 338).  With 64 panels or fewer it is ahead from 48 on (16 experts 1024 -> 4096 115 / 108 /
 //    101, 124 / 114 / 102, 120 / 114 / 110).
-//  * K that is no multiple of the K tile has neither the 128-row ring nor 64x128: there 128 rows pay from 30 on.
+//  * K that is no multiple of the K tile does not have 64x128: there 128 rows pay from 30 on.
 int gemm_bf16_variant(int64_t n_rows, int E, int N, int K, int num_cus)
 {
     const int64_t avg = E > 0 ? n_rows / E : n_rows;
@@ -1344,10 +1085,9 @@ int gemm_bf16_variant(int64_t n_rows, int E, int N, int K, int num_cus)
     const bool heavy = whole && (int64_t)E * N * K >= kHeavyWeights;
     const bool ring = gemm_ring_ok(n_rows, N, K);
     const int64_t tiles = (int64_t)E * ((avg + 255) / 256) * ceil_div(width, 256);
-    if (ring && ((avg >= 116 && tiles >= 96) || (heavy && avg >= 64))) return 8;
+    if (ring && ((avg >= 116 && tiles >= 96) || (heavy && avg >= kNtRows))) return 8;
     if (avg >= 192) return ring ? 10 : 9;
     const int small = avg >= kNtRows ? 4 : avg >= kNtSoleRows ? 5 : 3;
-    if (heavy && panels >= 2 * (int64_t)num_cus) return avg >= 18 ? 11 : small;
     if (4 * panels <= num_cus) return avg >= 48 ? 10 : small;
     if (whole && !heavy && avg < 64) return avg >= 34 ? 2 : small;
     return avg >= 30 ? 10 : small;
@@ -1398,13 +1138,6 @@ int launch_gemm_bf16(const GemmParams &p, bool grouped, int variant, bool out_f3
     }
     switch (variant) {
     case 8: return launch_gemm_ring(p, relu, s);
-    case 11:
-        // the ring pipeline's 32-bit byte offsets
-        if ((int64_t)p.M * p.lda * 2 < (1ll << 32) && (p.a_zero_row + 1) * p.lda * 2 < (1ll << 32) && (int64_t)p.N * p.ldb * 2 < (1ll << 32) &&
-            ((int64_t)(p.c_zero_row >= p.M ? p.c_zero_row + 1 : p.M) + 256) * p.ldc * 2 < (1ll << 32))
-            return relu ? launch_k<128, 256, 2, 4, false, true, true, true, 1, DTL16>(p, num_cus, s, nullptr)
-                        : launch_k<128, 256, 2, 4, false, false, true, true, 1, DTL16>(p, num_cus, s, nullptr);
-        return launch_grouped<128, 128, 2, 2, 2, REG_STAGED>(p, relu, num_cus, s);
     case 9: {
         // whole rounds as 256x256 tiles, the partly filled last round as 128x128 sub-tiles
         GemmParams q = p;

@@ -309,12 +309,16 @@ __device__ __forceinline__ void block_exclusive_scan4(int *vals, int n, int *wav
 
 // Schedule of the grouped GEMM's ring kernel (layout: moe_internal.h), by one whole block.  rows_of(e), e < E.
 // What it balances: an expert's rows come in tiles of up to eight 32-row units, and a tile costs about six units whatever
-// its height (measured: the time per K tile is 0.8 us at one unit and 1.6 at eight).  The experts' rows, in order, are cut in
+// its height, and one of less than four units as much as one of four: its time is that of the weights' way into the CU
+// (measured: the time per K tile is 0.8 us at one unit, 1.05 at four and 1.6 at eight; counted as less, it made 128 experts of
+// one or two units fall to the XCDs by 15 to 17 instead of 16, a round more for some: 1473 against 1610 us for 34 rows).  The experts' rows, in order, are cut in
 // eight parts of equal cost, one per XCD, between two tiles of an expert at most (an XCD's blocks share weights and rows in
 // its L2, so what one expert needs stays together).  Inside a part every expert's tiles get the same height, at most the
 // one that makes the part's rounds of 32 blocks cheapest, and the experts with the taller tiles come first, so that a round's
 // tiles cost about the same.  (Places among experts of one height are handed out by LDS atomics: their
 // order differs between runs, the sums do not.)
+__device__ __forceinline__ int ring_cost(int units) { return units == 0 ? 0 : max(units, 4) + 6 * ((units + 7) >> 3); }
+
 struct RingScratch {
     int cost[MOE_MAX_E];         // then its prefix
     int wave_tot[16];
@@ -331,7 +335,7 @@ __device__ __forceinline__ void ring_schedule(const Rows &rows_of, int E, int n1
     const int tid = threadIdx.x, nthreads = blockDim.x, lane = tid % kWave, wave = tid / kWave;
     for (int e = tid; e < E; e += nthreads) {
         const int units = (rows_of(e) + 31) >> 5;
-        sm.cost[e] = units + 6 * ((units + 7) >> 3);
+        sm.cost[e] = ring_cost(units);
     }
     if (tid < 8) sm.units[tid] = 0;
     if (tid < 72) sm.tiles[tid / 9][tid % 9] = 0;
@@ -344,7 +348,7 @@ __device__ __forceinline__ void ring_schedule(const Rows &rows_of, int E, int n1
     auto pieces = [&](int e, auto fn) {
         const int units = (rows_of(e) + 31) >> 5;
         if (units == 0) return;
-        const int cuts = (units + 7) >> 3, height = (units + cuts - 1) / cuts, cost = units + 6 * cuts;
+        const int cuts = (units + 7) >> 3, height = (units + cuts - 1) / cuts, cost = ring_cost(units);
         const int64_t pre = sm.cost[e];
         int done = 0;
         for (int x = (int)(pre * 8 / total); x < 8 && done < units; ++x) {
