@@ -553,14 +553,10 @@ __global__ __launch_bounds__(kThreads) void route_rank_kernel(const int32_t *__r
 // ------------------------------------------------------------------------------------------------
 static constexpr int kSmallRouteMax = 1024;  // assignments: one round of the block
 
-// Assignments up to which that block also beats the three launches.  A round costs by the distinct experts of a wave: us by 1100,
-// 2048, 3072, 4096 assignments, against 17.5 ... 19 for the three launches: 8 experts 13, 13, 13, 17; 16 experts 13, 13, 17, 22; 24 experts
-// 13, 15, 22, 28; 32 experts 14, 17, 25, 32; 48 experts 16, 20, 29, 37; 64 experts 18, 22, 32, 41.
-static int small_route_max(int E)
-{
-    const int n = 56 * kSmallRouteMax / E;
-    return n < kSmallRouteMax ? kSmallRouteMax : n > 4 * kSmallRouteMax ? 4 * kSmallRouteMax : n;
-}
+// Assignments up to which that block also beats the three launches, us by 1024, 1536, 2048, 3072 assignments against 8.2 ... 9.7
+// for the three launches: 8 experts 5.0, 6.3, 7.4, 9.8; 16 experts 5.1, 6.5, 7.5, 9.9; 32 experts 5.2, 6.6, 8.1.
+static constexpr int kRouteBlockMax = 2 * kSmallRouteMax;
+static_assert(kRouteBlockMax < 1 << 15 && MOE_MAX_E <= 1024, "the block's scan keeps rows and tiles in halves of a word, an expert per thread");
 
 __device__ __forceinline__ void route_small(const int32_t *idx, int n_assign, int E, int k, int32_t *__restrict__ counts,
                                             int32_t *__restrict__ offsets, int32_t *__restrict__ dst_row,
@@ -568,18 +564,24 @@ __device__ __forceinline__ void route_small(const int32_t *idx, int n_assign, in
                                             int32_t *__restrict__ tile_row, int32_t *__restrict__ num_tiles, int max_m_tiles,
                                             int ring_n1, int ring_n2)
 {
-    __shared__ int hist[MOE_MAX_E];   // counts, then the running totals of the ranking pass
+    __shared__ int hist[MOE_MAX_E];   // counts
+    __shared__ int seen[MOE_MAX_E];   // running totals of the ranking pass
     __shared__ int start[MOE_MAX_E];  // first row of every expert
     __shared__ int wave_tot[16];
     const int lane = threadIdx.x % kWave;
     const int wave = threadIdx.x / kWave;
-    for (int e = threadIdx.x; e < MOE_MAX_E; e += 1024) hist[e] = 0;
+    hist[threadIdx.x] = 0;  // 1024 threads, at most as many experts
+    seen[threadIdx.x] = 0;
     __syncthreads();
     for (int a = threadIdx.x; a < n_assign; a += 1024) atomicAdd(&hist[clamp_expert(idx[a], E)], 1);
     __syncthreads();
-    // exclusive scan over the experts: thread e owns expert e (E <= 1024)
+    // exclusive scan over the experts, thread e owns expert e: rows in the low half of a word, tiles of the grouped GEMM's M-tile
+    // map in the high half (at most kRouteBlockMax of either)
+    const bool map = tile_bm > 0 && tile_bm != kRingMap;  // uniform over the block
     const int cnt = threadIdx.x < E ? hist[threadIdx.x] : 0;
-    int incl = cnt;
+    const int nt = map ? (cnt + tile_bm - 1) / tile_bm : 0;
+    const int both = cnt | nt << 16;
+    int incl = both;
 #pragma unroll
     for (int off = 1; off < kWave; off <<= 1) {
         const int up = __shfl_up(incl, off, kWave);
@@ -587,32 +589,17 @@ __device__ __forceinline__ void route_small(const int32_t *idx, int n_assign, in
     }
     if (lane == kWave - 1) wave_tot[wave] = incl;
     __syncthreads();
-    int wbase = 0;
-    for (int w2 = 0; w2 < wave; ++w2) wbase += wave_tot[w2];
-    const int my_off = wbase + incl - cnt;
+    int before = incl - both;
+    for (int w2 = 0; w2 < wave; ++w2) before += wave_tot[w2];
+    const int my_off = before & 0xffff;
     if (threadIdx.x < E) {
         counts[threadIdx.x] = cnt;
         offsets[threadIdx.x] = my_off;
         start[threadIdx.x] = my_off;
     }
     if (threadIdx.x == 0) offsets[E] = n_assign;
-    if (tile_bm == kRingMap) {
-        __shared__ RingScratch ring;
-        ring_schedule([&](int e) { return hist[e]; }, E, ring_n1, ring_n2, tile_expert, tile_row, max_m_tiles, num_tiles, ring);
-    } else if (tile_bm > 0) {  // uniform over the block: the grouped GEMM's M-tile map, as route_rank_kernel's block 0 writes it
-        const int nt = (threadIdx.x < E && cnt > 0) ? (cnt + tile_bm - 1) / tile_bm : 0;
-        int incl_t = nt;
-#pragma unroll
-        for (int off = 1; off < kWave; off <<= 1) {
-            const int up = __shfl_up(incl_t, off, kWave);
-            if (lane >= off) incl_t += up;
-        }
-        __syncthreads();  // wave_tot is reused
-        if (lane == kWave - 1) wave_tot[wave] = incl_t;
-        __syncthreads();
-        int tbase = 0;
-        for (int w2 = 0; w2 < wave; ++w2) tbase += wave_tot[w2];
-        const int first = tbase + incl_t - nt;
+    if (map) {  // as route_rank_kernel's block 0 writes it
+        const int first = before >> 16;
         for (int i = 0; i < nt; ++i) {
             const int ti = first + i;
             if (ti < max_m_tiles) {
@@ -621,53 +608,39 @@ __device__ __forceinline__ void route_small(const int32_t *idx, int n_assign, in
             }
         }
         if (threadIdx.x == 1023) num_tiles[0] = min(first + nt, max_m_tiles);
+    } else if (tile_bm > 0) {
+        __shared__ RingScratch ring;
+        ring_schedule([&](int e) { return hist[e]; }, E, ring_n1, ring_n2, tile_expert, tile_row, max_m_tiles, num_tiles, ring);
     }
     __syncthreads();
-    for (int e = threadIdx.x; e < MOE_MAX_E; e += 1024) hist[e] = 0;  // now: assignments ranked so far
-    __syncthreads();
     const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
+    int nbits = 0;
+    while ((1 << nbits) < E) ++nbits;
     for (int a0 = 0; a0 < n_assign; a0 += 1024) {  // trip count uniform over the block
         const int a = a0 + threadIdx.x;
         const bool live = a < n_assign;
         const int e = live ? clamp_expert(idx[a], E) : -1;
-        // lanes of the wave with the same expert: one ballot per distinct expert present
-        int below = 0, same = 0, leader = 0;
-        uint64_t todo = __ballot(live);
-        while (todo) {
-            const int src = __ffsll((unsigned long long)todo) - 1;
-            const int e0 = __shfl(e, src, kWave);
-            const uint64_t mask = __ballot(e == e0);
-            if (e == e0) {
-                below = __popcll(mask & lt_mask);
-                same = __popcll(mask);
-                leader = (lane == src);
-            }
-            todo &= ~mask;
+        // lanes of the wave with the same expert, by one ballot per bit of the index (see route_rank_kernel).  One per expert
+        // present, as here before, made this loop the block's time: 64 tokens over 128 experts 18.6 us with their top-k, now 12.4.
+        uint64_t mask = __ballot(live);
+        for (int b = 0; b < nbits; ++b) {
+            const uint64_t bal = __ballot(live && ((e >> b) & 1));
+            mask &= ((e >> b) & 1) ? bal : ~bal;
         }
+        const int below = __popcll(mask & lt_mask), same = __popcll(mask);
+        const int first = live ? __ffsll((unsigned long long)mask) - 1 : lane;  // the group's first lane
+        const bool leader = live && first == lane;
         // the waves take their turns in order; the first lane of every expert group moves the total
         int base = 0;
         const int live_waves = min(16, (n_assign - a0 + kWave - 1) / kWave);  // uniform over the block
         for (int w2 = 0; w2 < live_waves; ++w2) {
-            if (wave == w2 && live && leader) {
-                base = hist[e];
-                hist[e] = base + same;
+            if (wave == w2 && leader) {
+                base = seen[e];
+                seen[e] = base + same;
             }
             __syncthreads();
         }
-        // hand the group's base to its other lanes
-        {
-            uint64_t todo2 = __ballot(live);
-            int got = base;
-            while (todo2) {
-                const int src = __ffsll((unsigned long long)todo2) - 1;
-                const int e0 = __shfl(e, src, kWave);
-                const int b0 = __shfl(base, src, kWave);
-                const uint64_t mask = __ballot(e == e0);
-                if (e == e0) got = b0;
-                todo2 &= ~mask;
-            }
-            base = got;
-        }
+        base = __shfl(base, first, kWave);  // to the group's other lanes
         if (live) {
             const int r = start[e] + base + below;
             dst_row[a] = r;
@@ -734,7 +707,7 @@ bool route_uses_hist(int T, int k) { return (int64_t)T * k > kSmallRouteMax; }
 int launch_route(const int32_t *idx, int T, int E, int k, const RouteOut &o, int32_t *block_hist, hipStream_t s, int hist_tokens)
 {
     ProfScope ps("route", s);  // histogram + prefix + rank together
-    if ((int64_t)T * k <= (hist_tokens > 0 ? kSmallRouteMax : small_route_max(E))) {  // a histogram that is there saves a launch
+    if ((int64_t)T * k <= (hist_tokens > 0 ? kSmallRouteMax : kRouteBlockMax)) {  // a histogram that is there saves a launch
         hipLaunchKernelGGL(route_small_kernel, dim3(1), dim3(1024), 0, s, idx, T * k, E, k, o);
         MOE_LAUNCH_CHECK("route_small_kernel");
         return MOE_OK;
