@@ -1059,7 +1059,8 @@ int gemm_bf16_variant_block_m(int v)
 //      1304 / 1304; 34 rows 1476 / 1554, 1594 / 1594, 1645 / 1613; 64 rows 1556 / 1588, 1750 / 1683, 1840 / 1688; 100 rows
 //      1611 / 1661, 1993 / 1795, 2129 / 1868;
 //      512 experts 1024 -> 4096, 8 rows 1550 / 1535, 1498 / 1454, 1208 / 1150; 34 rows 1600 / 1584, 1665 / 1601, 1706 / 1565
-//      (of the 128 experts only an even batch of 12 to 50 rows is behind, by 1 to 8 %: a 128x256 ring of fixed height ran there)
+//      (of the 128 experts only an even batch of 20 to 80 rows is behind, by 3 to 4 %, layer 1449 / 1504 at 25 rows, 1579 / 1629 at 78: a
+//      128x256 ring of fixed height ran there; the same rows skewed are 2 % behind to 6 % ahead, and the host sees the mean only)
 //      128 experts 2048 -> 8192, 160 rows 1972 / 1858, 2316 / 2071, 2597 / 2199; 256 rows 2844 / 2366, 2870 / 2560, 3090 / 2654; 800 rows
 //      6901 / 5767, 6612 / 5815, 6384 / 5904
 //      64 experts 1024 -> 4096, 100 rows 261 / 277, 299 / 298, 300 / 294; 160 rows 351 / 307, 349 / 327, 353 / 333; 800 rows

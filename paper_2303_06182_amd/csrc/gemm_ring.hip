@@ -26,7 +26,8 @@
 //      the other register set and block 0 at once, block i in place behind its last MFMA) and the loads of the K tile
 //      two ahead, both halves of a 16-row group back to back (the second request finds the line in the L1 or merges
 //      with the first), the first half into slot u + 4, the second into slot u + 5 = u: the weights in the even step,
-//      the rows in the odd one behind its wait, so that the weights, which come from further away, have longer to land.
+//      the rows in the odd one behind its wait, so that the weights, which come from further away, have longer to land;
+//      the other way round in tiles of up to 128 rows, where HBM sets the pace.
 //      "At most as many outstanding as the even step issued" is the wait of point 2.
 // A slot row is 64 bytes: 16-byte chunk c of row r sits at position c ^ ((r >> 2) & 3), which keeps the 16 lanes x 16
 // bytes of a fragment read on 16 different bank groups; the permutation is applied on the global side of the load,
@@ -253,7 +254,8 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
         for (int ni = 1; ni < NI; ++ni) mfma(std::false_type{}, 0, ni);
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("" ::: "memory");
-        // lgkmcnt(0); odd steps: at most the weight loads of the even step before may be outstanding
+        // lgkmcnt(0); odd steps: at most the loads of the even step before may be outstanding
+        static_assert(AG == BG, "either operand's loads are as many");
         if (P == 1)
             __builtin_amdgcn_s_waitcnt(0x0070 | (2 * BG));
         else
@@ -264,7 +266,7 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
         const int nslot = r_slot + 1 == NSLOT ? 0 : r_slot + 1;
 #pragma unroll
         for (int ni = 0; ni < NI; ++ni) w16[P ^ 1][ni] = read_b(nslot, ni);
-        if constexpr (M > 1) a16[0] = read_a(nslot, 0);
+        a16[0] = read_a(nslot, 0);
         a16[M - 1 + (P ^ 1)] = read_a(nslot, M - 1);
         __builtin_amdgcn_sched_barrier(0);
         // the step's loads, the j-th behind MFMA j * POST / 4 of those behind the barrier
@@ -272,7 +274,14 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
 #pragma unroll
             for (int j = 0; j < 4; ++j)
                 if (j * POST / 4 == at) {
-                    if constexpr (P == 0) {
+                    // Up to four blocks a K tile takes as long as HBM takes for its weights, and asking for them in the odd step, one
+                    // K tile ahead instead of one and a half, is the faster order (one pair in each step is between).  us per GEMM, 128
+                    // experts 2048 -> 8192, before / after: 25 rows per expert 795 / 743 and 771 / 717, 39 rows 780 / 774 and 771 /
+                    // 728, 39 skewed 790 / 792 and 773 / 757, 78 rows 826 / 824 and 796 / 773.  With full tiles the same or 1 % slower.
+                    if constexpr (M <= 4) {
+                        if constexpr (P == 0) issue_a(j >> 1, j & 1);
+                        else issue_b(j >> 1, j & 1);
+                    } else if constexpr (P == 0) {
                         issue_b(j >> 1, j & 1);
                     } else {
                         // A group past the tile's end would only fill zeros.  Stepping over it pays where the steps are short: the
@@ -281,7 +290,6 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
                     }
                 }
         };
-        if constexpr (POST == 0) loads_at(0);
 #pragma unroll
         for (int mi = 1; mi < M; ++mi) {
 #pragma unroll
@@ -393,7 +401,9 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
     while (true) {
-        const int blocks = (t.row_end - t.row0 + 31) >> 5;
+        // One block per wave runs as two: with one, a step's loads leave in a burst behind the barrier (25 rows per expert, 128 experts
+        // 2048 -> 8192: 768 and 744 us where two blocks take 758 and 740).
+        const int blocks = max(2, (t.row_end - t.row0 + 31) >> 5);
 #define MOE_RING_CASE(M) if (opaque(blocks) == M) run_tile(t, std::integral_constant<int, M>{})
         MOE_RING_CASE(8);
         MOE_RING_CASE(7);
@@ -402,7 +412,6 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
         MOE_RING_CASE(4);
         MOE_RING_CASE(3);
         MOE_RING_CASE(2);
-        MOE_RING_CASE(1);
 #undef MOE_RING_CASE
         if (!l_more) break;  // the stream has moved on already
         t = nx;
