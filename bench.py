@@ -57,6 +57,8 @@ def profile_kernel_name(kernel: str):
         if not grouped:
             return "gate_gemm" if (out_f32 or k.startswith("gemm_f32")) else None
         return "expert_gemm1" if relu else "expert_gemm2"
+    if k.startswith("gemm_ring_kernel<"):  # <RELU, RAGGED>
+        return "expert_gemm1" if k[k.index("<") + 1:].startswith("true") else "expert_gemm2"
     if k.startswith("gemm_stream_kernel<"):  # <weight storage, RELU, ...>
         args = [a.strip() for a in k[k.index("<") + 1:].rstrip(">").split(",")]
         return None if args[0] != "0" else "expert_gemm1" if args[1] == "true" else "expert_gemm2"
@@ -71,8 +73,8 @@ def traffic_from_profile(workload: str, profiles_dir: str = None):
     """HBM-side bytes per launch of every kernel of the layer, from the committed rocprofv3 counter summary
     profiles/moe_layer_forward_<workload>.txt: the FETCH_SIZE and WRITE_SIZE sections (KiB per dispatch, two
     --pmc runs), each scaled by what the same counter reads for the 1 GiB-read + 1 GiB-write calibration kernel
-    of the same run (the row of torch's elementwise add).  A step made of several launches (an expert GEMM's main and
-    tail launch, the routing kernels) is the sum over them.  {} when there is no summary for the workload."""
+    of the same run (the row of torch's elementwise add).  A step made of several launches (the routing
+    kernels) is the sum over them.  {} when there is no summary for the workload."""
     path = os.path.join(profiles_dir or os.path.join(ROOT, "profiles"), "moe_layer_forward_%s.txt" % workload)
     if not os.path.exists(path):
         return {}

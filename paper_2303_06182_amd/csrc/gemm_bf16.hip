@@ -1066,6 +1066,7 @@ int gemm_bf16_variant_block_m(int v)
 //      64 experts 1024 -> 4096, 100 rows 261 / 277, 299 / 298, 300 / 294; 160 rows 351 / 307, 349 / 327, 353 / 333; 800 rows
 //      956 / 853, 903 / 825, 904 / 873
 //      24 experts 1000 -> 4000, 128 rows 190 / 157, 179 / 161, 180 / 160
+//    (taken before the low tiles' later weight requests, gemm_ring.hip, which took 3 to 6 % off the figures of 8 up to 64 rows.)
 //    They need tiles enough for the chip: with fewer than 96 in the GEMM with fewer columns 128x128 is ahead (10 / 8: 8 experts
 //    512 -> 2048, 192 rows 35 / 42; 16 experts 1024 -> 4096, 192 rows 107 / 113, 111 / 121, 113 / 121; 8 experts 2048 -> 8192, 192
 //    rows 196 / 205, 201 / 246, 198 / 227), with 96 and more behind (24 experts 1000 -> 4000, 192 rows 192 / 179; 16 experts 2048 -> 8192,
