@@ -46,6 +46,7 @@
 
 #include "gemm_bf16_dev.h"
 #include "moe_internal.h"
+#include "ring_schedule.h"
 
 namespace moe355 {
 
@@ -115,11 +116,9 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
         w_cuts = 0, w_expert = 0, w_row0 = 0, w_row_end = 0;
         if (w_base + lane < x_last) {
             w_expert = p.ring_list[w_base + lane];
-            const int first = p.offsets[w_expert];
-            w_row0 = first, w_row_end = p.offsets[w_expert + 1];
-            if (w_expert == cut_first >> kRingCutShift) w_row0 = first + 32 * (cut_first & ((1 << kRingCutShift) - 1));
-            if (w_expert == cut_last >> kRingCutShift) w_row_end = min(w_row_end, first + 32 * (cut_last & ((1 << kRingCutShift) - 1)));
-            w_cuts = (int)((uint32_t)(((w_row_end - w_row0 + 31) >> 5) + x_cap - 1) / (uint32_t)x_cap);
+            w_row0 = p.offsets[w_expert], w_row_end = p.offsets[w_expert + 1];
+            ring_clip(w_expert, cut_first, cut_last, w_row0, w_row_end);
+            w_cuts = (int)((uint32_t)(ring_units(w_row_end - w_row0) + x_cap - 1) / (uint32_t)x_cap);
         }
         int incl = w_cuts;
 #pragma unroll

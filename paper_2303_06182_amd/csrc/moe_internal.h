@@ -161,10 +161,10 @@ int launch_tile_map(const int32_t *offsets, int E, int block_m, int32_t *tile_ex
 // Schedule of the ring kernel, in the place of a tile map.  For each of the layer's two GEMMs a list of experts grouped by
 // XCD, the first GEMM's in tile_expert, the second's in tile_row.  Among the 64 words at num_tiles: kRingFirst + x, where XCD
 // x's part of the lists begins (x = 8: where the last ends); kRingCut + x, the expert cut between XCD x - 1 and x and the
-// 32-row unit of it that the latter begins with (expert << kRingCutShift | unit; MOE_MAX_E as expert: none); kRingCap + x, the
+// 32-row unit of it that the former ends in front of (expert << kRingCutShift | unit; MOE_MAX_E as expert: none); kRingCap + x, the
 // greatest tile height in units (bits 0 .. 7 first, 8 .. 15 second GEMM).
 static constexpr int kRingMap = 1 << 30;  // tile height that stands for it
-static constexpr int kRingFirst = 8, kRingCut = 17, kRingCap = 26, kRingCutShift = 20;
+static constexpr int kRingFirst = 8, kRingCut = 17, kRingCap = 26;
 
 // ---- routing -------------------------------------------------------------------------------------
 int launch_topk(float *logits, int T, int E, int k, int renorm, int32_t *idx, float *w, hipStream_t s, int n_parts = 1,

@@ -6,6 +6,7 @@
 // stable argsort (ascending token inside each expert) and costs O(N) instead of O(N log N).
 // Nothing uses atomics on global memory, so the permutation is the same on every run.
 #include "moe_internal.h"
+#include "ring_schedule.h"
 
 namespace moe355 {
 
@@ -317,8 +318,6 @@ __device__ __forceinline__ void block_exclusive_scan4(int *vals, int n, int *wav
 // one that makes the part's rounds of 32 blocks cheapest, and the experts with the taller tiles come first, so that a round's
 // tiles cost about the same.  (Places among experts of one height are handed out by LDS atomics: their
 // order differs between runs, the sums do not.)
-__device__ __forceinline__ int ring_cost(int units) { return units == 0 ? 0 : max(units, 4) + 6 * ((units + 7) >> 3); }
-
 struct RingScratch {
     int cost[MOE_MAX_E];         // then its prefix
     int wave_tot[16];
@@ -334,8 +333,7 @@ __device__ __forceinline__ void ring_schedule(const Rows &rows_of, int E, int n1
 {
     const int tid = threadIdx.x, nthreads = blockDim.x, lane = tid % kWave, wave = tid / kWave;
     for (int e = tid; e < E; e += nthreads) {
-        const int units = (rows_of(e) + 31) >> 5;
-        sm.cost[e] = ring_cost(units);
+        sm.cost[e] = ring_cost(ring_units(rows_of(e)));
     }
     if (tid < 8) sm.units[tid] = 0;
     if (tid < 72) sm.tiles[tid / 9][tid % 9] = 0;
@@ -344,27 +342,16 @@ __device__ __forceinline__ void ring_schedule(const Rows &rows_of, int E, int n1
     __syncthreads();
     int total = 0;
     block_exclusive_scan4(sm.cost, E, sm.wave_tot, total);
-    // the pieces of expert e: fn(part, first unit, units)
-    auto pieces = [&](int e, auto fn) {
-        const int units = (rows_of(e) + 31) >> 5;
-        if (units == 0) return;
-        const int cuts = (units + 7) >> 3, height = (units + cuts - 1) / cuts, cost = ring_cost(units);
-        const int64_t pre = sm.cost[e];
-        int done = 0;
-        for (int x = (int)(pre * 8 / total); x < 8 && done < units; ++x) {
-            const int64_t in = (int64_t)total * (x + 1) - 8 * pre;  // 8 x cost of the expert in front of the part's end
-            int end = x == 7 ? units : (int)min((int64_t)cuts, (2 * in * cuts + 8 * cost) / (16 * (int64_t)cost)) * height;
-            end = min(end, units);
-            if (end > done) fn(x, done, end - done);
-            done = max(done, end);
-        }
-    };
+    auto pieces = [&](int e, auto piece, auto cut) { ring_pieces(ring_units(rows_of(e)), sm.cost[e], total, piece, cut); };
+    auto no_cut = [](int, int) {};
     for (int e = tid; e < E; e += nthreads)
-        pieces(e, [&](int x, int first, int units) {
-            if (first > 0) words[kRingCut + x] = e << kRingCutShift | first;  // cut in front of part x
-            atomicAdd(&sm.units[x], units);
-            for (int h = 1; h <= 8; ++h) atomicAdd(&sm.tiles[x][h], (units + h - 1) / h);
-        });
+        pieces(
+            e,
+            [&](int x, int, int units) {
+                atomicAdd(&sm.units[x], units);
+                for (int h = 1; h <= 8; ++h) atomicAdd(&sm.tiles[x][h], (units + h - 1) / h);
+            },
+            [&](int x, int first) { words[kRingCut + x] = e << kRingCutShift | first; });
     __syncthreads();
     if (tid < 16) {
         const int x = tid & 7, n = tid < 8 ? n1 : n2;
@@ -386,9 +373,12 @@ __device__ __forceinline__ void ring_schedule(const Rows &rows_of, int E, int n1
         return &sm.bin[g][8 * x + 8 - (units + k - 1) / k];
     };
     for (int e = tid; e < E; e += nthreads)
-        pieces(e, [&](int x, int, int units) {
-            for (int g = 0; g < 2; ++g) atomicAdd(bin_of(g, x, units), 1);
-        });
+        pieces(
+            e,
+            [&](int x, int, int units) {
+                for (int g = 0; g < 2; ++g) atomicAdd(bin_of(g, x, units), 1);
+            },
+            no_cut);
     __syncthreads();
     if (wave < 2) {
         const int v = sm.bin[wave][lane];
@@ -404,12 +394,15 @@ __device__ __forceinline__ void ring_schedule(const Rows &rows_of, int E, int n1
     }
     __syncthreads();
     for (int e = tid; e < E; e += nthreads)
-        pieces(e, [&](int x, int, int units) {
-            for (int g = 0; g < 2; ++g) {
-                const int at = atomicAdd(bin_of(g, x, units), 1);
-                if (at < max_list) (g == 0 ? list1 : list2)[at] = e;  // at most E + 7 places are needed
-            }
-        });
+        pieces(
+            e,
+            [&](int x, int, int units) {
+                for (int g = 0; g < 2; ++g) {
+                    const int at = atomicAdd(bin_of(g, x, units), 1);
+                    if (at < max_list) (g == 0 ? list1 : list2)[at] = e;  // at most E + 7 places are needed
+                }
+            },
+            no_cut);
 }
 
 // Stable position of every assignment.  Block b ranks its 256 tokens:
