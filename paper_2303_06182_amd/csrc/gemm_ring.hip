@@ -38,7 +38,8 @@
 // trip through LDS (all of which the ring holds).
 //
 // Launch: PERSISTENT, one block per CU.  Workgroups are handed to the 8 XCDs round-robin and each XCD has its own L2,
-// so the schedule (ring_schedule, route.hip) gives each a part of the experts' rows of equal cost.
+// so the schedule (ring_schedule, route.hip) gives each a part of the experts' rows of equal cost, or, where the rows are
+// too few for that, of the column tiles.
 // The load cursor walks the block's whole sequence of (tile, K tile) pairs, so the first K tiles of the NEXT tile are
 // loaded during the last steps of the current one and the epilogue's stores overlap the next tile.
 #include <mutex>
@@ -102,12 +103,14 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
     // way round in every second round, so that the blocks that begin with the taller tiles of a round end with the shorter
     // ones of the next.
     const int n_tiles = (p.N + BN - 1) / BN;
-    int x_first, x_last, cut_first, cut_last, x_cap;
+    int x_first, x_last, cut_first, cut_last, x_cap, shared;
     {
         const int32_t *const w = p.ring_words + (blockIdx.x & 7);
-        uniform_load2(w + kRingFirst, w + kRingFirst + 1, x_first, x_last);
+        uniform_load2(w + kRingFirst, w + kRingLast, x_first, x_last);
         uniform_load2(w + kRingCut, w + kRingCut + 1, cut_first, cut_last);
-        x_cap = (uniform_load(w + kRingCap) >> p.ring_cap_shift) & 15;
+        const int caps = uniform_load(w + kRingCap);
+        x_cap = (caps >> p.ring_cap_shift) & 15;
+        shared = caps >> kRingShared & 1;
     }
     // the experts, 64 at a time, one per lane: row range, tiles along the rows, tiles before it
     int w_base = __builtin_amdgcn_readfirstlane(x_first), w_pos = 0, w_total = 0;
@@ -132,6 +135,12 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
     load_window();
     const int s_blk = blockIdx.x >> 3;
     int pos = s_blk, pos_next = 63 - s_blk;
+    if (shared) {  // the one list of all XCDs, at most kRingSharedTiles experts and so one window: an eighth of its tiles each
+        const int first = ring_share(w_total, blockIdx.x & 7);
+        w_total = ring_share(w_total, (blockIdx.x & 7) + 1);
+        pos += first;
+        pos_next += first;
+    }
     RingTile nx;  // the stream's next tile
     auto next_tile_pos = [&]() __attribute__((always_inline)) -> bool {
         while (pos - w_pos >= w_total) {

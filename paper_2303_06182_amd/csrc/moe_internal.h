@@ -159,12 +159,13 @@ int launch_tile_map(const int32_t *offsets, int E, int block_m, int32_t *tile_ex
                     int32_t *num_tiles, int max_m_tiles, const int32_t *stage_of, int stage, hipStream_t s, int ring_n1 = 0, int ring_n2 = 0);
 
 // Schedule of the ring kernel, in the place of a tile map.  For each of the layer's two GEMMs a list of experts grouped by
-// XCD, the first GEMM's in tile_expert, the second's in tile_row.  Among the 64 words at num_tiles: kRingFirst + x, where XCD
-// x's part of the lists begins (x = 8: where the last ends); kRingCut + x, the expert cut between XCD x - 1 and x and the
-// 32-row unit of it that the former ends in front of (expert << kRingCutShift | unit; MOE_MAX_E as expert: none); kRingCap + x, the
-// greatest tile height in units (bits 0 .. 7 first, 8 .. 15 second GEMM).
+// XCD, the first GEMM's in tile_expert, the second's in tile_row.  Among the 64 words at num_tiles: kRingFirst + x and kRingLast
+// + x, where XCD x's part of the lists begins and ends; kRingCut + x, the expert cut between XCD x - 1 and x and the 32-row
+// unit of it that the former ends in front of (expert << kRingCutShift | unit; MOE_MAX_E as expert: none); kRingCap + x, the
+// greatest tile height in units (bits 0 .. 7 first, 8 .. 15 second GEMM) and, as bit kRingShared, that all XCDs have the same
+// list and each takes a part of its column tiles.
 static constexpr int kRingMap = 1 << 30;  // tile height that stands for it
-static constexpr int kRingFirst = 8, kRingCut = 17, kRingCap = 26;
+static constexpr int kRingFirst = 8, kRingLast = 16, kRingCut = 24, kRingCap = 33, kRingShared = 16;
 
 // ---- routing -------------------------------------------------------------------------------------
 int launch_topk(float *logits, int T, int E, int k, int renorm, int32_t *idx, float *w, hipStream_t s, int n_parts = 1,

@@ -36,6 +36,13 @@ __host__ __device__ __forceinline__ void ring_pieces(int units, int64_t pre, int
     }
 }
 
+// Where XCD x's tiles of a list of so many begin that all XCDs share.
+__host__ __device__ __forceinline__ int ring_share(int tiles, int x)
+{
+    const int at = ((tiles + 7) >> 3) * x;
+    return at < tiles ? at : tiles;
+}
+
 // Of the rows row0 ... row_end of an expert in a part's list, those that the part has; cut_first and cut_last are the cut
 // words of the part and of the one behind it.
 __host__ __device__ __forceinline__ void ring_clip(int expert, int cut_first, int cut_last, int &row0, int &row_end)

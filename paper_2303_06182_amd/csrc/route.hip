@@ -318,6 +318,17 @@ __device__ __forceinline__ void block_exclusive_scan4(int *vals, int n, int *wav
 // one that makes the part's rounds of 32 blocks cheapest, and the experts with the taller tiles come first, so that a round's
 // tiles cost about the same.  (Places among experts of one height are handed out by LDS atomics: their
 // order differs between runs, the sums do not.)
+//
+// Up to this many row tiles of a batch the XCDs share one list of experts and each takes an eighth of its output tiles: parts
+// of whole row tiles leave XCDs idle then, or with twice the others' work.  The list is in the experts' order: sorted by
+// height the first eighth would cost the most.  FFN in us, parts / shared: 128 experts 2048 -> 8192, 1024 rows on one expert 151 / 137,
+// on four 189 / 158; 8 experts 4096 -> 14336, 1024 rows on four 477 / 374, on one 401 / 288, 2000 evenly spread 732 / 599; 4
+// experts 8192 -> 28672, 400 rows on two 1238 / 661; 8 experts 2048 -> 8192, 2000 rows 265 / 230, 6400 rows 412 / 409.  Where both balance it is
+// the same (32 experts 2048 -> 8192, 256 rows 376 / 376, 3200 rows 431 / 425).  (Dealing the rounds of the whole chip over the XCDs instead, 32
+// neighbours on the list each, cost 32 even experts 10 %.)
+static constexpr int kRingSharedTiles = 32;
+static_assert(kRingSharedTiles <= kWave, "the ring kernel expects a shared list in one window");
+
 struct RingScratch {
     int cost[MOE_MAX_E];         // then its prefix
     int wave_tot[16];
@@ -342,7 +353,11 @@ __device__ __forceinline__ void ring_schedule(const Rows &rows_of, int E, int n1
     __syncthreads();
     int total = 0;
     block_exclusive_scan4(sm.cost, E, sm.wave_tot, total);
-    auto pieces = [&](int e, auto piece, auto cut) { ring_pieces(ring_units(rows_of(e)), sm.cost[e], total, piece, cut); };
+    bool shared = false;
+    auto pieces = [&](int e, auto piece, auto cut) {
+        if (!shared) ring_pieces(ring_units(rows_of(e)), sm.cost[e], total, piece, cut);
+        else if (ring_units(rows_of(e)) > 0) piece(0, 0, ring_units(rows_of(e)));
+    };
     auto no_cut = [](int, int) {};
     for (int e = tid; e < E; e += nthreads)
         pieces(
@@ -353,24 +368,38 @@ __device__ __forceinline__ void ring_schedule(const Rows &rows_of, int E, int n1
             },
             [&](int x, int first) { words[kRingCut + x] = e << kRingCutShift | first; });
     __syncthreads();
+    int row_tiles = 0;
+#pragma unroll
+    for (int x = 0; x < 8; ++x) row_tiles += sm.tiles[x][8];
+    shared = row_tiles <= kRingSharedTiles;  // uniform over the block
     if (tid < 16) {
-        const int x = tid & 7, n = tid < 8 ? n1 : n2;
+        const int x = tid & 7, n = tid < 8 ? n1 : n2, blocks = shared ? 256 : 32;
+        auto sum = [&](auto of) {  // of part x, or of all
+            int v = of(x);
+            if (shared) {
+                v = 0;
+                for (int i = 0; i < 8; ++i) v += of(i);
+            }
+            return v;
+        };
+        const int units = sum([&](int i) { return sm.units[i]; });
         float best = 0.f;
         int cap = 8;
         for (int h = 8; h >= 1; --h) {
-            const int tiles = sm.tiles[x][h];
+            const int tiles = sum([&](int i) { return sm.tiles[i][h]; });
             // below four units only to give every block of a single round a tile
-            if (tiles == 0 || (h < 4 && (int64_t)tiles * n > 32)) break;
-            const float c = (float)(((int64_t)tiles * n + 31) / 32) * (6.f + (float)sm.units[x] / (float)tiles);
+            if (tiles == 0 || (h < 4 && (int64_t)tiles * n > blocks)) break;
+            const float c = (float)(((int64_t)tiles * n + blocks - 1) / blocks) * (6.f + (float)units / (float)tiles);
             if (h == 8 || c < 0.97f * best) best = c, cap = h;
         }
         sm.cap[tid >> 3][x] = cap;
     }
     __syncthreads();
-    if (tid < 8) words[kRingCap + tid] = sm.cap[0][tid] | sm.cap[1][tid] << 8;
+    if (tid < 8) words[kRingCap + tid] = sm.cap[0][tid] | sm.cap[1][tid] << 8 | (int)shared << kRingShared;
+    if (shared && tid < 9) words[kRingCut + tid] = MOE_MAX_E << kRingCutShift;
     auto bin_of = [&](int g, int x, int units) {
         const int k = (units + sm.cap[g][x] - 1) / sm.cap[g][x];
-        return &sm.bin[g][8 * x + 8 - (units + k - 1) / k];
+        return &sm.bin[g][shared ? 0 : 8 * x + 8 - (units + k - 1) / k];
     };
     for (int e = tid; e < E; e += nthreads)
         pieces(
@@ -389,8 +418,10 @@ __device__ __forceinline__ void ring_schedule(const Rows &rows_of, int E, int n1
             if (lane >= off) incl += up;
         }
         sm.bin[wave][lane] = incl - v;
-        if (wave == 0 && (lane & 7) == 0) words[kRingFirst + (lane >> 3)] = incl - v;  // the same for both GEMMs
-        if (wave == 0 && lane == kWave - 1) words[kRingFirst + 8] = incl;
+        // the parts' places, the same for both GEMMs (shared: all experts are in the first bin)
+        if (wave == 0 && (lane & 7) == 0) words[kRingFirst + (lane >> 3)] = shared ? 0 : incl - v;
+        const int part_end = __shfl(incl, shared ? kWave - 1 : lane, kWave);
+        if (wave == 0 && (lane & 7) == 7) words[kRingLast + (lane >> 3)] = part_end;
     }
     __syncthreads();
     for (int e = tid; e < E; e += nthreads)

@@ -36,3 +36,9 @@ extern "C" int ring_cover(const int *rows, int E, int *covered, int *part_cost)
     }
     return all;
 }
+
+// first[x] .. first[x + 1]: what XCD x takes of a list of so many tiles that all share
+extern "C" void ring_shares(int tiles, int *first)
+{
+    for (int x = 0; x < 9; ++x) first[x] = ring_share(tiles, x);
+}

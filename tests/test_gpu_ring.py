@@ -1,6 +1,6 @@
 """The expert GEMM whose tiles are cut to an expert's rows (gemm_ring.hip) and its schedule: row counts around the 32-row
-units and the 256-row tile, one expert spread over several XCDs, idle experts, K that ends inside a K tile, column tiles
-that end inside the matrix."""
+units and the 256-row tile, one expert spread over several XCDs, so few rows that the XCDs share them, idle experts, K that
+ends inside a K tile, column tiles that end inside the matrix."""
 import numpy as np
 import pytest
 import torch
@@ -21,6 +21,10 @@ def counts_of(kind, E):
     elif kind == "hot":        # one expert holds most of the rows, its neighbours a handful
         c = EDGES + [int(v) for v in rng.integers(0, 40, E - len(EDGES))]
         c[len(EDGES)] = 116 * E
+    elif kind.startswith("few"):   # so many active experts, one to eight row tiles each
+        c = [0] * E
+        for i in range(int(kind[3:])):
+            c[(5 * i + 2) % E] = 116 * E // int(kind[3:]) + 37 * i
     else:                      # few active experts, far apart
         c = [0] * E
         c[3], c[4], c[E - 1] = 50 * E, 33, 67 * E
@@ -29,7 +33,8 @@ def counts_of(kind, E):
 
 @pytest.mark.parametrize("kind,E,D,F,bias", [
     ("even", 96, 128, 256, False), ("even", 56, 264, 328, True), ("hot", 100, 520, 136, True), ("hot", 56, 512, 264, False),
-    ("sparse", 52, 328, 320, True), ("even", 97, 72, 520, True)])
+    ("sparse", 52, 328, 320, True), ("even", 97, 72, 520, True),
+    ("few1", 8, 3080, 3144, True), ("few2", 8, 3080, 3144, False), ("few7", 8, 3072, 3080, False), ("few8", 32, 768, 776, True)])
 def test_rows_of_every_height(kind, E, D, F, bias):
     print("ring", kind, E, D, F, flush=True)
     counts = counts_of(kind, E)

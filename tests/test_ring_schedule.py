@@ -45,3 +45,11 @@ def test_random_batches(lib):
         weight = 1.0 / np.arange(1, len(active) + 1) ** rng.choice([0.0, 0.8, 1.2])
         counts[active] = rng.multinomial(n, weight / weight.sum())
         check(lib, counts)
+
+
+def test_shared_list(lib):
+    first = np.zeros(9, dtype=np.int32)
+    for tiles in list(range(0, 300)) + [32 * 112, 32 * 4096 + 1]:
+        lib.ring_shares(tiles, first.ctypes.data_as(ctypes.c_void_p))
+        assert first[0] == 0 and first[8] == tiles and np.all(np.diff(first) >= 0)
+        assert np.diff(first).max() == -(-tiles // 8)
