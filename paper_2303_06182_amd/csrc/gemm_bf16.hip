@@ -56,6 +56,7 @@
 namespace moe355 {
 
 bool gemm_ring_ok(int64_t n_rows, int N, int K);
+bool gemm_ring_addresses(int64_t n_rows, int N, int K);
 int launch_gemm_ring(const GemmParams &p, bool relu, hipStream_t s);
 
 static constexpr int BK = 64;
@@ -1052,31 +1053,43 @@ int gemm_bf16_variant_block_m(int v)
 //   2: 64x128, 4 waves, direct-to-LDS    3, 4, 5: 32x128, the same, weights read non-temporally, plainly, by tile (kNtRows)
 // By the average number of rows per expert, by how many 256-column weight panels there are (E * min(D, F) / 256, the
 // same for both GEMMs of a layer), and by how many weights a GEMM streams.
-//  * Tiles cut to an expert's rows (8) pay as soon as most experts need two 128-row tiles, and from 8 rows on for GEMMs of
-//    2^29 weights and more (1 GB, four times the last-level cache), whose time is that of one pass over an expert's weights.
-//    FFN in us, what ran before / 8, evenly spread, skewed (exponent 0.8), more skewed (1.2) rows:
-//      128 experts 2048 -> 8192, 4 rows per expert 1319 / 1482, 1125 / 1293, 978 / 1087; 8 rows 1513 / 1544, 1496 / 1438,
-//      1304 / 1304; 34 rows 1476 / 1554, 1594 / 1594, 1645 / 1613; 64 rows 1556 / 1588, 1750 / 1683, 1840 / 1688; 100 rows
-//      1611 / 1661, 1993 / 1795, 2129 / 1868;
-//      512 experts 1024 -> 4096, 8 rows 1550 / 1535, 1498 / 1454, 1208 / 1150; 34 rows 1600 / 1584, 1665 / 1601, 1706 / 1565
-//      (of the 128 experts only an even batch of 20 to 80 rows is behind, by 3 to 4 %, layer 1449 / 1504 at 25 rows, 1579 / 1629 at 78: a
-//      128x256 ring of fixed height ran there; the same rows skewed are 2 % behind to 6 % ahead, and the host sees the mean only)
-//      128 experts 2048 -> 8192, 160 rows 1972 / 1858, 2316 / 2071, 2597 / 2199; 256 rows 2844 / 2366, 2870 / 2560, 3090 / 2654; 800 rows
-//      6901 / 5767, 6612 / 5815, 6384 / 5904
-//      64 experts 1024 -> 4096, 100 rows 261 / 277, 299 / 298, 300 / 294; 160 rows 351 / 307, 349 / 327, 353 / 333; 800 rows
-//      956 / 853, 903 / 825, 904 / 873
-//      24 experts 1000 -> 4000, 128 rows 190 / 157, 179 / 161, 180 / 160
-//    (taken before the low tiles' later weight requests, gemm_ring.hip, which took 3 to 6 % off the figures of 8 up to 64 rows.)
-//    They need tiles enough for the chip: with fewer than 96 in the GEMM with fewer columns 128x128 is ahead (10 / 8: 8 experts
-//    512 -> 2048, 192 rows 35 / 42; 16 experts 1024 -> 4096, 192 rows 107 / 113, 111 / 121, 113 / 121; 8 experts 2048 -> 8192, 192
-//    rows 196 / 205, 201 / 246, 198 / 227), with 96 and more behind (24 experts 1000 -> 4000, 192 rows 192 / 179; 16 experts 2048 -> 8192,
-//    256 rows 446 / 400, 478 / 377, 439 / 408).
-//    With fewer weights it does not pay below that (8 / small tiles at 24 rows: 128 experts 512 -> 2048 137 / 137, 159 / 135, 157 / 133).
-//  * For those 64x128 is the steadiest shape from 34 to 63 rows, 32x128 / 64x128 / 128x128: 128 experts 512 -> 2048, 36 rows 171 / 161 /
+//  * Tiles cut to an expert's rows (8) pay from 116 rows on, where most experts need two 128-row tiles: over six layers (24, 32,
+//    48 experts 1000 -> 4000; 32, 64 experts 1024 -> 4096; 16 experts 2048 -> 8192) and even, skewed (exponent 0.5) and more skewed (0.8)
+//    loads the mean of 10 / 8 is 0.92 at 108 rows, 1.01 at 116, 1.03 at 124, 1.05 at 128, 1.09 at 150, either way by the layer and
+//    the load: FFN in us, 10 / 8, at 116 rows, 24 experts 1000 -> 4000 134 / 166, 134 / 166, 189 / 166; 48 experts
+//    249 / 232, 312 / 248, 285 / 253; 64 experts 1024 -> 4096 298 / 277, 299 / 325, 307 / 313; at 150 rows 339 / 289, 356 / 324, 352 / 325.
+//    Up to 768 columns and K, a tile's few K tiles do not make up for its start, and it takes 192 rows: 128 experts 512 -> 2048, 116 rows
+//    171 / 174, 172 / 192, 172 / 191, 150 rows 205 / 214, 189 / 192, 191 / 198, 192 rows 204 / 200, 211 / 210, 212 / 214; 158 experts
+//    384 -> 1536, 123 rows, even, skewed 129 / 143, 127 / 152; 64 experts 512 -> 2048, 256 rows 136 / 129, 136 / 129, 400 rows 177 / 147, 176 / 172.
+//  * They need tiles enough for the chip, 96 in the GEMM with fewer columns, and with fewer than 112 at least 120 rows.  Over 45 random
+//    layers (12 to 60 experts, 784 to 2032 -> 872 to 7928) and the same kinds of load the mean of 10 / 8 is 0.78 at 80 to 95 tiles; at
+//    96 to 111 tiles 0.85 with 116 to 119 rows, 0.98 with 120 to 127, 1.06 with 128 to 132; at 112 to 140 tiles 1.02, 1.05 and 1.08.
+//    With more rows, 10 / 8, even, skewed (0.5), more skewed (0.8), 64 to 95 tiles: 5 experts 2048 -> 4096, 298 rows 92 / 118, 93 / 119, 93 / 119; 13 experts 1536 -> 1536, 241 rows 73 / 81, 70 / 82, 76 / 83; 16 experts 1024
+//    -> 4096, 224 rows 105 / 118, 130 / 127, 133 / 127; 5 experts 4096 -> 14336, 197 rows 436 / 446, 485 / 441, 471 / 449; 96 to 128 tiles: 6 experts 2048
+//    -> 8192, 398 rows 250 / 238, 243 / 237, 250 / 243; 12 experts 2048 -> 4096, 176 rows 141 / 142, 158 / 142, 161 / 147; 14 experts 2048 -> 8192,
+//    170 rows 293 / 271, 313 / 280, 306 / 292; 8 experts 4096 -> 14336, 128 rows, even 530 / 476.  The GEMM with fewer columns counts, also
+//    where the other one has many: 8 experts 256 -> 3328, 1500 rows (48 and 624) 80 / 103, 82 / 107.  An even batch with a mean just
+//    below 256 rows needs two tiles for a part of its experts and counts so: 250 rows, 16 experts 1024 -> 4096 134 / 132, 132 / 132,
+//    131 / 130; 8 experts 2048 -> 8192 244 / 230, 241 / 234, 262 / 236.
+//  * GEMMs of 2^29 weights and more (1 GB, four times the last-level cache) take the time of one pass over an expert's weights.
+//    There they pay from 8 rows on, given two 256-column panels per CU.  What ran before / 8, even, skewed (0.8):
+//      128 experts 2048 -> 8192, 4 rows per expert 1319 / 1482, 1125 / 1293; 8 rows 1525 / 1427, 1549 / 1416; 25 rows 1453 / 1479, 1605 / 1642;
+//      39 rows 1479 / 1508, 1648 / 1640; 78 rows 1588 / 1627, 1759 / 1786; 100 rows 1630 / 1693, 1973 / 1831 (2 to 4 % behind on
+//      even batches of 25 to 100 rows: a 128x256 ring of fixed height ran there)
+//      512 experts 1024 -> 4096, 8 rows 1513 / 1460, 1485 / 1427; 34 rows 1599 / 1569, 1691 / 1657; 64 rows 1685 / 1658, 1869 / 1794
+//      64 experts 2048 -> 8192, 16 rows 787 / 762, 831 / 755; 64 rows 771 / 793, 921 / 926; half of the experts idle 394 / 387, 431 / 443
+//    With one panel per CU and less they lose where rows are even or experts idle, 10 or 4 / 8, even, half of the experts idle,
+//    skewed: 16 experts 4096 -> 14336, 32 rows 714 / 770, 397 / 476, 770 / 766; 100 rows 766 / 806, 564 / 527, 991 / 1007; 32 experts
+//    2048 -> 8192, 8 rows 388 / 376, 219 / 245, 424 / 375; 4 experts 8192 -> 28672, 100 rows 760 / 887, 605 / 661.
+//    With fewer weights 8 does not pay at few rows (8 / small tiles at 24 rows: 128 experts 512 -> 2048 137 / 137, 159 / 135, 157 / 133).
+//  * With fewer weights 64x128 is the steadiest shape from 34 to 63 rows, 32x128 / 64x128 / 128x128: 128 experts 512 -> 2048, 36 rows 171 / 161 /
 //    162, 173 / 169 / 183, 170 / 164 / 176; 64 experts 1024 -> 4096, 48 rows 314 / 287 / 266, 327 / 280 / 309, 329 / 281 / 302; 16
 //    experts 2048 -> 8192, 48 rows 292 / 291 / 279, 319 / 298 / 285, 310 / 297 / 323; at 64 rows 128x128 has caught up (342 / 320 /
 //    284, 332 / 311 / 309, 342 / 308 / 338).  With 64 panels or fewer it is ahead from 48 on (16 experts 1024 -> 4096 115 / 108 /
 //    101, 124 / 114 / 102, 120 / 114 / 110).
+//  * No dimension of 64 and less: 10 is ahead there of 256-row tiles too (9 / 10: 64 experts 64 -> 256, 800 rows 30 / 24; 64 -> 1024
+//    62 / 55; 16 experts 4096 -> 64, 1000 rows 95 / 85; 128 experts 40 -> 512, 1000 rows 82 / 69).  9 is for operands that 8 cannot address
+//    (9 / 10: 8 experts 2048 -> 8192, 33750 rows 15550 / 20945; 8 experts 1000 -> 8200, 33000 rows 9183 / 16220).
 //  * K that is no multiple of the K tile does not have 64x128: there 128 rows pay from 30 on.
 int gemm_bf16_variant(int64_t n_rows, int E, int N, int K, int num_cus)
 {
@@ -1085,10 +1098,11 @@ int gemm_bf16_variant(int64_t n_rows, int E, int N, int K, int num_cus)
     const int64_t panels = (int64_t)E * width / 256;
     const bool whole = N % BK == 0 && K % BK == 0;
     const bool heavy = whole && (int64_t)E * N * K >= kHeavyWeights;
-    const bool ring = gemm_ring_ok(n_rows, N, K);
-    const int64_t tiles = (int64_t)E * ((avg + 255) / 256) * ceil_div(width, 256);
-    if (ring && ((avg >= 116 && tiles >= 96) || (heavy && avg >= kNtRows))) return 8;
-    if (avg >= 192) return ring ? 10 : 9;
+    const int64_t tiles = (int64_t)E * ((avg + 8 + 255) / 256) * ceil_div(width, 256);
+    if (gemm_ring_ok(n_rows, N, K) &&
+        ((tiles >= 96 && avg >= (width <= 768 ? 192 : tiles < 112 ? 120 : 116)) || (heavy && avg >= kNtRows && panels >= 2 * (int64_t)num_cus)))
+        return 8;
+    if (avg >= 192) return gemm_ring_addresses(n_rows, N, K) ? 10 : 9;
     const int small = avg >= kNtRows ? 4 : avg >= kNtSoleRows ? 5 : 3;
     if (4 * panels <= num_cus) return avg >= 48 ? 10 : small;
     if (whole && !heavy && avg < 64) return avg >= 34 ? 2 : small;

@@ -444,12 +444,14 @@ static int launch_ring_t(const GemmParams &p, hipStream_t s)
 }
 
 // For both GEMMs of a layer (N and K swap places): the kernel addresses its operands and C with 32-bit byte offsets from
-// one base, and its load stream is two K tiles ahead.
-bool gemm_ring_ok(int64_t n_rows, int N, int K)
+// one base, ...
+bool gemm_ring_addresses(int64_t n_rows, int N, int K)
 {
     const int64_t wide = N > K ? N : K;
-    return N > BK && K > BK && (n_rows + 1) * wide * 2 <= (int64_t)kNowhere && (int64_t)N * K * 2 <= (int64_t)kNowhere;
+    return (n_rows + 1) * wide * 2 <= (int64_t)kNowhere && (int64_t)N * K * 2 <= (int64_t)kNowhere;
 }
+// ... and its load stream is two K tiles ahead.
+bool gemm_ring_ok(int64_t n_rows, int N, int K) { return N > BK && K > BK && gemm_ring_addresses(n_rows, N, K); }
 
 int launch_gemm_ring(const GemmParams &p, bool relu, hipStream_t s)
 {

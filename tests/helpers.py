@@ -1,9 +1,11 @@
 """Helpers shared by the GPU parity tests (tests may use both the oracle and the library)."""
+import ctypes
+
 import numpy as np
 import torch
 
 from oracle import moe_oracle as orc
-from paper_2303_06182_amd import workloads as wl
+from paper_2303_06182_amd import binding, workloads as wl
 
 # Tolerances of the layer output against the fp64 oracle, as normalised max error
 #   max_i |y_gpu - y_ref| / max_i |y_ref|
@@ -87,3 +89,16 @@ def guarded_inputs(w: wl.Workload, device="cpu", with_ffn_bias=False):
 
     redraws = wl.clear_margins(w, inp["x"], margin_fn, delta=MARGIN)
     return inp, redraws
+
+
+# gemm_bf16_variant's shapes (gemm_bf16.hip)
+TILE_SHAPES = {2: "64x128", 3: "32x128", 4: "32x128", 5: "32x128", 8: "cut to rows", 9: "256x256", 10: "128x128"}
+
+
+def expert_tile_shape(n_rows: int, E: int, F: int, D: int, cus: int = 256) -> str:
+    """The tile shape that the library chooses for a layer's bf16 expert GEMMs: its own rule, through its symbol."""
+    rule = binding.load_library()["_ZN6moe35517gemm_bf16_variantEliiii"]
+    rule.argtypes, rule.restype = [ctypes.c_int64] + [ctypes.c_int] * 4, ctypes.c_int
+    first, second = rule(n_rows, E, F, D, cus), rule(n_rows, E, D, F, cus)
+    assert first == second   # the GEMMs of a layer share a tile map
+    return TILE_SHAPES[first]
