@@ -332,8 +332,8 @@ static_assert(kRingSharedTiles <= kWave, "the ring kernel expects a shared list 
 struct RingScratch {
     int cost[MOE_MAX_E];         // then its prefix
     int wave_tot[16];
-    int units[8];                // of every part
-    int tiles[8][9];             // ... cut to a height of at most h
+    int units[9];                // of every part; last: of all
+    int tiles[9][9];             // ... cut to a height of at most h
     int cap[2][8];
     int bin[2][64];              // experts by GEMM, part and height (8 first), then the first place of each
 };
@@ -343,9 +343,7 @@ __device__ __forceinline__ void ring_schedule(const Rows &rows_of, int E, int n1
                                               int32_t *__restrict__ list2, int max_list, int32_t *__restrict__ words, RingScratch &sm)
 {
     const int tid = threadIdx.x, nthreads = blockDim.x, lane = tid % kWave, wave = tid / kWave;
-    for (int e = tid; e < E; e += nthreads) {
-        sm.cost[e] = ring_cost(ring_units(rows_of(e)));
-    }
+    for (int e = tid; e < E; e += nthreads) sm.cost[e] = ring_cost(ring_units(rows_of(e)));
     if (tid < 8) sm.units[tid] = 0;
     if (tid < 72) sm.tiles[tid / 9][tid % 9] = 0;
     if (tid < 128) sm.bin[tid / 64][tid % 64] = 0;
@@ -353,15 +351,9 @@ __device__ __forceinline__ void ring_schedule(const Rows &rows_of, int E, int n1
     __syncthreads();
     int total = 0;
     block_exclusive_scan4(sm.cost, E, sm.wave_tot, total);
-    bool shared = false;
-    auto pieces = [&](int e, auto piece, auto cut) {
-        if (!shared) ring_pieces(ring_units(rows_of(e)), sm.cost[e], total, piece, cut);
-        else if (ring_units(rows_of(e)) > 0) piece(0, 0, ring_units(rows_of(e)));
-    };
-    auto no_cut = [](int, int) {};
     for (int e = tid; e < E; e += nthreads)
-        pieces(
-            e,
+        ring_pieces(
+            ring_units(rows_of(e)), sm.cost[e], total,
             [&](int x, int, int units) {
                 atomicAdd(&sm.units[x], units);
                 for (int h = 1; h <= 8; ++h) atomicAdd(&sm.tiles[x][h], (units + h - 1) / h);
@@ -371,43 +363,45 @@ __device__ __forceinline__ void ring_schedule(const Rows &rows_of, int E, int n1
     int row_tiles = 0;
 #pragma unroll
     for (int x = 0; x < 8; ++x) row_tiles += sm.tiles[x][8];
-    shared = row_tiles <= kRingSharedTiles;  // uniform over the block
+    const bool shared = row_tiles <= kRingSharedTiles;  // uniform over the block
+    auto pieces = [&](int e, auto piece) {
+        if (!shared) ring_pieces(ring_units(rows_of(e)), sm.cost[e], total, piece, [](int, int) {});
+        else if (ring_units(rows_of(e)) > 0) piece(0, 0, ring_units(rows_of(e)));
+    };
+    if (shared) {
+        if (tid < 9) {
+            int v = 0;
+#pragma unroll
+            for (int x = 0; x < 8; ++x) v += tid == 0 ? sm.units[x] : sm.tiles[x][tid];
+            (tid == 0 ? sm.units[8] : sm.tiles[8][tid]) = v;
+            words[kRingCut + tid] = MOE_MAX_E << kRingCutShift;
+        }
+        __syncthreads();
+    }
     if (tid < 16) {
-        const int x = tid & 7, n = tid < 8 ? n1 : n2, blocks = shared ? 256 : 32;
-        auto sum = [&](auto of) {  // of part x, or of all
-            int v = of(x);
-            if (shared) {
-                v = 0;
-                for (int i = 0; i < 8; ++i) v += of(i);
-            }
-            return v;
-        };
-        const int units = sum([&](int i) { return sm.units[i]; });
+        const int part = tid & 7, x = shared ? 8 : part, n = tid < 8 ? n1 : n2, blocks = shared ? 256 : 32;
+        const int units = sm.units[x];
         float best = 0.f;
         int cap = 8;
         for (int h = 8; h >= 1; --h) {
-            const int tiles = sum([&](int i) { return sm.tiles[i][h]; });
+            const int tiles = sm.tiles[x][h];
             // below four units only to give every block of a single round a tile
             if (tiles == 0 || (h < 4 && (int64_t)tiles * n > blocks)) break;
             const float c = (float)(((int64_t)tiles * n + blocks - 1) / blocks) * (6.f + (float)units / (float)tiles);
             if (h == 8 || c < 0.97f * best) best = c, cap = h;
         }
-        sm.cap[tid >> 3][x] = cap;
+        sm.cap[tid >> 3][part] = cap;
     }
     __syncthreads();
     if (tid < 8) words[kRingCap + tid] = sm.cap[0][tid] | sm.cap[1][tid] << 8 | (int)shared << kRingShared;
-    if (shared && tid < 9) words[kRingCut + tid] = MOE_MAX_E << kRingCutShift;
     auto bin_of = [&](int g, int x, int units) {
         const int k = (units + sm.cap[g][x] - 1) / sm.cap[g][x];
         return &sm.bin[g][shared ? 0 : 8 * x + 8 - (units + k - 1) / k];
     };
     for (int e = tid; e < E; e += nthreads)
-        pieces(
-            e,
-            [&](int x, int, int units) {
-                for (int g = 0; g < 2; ++g) atomicAdd(bin_of(g, x, units), 1);
-            },
-            no_cut);
+        pieces(e, [&](int x, int, int units) {
+            for (int g = 0; g < 2; ++g) atomicAdd(bin_of(g, x, units), 1);
+        });
     __syncthreads();
     if (wave < 2) {
         const int v = sm.bin[wave][lane];
@@ -425,15 +419,12 @@ __device__ __forceinline__ void ring_schedule(const Rows &rows_of, int E, int n1
     }
     __syncthreads();
     for (int e = tid; e < E; e += nthreads)
-        pieces(
-            e,
-            [&](int x, int, int units) {
-                for (int g = 0; g < 2; ++g) {
-                    const int at = atomicAdd(bin_of(g, x, units), 1);
-                    if (at < max_list) (g == 0 ? list1 : list2)[at] = e;  // at most E + 7 places are needed
-                }
-            },
-            no_cut);
+        pieces(e, [&](int x, int, int units) {
+            for (int g = 0; g < 2; ++g) {
+                const int at = atomicAdd(bin_of(g, x, units), 1);
+                if (at < max_list) (g == 0 ? list1 : list2)[at] = e;  // at most E + 7 places are needed
+            }
+        });
 }
 
 // Stable position of every assignment.  Block b ranks its 256 tokens:
