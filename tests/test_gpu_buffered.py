@@ -9,7 +9,7 @@ import torch
 from oracle import expert_cache as ec
 from oracle import moe_oracle as orc
 from paper_2303_06182_amd import binding, workloads as wl
-from helpers import TOL, norm_max_err, to_np
+from helpers import expert_tile_shape, TOL, norm_max_err, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -83,9 +83,10 @@ def test_buffered_many_tokens_and_skew(dev):
 
 
 def test_buffered_large_tiles(dev):
-    # stages of three experts with 3000 rows each: 36 row tiles x 13 column tiles per stage, i.e. the 256-row
-    # tiles' main launch reads its weights through the slot table; bit-identical to the resident call
+    # stages of three experts with 3000 rows each: the tiles cut to the experts' rows read their weights through the slot
+    # table, and a stage's schedule leaves the other experts out; bit-identical to the resident call
     w = wl.CONFIGS["mt_encoder"].scaled(name="enc_mid", T=12000, D=256, F=3328, E=8)
+    assert expert_tile_shape(w.T * w.k, w.E, w.F, w.D) == "cut to rows"
     run_trace(w, [3, 8], n_steps=2)
 
 

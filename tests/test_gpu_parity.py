@@ -12,7 +12,7 @@ import torch
 
 from oracle import moe_oracle as orc
 from paper_2303_06182_amd import binding, workloads as wl
-from helpers import (LOGIT_ATOL, LOGIT_RTOL, RMS_TOL, TOL, W_TOL, guarded_inputs, norm_max_err, p999_rel_err,
+from helpers import (LOGIT_ATOL, LOGIT_RTOL, RMS_TOL, TOL, W_TOL, expert_tile_shape, guarded_inputs, norm_max_err, p999_rel_err,
                      rms_rel_err, to_np, worst_row_rms_rel_err)
 
 pytestmark = pytest.mark.gpu
@@ -268,16 +268,13 @@ FFN_CASES = [
     ("f32", [65, 0, 130, 1], 96, 72, True),
     ("f32", [65, 0, 130, 1], 72, 96, True),
     ("f32", [200, 63, 64, 0, 129], 1024, 160, False),
-    # 256-row tiles: 24 M tiles x 13 N tiles = 312 tiles on 256 CUs -> one whole round in the main
-    # launch, 56 leftover tiles as 128x128 sub-tiles in the tail launch; the second GEMM (24 tiles)
-    # runs in the tail launch alone
+    # many rows, too few 256-row tiles for the chip in the GEMM with fewer columns: 128x128 tiles in both GEMMs
     ("bf16", [1100, 0, 900, 257, 1500, 640, 3, 700], 256, 3328, False),
-    # 24 x 17 = 408 tiles: the 152 leftover tiles are too many for the tail launch, two main rounds
     ("bf16", [1100, 0, 900, 257, 1500, 640, 3, 700], 256, 4352, True),
-    # 256-row tiles whose last column tile is partly outside the matrix, in both GEMMs (F = 12.5, D = 11.25 column
-    # tiles; 24 x 13 and 24 x 12 tiles: a whole round each in the main launch), with offsets
+    # tiles cut to the experts' rows whose last column tile is partly outside the matrix, in both GEMMs (F = 12.5, D =
+    # 11.25 column tiles), with offsets
     ("bf16", [1100, 0, 900, 257, 1500, 640, 3, 700], 2880, 3200, True),
-    # a single K tile per output tile in the first GEMM (the load stream changes tile after every K tile)
+    # a single K tile per output tile in the first GEMM
     ("bf16", [1100, 0, 900, 257, 1500, 640, 3, 700], 64, 3328, False),
 ]
 
@@ -422,11 +419,12 @@ FULL = [("tiny_f32", None), ("lm", None), ("mt_encoder", None), ("mt_decoder", N
 
 
 def test_layer_forward_large_tiles_with_odd_dimensions(dev):
-    """A mid-size layer on the 256-row tiles' main launch (8 experts with about 5000 rows each: 160 row tiles x 13
+    """A mid-size layer on the tiles cut to the experts' rows (8 experts with about 5000 rows each: 160 row tiles x 13
     and x 2 column tiles) whose dimensions are not multiples of the tile: D = 320 (five K tiles, a column tile and
     a quarter in the second GEMM), F = 3200 (12.5 column tiles in the first GEMM, 50 K tiles in the second), with
     offsets in both GEMMs and the rows of the first gathered from x; every token compared."""
     w = wl.CONFIGS["mt_encoder"].scaled(name="ring_odd", T=20000, D=320, F=3200, E=8)
+    assert expert_tile_shape(w.T * w.k, w.E, w.F, w.D) == "cut to rows"
     say("layer large tiles, odd dimensions", w)
     run_layer_and_check(w, with_ffn_bias=True, device="cuda")
 
@@ -547,8 +545,9 @@ def test_layer_forward_can_be_captured_in_a_graph(dev, kind):
     if kind == "bf16_mid":
         w = wl.CONFIGS["lm"].scaled(name="graph", T=1500, D=256, F=512, E=16)
     elif kind == "bf16_large_tiles":
-        # 256-row tiles: main launch (the ring-of-K-steps kernel, all of the CU's LDS) and tail launch in the graph
-        w = wl.CONFIGS["mt_encoder"].scaled(name="graph_large", T=6000, D=256, F=3328, E=8)
+        # tiles cut to the experts' rows: the kernel with all of the CU's LDS and the schedule that the routing leaves for it
+        w = wl.CONFIGS["mt_encoder"].scaled(name="graph_large", T=16000, D=256, F=3328, E=8)
+        assert expert_tile_shape(w.T * w.k, w.E, w.F, w.D) == "cut to rows"
     else:
         w = wl.CONFIGS["mt_decoder"].scaled(name="graph_dec", D=512, F=1024, E=32)
     g = cuda(wl.make_inputs(w))

@@ -32,7 +32,7 @@ RAGGED = [
     ([3, 0, 20] * 100, 72, 1032, False),            # 32-row tiles, more of them than the streaming form takes
     ([64, 0, 130, 50], 200, 328, True),             # 128-row tiles, few rows per expert
     ([100, 257, 0, 60, 128], 1000, 136, False),     # 128-row tiles
-    ([300, 0, 513, 1], 264, 456, True),             # 256-row tiles and their tail launch
+    ([300, 0, 513, 1], 264, 456, True),             # 128-row tiles, too few for tiles cut to the rows
     ([1, 0, 17, 33], 264, 328, True),               # streaming form, eight waves: fewer steps of K than waves
     ([1, 0, 17, 33, 8, 0, 2, 31] * 2, 264, 1032, True),     # ... four waves and 32 columns in the first GEMM
 ]

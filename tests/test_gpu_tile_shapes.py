@@ -1,29 +1,14 @@
 """The expert GEMM's tile shapes that only some sizes reach, against the fp64 oracle.  Each case names the shape it is
-for and is checked against a copy of the choice, so that it cannot drift to another one."""
+for and asks the library whether that is its choice, so that it cannot drift to another one."""
 import numpy as np
 import pytest
 import torch
 
 from oracle import moe_oracle as orc
 from paper_2303_06182_amd import binding, workloads as wl
-from helpers import TOL, norm_max_err, to_np, worst_row_rms_rel_err
+from helpers import TOL, expert_tile_shape, norm_max_err, to_np, worst_row_rms_rel_err
 
 pytestmark = pytest.mark.gpu
-
-
-def bf16_shape(n_rows, E, N, K, cus):
-    """gemm_bf16_variant (gemm_bf16.hip), N and K whole K tiles."""
-    avg, width = n_rows // E, min(N, K)
-    panels, heavy = E * width // 256, E * N * K >= 1 << 29
-    if avg >= 192 or (heavy and avg >= (112 if width >= 2048 else 128)):
-        return "256x256"
-    if heavy and panels >= 2 * cus:
-        return "128x256" if avg >= 18 else "32x128"
-    if 4 * panels <= cus:
-        return "128x128" if avg >= 48 else "32x128"
-    if not heavy and avg < 64:
-        return "64x128" if avg >= 34 else "32x128"
-    return "128x128" if avg >= 30 else "32x128"
 
 
 def ragged(E, edges, lo, hi, seed):
@@ -37,7 +22,7 @@ def run(shape, counts, D, F):
     print("tile shape", shape, len(counts), D, F, sum(counts), flush=True)
     E, N = len(counts), int(sum(counts))
     cus = torch.cuda.get_device_properties(0).multi_processor_count
-    assert bf16_shape(N, E, F, D, cus) == shape
+    assert expert_tile_shape(N, E, F, D, cus) == shape
     offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
     g = torch.Generator(device="cuda").manual_seed(7)
     t = lambda s, std: torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=g)
@@ -58,23 +43,27 @@ def test_64x128():
     run("64x128", ragged(80, [0, 1, 63, 64, 65, 33, 0, 127, 128, 129], 20, 60, 1), 256, 320)
 
 
-EDGES = [0, 1, 127, 128, 129, 257, 33, 0, 64, 65, 16, 17]   # around the 128-row tile
+EDGES = [0, 1, 127, 128, 129, 257, 33, 0, 64, 65, 16, 17]   # around half a tile and a tile and a bit
 
 
-def test_128x256_ring():
-    run("128x256", ragged(512, EDGES, 5, 40, 2), 1088, 1088)   # 17 K tiles, a last column tile of 64
+def test_cut_tiles_with_few_rows():
+    run("cut to rows", ragged(512, EDGES, 5, 40, 2), 1088, 1088)   # 17 K tiles, a last column tile of 64
 
 
-def test_256x256_ring_below_192_rows():
-    run("256x256", ragged(512, EDGES, 120, 150, 3), 1088, 1088)
+def test_cut_tiles_of_about_half_the_height():
+    run("cut to rows", ragged(512, EDGES, 120, 150, 3), 1088, 1088)
 
 
-def test_layer_on_the_128x256_ring():
+def test_128x128_with_many_rows():
+    run("128x128", [1100, 0, 900, 257, 1500, 640, 3, 700], 264, 3328)   # too few tiles to cut, K that ends inside a K tile
+
+
+def test_layer_on_cut_tiles():
     """Rows gathered from the token array by the first GEMM; the tokens of the fullest expert (several tiles) and a sample of
     the others against the oracle."""
     T, D, F, E, k = 6000, 1024, 1088, 512, 2
     cus = torch.cuda.get_device_properties(0).multi_processor_count
-    assert bf16_shape(T * k, E, F, D, cus) == "128x256"
+    assert expert_tile_shape(T * k, E, F, D, cus) == "cut to rows"
     g = torch.Generator(device="cuda").manual_seed(8)
     t = lambda s, std: torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=g)
     x, wg, w1, w2 = t((T, D), 1.0), t((E, D), 10 * D ** -0.5), t((E, F, D), D ** -0.5), t((E, D, F), F ** -0.5)
