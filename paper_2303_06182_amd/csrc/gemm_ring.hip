@@ -61,7 +61,10 @@ constexpr int NSLOT = 5, SLOT_BYTES = (BM + BN) * 64;
 constexpr int MI = 8, NI = 4;                              // 16-row and 16-column blocks of a wave, at most
 constexpr int AG = BM / 16 / NWAVE, BG = BN / 16 / NWAVE;  // 16-row groups a wave loads per K tile
 constexpr int GROUP_M = 4;
-constexpr uint32_t kNowhere = 0xf0000000u;  // byte offset past the end of every operand
+// Byte offset past the end of every operand, which stays past it, and below 2^32, when a K tile's offset (2 MiB: K up to kWideMax)
+// is added.
+constexpr uint32_t kNowhere = 0xffe00000u;
+constexpr int kWideMax = (1 << 20) - 4 * BK;
 
 struct RingTile {
     int row0, row_end, expert, n0;
@@ -448,7 +451,7 @@ static int launch_ring_t(const GemmParams &p, hipStream_t s)
 bool gemm_ring_addresses(int64_t n_rows, int N, int K)
 {
     const int64_t wide = N > K ? N : K;
-    return (n_rows + 1) * wide * 2 <= (int64_t)kNowhere && (int64_t)N * K * 2 <= (int64_t)kNowhere;
+    return wide <= kWideMax && (n_rows + 1) * wide * 2 <= (int64_t)kNowhere && (int64_t)N * K * 2 <= (int64_t)kNowhere;
 }
 // ... and its load stream is two K tiles ahead.
 bool gemm_ring_ok(int64_t n_rows, int N, int K) { return N > BK && K > BK && gemm_ring_addresses(n_rows, N, K); }

@@ -81,3 +81,28 @@ def test_layer_on_cut_tiles():
     ref = orc.layer_tokens(x[tok].cpu(), w1[sel].cpu(), w2[sel].cpu(), local.reshape(len(tok), k).astype(np.int32), gw[tok])
     assert norm_max_err(y[tok], ref) <= TOL["bf16"]
     assert worst_row_rms_rel_err(y[tok], ref) <= 2.0 ** -7
+
+
+@pytest.mark.parametrize("shape,D,F,n_rows", [
+    ("cut to rows", 128, 8192, 261900),     # hidden rows of just below 4 GiB: the last ones' 32-bit byte offsets
+    ("256x256", 128, 8192, 262400),         # ... of more: whole rounds of 256x256 tiles and the rest as 128x128
+    ("256x256", 72, 8200, 262500)])         # ... with K that ends inside a K tile in both GEMMs
+def test_operands_around_4_gib(shape, D, F, n_rows):
+    print("4 GiB", shape, D, F, n_rows, flush=True)
+    counts = [70000, 1, 0, n_rows - 70000 - 1 - 300, 300]
+    E, offsets = len(counts), np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    assert expert_tile_shape(n_rows, E, F, D, torch.cuda.get_device_properties(0).multi_processor_count) == shape
+    g = torch.Generator(device="cuda").manual_seed(9)
+    t = lambda s, std: torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=g)
+    xp, w1, w2, b1, b2 = t((n_rows, D), 1.0), t((E, F, D), D ** -0.5), t((E, D, F), F ** -0.5), t((E, F), 0.5), t((E, D), 0.5)
+    w1[2], w2[2] = float("nan"), float("nan")
+    yp = binding.MoeLayer(n_rows, D, F, E, 1, "bf16").moe_expert_ffn(xp, torch.from_numpy(offsets).cuda(), w1, w2, b1, b2)
+    assert bool(torch.isfinite(yp).all())
+    # every expert's first and last rows, and some in between
+    rows = [np.unique(np.concatenate([np.arange(min(c, 40)), np.arange(max(0, c - 40), c), np.arange(0, c, 1501)])) for c in counts]
+    sel = torch.from_numpy(np.concatenate([o + r for o, r in zip(offsets, rows)])).cuda().long()
+    ref = orc.expert_ffn(xp[sel].cpu(), np.concatenate([[0], np.cumsum([len(r) for r in rows])]).astype(np.int32),
+                         w1.nan_to_num().cpu(), w2.nan_to_num().cpu(), b1.cpu(), b2.cpu())
+    got = to_np(yp[sel])
+    assert norm_max_err(got, ref) <= TOL["bf16"]
+    assert worst_row_rms_rel_err(got, ref) <= 2.0 ** -7
