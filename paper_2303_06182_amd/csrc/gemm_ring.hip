@@ -407,7 +407,7 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
     }
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0x0f70 | (2 * BG));  // the first K tile has landed: the second's weight loads are younger
+    __builtin_amdgcn_s_waitcnt(0x0f70 | (2 * AG + 2 * BG));  // the first K tile has landed: the second's loads are younger
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
