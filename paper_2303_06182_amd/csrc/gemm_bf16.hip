@@ -1058,9 +1058,12 @@ int gemm_bf16_variant_block_m(int v)
 //    loads the mean of 10 / 8 is 0.92 at 108 rows, 1.01 at 116, 1.03 at 124, 1.05 at 128, 1.09 at 150, either way by the layer and
 //    the load: FFN in us, 10 / 8, at 116 rows, 24 experts 1000 -> 4000 134 / 166, 134 / 166, 189 / 166; 48 experts
 //    249 / 232, 312 / 248, 285 / 253; 64 experts 1024 -> 4096 298 / 277, 299 / 325, 307 / 313; at 150 rows 339 / 289, 356 / 324, 352 / 325.
-//    Up to 768 columns and K, a tile's few K tiles do not make up for its start, and it takes 192 rows: 128 experts 512 -> 2048, 116 rows
-//    171 / 174, 172 / 192, 172 / 191, 150 rows 205 / 214, 189 / 192, 191 / 198, 192 rows 204 / 200, 211 / 210, 212 / 214; 158 experts
-//    384 -> 1536, 123 rows, even, skewed 129 / 143, 127 / 152; 64 experts 512 -> 2048, 256 rows 136 / 129, 136 / 129, 400 rows 177 / 147, 176 / 172.
+//  * With a dimension of 768 or less, one GEMM has few K tiles a tile, which do not make up for its start, and the other few
+//    columns: there it takes 192 rows, 144 tiles and 1024 as the other dimension.  Over 211 random layers with such a dimension,
+//    192 rows and more, and the three kinds of load the better of the two shapes is missed by 1.1 % in the mean, by 4.8 % without the last two conditions and by
+//    4.0 % with 128x128 throughout.  10 / 8, even, skewed (0.5), more skewed (0.8): 128 experts 512 -> 2048, 150 rows 205 / 214, 189 / 192,
+//    191 / 198, 192 rows 204 / 198, 211 / 210, 212 / 213; 64 experts 512 -> 2048, 400 rows, even, more skewed 177 / 147, 176 / 172; 191 experts
+//    256 -> 256, 228 rows 42 / 48; 25 experts 384 -> 1536, 477 rows 65 / 80, 66 / 78.
 //  * They need tiles enough for the chip, 96 in the GEMM with fewer columns, and with fewer than 112 at least 120 rows.  Over 45 random
 //    layers (12 to 60 experts, 784 to 2032 -> 872 to 7928) and the same kinds of load the mean of 10 / 8 is 0.78 at 80 to 95 tiles; at
 //    96 to 111 tiles 0.85 with 116 to 119 rows, 0.98 with 120 to 127, 1.06 with 128 to 132; at 112 to 140 tiles 1.02, 1.05 and 1.08.
@@ -1100,7 +1103,7 @@ int gemm_bf16_variant(int64_t n_rows, int E, int N, int K, int num_cus)
     const bool heavy = whole && (int64_t)E * N * K >= kHeavyWeights;
     const int64_t tiles = (int64_t)E * ((avg + 8 + 255) / 256) * ceil_div(width, 256);
     if (gemm_ring_ok(n_rows, N, K) &&
-        ((tiles >= 96 && avg >= (width <= 768 ? 192 : tiles < 112 ? 120 : 116)) || (heavy && avg >= kNtRows && panels >= 2 * (int64_t)num_cus)))
+        ((width <= 768 ? avg >= 192 && tiles >= 144 && (N > K ? N : K) >= 1024 : tiles >= 96 && avg >= (tiles < 112 ? 120 : 116)) || (heavy && avg >= kNtRows && panels >= 2 * (int64_t)num_cus)))
         return 8;
     if (avg >= 192) return gemm_ring_addresses(n_rows, N, K) ? 10 : 9;
     const int small = avg >= kNtRows ? 4 : avg >= kNtSoleRows ? 5 : 3;

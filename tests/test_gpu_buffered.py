@@ -83,9 +83,9 @@ def test_buffered_many_tokens_and_skew(dev):
 
 
 def test_buffered_large_tiles(dev):
-    # stages of three experts with 3000 rows each: the tiles cut to the experts' rows read their weights through the slot
+    # stages of three experts with 5000 rows each: the tiles cut to the experts' rows read their weights through the slot
     # table, and a stage's schedule leaves the other experts out; bit-identical to the resident call
-    w = wl.CONFIGS["mt_encoder"].scaled(name="enc_mid", T=12000, D=256, F=3328, E=8)
+    w = wl.CONFIGS["mt_encoder"].scaled(name="enc_mid", T=20000, D=256, F=3328, E=8)
     assert expert_tile_shape(w.T * w.k, w.E, w.F, w.D) == "cut to rows"
     run_trace(w, [3, 8], n_steps=2)
 

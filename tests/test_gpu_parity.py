@@ -546,7 +546,7 @@ def test_layer_forward_can_be_captured_in_a_graph(dev, kind):
         w = wl.CONFIGS["lm"].scaled(name="graph", T=1500, D=256, F=512, E=16)
     elif kind == "bf16_large_tiles":
         # tiles cut to the experts' rows: the kernel with all of the CU's LDS and the schedule that the routing leaves for it
-        w = wl.CONFIGS["mt_encoder"].scaled(name="graph_large", T=16000, D=256, F=3328, E=8)
+        w = wl.CONFIGS["mt_encoder"].scaled(name="graph_large", T=20000, D=256, F=3328, E=8)
         assert expert_tile_shape(w.T * w.k, w.E, w.F, w.D) == "cut to rows"
     else:
         w = wl.CONFIGS["mt_decoder"].scaled(name="graph_dec", D=512, F=1024, E=32)

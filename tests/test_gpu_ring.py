@@ -24,7 +24,7 @@ def counts_of(kind, E):
     elif kind.startswith("few"):   # so many active experts, one to eight row tiles each
         c = [0] * E
         for i in range(int(kind[3:])):
-            c[(5 * i + 2) % E] = (124 if E == 8 else 200) * E // int(kind[3:]) + 37 * i
+            c[(5 * i + 2) % E] = 124 * E // int(kind[3:]) + 37 * i
     else:                      # few active experts, far apart
         c = [0] * E
         c[3], c[4], c[E - 1] = 90 * E, 33, 110 * E
@@ -32,9 +32,9 @@ def counts_of(kind, E):
 
 
 @pytest.mark.parametrize("kind,E,D,F,bias", [
-    ("even", 96, 128, 256, False), ("even", 56, 264, 328, True), ("hot", 100, 520, 136, True), ("hot", 56, 512, 264, False),
-    ("sparse", 52, 328, 320, True), ("even", 97, 72, 520, True),
-    ("few1", 8, 3080, 3144, True), ("few2", 8, 3080, 3144, False), ("few7", 8, 3072, 3080, False), ("few6", 32, 768, 776, True)])
+    ("even", 150, 128, 1024, False), ("even", 80, 264, 1032, True), ("hot", 100, 520, 1032, True), ("hot", 80, 1024, 264, False),
+    ("sparse", 76, 328, 1344, True), ("even", 150, 72, 1032, True),
+    ("few1", 8, 3080, 3144, True), ("few2", 8, 3080, 3144, False), ("few7", 8, 3072, 3080, False), ("few6", 16, 1544, 1608, True)])
 def test_rows_of_every_height(kind, E, D, F, bias):
     print("ring", kind, E, D, F, flush=True)
     counts = counts_of(kind, E)
