@@ -38,8 +38,8 @@
 // trip through LDS (all of which the ring holds).
 //
 // Launch: PERSISTENT, one block per CU.  Workgroups are handed to the 8 XCDs round-robin and each XCD has its own L2,
-// so the schedule (ring_schedule, route.hip) gives each a part of the experts' rows of equal cost, or, where the rows are
-// too few for that, of the column tiles.
+// so the schedule (ring_schedule, route.hip) gives each a part of the experts' rows of equal cost, or, where that does not
+// come out, an eighth of all output tiles.
 // The load cursor walks the block's whole sequence of (tile, K tile) pairs, so the first K tiles of the NEXT tile are
 // loaded during the last steps of the current one and the epilogue's stores overlap the next tile.
 #include <mutex>
@@ -61,10 +61,11 @@ constexpr int NSLOT = 5, SLOT_BYTES = (BM + BN) * 64;
 constexpr int MI = 8, NI = 4;                              // 16-row and 16-column blocks of a wave, at most
 constexpr int AG = BM / 16 / NWAVE, BG = BN / 16 / NWAVE;  // 16-row groups a wave loads per K tile
 constexpr int GROUP_M = 4;
-// Byte offset past the end of every operand, which stays past it, and below 2^32, when a K tile's offset (2 MiB: K up to kWideMax)
-// is added.
-constexpr uint32_t kNowhere = 0xffe00000u;
-constexpr int kWideMax = (1 << 20) - 4 * BK;
+// Byte offset past the end of every operand, which stays past it, and below 2^32, when a K tile's offset is added (64 MiB: an
+// operand with 65 rows has less a row).  Not closer to 2^32: the loads of rows past a tile's end take longer there (128 experts 2048 ->
+// 8192, 1024 skewed rows, FFN in us, 0xf0000000 7135, 0xf8000000 7142, 0xfc000000 7152, 0xfe000000 7201, 0xffe00000 7208; 16 experts, 2048 rows
+// 1845, 1847, 1835, 1859, 1860).
+constexpr uint32_t kNowhere = 0xfc000000u;
 
 struct RingTile {
     int row0, row_end, expert, n0;
@@ -138,7 +139,7 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
     load_window();
     const int s_blk = blockIdx.x >> 3;
     int pos = s_blk, pos_next = 63 - s_blk;
-    if (shared) {  // the one list of all XCDs, at most kRingSharedTiles experts and so one window: an eighth of its tiles each
+    if (shared) {  // the one list of all XCDs, at most 64 experts and so one window: an eighth of its tiles each
         const int first = ring_share(w_total, blockIdx.x & 7);
         w_total = ring_share(w_total, (blockIdx.x & 7) + 1);
         pos += first;
@@ -451,7 +452,7 @@ static int launch_ring_t(const GemmParams &p, hipStream_t s)
 bool gemm_ring_addresses(int64_t n_rows, int N, int K)
 {
     const int64_t wide = N > K ? N : K;
-    return wide <= kWideMax && (n_rows + 1) * wide * 2 <= (int64_t)kNowhere && (int64_t)N * K * 2 <= (int64_t)kNowhere;
+    return (n_rows + 1) * wide * 2 <= (int64_t)kNowhere && (int64_t)N * K * 2 <= (int64_t)kNowhere;
 }
 // ... and its load stream is two K tiles ahead.
 bool gemm_ring_ok(int64_t n_rows, int N, int K) { return N > BK && K > BK && gemm_ring_addresses(n_rows, N, K); }

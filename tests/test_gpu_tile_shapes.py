@@ -84,7 +84,7 @@ def test_layer_on_cut_tiles():
 
 
 @pytest.mark.parametrize("shape,D,F,n_rows", [
-    ("cut to rows", 128, 8192, 261900),     # hidden rows of just below 4 GiB: the last ones' 32-bit byte offsets
+    ("cut to rows", 128, 8192, 258000),     # hidden rows of 3.94 GiB: the last ones' 32-bit byte offsets
     ("256x256", 128, 8192, 262400),         # ... of more: whole rounds of 256x256 tiles and the rest as 128x128
     ("256x256", 72, 8200, 262500)])         # ... with K that ends inside a K tile in both GEMMs
 def test_operands_around_4_gib(shape, D, F, n_rows):
