@@ -319,22 +319,27 @@ __device__ __forceinline__ void block_exclusive_scan4(int *vals, int n, int *wav
 // tiles cost about the same.  (Places among experts of one height are handed out by LDS atomics: their
 // order differs between runs, the sums do not.)
 //
-// Up to this many row tiles of a batch the XCDs share one list of experts and each takes an eighth of its output tiles: parts
-// of whole row tiles leave XCDs idle then, or with twice the others' work.  The list is in the experts' order: sorted by
-// height the first eighth would cost the most.  FFN in us, parts / shared: 128 experts 2048 -> 8192, 1024 rows on one expert 151 / 137,
-// on four 189 / 158; 8 experts 4096 -> 14336, 1024 rows on four 477 / 374, on one 401 / 288, 2000 evenly spread 732 / 599; 4
-// experts 8192 -> 28672, 400 rows on two 1238 / 661; 8 experts 2048 -> 8192, 2000 rows 265 / 230, 6400 rows 412 / 409.  Where both balance it is
-// the same (32 experts 2048 -> 8192, 256 rows 376 / 376, 3200 rows 431 / 425).  (Dealing the rounds of the whole chip over the XCDs instead, 32
-// neighbours on the list each, cost 32 even experts 10 %.)
+// The XCDs share one list of experts, and each takes an eighth of its output tiles, where parts of whole row tiles do not come
+// out: with up to kRingSharedTiles row tiles, of which some XCDs would get none or twice the others', and where the
+// slowest part's rounds cost more than those of the eighths by kRingSharedGain (and a window of the kernel's holds the experts).  The
+// list is in the experts' order: sorted by height the first eighth would cost the most.  FFN in us, parts / shared: 128 experts 2048
+// -> 8192, 1024 rows on one expert 151 / 137, on four 189 / 158; 8 experts 4096 -> 14336, 1024 rows on four 477 / 374, on one 401 / 288, 2000
+// evenly spread 732 / 599; 4 experts 8192 -> 28672, 400 rows on two 1238 / 661; 32 experts 2048 -> 8192, 256 rows 376 / 376, 3200 rows 431 /
+// 425.  With more row tiles what it takes is the estimate plus a twentieth (an eighth's heights are mixed), estimate and measured
+// ratio: 42 experts 768 -> 1536, 372 rows each 0.65, 0.73; 25 experts 1280 -> 1280, 857 rows 0.74, 0.78; 32 experts 1024 -> 4096, 256 rows 0.84, 0.91; 64
+// experts 1024 -> 4096, 256 rows, more and less skewed 0.90, 0.99 and 0.95, 1.03; 16 experts 2048 -> 8192, 500 rows 1.00, 1.06.
+// (Dealing the rounds of the whole chip over the XCDs instead, 32 neighbours on the list each, cost 32 even experts 10 %.)
 static constexpr int kRingSharedTiles = 32;
+static constexpr float kRingSharedGain = 0.88f;
 static_assert(kRingSharedTiles <= kWave, "the ring kernel expects a shared list in one window");
 
 struct RingScratch {
     int cost[MOE_MAX_E];         // then its prefix
     int wave_tot[16];
-    int units[9];                // of every part; last: of all
-    int tiles[9][9];             // ... cut to a height of at most h
+    int units[8];                // of every part
+    int tiles[8][9];             // ... cut to a height of at most h
     int cap[2][8];
+    int shared;
     int bin[2][64];              // experts by GEMM, part and height (8 first), then the first place of each
 };
 
@@ -360,40 +365,48 @@ __device__ __forceinline__ void ring_schedule(const Rows &rows_of, int E, int n1
             },
             [&](int x, int first) { words[kRingCut + x] = e << kRingCutShift | first; });
     __syncthreads();
-    int row_tiles = 0;
+    if (wave == 0) {
+        // lanes 0 .. 7 and 8 .. 15: the parts of the first and of the second GEMM; 16 and 17: the GEMMs with one list for all XCDs
+        int all = 0;  // lane h: row tiles of all parts cut to a height of at most h; lane 0: units
+        if (lane < 9)
 #pragma unroll
-    for (int x = 0; x < 8; ++x) row_tiles += sm.tiles[x][8];
-    const bool shared = row_tiles <= kRingSharedTiles;  // uniform over the block
+            for (int x = 0; x < 8; ++x) all += lane == 0 ? sm.units[x] : sm.tiles[x][lane];
+        const int row_tiles = __shfl(all, 8, kWave), all_units = __shfl(all, 0, kWave);
+        const bool one_list = lane >= 16;
+        const int x = lane & 7, n = (one_list ? lane & 1 : lane >> 3) == 0 ? n1 : n2, log_blocks = one_list ? 8 : 5;
+        const float units = (float)(one_list ? all_units : sm.units[x]);
+        float best = 0.f;
+        int cap = 8;
+        bool open = true;
+#pragma unroll
+        for (int h = 8; h >= 1; --h) {
+            const int all_h = __shfl(all, h, kWave);
+            const int tiles = one_list ? all_h : sm.tiles[x][h];
+            const int64_t out = (int64_t)tiles * n;
+            // below four units only to give every block of a single round a tile
+            open = open && tiles > 0 && (h >= 4 || out <= 1 << log_blocks);
+            const float c = (float)((out + (1 << log_blocks) - 1) >> log_blocks) * (6.f + units / (float)tiles);
+            if (open && (h == 8 || c < 0.97f * best)) best = c, cap = h;
+        }
+        float slowest = best;  // of the GEMM's parts
+#pragma unroll
+        for (int m = 1; m < 8; m <<= 1) slowest = fmaxf(slowest, __shfl_xor(slowest, m, kWave));
+        // a GEMM's K loop is as long as the other one has columns
+        const float parts = __shfl(slowest, 0, kWave) * (float)n2 + __shfl(slowest, 8, kWave) * (float)n1;
+        const float eighths = __shfl(best, 16, kWave) * (float)n2 + __shfl(best, 17, kWave) * (float)n1;
+        const bool share = row_tiles <= kRingSharedTiles || (min(E, row_tiles) <= kWave && eighths < kRingSharedGain * parts);
+        const int cap_all = __shfl(cap, 16 + (lane >> 3 & 1), kWave);
+        if (lane < 16) sm.cap[lane >> 3][x] = share ? cap_all : cap;
+        if (lane == 0) sm.shared = share;
+    }
+    __syncthreads();
+    const bool shared = sm.shared;
     auto pieces = [&](int e, auto piece) {
         if (!shared) ring_pieces(ring_units(rows_of(e)), sm.cost[e], total, piece, [](int, int) {});
         else if (ring_units(rows_of(e)) > 0) piece(0, 0, ring_units(rows_of(e)));
     };
-    if (shared) {
-        if (tid < 9) {
-            int v = 0;
-#pragma unroll
-            for (int x = 0; x < 8; ++x) v += tid == 0 ? sm.units[x] : sm.tiles[x][tid];
-            (tid == 0 ? sm.units[8] : sm.tiles[8][tid]) = v;
-            words[kRingCut + tid] = MOE_MAX_E << kRingCutShift;
-        }
-        __syncthreads();
-    }
-    if (tid < 16) {
-        const int part = tid & 7, x = shared ? 8 : part, n = tid < 8 ? n1 : n2, blocks = shared ? 256 : 32;
-        const int units = sm.units[x];
-        float best = 0.f;
-        int cap = 8;
-        for (int h = 8; h >= 1; --h) {
-            const int tiles = sm.tiles[x][h];
-            // below four units only to give every block of a single round a tile
-            if (tiles == 0 || (h < 4 && (int64_t)tiles * n > blocks)) break;
-            const float c = (float)(((int64_t)tiles * n + blocks - 1) / blocks) * (6.f + (float)units / (float)tiles);
-            if (h == 8 || c < 0.97f * best) best = c, cap = h;
-        }
-        sm.cap[tid >> 3][part] = cap;
-    }
-    __syncthreads();
     if (tid < 8) words[kRingCap + tid] = sm.cap[0][tid] | sm.cap[1][tid] << 8 | (int)shared << kRingShared;
+    if (shared && tid < 9) words[kRingCut + tid] = MOE_MAX_E << kRingCutShift;
     auto bin_of = [&](int g, int x, int units) {
         const int k = (units + sm.cap[g][x] - 1) / sm.cap[g][x];
         return &sm.bin[g][shared ? 0 : 8 * x + 8 - (units + k - 1) / k];
