@@ -1053,27 +1053,31 @@ int gemm_bf16_variant_block_m(int v)
 //   2: 64x128, 4 waves, direct-to-LDS    3, 4, 5: 32x128, the same, weights read non-temporally, plainly, by tile (kNtRows)
 // By the average number of rows per expert, by how many 256-column weight panels there are (E * min(D, F) / 256, the
 // same for both GEMMs of a layer), and by how many weights a GEMM streams.
-//  * Tiles cut to an expert's rows (8) pay from 116 rows on, where most experts need two 128-row tiles: over six layers (24, 32,
-//    48 experts 1000 -> 4000; 32, 64 experts 1024 -> 4096; 16 experts 2048 -> 8192) and even, skewed (exponent 0.5) and more skewed (0.8)
-//    loads the mean of 10 / 8 is 0.92 at 108 rows, 1.01 at 116, 1.03 at 124, 1.05 at 128, 1.09 at 150, either way by the layer and
-//    the load: FFN in us, 10 / 8, at 116 rows, 24 experts 1000 -> 4000 134 / 166, 134 / 166, 189 / 166; 48 experts
-//    249 / 232, 312 / 248, 285 / 253; 64 experts 1024 -> 4096 298 / 277, 299 / 325, 307 / 313; at 150 rows 339 / 289, 356 / 324, 352 / 325.
+//  * Tiles cut to an expert's rows (8) pay from 116 rows on, where most experts need two 128-row tiles: over six layers (24,
+//    32, 48 experts 1000 -> 4000; 32, 64 experts 1024 -> 4096; 16 experts 2048 -> 8192) and even, skewed (exponent 0.5) and
+//    more skewed (0.8) loads the mean of 10 / 8 is 0.92 at 108 rows, 1.01 at 116, 1.03 at 124, 1.05 at 128, 1.09 at 150, either
+//    way by the layer and the load: FFN in us, 10 / 8, at 116 rows, 24 experts 1000 -> 4000 134 / 166, 134 / 166, 189 / 166; 48
+//    experts 249 / 232, 312 / 248, 285 / 253; 64 experts 1024 -> 4096 298 / 277, 299 / 325, 307 / 313; at 150 rows 339 / 289,
+//    356 / 324, 352 / 325.
 //  * With a dimension of 768 or less, one GEMM has few K tiles a tile, which do not make up for its start, and the other few
-//    columns: there it takes 192 rows, 144 tiles and 1024 as the other dimension.  Over 211 random layers with such a dimension,
-//    192 rows and more, and the three kinds of load the better of the two shapes is missed by 1.1 % in the mean, by 4.8 % without the last two conditions and by
-//    4.0 % with 128x128 throughout.  10 / 8, even, skewed (0.5), more skewed (0.8): 128 experts 512 -> 2048, 150 rows 205 / 214, 189 / 192,
-//    191 / 198, 192 rows 204 / 198, 211 / 210, 212 / 213; 64 experts 512 -> 2048, 400 rows, even, more skewed 177 / 147, 176 / 172; 191 experts
-//    256 -> 256, 228 rows 42 / 48; 25 experts 384 -> 1536, 477 rows 65 / 80, 66 / 78.
-//  * They need tiles enough for the chip, 96 in the GEMM with fewer columns, and with fewer than 112 at least 120 rows.  Over 45 random
-//    layers (12 to 60 experts, 784 to 2032 -> 872 to 7928) and the same kinds of load the mean of 10 / 8 is 0.78 at 80 to 95 tiles; at
-//    96 to 111 tiles 0.85 with 116 to 119 rows, 0.98 with 120 to 127, 1.06 with 128 to 132; at 112 to 140 tiles 1.02, 1.05 and 1.08.
-//    With more rows, 10 / 8, even, skewed (0.5), more skewed (0.8), 64 to 95 tiles: 5 experts 2048 -> 4096, 298 rows 92 / 118, 93 / 119, 93 / 119; 13 experts 1536 -> 1536, 241 rows 73 / 81, 70 / 82, 76 / 83; 16 experts 1024
-//    -> 4096, 224 rows 105 / 118, 130 / 127, 133 / 127; 5 experts 4096 -> 14336, 197 rows 436 / 446, 485 / 441, 471 / 449; 96 to 128 tiles: 6 experts 2048
-//    -> 8192, 398 rows 250 / 238, 243 / 237, 250 / 243; 12 experts 2048 -> 4096, 176 rows 141 / 142, 158 / 142, 161 / 147; 14 experts 2048 -> 8192,
-//    170 rows 293 / 271, 313 / 280, 306 / 292; 8 experts 4096 -> 14336, 128 rows, even 530 / 476.  The GEMM with fewer columns counts, also
-//    where the other one has many: 8 experts 256 -> 3328, 1500 rows (48 and 624) 80 / 103, 82 / 107.  An even batch with a mean just
-//    below 256 rows needs two tiles for a part of its experts and counts so: 250 rows, 16 experts 1024 -> 4096 134 / 132, 132 / 132,
-//    131 / 130; 8 experts 2048 -> 8192 244 / 230, 241 / 234, 262 / 236.
+//    columns: there it takes 192 rows, 144 tiles and 1024 as the other dimension.  Over 211 random layers with such a
+//    dimension, 192 rows and more, and the three kinds of load the better of the two shapes is missed by 1.1 % in the mean, by
+//    4.8 % without the last two conditions and by 4.0 % with 128x128 throughout.  10 / 8, even, skewed (0.5), more skewed
+//    (0.8): 128 experts 512 -> 2048, 150 rows 205 / 214, 189 / 192, 191 / 198, 192 rows 204 / 198, 211 / 210, 212 / 213; 64
+//    experts 512 -> 2048, 400 rows, even, more skewed 177 / 147, 176 / 172; 191 experts 256 -> 256, 228 rows 42 / 48; 25
+//    experts 384 -> 1536, 477 rows 65 / 80, 66 / 78.
+//  * They need tiles enough for the chip, 96 in the GEMM with fewer columns, and with fewer than 112 at least 120 rows.  Over
+//    45 random layers (12 to 60 experts, 784 to 2032 -> 872 to 7928) and the same kinds of load the mean of 10 / 8 is 0.78 at
+//    80 to 95 tiles; at 96 to 111 tiles 0.85 with 116 to 119 rows, 0.98 with 120 to 127, 1.06 with 128 to 132; at 112 to 140
+//    tiles 1.02, 1.05 and 1.08.  With more rows, 10 / 8, even, skewed (0.5), more skewed (0.8), 64 to 95 tiles: 5 experts 2048
+//    -> 4096, 298 rows 92 / 118, 93 / 119, 93 / 119; 13 experts 1536 -> 1536, 241 rows 73 / 81, 70 / 82, 76 / 83; 16 experts
+//    1024 -> 4096, 224 rows 105 / 118, 130 / 127, 133 / 127; 5 experts 4096 -> 14336, 197 rows 436 / 446, 485 / 441, 471 / 449;
+//    96 to 128 tiles: 6 experts 2048 -> 8192, 398 rows 250 / 238, 243 / 237, 250 / 243; 12 experts 2048 -> 4096, 176 rows 141 /
+//    142, 158 / 142, 161 / 147; 14 experts 2048 -> 8192, 170 rows 293 / 271, 313 / 280, 306 / 292; 8 experts 4096 -> 14336, 128
+//    rows, even 530 / 476.  The GEMM with fewer columns counts, also where the other one has many: 8 experts 256 -> 3328, 1500
+//    rows (48 and 624) 80 / 103, 82 / 107.  An even batch with a mean just below 256 rows needs two tiles for a part of its
+//    experts and counts so: 250 rows, 16 experts 1024 -> 4096 134 / 132, 132 / 132, 131 / 130; 8 experts 2048 -> 8192 244 /
+//    230, 241 / 234, 262 / 236.
 //  * GEMMs of 2^29 weights and more (1 GB, four times the last-level cache) take the time of one pass over an expert's weights.
 //    There they pay from 8 rows on, given two 256-column panels per CU.  What ran before / 8, even, skewed (0.8):
 //      128 experts 2048 -> 8192, 4 rows per expert 1319 / 1482, 1125 / 1293; 8 rows 1525 / 1427, 1549 / 1416; 25 rows 1453 / 1479, 1605 / 1642;
@@ -1082,17 +1086,19 @@ int gemm_bf16_variant_block_m(int v)
 //      512 experts 1024 -> 4096, 8 rows 1513 / 1460, 1485 / 1427; 34 rows 1599 / 1569, 1691 / 1657; 64 rows 1685 / 1658, 1869 / 1794
 //      64 experts 2048 -> 8192, 16 rows 787 / 762, 831 / 755; 64 rows 771 / 793, 921 / 926; half of the experts idle 394 / 387, 431 / 443
 //    With one panel per CU and less they lose where rows are even or experts idle, 10 or 4 / 8, even, half of the experts idle,
-//    skewed: 16 experts 4096 -> 14336, 32 rows 714 / 770, 397 / 476, 770 / 766; 100 rows 766 / 806, 564 / 527, 991 / 1007; 32 experts
-//    2048 -> 8192, 8 rows 388 / 376, 219 / 245, 424 / 375; 4 experts 8192 -> 28672, 100 rows 760 / 887, 605 / 661.
-//    With fewer weights 8 does not pay at few rows (8 / small tiles at 24 rows: 128 experts 512 -> 2048 137 / 137, 159 / 135, 157 / 133).
-//  * With fewer weights 64x128 is the steadiest shape from 34 to 63 rows, 32x128 / 64x128 / 128x128: 128 experts 512 -> 2048, 36 rows 171 / 161 /
-//    162, 173 / 169 / 183, 170 / 164 / 176; 64 experts 1024 -> 4096, 48 rows 314 / 287 / 266, 327 / 280 / 309, 329 / 281 / 302; 16
-//    experts 2048 -> 8192, 48 rows 292 / 291 / 279, 319 / 298 / 285, 310 / 297 / 323; at 64 rows 128x128 has caught up (342 / 320 /
-//    284, 332 / 311 / 309, 342 / 308 / 338).  With 64 panels or fewer it is ahead from 48 on (16 experts 1024 -> 4096 115 / 108 /
-//    101, 124 / 114 / 102, 120 / 114 / 110).
-//  * No dimension of 64 and less: 10 is ahead there of 256-row tiles too (9 / 10: 64 experts 64 -> 256, 800 rows 30 / 24; 64 -> 1024
-//    62 / 55; 16 experts 4096 -> 64, 1000 rows 95 / 85; 128 experts 40 -> 512, 1000 rows 82 / 69).  9 is for operands that 8 cannot address
-//    (9 / 10: 8 experts 2048 -> 8192, 33750 rows 15550 / 20945; 8 experts 1000 -> 8200, 33000 rows 9183 / 16220).
+//    skewed: 16 experts 4096 -> 14336, 32 rows 714 / 770, 397 / 476, 770 / 766; 100 rows 766 / 806, 564 / 527, 991 / 1007; 32
+//    experts 2048 -> 8192, 8 rows 388 / 376, 219 / 245, 424 / 375; 4 experts 8192 -> 28672, 100 rows 760 / 887, 605 / 661.  With
+//    fewer weights 8 does not pay at few rows (8 / small tiles at 24 rows: 128 experts 512 -> 2048 137 / 137, 159 / 135, 157 /
+//    133).
+//  * With fewer weights 64x128 is the steadiest shape from 34 to 63 rows, 32x128 / 64x128 / 128x128: 128 experts 512 -> 2048,
+//    36 rows 171 / 161 / 162, 173 / 169 / 183, 170 / 164 / 176; 64 experts 1024 -> 4096, 48 rows 314 / 287 / 266, 327 / 280 /
+//    309, 329 / 281 / 302; 16 experts 2048 -> 8192, 48 rows 292 / 291 / 279, 319 / 298 / 285, 310 / 297 / 323; at 64 rows
+//    128x128 has caught up (342 / 320 / 284, 332 / 311 / 309, 342 / 308 / 338).  With 64 panels or fewer it is ahead from 48 on
+//    (16 experts 1024 -> 4096 115 / 108 / 101, 124 / 114 / 102, 120 / 114 / 110).
+//  * No dimension of 64 and less: 10 is ahead there of 256-row tiles too (9 / 10: 64 experts 64 -> 256, 800 rows 30 / 24; 64 ->
+//    1024 62 / 55; 16 experts 4096 -> 64, 1000 rows 95 / 85; 128 experts 40 -> 512, 1000 rows 82 / 69).  9 is for operands that
+//    8 cannot address (9 / 10: 8 experts 2048 -> 8192, 33750 rows 15550 / 20945; 8 experts 1000 -> 8200, 33000 rows 9183 /
+//    16220).
 //  * K that is no multiple of the K tile does not have 64x128: there 128 rows pay from 30 on.
 int gemm_bf16_variant(int64_t n_rows, int E, int N, int K, int num_cus)
 {
@@ -1102,9 +1108,10 @@ int gemm_bf16_variant(int64_t n_rows, int E, int N, int K, int num_cus)
     const bool whole = N % BK == 0 && K % BK == 0;
     const bool heavy = whole && (int64_t)E * N * K >= kHeavyWeights;
     const int64_t tiles = (int64_t)E * ((avg + 8 + 255) / 256) * ceil_div(width, 256);
-    if (gemm_ring_ok(n_rows, N, K) &&
-        ((width <= 768 ? avg >= 192 && tiles >= 144 && (N > K ? N : K) >= 1024 : tiles >= 96 && avg >= (tiles < 112 ? 120 : 116)) || (heavy && avg >= kNtRows && panels >= 2 * (int64_t)num_cus)))
-        return 8;
+    const bool fills = width <= 768 ? avg >= 192 && tiles >= 144 && (N > K ? N : K) >= 1024
+                                    : tiles >= 96 && avg >= (tiles < 112 ? 120 : 116);
+    const bool streams = heavy && avg >= kNtRows && panels >= 2 * (int64_t)num_cus;
+    if (gemm_ring_ok(n_rows, N, K) && (fills || streams)) return 8;
     if (avg >= 192) return gemm_ring_addresses(n_rows, N, K) ? 10 : 9;
     const int small = avg >= kNtRows ? 4 : avg >= kNtSoleRows ? 5 : 3;
     if (4 * panels <= num_cus) return avg >= 48 ? 10 : small;

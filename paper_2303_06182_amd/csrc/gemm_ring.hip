@@ -442,6 +442,7 @@ static int launch_ring_t(const GemmParams &p, hipStream_t s)
         setup_rc = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
     });
     MOE_HIP_CHECK(setup_rc);
+    // the schedule's 8 XCDs of 32 blocks; with fewer CUs the blocks take turns, which is right and not balanced
     hipLaunchKernelGGL(kern, dim3(256), dim3(THREADS), smem, s, p);
     MOE_LAUNCH_CHECK("gemm_ring_kernel");
     return MOE_OK;

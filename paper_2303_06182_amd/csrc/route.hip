@@ -311,24 +311,27 @@ __device__ __forceinline__ void block_exclusive_scan4(int *vals, int n, int *wav
 // Schedule of the grouped GEMM's ring kernel (layout: moe_internal.h), by one whole block.  rows_of(e), e < E.
 // What it balances: an expert's rows come in tiles of up to eight 32-row units, and a tile costs about six units whatever
 // its height, and one of less than four units as much as one of four: its time is that of the weights' way into the CU
-// (measured: the time per K tile is 0.8 us at one unit, 1.05 at four and 1.6 at eight; counted as less, it made 128 experts of
-// one or two units fall to the XCDs by 15 to 17 instead of 16, a round more for some: 1473 against 1610 us for 34 rows).  The experts' rows, in order, are cut in
-// eight parts of equal cost, one per XCD, between two tiles of an expert at most (an XCD's blocks share weights and rows in
-// its L2, so what one expert needs stays together).  Inside a part every expert's tiles get the same height, at most the
-// one that makes the part's rounds of 32 blocks cheapest, and the experts with the taller tiles come first, so that a round's
-// tiles cost about the same.  (Places among experts of one height are handed out by LDS atomics: their
-// order differs between runs, the sums do not.)
+// (fitted to K tiles of 0.8 us at one unit, 1.05 at four and 1.6 at eight; where all CUs stream weights of their own from HBM, 8
+// experts 8192 -> 8192, they take 1.54, 1.70 and 2.10; counted as less, a low tile made 128 experts of one or two units fall to the XCDs by
+// 15 to 17 instead of 16, a round more for some: 1473 against 1610 us for 34 rows).  The choice of a height leaves that floor out: it
+// compares heights for the same rows, and with the floor no round would be spread over idle blocks.
+// The experts' rows, in order, are cut in eight parts of equal cost, one per XCD, between two tiles of an expert at most
+// (an XCD's blocks share weights and rows in its L2, so what one expert needs stays together).  Inside a part every expert's tiles
+// get the same height, at most the one that makes the part's rounds of 32 blocks cheapest, and the experts with the taller tiles
+// come first, so that a round's tiles cost about the same.  (Places among experts of one height are handed out by LDS atomics:
+// their order differs between runs, the sums do not.)
 //
-// The XCDs share one list of experts, and each takes an eighth of its output tiles, where parts of whole row tiles do not come
-// out: with up to kRingSharedTiles row tiles, of which some XCDs would get none or twice the others', and where the
-// slowest part's rounds cost more than those of the eighths by kRingSharedGain (and a window of the kernel's holds the experts).  The
-// list is in the experts' order: sorted by height the first eighth would cost the most.  FFN in us, parts / shared: 128 experts 2048
-// -> 8192, 1024 rows on one expert 151 / 137, on four 189 / 158; 8 experts 4096 -> 14336, 1024 rows on four 477 / 374, on one 401 / 288, 2000
-// evenly spread 732 / 599; 4 experts 8192 -> 28672, 400 rows on two 1238 / 661; 32 experts 2048 -> 8192, 256 rows 376 / 376, 3200 rows 431 /
-// 425.  With more row tiles what it takes is the estimate plus a twentieth (an eighth's heights are mixed), estimate and measured
-// ratio: 42 experts 768 -> 1536, 372 rows each 0.65, 0.73; 25 experts 1280 -> 1280, 857 rows 0.74, 0.78; 32 experts 1024 -> 4096, 256 rows 0.84, 0.91; 64
-// experts 1024 -> 4096, 256 rows, more and less skewed 0.90, 0.99 and 0.95, 1.03; 16 experts 2048 -> 8192, 500 rows 1.00, 1.06.
-// (Dealing the rounds of the whole chip over the XCDs instead, 32 neighbours on the list each, cost 32 even experts 10 %.)
+// Where parts of whole row tiles do not come out, the XCDs share one list of experts and each takes an eighth of its output tiles:
+// with up to kRingSharedTiles row tiles, of which some XCDs would get none or twice the others', and, if a window of the
+// kernel's holds the experts, where the eighths' rounds are estimated at less than kRingSharedGain of the slowest part's.  The list
+// is in the experts' order: sorted by height the first eighth would cost the most.
+// FFN in us, parts / shared: 128 experts 2048 -> 8192, 1024 rows on one expert 151 / 137, on four 189 / 158; 8 experts 4096 -> 14336, 1024
+// rows on four 477 / 374, on one 401 / 288, 2000 evenly spread 732 / 599; 4 experts 8192 -> 28672, 400 rows on two 1238 / 661; 32 experts
+// 2048 -> 8192, 256 rows 376 / 376, 3200 rows 431 / 425.  With more row tiles the time's ratio is the estimated one plus a twentieth,
+// because an eighth's heights are mixed: 42 experts 768 -> 1536, 372 rows each 0.65, measured 0.73; 25 experts 1280 -> 1280, 857 rows 0.74,
+// 0.78; 32 experts 1024 -> 4096, 256 rows 0.84, 0.91; 64 experts 1024 -> 4096, 256 rows, more and less skewed 0.90, 0.99 and 0.95, 1.03; 16
+// experts 2048 -> 8192, 500 rows 1.00, 1.06.  (Dealing the rounds of the whole chip over the XCDs instead, 32 neighbours on the
+// list each, cost 32 even experts 10 %.)
 static constexpr int kRingSharedTiles = 32;
 static constexpr float kRingSharedGain = 0.88f;
 static_assert(kRingSharedTiles <= kWave, "the ring kernel expects a shared list in one window");
