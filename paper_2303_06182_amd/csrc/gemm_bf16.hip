@@ -1085,6 +1085,9 @@ int gemm_bf16_variant_block_m(int v)
 //      even batches of 25 to 100 rows: a 128x256 ring of fixed height ran there)
 //      512 experts 1024 -> 4096, 8 rows 1513 / 1460, 1485 / 1427; 34 rows 1599 / 1569, 1691 / 1657; 64 rows 1685 / 1658, 1869 / 1794
 //      64 experts 2048 -> 8192, 16 rows 787 / 762, 831 / 755; 64 rows 771 / 793, 921 / 926; half of the experts idle 394 / 387, 431 / 443
+//    Not with a dimension of 768 or less, which the shapes for fewer weights serve (32x128, 64x128 or 128x128 / 8: 512 experts
+//    512 -> 2048, 8 rows 384 / 401, 393 / 400; 40 rows 443 / 452, 472 / 499; 64 rows 491 / 489, 509 / 528; 1024 experts 512 -> 1024, 8
+//    rows 401 / 430, 383 / 410; 400 experts 768 -> 2048, 24 rows 490 / 513, 514 / 525).
 //    With one panel per CU and less they lose where rows are even or experts idle, 10 or 4 / 8, even, half of the experts idle,
 //    skewed: 16 experts 4096 -> 14336, 32 rows 714 / 770, 397 / 476, 770 / 766; 100 rows 766 / 806, 564 / 527, 991 / 1007; 32
 //    experts 2048 -> 8192, 8 rows 388 / 376, 219 / 245, 424 / 375; 4 experts 8192 -> 28672, 100 rows 760 / 887, 605 / 661.  With
@@ -1106,7 +1109,7 @@ int gemm_bf16_variant(int64_t n_rows, int E, int N, int K, int num_cus)
     const int width = N < K ? N : K;
     const int64_t panels = (int64_t)E * width / 256;
     const bool whole = N % BK == 0 && K % BK == 0;
-    const bool heavy = whole && (int64_t)E * N * K >= kHeavyWeights;
+    const bool heavy = whole && width > 768 && (int64_t)E * N * K >= kHeavyWeights;
     const int64_t tiles = (int64_t)E * ((avg + 8 + 255) / 256) * ceil_div(width, 256);
     const bool fills = width <= 768 ? avg >= 192 && tiles >= 144 && (N > K ? N : K) >= 1024
                                     : tiles >= 96 && avg >= (tiles < 112 ? 120 : 116);

@@ -8,6 +8,7 @@ from helpers import expert_tile_shape
     # few rows per expert: 2^29 weights and two 256-column panels per CU, or the small tiles
     (128, 2048, 8192, 8, "cut to rows"), (128, 2048, 8192, 7, "32x128"), (512, 1024, 4096, 8, "cut to rows"),
     (128, 512, 2048, 24, "32x128"), (64, 2048, 8192, 30, "cut to rows"),
+    (512, 512, 2048, 8, "32x128"), (512, 512, 2048, 40, "64x128"), (512, 512, 2048, 100, "128x128"),
     (32, 2048, 8192, 29, "32x128"), (32, 2048, 8192, 64, "128x128"), (16, 4096, 14336, 32, "128x128"),
     (16, 4096, 14336, 100, "128x128"), (8, 6144, 16384, 8, "32x128"), (8, 6144, 16384, 100, "128x128"),
     (4, 8192, 28672, 8, "32x128"), (4, 8192, 28672, 100, "128x128"), (8, 4096, 14336, 100, "128x128"),
