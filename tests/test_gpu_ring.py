@@ -21,6 +21,8 @@ def counts_of(kind, E):
     elif kind == "hot":        # one expert holds most of the rows, its neighbours a handful
         c = EDGES + [int(v) for v in rng.integers(0, 40, E - len(EDGES))]
         c[len(EDGES)] = 200 * E
+    elif kind == "level":      # parts of whole row tiles have a tile more than blocks: the XCDs share the tiles
+        c = [372 + e % 3 for e in range(E)]
     elif kind.startswith("few"):   # so many active experts, one to eight row tiles each
         c = [0] * E
         for i in range(int(kind[3:])):
@@ -34,7 +36,8 @@ def counts_of(kind, E):
 @pytest.mark.parametrize("kind,E,D,F,bias", [
     ("even", 150, 128, 1024, False), ("even", 80, 264, 1032, True), ("hot", 100, 520, 1032, True), ("hot", 80, 1024, 264, False),
     ("sparse", 76, 328, 1344, True), ("even", 150, 72, 1032, True),
-    ("few1", 8, 3080, 3144, True), ("few2", 8, 3080, 3144, False), ("few7", 8, 3072, 3080, False), ("few6", 16, 1544, 1608, True)])
+    ("few1", 8, 3080, 3144, True), ("few2", 8, 3080, 3144, False), ("few7", 8, 3072, 3080, False), ("few6", 16, 1544, 1608, True),
+    ("level", 42, 520, 1288, True)])
 def test_rows_of_every_height(kind, E, D, F, bias):
     print("ring", kind, E, D, F, flush=True)
     counts = counts_of(kind, E)
