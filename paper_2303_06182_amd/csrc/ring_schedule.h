@@ -36,6 +36,32 @@ __host__ __device__ __forceinline__ void ring_pieces(int units, int64_t pre, int
     }
 }
 
+// What the rounds of 2^log_blocks blocks cost that take n output tiles of each row tile, at the best of the heights tried, and
+// that height: tried from 8 down, with the row tiles that the units make at each.  Below four units only to give every block of a
+// single round a tile.
+struct RingRounds {
+    float cost = 0.f;
+    int height = 8;
+    bool open = true;
+};
+__host__ __device__ __forceinline__ void ring_try_height(RingRounds &r, int h, int tiles, float units, int n, int log_blocks)
+{
+    const int64_t out = (int64_t)tiles * n;
+    r.open = r.open && tiles > 0 && (h >= 4 || out <= 1 << log_blocks);
+    const float c = (float)((out + (1 << log_blocks) - 1) >> log_blocks) * (6.f + units / (float)tiles);
+    if (r.open && (h == 8 || c < 0.97f * r.cost)) r.cost = c, r.height = h;
+}
+
+// Whether all XCDs share one list of experts, given the estimated cost of their eighths of it and of the slowest parts: see
+// ring_schedule.
+static constexpr int kRingSharedTiles = 32, kRingWindow = 64;
+static constexpr float kRingSharedGain = 0.88f, kRingSharedFewGain = 0.95f;
+static_assert(kRingSharedTiles <= kRingWindow, "the ring kernel expects a shared list in one window");
+__host__ __device__ __forceinline__ bool ring_shares_pay(int E, int row_tiles, float eighths, float parts)
+{
+    return (E < row_tiles ? E : row_tiles) <= kRingWindow && eighths < (row_tiles <= kRingSharedTiles ? kRingSharedFewGain : kRingSharedGain) * parts;
+}
+
 // Where XCD x's tiles of a list of so many begin that all XCDs share.
 __host__ __device__ __forceinline__ int ring_share(int tiles, int x)
 {

@@ -322,19 +322,18 @@ __device__ __forceinline__ void block_exclusive_scan4(int *vals, int n, int *wav
 // their order differs between runs, the sums do not.)
 //
 // Where parts of whole row tiles do not come out, the XCDs share one list of experts and each takes an eighth of its output tiles:
-// with up to kRingSharedTiles row tiles, of which some XCDs would get none or twice the others', and, if a window of the
-// kernel's holds the experts, where the eighths' rounds are estimated at less than kRingSharedGain of the slowest part's.  The list
-// is in the experts' order: sorted by height the first eighth would cost the most.
+// if a window of the kernel's holds the experts and the eighths' rounds are estimated at less than kRingSharedGain of the slowest
+// part's, with up to kRingSharedTiles row tiles kRingSharedFewGain.  The list is in the experts' order: sorted by height the first
+// eighth would cost the most.
 // FFN in us, parts / shared: 128 experts 2048 -> 8192, 1024 rows on one expert 151 / 137, on four 189 / 158; 8 experts 4096 -> 14336, 1024
-// rows on four 477 / 374, on one 401 / 288, 2000 evenly spread 732 / 599; 4 experts 8192 -> 28672, 400 rows on two 1238 / 661; 32 experts
-// 2048 -> 8192, 256 rows 376 / 376, 3200 rows 431 / 425.  With more row tiles the time's ratio is the estimated one plus a twentieth,
-// because an eighth's heights are mixed: 42 experts 768 -> 1536, 372 rows each 0.65, measured 0.73; 25 experts 1280 -> 1280, 857 rows 0.74,
-// 0.78; 32 experts 1024 -> 4096, 256 rows 0.84, 0.91; 64 experts 1024 -> 4096, 256 rows, more and less skewed 0.90, 0.99 and 0.95, 1.03; 16
-// experts 2048 -> 8192, 500 rows 1.00, 1.06.  (Dealing the rounds of the whole chip over the XCDs instead, 32 neighbours on the
-// list each, cost 32 even experts 10 %.)
-static constexpr int kRingSharedTiles = 32;
-static constexpr float kRingSharedGain = 0.88f;
-static_assert(kRingSharedTiles <= kWave, "the ring kernel expects a shared list in one window");
+// rows on four 477 / 374, on one 401 / 288; 4 experts 8192 -> 28672, 400 rows on two 1238 / 661.  With more than kRingSharedTiles row
+// tiles the time's ratio is the estimated one plus a twentieth, because an eighth's heights are mixed: 42 experts 768 -> 1536, 372 rows
+// each 0.65, measured 0.73; 25 experts 1280 -> 1280, 857 rows 0.74, 0.78; 32 experts 1024 -> 4096, 256 rows 0.84, 0.91; 64 experts
+// 1024 -> 4096, 256 rows, more and less skewed 0.90, 0.99 and 0.95, 1.03; 16 experts 2048 -> 8192, 500 rows 1.00, 1.06.  With fewer it
+// is spread about the estimate: 92 batches of 8 and 16 experts, 1024 -> 4096, 2048 -> 8192 and 4096 -> 14336, with 245 to 340 rows each
+// measured 0.81 to 0.98 where it is below 0.92, 0.95 to 1.03 up to 0.95, 0.96 to 1.04 up to 0.98 and 0.98 to 1.14 above (8 experts 4096 ->
+// 14336, parts / shared: 245 rows 764 / 620 at 0.69, 273 rows 615 / 694 at 0.98 and 616 / 702 at 1.02).
+// (Dealing the rounds of the whole chip over the XCDs instead, 32 neighbours on the list each, cost 32 even experts 10 %.)
 
 struct RingScratch {
     int cost[MOE_MAX_E];         // then its prefix
@@ -378,28 +377,21 @@ __device__ __forceinline__ void ring_schedule(const Rows &rows_of, int E, int n1
         const bool one_list = lane >= 16;
         const int x = lane & 7, n = (one_list ? lane & 1 : lane >> 3) == 0 ? n1 : n2, log_blocks = one_list ? 8 : 5;
         const float units = (float)(one_list ? all_units : sm.units[x]);
-        float best = 0.f;
-        int cap = 8;
-        bool open = true;
+        RingRounds rounds;
 #pragma unroll
         for (int h = 8; h >= 1; --h) {
             const int all_h = __shfl(all, h, kWave);
-            const int tiles = one_list ? all_h : sm.tiles[x][h];
-            const int64_t out = (int64_t)tiles * n;
-            // below four units only to give every block of a single round a tile
-            open = open && tiles > 0 && (h >= 4 || out <= 1 << log_blocks);
-            const float c = (float)((out + (1 << log_blocks) - 1) >> log_blocks) * (6.f + units / (float)tiles);
-            if (open && (h == 8 || c < 0.97f * best)) best = c, cap = h;
+            ring_try_height(rounds, h, one_list ? all_h : sm.tiles[x][h], units, n, log_blocks);
         }
-        float slowest = best;  // of the GEMM's parts
+        float slowest = rounds.cost;  // of the GEMM's parts
 #pragma unroll
         for (int m = 1; m < 8; m <<= 1) slowest = fmaxf(slowest, __shfl_xor(slowest, m, kWave));
         // a GEMM's K loop is as long as the other one has columns
         const float parts = __shfl(slowest, 0, kWave) * (float)n2 + __shfl(slowest, 8, kWave) * (float)n1;
-        const float eighths = __shfl(best, 16, kWave) * (float)n2 + __shfl(best, 17, kWave) * (float)n1;
-        const bool share = row_tiles <= kRingSharedTiles || (min(E, row_tiles) <= kWave && eighths < kRingSharedGain * parts);
-        const int cap_all = __shfl(cap, 16 + (lane >> 3 & 1), kWave);
-        if (lane < 16) sm.cap[lane >> 3][x] = share ? cap_all : cap;
+        const float eighths = __shfl(rounds.cost, 16, kWave) * (float)n2 + __shfl(rounds.cost, 17, kWave) * (float)n1;
+        const bool share = ring_shares_pay(E, row_tiles, eighths, parts);
+        const int cap_all = __shfl(rounds.height, 16 + (lane >> 3 & 1), kWave);
+        if (lane < 16) sm.cap[lane >> 3][x] = share ? cap_all : rounds.height;
         if (lane == 0) sm.shared = share;
     }
     __syncthreads();

@@ -53,3 +53,16 @@ def test_shared_list(lib):
         lib.ring_shares(tiles, first.ctypes.data_as(ctypes.c_void_p))
         assert first[0] == 0 and first[8] == tiles and np.all(np.diff(first) >= 0)
         assert np.diff(first).max() == -(-tiles // 8)
+
+
+@pytest.mark.parametrize("counts,n1,n2,shared", [
+    # fewer row tiles than XCDs, or a part with twice the others' tiles
+    ([0, 1024] + [0] * 6, 56, 16, True), ([256, 0, 256, 0, 256, 0, 0, 256], 56, 16, True), ([200, 200, 0, 0], 112, 32, True),
+    ([260, 237, 257, 265, 231, 256, 228, 226], 56, 16, True), ([372] * 42, 6, 3, True),
+    # parts that come out as well as eighths of one list, or better: two row tiles each but for one, one row tile each
+    ([268, 280, 271, 264, 246, 272, 282, 301], 56, 16, False), ([284, 311, 258, 258, 278, 290, 285, 276], 56, 16, False),
+    ([250, 231, 242, 247, 261, 218, 227, 238, 241, 269, 240, 243, 239, 273, 246, 255], 32, 8, False),
+    ([256] * 32, 32, 8, False), ([0] * 8, 32, 8, False)])
+def test_when_all_share(lib, counts, n1, n2, shared):
+    rows = np.asarray(counts, dtype=np.int32)
+    assert bool(lib.ring_is_shared(rows.ctypes.data_as(ctypes.c_void_p), len(rows), n1, n2)) == shared
