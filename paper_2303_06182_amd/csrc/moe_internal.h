@@ -163,7 +163,7 @@ int launch_tile_map(const int32_t *offsets, int E, int block_m, int32_t *tile_ex
 // + x, where XCD x's part of the lists begins and ends; kRingCut + x, the expert cut between XCD x - 1 and x and the 32-row
 // unit of it that the former ends in front of (expert << kRingCutShift | unit; MOE_MAX_E as expert: none); kRingCap + x, the
 // greatest tile height in units (bits 0 .. 7 first, 8 .. 15 second GEMM) and, as bit kRingShared, that all XCDs have the same
-// list and each takes a part of its column tiles.
+// list and each takes an eighth of its output tiles.
 static constexpr int kRingMap = 1 << 30;  // tile height that stands for it
 static constexpr int kRingFirst = 8, kRingLast = 16, kRingCut = 24, kRingCap = 33, kRingShared = 16;
 
