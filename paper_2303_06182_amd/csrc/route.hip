@@ -338,8 +338,7 @@ __device__ __forceinline__ void block_exclusive_scan4(int *vals, int n, int *wav
 struct RingScratch {
     int cost[MOE_MAX_E];         // then its prefix
     int wave_tot[16];
-    int units[8];                // of every part
-    int tiles[8][9];             // ... cut to a height of at most h
+    int tiles[8][9];             // of every part, cut to a height of at most h; [0]: its units
     int cap[2][8];
     int shared;
     int bin[2][64];              // experts by GEMM, part and height (8 first), then the first place of each
@@ -351,7 +350,6 @@ __device__ __forceinline__ void ring_schedule(const Rows &rows_of, int E, int n1
 {
     const int tid = threadIdx.x, nthreads = blockDim.x, lane = tid % kWave, wave = tid / kWave;
     for (int e = tid; e < E; e += nthreads) sm.cost[e] = ring_cost(ring_units(rows_of(e)));
-    if (tid < 8) sm.units[tid] = 0;
     if (tid < 72) sm.tiles[tid / 9][tid % 9] = 0;
     if (tid < 128) sm.bin[tid / 64][tid % 64] = 0;
     if (tid < 9) words[kRingCut + tid] = MOE_MAX_E << kRingCutShift;  // no expert
@@ -362,7 +360,7 @@ __device__ __forceinline__ void ring_schedule(const Rows &rows_of, int E, int n1
         ring_pieces(
             ring_units(rows_of(e)), sm.cost[e], total,
             [&](int x, int, int units) {
-                atomicAdd(&sm.units[x], units);
+                atomicAdd(&sm.tiles[x][0], units);
                 for (int h = 1; h <= 8; ++h) atomicAdd(&sm.tiles[x][h], (units + h - 1) / h);
             },
             [&](int x, int first) { words[kRingCut + x] = e << kRingCutShift | first; });
@@ -372,17 +370,24 @@ __device__ __forceinline__ void ring_schedule(const Rows &rows_of, int E, int n1
         int all = 0;  // lane h: row tiles of all parts cut to a height of at most h; lane 0: units
         if (lane < 9)
 #pragma unroll
-            for (int x = 0; x < 8; ++x) all += lane == 0 ? sm.units[x] : sm.tiles[x][lane];
-        const int row_tiles = __shfl(all, 8, kWave), all_units = __shfl(all, 0, kWave);
+            for (int x = 0; x < 8; ++x) all += sm.tiles[x][lane];
+        const int row_tiles = __shfl(all, 8, kWave);
         const bool one_list = lane >= 16;
         const int x = lane & 7, n = (one_list ? lane & 1 : lane >> 3) == 0 ? n1 : n2, log_blocks = one_list ? 8 : 5;
-        const float units = (float)(one_list ? all_units : sm.units[x]);
+        // read at once: each read where one_list says so is a branch and a wait of its own (layer of 24 experts 1000 -> 4000, 3001
+        // tokens, 197.0 us that way, 196.0 this way)
+        int tiles[9];
+#pragma unroll
+        for (int h = 0; h <= 8; ++h) tiles[h] = sm.tiles[x][h];
+#pragma unroll
+        for (int h = 0; h <= 8; ++h) {
+            const int all_h = __shfl(all, h, kWave);
+            tiles[h] = one_list ? all_h : tiles[h];
+        }
+        const float units = (float)tiles[0];
         RingRounds rounds;
 #pragma unroll
-        for (int h = 8; h >= 1; --h) {
-            const int all_h = __shfl(all, h, kWave);
-            ring_try_height(rounds, h, one_list ? all_h : sm.tiles[x][h], units, n, log_blocks);
-        }
+        for (int h = 8; h >= 1; --h) ring_try_height(rounds, h, tiles[h], units, n, log_blocks);
         float slowest = rounds.cost;  // of the GEMM's parts
 #pragma unroll
         for (int m = 1; m < 8; m <<= 1) slowest = fmaxf(slowest, __shfl_xor(slowest, m, kWave));
