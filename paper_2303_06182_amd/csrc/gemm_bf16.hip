@@ -57,7 +57,8 @@ namespace moe355 {
 
 bool gemm_ring_ok(int64_t n_rows, int N, int K);
 bool gemm_ring_addresses(int64_t n_rows, int N, int K);
-int launch_gemm_ring(const GemmParams &p, bool relu, hipStream_t s);
+bool gemm_ring_quant_ok(int64_t n_rows, int N, int K);
+int launch_gemm_ring(const GemmParams &p, int wbits, bool relu, hipStream_t s);
 
 static constexpr int BK = 64;
 static constexpr int GROUP_M = 4;
@@ -989,13 +990,36 @@ static constexpr int kNtRows = 8, kNtSoleRows = 2;
 // Weights of one GEMM (all experts) from which on its time is that of streaming them
 static constexpr int64_t kHeavyWeights = 1ll << 29;
 
-// 8-bit weights are for the weight-streaming regime: always the small tiles, three LDS stages deep (36 KB with 32 rows:
+// Quantised weights on tiles cut to an expert's rows (28: e4m3, 49: mxfp4; gemm_ring.hip), which take a tile's weights once for up to
+// 256 rows where the small tiles take them, and widen them, once for 64: from so many rows per expert on, and so much
+// work in all that it pays for the schedule (7 us) and for a last round of tall tiles.  FFN in us, 64x128 / 28 and 64x256 / 49,
+// even and skewed (0.8):
+//   128 experts 2048 -> 8192, 48 rows per expert e4m3 889 / 848, 1041 / 987; 64 rows 914 / 869, 1186 / 1032 and 679 / 788, 963 / 971;
+//   128 rows 1469 / 1150, 1777 / 1329 and 1242 / 1056, 1493 / 1241; 512 rows 5326 / 3265, 5798 / 3580 and 4552 / 3140, 4831 / 3400
+//   64 experts 1024 -> 4096, 64 rows 142 / 135, 165 / 180 and 110 / 122, 135 / 181; 128 rows 204 / 175, 226 / 227 and 171 / 156, 223 / 222;
+//   256 rows 364 / 258, 397 / 316 and 329 / 230, 370 / 290
+//   16 experts 1024 -> 4096, 128 rows 72 / 80, 82 / 91 and 79 / 81, 89 / 92; 256 rows 102 / 99, 112 / 110 and 100 / 92, 123 / 106
+//   8 experts 512 -> 2048, old / new at 1024 rows 0.99, 0.93 and 1.05, 1.07, at 1536 rows 1.08, 1.16 and 1.16, 1.10
+// The least work is rows * D * F of base + per_weight * D * F up to most, a quarter more with a dimension of 768 or less (few columns
+// and long K loops in one GEMM).  Over 35 layers of 2 to 512 experts, 256 -> 1024 to 4096 -> 14336, 32 to 4096 rows, even, skewed
+// (0.5, 0.8) and half idle, the 1762 batches on the new side of the line take 0.80 of the old time in the mean, 1.16 at worst.
+static bool quant_ring_pays(int64_t n_rows, int E, int N, int K, int64_t least_rows, double base, double per_weight, double most)
+{
+    const double weights = (double)N * K;
+    double work = base + per_weight * weights;
+    if (work > most) work = most;
+    if ((N < K ? N : K) <= 768) work *= 1.25;
+    return n_rows >= least_rows * E && (double)n_rows * weights >= work;
+}
+
+// 8-bit weights with fewer rows: the small tiles, three LDS stages deep (36 KB with 32 rows:
 // four blocks per CU; a fourth stage leaves room for three: 16 experts 2048 -> 8192, 100 tokens 129 -> 137 us, 128 experts,
-// 512 tokens 786 -> 797), whatever the row count.  (Measured on 128 experts of 2048 x 8192 with 1 to 64 rows each: 2 to 6
+// 512 tokens 786 -> 797).  (Measured on 128 experts of 2048 x 8192 with 1 to 64 rows each: 2 to 6
 // stages, 32x64 and 32x256 tiles and up to 6 blocks per CU all land within +-8 % of these two.)
-int gemm_bf16_variant_w8(int64_t n_rows, int E)
+int gemm_bf16_variant_w8(int64_t n_rows, int E, int N, int K)
 {
     const int64_t avg = E > 0 ? n_rows / E : n_rows;
+    if (gemm_ring_quant_ok(n_rows, N, K) && quant_ring_pays(n_rows, E, N, K, (int64_t)E * N * K >= 2 * kHeavyWeights ? 48 : 80, 12e9, 1000., 30e9)) return 28;
     // 64-row tiles, us against 32-row ones (128 experts 2048 -> 8192 / 64 experts 1024 -> 4096): 24 rows 942 / 993 and
     // 165 / 151, 36 rows 998 / 1250 and 171 / 203.  With fewer experts their smaller number counts for more, above all
     // where the rows are spread unevenly: 32 experts 2048 -> 8192, skewed, 30 rows 285 / 267, 36 rows 287 / 312; 8 experts
@@ -1003,7 +1027,7 @@ int gemm_bf16_variant_w8(int64_t n_rows, int E)
     return avg >= (E >= 64 ? 28 : E >= 32 ? 34 : 48) ? 22 : avg >= kNtRows ? 24 : avg >= kNtSoleRows ? 25 : 23;
 }
 
-// 4-bit weights: 43 = 32x256, 48 = 64x256, three LDS stages each plus the two scale buffers (32x256: 44 KB,
+// 4-bit weights with fewer rows: 43 = 32x256, 48 = 64x256, three LDS stages each plus the two scale buffers (32x256: 44 KB,
 // three blocks per CU; a fourth stage would leave room for two, 0.141 -> 0.154 ms on the decoder's first
 // GEMM; two stages 0.150).  (Measured on 128 experts of 2048 x 8192
 // with 1 to 64 rows each: 256 columns per tile beat 128 by 25-30 % -- the A tile, re-read once per column
@@ -1019,6 +1043,7 @@ int gemm_bf16_variant_w4(int64_t n_rows, int E, int N, int K, int num_cus)
 {
     const int64_t avg = E > 0 ? n_rows / E : n_rows;
     const int64_t panels = (int64_t)E * (N < K ? N : K) / 256;
+    if (gemm_ring_quant_ok(n_rows, N, K) && quant_ring_pays(n_rows, E, N, K, (int64_t)E * N * K >= 2 * kHeavyWeights || panels >= 512 ? 80 : 112, 6e9, 1500., 15e9)) return 49;
     return avg >= (4 * panels <= num_cus ? 96 : (int64_t)E * N * K >= 2 * kHeavyWeights ? 44 : 56) ? 48 : avg >= kNtRows ? 44 : 43;
 }
 
@@ -1039,7 +1064,7 @@ int gemm_bf16_gate_split(int M, int N, int K, int num_cus)
 int gemm_bf16_variant_block_m(int v)
 {
     switch (v) {
-    case 8: return kRingMap;
+    case 8: case 28: case 49: return kRingMap;
     case 10: return 128;
     case 2: case 22: case 48: return 64;
     case 3: case 4: case 5: case 23: case 24: case 25: case 43: case 44: return 32;
@@ -1166,7 +1191,9 @@ int launch_gemm_bf16(const GemmParams &p, bool grouped, int variant, bool out_f3
         if (taken || rc != MOE_OK) return rc;
     }
     switch (variant) {
-    case 8: return launch_gemm_ring(p, relu, s);
+    case 8: return launch_gemm_ring(p, 0, relu, s);
+    case 28: return launch_gemm_ring(p, 8, relu, s);
+    case 49: return launch_gemm_ring(p, 4, relu, s);
     case 9: {
         // whole rounds as 256x256 tiles, the partly filled last round as 128x128 sub-tiles
         GemmParams q = p;

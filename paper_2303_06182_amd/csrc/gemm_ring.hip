@@ -37,6 +37,14 @@
 // 8 consecutive columns 32 p + 8 * (lane / 16) ... of token row lane % 16 and leave as one 16-byte store, without a
 // trip through LDS (all of which the ring holds).
 //
+// Weights of 8 or 4 bits (BQ) go to LDS as they are stored and are widened to bf16 in registers, 8 per lane and fragment by
+// four v_cvt_scalef32_pk_bf16_* (mxfp4: with the block's scale; e4m3: the expert's scale multiplies the sums), behind the MFMAs
+// of the step before theirs, where vector instructions are free; both wave rows widen the same fragments.  A K tile of 256 columns is 16 or 8 KB
+// instead of 32, so the rows get seven slots and everything is loaded three K tiles ahead instead of two: what then bounds tiles
+// of few rows is the latency of the loads (with two K tiles ahead 128 experts 2048 -> 8192, 64 rows per expert, FFN: e4m3 930 us, now
+// 869, mxfp4 861, now 788; with the weights alone, by four waves of their own, four and six ahead 888 and 878: the CU's loads return in
+// order).  Full tiles run at 1.35 (e4m3) and 1.40 PFLOP/s (same layer, 512 rows), where bf16 weights reach 1.15: there is half as much to load.
+//
 // Launch: PERSISTENT, one block per CU.  Workgroups are handed to the 8 XCDs round-robin and each XCD has its own L2,
 // so the schedule (ring_schedule, route.hip) gives each a part of the experts' rows of equal cost, or, where that does not
 // come out, an eighth of all output tiles.
@@ -67,6 +75,15 @@ constexpr int GROUP_M = 4;
 // 1845, 1847, 1835, 1859, 1860).
 constexpr uint32_t kNowhere = 0xfc000000u;
 
+// Quantised weights: seven slots of rows; behind them the weights' K tiles, three or four (a K tile's last read is in its even step, so
+// that three do for loads issued in the odd one); behind them mxfp4's block scales in groups of 16 bytes a column (8 K tiles'
+// worth, fewer at a tile's end).  Three K tiles lie in three groups at most, as two short groups are never neighbours.
+constexpr int Q_SLOTS = 7, Q_AHEAD = 3, Q_SCALES = BN * 16, Q_SCALE_BUFS = 3;
+constexpr int q_ring(int bq) { return bq == 8 ? 3 : bq == 4 ? 4 : 0; }
+constexpr int q_tile_bytes(int bq) { return bq == 8 ? BN * 64 : bq == 4 ? BN * 32 : 0; }
+template <int BQ> struct QuantRaw { typedef u32x2 type; };   // a lane's 8 weights
+template <> struct QuantRaw<4> { typedef u32_lds type; };
+
 struct RingTile {
     int row0, row_end, expert, n0;
 };
@@ -92,9 +109,15 @@ __device__ __forceinline__ int opaque(int v)
 
 }  // namespace
 
-template <bool RELU, bool RAGGED>
+template <bool RELU, bool RAGGED, int BQ = 0>
 __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
 {
+    constexpr bool Q = BQ != 0, B4 = BQ == 4;
+    static_assert(!Q || !RAGGED, "8- and 4-bit weights come in whole K tiles");
+    constexpr int SLOT = Q ? BM * 64 : SLOT_BYTES;
+    constexpr int SLOTS = Q ? Q_SLOTS : NSLOT, AHEAD = Q ? Q_AHEAD : 2;
+    constexpr int QT = q_tile_bytes(BQ), Q_RING = q_ring(BQ), QB = SLOTS * SLOT, QS = QB + Q_RING * QT;  // quantised weights: size of a K tile, LDS offsets of the first and of the block scales
+    constexpr int NBL = Q ? QT / 1024 / NWAVE : 0;  // a wave's loads of a K tile of weights
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem_raw[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -184,7 +207,7 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
     const int frag_off = row16 * 64 + ((kq ^ ((row16 >> 2) & 3)) << 4);
     const uint8_t *fragA = smem_raw + wm * 1024 + frag_off;
     const uint8_t *fragB = smem_raw + BM * 64 + (wn * WTN) * 64 + frag_off;
-    auto read_a = [&](int slot, int block) __attribute__((always_inline)) { return *reinterpret_cast<const bf16x8 *>(fragA + slot * SLOT_BYTES + block * 2048); };
+    auto read_a = [&](int slot, int block) __attribute__((always_inline)) { return *reinterpret_cast<const bf16x8 *>(fragA + slot * SLOT + block * 2048); };
     auto read_b = [&](int slot, int block) __attribute__((always_inline)) { return *reinterpret_cast<const bf16x8 *>(fragB + slot * SLOT_BYTES + block * 1024); };
 
     // ---- load stream
@@ -197,7 +220,7 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
     const __amdgpu_buffer_rsrc_t bufA = __builtin_amdgcn_make_buffer_rsrc(const_cast<void *>(p.A), 0, (int)kNowhere, 0x00020000);
     __amdgpu_buffer_rsrc_t bufB = bufA;  // the expert's weights
     const __amdgpu_buffer_rsrc_t bufC = __builtin_amdgcn_make_buffer_rsrc(p.C, 0, (int)kNowhere, 0x00020000);
-    uint32_t a_voff[AG], b_voff[BG];
+    uint32_t a_voff[AG], b_voff[BG], s_voff = 0;
     const int ld_row = lane >> 2;                         // row inside the 16-row group
     const int ld_chunk = (lane & 3) ^ ((lane >> 4) & 3);  // K chunk this lane fetches for its LDS position
     int b_col[BG];                                        // column of the tile this lane fetches in group g
@@ -207,12 +230,19 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
         const int x = rho % WTN, xi = x >> 4, xr = x & 15;
         b_col[g] = (rho / WTN) * WTN + 32 * (xi >> 1) + 8 * (xr >> 2) + 4 * (xi & 1) + (xr & 3);
     }
+    uint32_t q_lane[BG];  // quantised weights: the lane's 16 bytes of a 1 KB block, rows of 64 / 32 bytes (see read_q)
+#pragma unroll
+    for (int g = 0; g < BG; ++g)
+        q_lane[g] = B4 ? (lane >> 1) * 32 + (((lane & 1) ^ (lane >> 4 & 1)) << 4) : (lane >> 2) * 64 + (((lane & 3) ^ ((2 * g + (lane >> 5)) & 3)) << 4);
+    __amdgpu_buffer_rsrc_t bufS = bufA;  // the expert's block scales
+    int w_q = 0, w_s = 0;                // the stream's K tile of weights, and its group of block scales, in LDS
+    (void)q_lane, (void)bufS, (void)w_q, (void)w_s, (void)s_voff;
     auto set_ptrs = [&]() __attribute__((always_inline)) {
         const RingTile &ti = nx;
         const int slot = p.b_slot ? __builtin_amdgcn_readfirstlane(uniform_load(p.b_slot + ti.expert)) : ti.expert;
         const int rows = __builtin_amdgcn_readfirstlane(ti.row_end - ti.row0);
         l_groups = rows > (8 + wave) * 16 ? 2 : rows > wave * 16 ? 1 : 0;
-        bufB = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(static_cast<const uint8_t *>(p.B) + (int64_t)slot * p.strideB * 2), 0, (int)kNowhere, 0x00020000);
+        bufB = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(static_cast<const uint8_t *>(p.B) + (int64_t)slot * p.strideB * (Q ? 1 : 2)), 0, (int)kNowhere, 0x00020000);
 #pragma unroll
         for (int g = 0; g < AG; ++g) {
             const int r = (g * NWAVE + wave) * 16 + ld_row;
@@ -221,22 +251,47 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
             if (p.a_rows) gr = p.a_rows[gr];
             a_voff[g] = live ? (uint32_t)gr * (uint32_t)p.lda * 2u + ld_chunk * 16 : kNowhere;
         }
+        if constexpr (Q) {
+            constexpr int ROWS = B4 ? 32 : 16;  // of a block; N is a multiple of it
+#pragma unroll
+            for (int g = 0; g < NBL; ++g) {
+                const int col = ti.n0 + (wave * NBL + g) * ROWS;
+                b_voff[g] = col < p.N ? (uint32_t)(col / ROWS) * (uint32_t)(KT * 1024) + q_lane[g] : kNowhere;
+            }
+            if constexpr (B4) {
+                const int col = ti.n0 + (wave & 3) * 64 + (lane >> 5) * 32;
+                bufS = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint8_t *>(p.b_blk_scale + (int64_t)ti.expert * p.stride_blk_scale), 0, (int)kNowhere, 0x00020000);
+                s_voff = col < p.N ? (uint32_t)(col >> 5) * (uint32_t)((KT + 7) >> 3) * 512u + (lane & 31) * 16 : kNowhere;
+            }
+            return;
+        }
 #pragma unroll
         for (int g = 0; g < BG; ++g)
             b_voff[g] = ti.n0 + b_col[g] < p.N ? (uint32_t)(ti.n0 + b_col[g]) * (uint32_t)p.ldb * 2u + ld_chunk * 16 : kNowhere;
     };
     auto issue = [&](__amdgpu_buffer_rsrc_t buf, uint32_t voff, int h, int lds_off) __attribute__((always_inline)) {
         int slot = w_slot + h;
-        if (slot >= NSLOT) slot -= NSLOT;
+        if (slot >= SLOTS) slot -= SLOTS;
         if (RAGGED && l_kt * BK + h * 32 + ld_chunk * 8 >= K) voff = kNowhere;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(buf, (lds_void *)(smem_raw + slot * SLOT_BYTES + lds_off), 16, voff, l_kt * 128 + h * 64, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(buf, (lds_void *)(smem_raw + slot * SLOT + lds_off), 16, voff, l_kt * 128 + h * 64, 0, 0);
     };
     auto issue_a = [&](int g, int h) __attribute__((always_inline)) { issue(bufA, a_voff[g], h, (g * NWAVE + wave) * 1024); };
     auto issue_b = [&](int g, int h) __attribute__((always_inline)) { issue(bufB, b_voff[g], h, BM * 64 + (wave * BG + g) * 1024); };
+    auto issue_q = [&](int g) __attribute__((always_inline)) {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(bufB, (lds_void *)(smem_raw + QB + w_q * QT + (wave * NBL + g) * 1024), 16, b_voff[g], l_kt * 1024, 0, 0);
+    };
+    auto issue_s = [&]() __attribute__((always_inline)) {  // the block scales of 8 K tiles, with the first of them
+        if ((l_kt & 7) == 0) {
+            if (wave < 4)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(bufS, (lds_void *)(smem_raw + QS + w_s * Q_SCALES + wave * 1024), 16, s_voff, l_kt * 64, 0, 0);
+            w_s = w_s + 1 == Q_SCALE_BUFS ? 0 : w_s + 1;
+        }
+    };
     auto next_k = [&]() __attribute__((always_inline)) {
         ++l_kt;
+        if constexpr (Q) w_q = w_q + 1 == Q_RING ? 0 : w_q + 1;
         w_slot += 2;
-        if (w_slot >= NSLOT) w_slot -= NSLOT;
+        if (w_slot >= SLOTS) w_slot -= SLOTS;
     };
     auto next_tile = [&]() __attribute__((always_inline)) {  // of the stream: the block's next one
         l_more = next_tile_pos();
@@ -244,7 +299,7 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
             l_kt = 0;
             set_ptrs();
         } else {
-            l_kt = KT - 2;  // past the end: re-read the last two K tiles into slots nobody reads
+            l_kt = KT - AHEAD;  // past the end: re-read the last K tiles into slots nobody reads
         }
         // lgkmcnt(0): no scalar load is in flight where this joins the K loop, whose waits then count LDS reads only
         __builtin_amdgcn_s_waitcnt(0xc07f);
@@ -254,6 +309,42 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
     // out with the first ones and the step's last LDS read is four MFMAs from the step's end
     bf16x8 a16[MI + 1], w16[2][NI];
     int r_slot = 0;  // slot of the step being multiplied
+    // Quantised weights: read as they are, widened behind the MFMAs of the step before theirs.
+    typename QuantRaw<BQ>::type raw[NI];
+    uint32_t sc[NI];                 // a K tile's two scale bytes
+    int r_q = 0, r_s = Q_SCALE_BUFS - 1, r_kt = 0;  // the K tile being multiplied
+    (void)raw, (void)sc, (void)r_q, (void)r_s, (void)r_kt;
+    const int q_row = wn * WTN + 8 * (row16 >> 2) + (row16 & 3);  // column of the lane's operand in block 0; in block ni 32 (ni / 2) + 4 (ni % 2) further
+    auto read_q = [&](int tile, int half) __attribute__((always_inline)) {
+        // chunk c of row r: e4m3 at c ^ ((r >> 3) & 3) of four, mxfp4 at c ^ ((r >> 3) & 1) of two
+        const int at = B4 ? q_row * 32 + ((half ^ (row16 >> 2 & 1)) << 4) + kq * 4 : q_row * 64 + (((2 * half + (kq >> 1)) ^ (row16 >> 2)) << 4) + (kq & 1) * 8;
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+            raw[ni] = *reinterpret_cast<const typename QuantRaw<BQ>::type *>(smem_raw + QB + tile * QT + at + (32 * (ni >> 1) + 4 * (ni & 1)) * (B4 ? 32 : 64));
+    };
+    auto read_scales = [&](int kt) __attribute__((always_inline)) {
+#pragma unroll
+        for (int ni = 0; ni < NI; ++ni)
+            sc[ni] = *reinterpret_cast<const u16_lds *>(smem_raw + QS + r_s * Q_SCALES + (q_row + 32 * (ni >> 1) + 4 * (ni & 1)) * 16 + ((kt & 7) << 1));
+    };
+    auto widen = [&](int set, int ni, int half) __attribute__((always_inline)) {
+        u32x4 w = {};
+        if constexpr (BQ == 8) {  // every e4m3 value is a bf16 value
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                w[2 * i] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(raw[ni][i], 1.f, false));
+                w[2 * i + 1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(raw[ni][i], 1.f, true));
+            }
+        } else if constexpr (B4) {
+            const float scale = __uint_as_float((half ? sc[ni] << 15 : sc[ni] << 23) & 0x7f800000u);  // 2^(byte - 127)
+            w[0] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(raw[ni], scale, 0));
+            w[1] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(raw[ni], scale, 1));
+            w[2] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(raw[ni], scale, 2));
+            w[3] = __builtin_bit_cast(uint32_t, __builtin_amdgcn_cvt_scalef32_pk_bf16_fp4(raw[ni], scale, 3));
+        }
+        asm volatile("" : "+v"(w));  // here, and not in front of the MFMA that reads it
+        w16[set][ni] = __builtin_bit_cast(bf16x8, w);
+    };
     // One step of a tile with M row blocks per wave; P: parity.
     auto step = [&](auto parity, auto blocks) __attribute__((always_inline)) {
         constexpr int P = decltype(parity)::value, M = decltype(blocks)::value;
@@ -266,23 +357,52 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
         for (int ni = 1; ni < NI; ++ni) mfma(std::false_type{}, 0, ni);
         __builtin_amdgcn_sched_barrier(0);
         asm volatile("" ::: "memory");
-        // lgkmcnt(0); odd steps: at most the loads of the even step before may be outstanding
+        // lgkmcnt(0); odd steps: at most the loads of the even step before may be outstanding, three K tiles ahead also those of
+        // the K tile before it
         static_assert(AG == BG, "either operand's loads are as many");
         if (P == 1)
-            __builtin_amdgcn_s_waitcnt(0x0070 | (2 * BG));
+            __builtin_amdgcn_s_waitcnt(0x0070 | (Q ? (BQ == 8 ? 6 + 2 : 5 + 3) : 2 * BG));
         else
             __builtin_amdgcn_s_waitcnt(0xc07f);
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
-        const int nslot = r_slot + 1 == NSLOT ? 0 : r_slot + 1;
+        const int nslot = r_slot + 1 == SLOTS ? 0 : r_slot + 1;
+        if constexpr (Q) {
+            if constexpr (P == 1) {
+                r_q = r_q + 1 == Q_RING ? 0 : r_q + 1;
+                ++r_kt;
+                if constexpr (B4) {
+                    if ((r_kt & 7) == 0 && r_kt < KT) r_s = r_s + 1 == Q_SCALE_BUFS ? 0 : r_s + 1;  // behind the last K tile the next tile's group is run_tile's
+                    read_scales(r_kt);
+                }
+            }
+            read_q(r_q, P ^ 1);
+        } else {
 #pragma unroll
-        for (int ni = 0; ni < NI; ++ni) w16[P ^ 1][ni] = read_b(nslot, ni);
+            for (int ni = 0; ni < NI; ++ni) w16[P ^ 1][ni] = read_b(nslot, ni);
+        }
         a16[0] = read_a(nslot, 0);
         a16[M - 1 + (P ^ 1)] = read_a(nslot, M - 1);
         __builtin_amdgcn_sched_barrier(0);
         // the step's loads, the j-th behind MFMA j * POST / 4 of those behind the barrier
         auto loads_at = [&](int at) __attribute__((always_inline)) {
+            if constexpr (Q) {
+                // one row group of the K tile three ahead; e4m3: the weights in the odd step (three K tiles of them, see above)
+                constexpr int LOADS = BQ == 8 ? (P ? 4 : 2) : P ? 2 : 3;
+                if constexpr (B4 && P == 0)
+                    if (at == 0) issue_s();
+#pragma unroll
+                for (int j = 0; j < LOADS; ++j)
+                    if (j * POST / LOADS == at) {
+                        if (j < 2) issue_a(P, j);
+                        else issue_q(j - 2);
+                    }
+#pragma unroll
+                for (int ni = 0; ni < NI; ++ni)
+                    if ((POST > 4 ? POST / 2 + ni * POST / 8 : POST - 1) == at) widen(P ^ 1, ni, P ^ 1);
+                return;
+            }
 #pragma unroll
             for (int j = 0; j < 4; ++j)
                 if (j * POST / 4 == at) {
@@ -319,6 +439,8 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
         constexpr int M = decltype(blocks)::value;
         const uint16_t *bias = static_cast<const uint16_t *>(p.bias);
         if (bias) bias += (int64_t)ti.expert * p.strideBias;
+        const float b_scale = BQ == 8 && p.b_scale ? __int_as_float(uniform_load(reinterpret_cast<const int32_t *>(p.b_scale) + ti.expert)) : 1.f;
+        (void)b_scale;
         const int col_base = ti.n0 + wn * WTN + 8 * kq;
         const uint32_t row_step = 32u * (uint32_t)p.ldc * 2u;  // bytes between two row blocks
         asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");  // see mfma_in_place
@@ -348,6 +470,10 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
 #pragma unroll
                     for (int q = 0; q < 4; ++q) {  // columns 2q, 2q + 1 of the 8: block 2pp + q / 2, registers 2 (q % 2), + 1
                         float v0 = acc[mi][2 * pp + (q >> 1)][2 * (q & 1)], v1 = acc[mi][2 * pp + (q >> 1)][2 * (q & 1) + 1];
+                        if constexpr (BQ == 8) {
+                            v0 *= b_scale;
+                            v1 *= b_scale;
+                        }
                         if constexpr (BIAS) {
                             v0 += __uint_as_float(bw[pp][q] << 16);
                             v1 += __uint_as_float(bw[pp][q] & 0xffff0000u);
@@ -381,12 +507,23 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
             for (int ni = 0; ni < NI; ++ni) asm volatile("" : "+v"(acc[mi][ni]));
         asm volatile("s_nop 7");
         // fragments of step 0, an even one (its slot has landed: the barrier before saw to it)
+        if constexpr (Q) {
+            r_kt = 0;
+            r_s = r_s + 1 == Q_SCALE_BUFS ? 0 : r_s + 1;  // a tile begins with a group of block scales of its own
+            if constexpr (B4) read_scales(0);
+            read_q(r_q, 0);
+        } else {
 #pragma unroll
-        for (int ni = 0; ni < NI; ++ni) w16[0][ni] = read_b(r_slot, ni);
+            for (int ni = 0; ni < NI; ++ni) w16[0][ni] = read_b(r_slot, ni);
+        }
 #pragma unroll
         for (int mi = 0; mi < M; ++mi) a16[mi] = read_a(r_slot, mi);
+        if constexpr (Q) {
+#pragma unroll
+            for (int ni = 0; ni < NI; ++ni) widen(0, ni, 0);
+        }
         for (int kt = 0; kt < KT; ++kt) {
-            if (kt == KT - 2) next_tile();  // the stream is two K tiles ahead
+            if (kt == KT - AHEAD) next_tile();
             step(std::integral_constant<int, 0>{}, blocks);
             step(std::integral_constant<int, 1>{}, blocks);
             next_k();
@@ -394,13 +531,19 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
         epilogue(ti, blocks);
     };
 
-    // prologue: the first two K tiles of the stream -> slots 0 .. 3
+    // prologue: the stream's first K tiles
     RingTile t = nx;
     set_ptrs();
 #pragma unroll 1
-    for (int rep = 0; rep < 2; ++rep) {
+    for (int rep = 0; rep < AHEAD; ++rep) {
+        if constexpr (Q) {
+            if constexpr (B4) issue_s();
 #pragma unroll
-        for (int j = 0; j < 4; ++j) issue_b(j >> 1, j & 1);
+            for (int g = 0; g < NBL; ++g) issue_q(g);
+        } else {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) issue_b(j >> 1, j & 1);
+        }
 #pragma unroll
         for (int j = 0; j < 4; ++j)
             issue_a(j >> 1, j & 1);
@@ -408,7 +551,7 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
     }
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_waitcnt(0x0f70 | (2 * AG + 2 * BG));  // the first K tile has landed: the second's loads are younger
+    __builtin_amdgcn_s_waitcnt(0x0f70 | (Q ? 2 * (4 + NBL) : 2 * AG + 2 * BG));  // the first K tile has landed: the others' loads are younger
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
@@ -431,11 +574,11 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no LDS write may outlive the block
 }
 
-template <bool RELU, bool RAGGED>
+template <bool RELU, bool RAGGED, int BQ = 0>
 static int launch_ring_t(const GemmParams &p, hipStream_t s)
 {
-    const size_t smem = (size_t)NSLOT * SLOT_BYTES;
-    auto kern = gemm_ring_kernel<RELU, RAGGED>;
+    const size_t smem = BQ == 0 ? NSLOT * SLOT_BYTES : Q_SLOTS * BM * 64 + q_ring(BQ) * q_tile_bytes(BQ) + (BQ == 4 ? Q_SCALE_BUFS * Q_SCALES : 0);
+    auto kern = gemm_ring_kernel<RELU, RAGGED, BQ>;
     static std::once_flag once;  // per instantiation, whichever host thread comes first
     static hipError_t setup_rc = hipSuccess;
     std::call_once(once, [&]() {
@@ -458,8 +601,22 @@ bool gemm_ring_addresses(int64_t n_rows, int N, int K)
 // ... and its load stream is two K tiles ahead.
 bool gemm_ring_ok(int64_t n_rows, int N, int K) { return N > BK && K > BK && gemm_ring_addresses(n_rows, N, K); }
 
-int launch_gemm_ring(const GemmParams &p, bool relu, hipStream_t s)
+// Quantised weights: the load stream is three K tiles ahead and never in the tile after next.
+static constexpr int kRingQuantK = 256;
+bool gemm_ring_quant_ok(int64_t n_rows, int N, int K)
 {
+    return N >= kRingQuantK && K >= kRingQuantK && N <= 1 << 22 && K <= 1 << 22 && gemm_ring_ok(n_rows, N, K);  // 16 K is added to kNowhere
+}
+
+// wbits: storage of the weights, 8 or 4, else bf16
+int launch_gemm_ring(const GemmParams &p, int wbits, bool relu, hipStream_t s)
+{
+    if (wbits && p.K < kRingQuantK) {
+        set_error("cut tiles over quantised weights need K (%d) of %d at least", p.K, kRingQuantK);
+        return MOE_ERR_UNSUPPORTED;
+    }
+    if (wbits == 8) return relu ? launch_ring_t<true, false, 8>(p, s) : launch_ring_t<false, false, 8>(p, s);
+    if (wbits == 4) return relu ? launch_ring_t<true, false, 4>(p, s) : launch_ring_t<false, false, 4>(p, s);
     if (p.K % BK != 0) return relu ? launch_ring_t<true, true>(p, s) : launch_ring_t<false, true>(p, s);
     return relu ? launch_ring_t<true, false>(p, s) : launch_ring_t<false, false>(p, s);
 }

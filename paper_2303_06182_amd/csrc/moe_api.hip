@@ -99,7 +99,7 @@ int gemm_bf16_variant_block_m(int variant);
 int launch_gemm_f32(const GemmParams &p, bool grouped, int variant, bool relu, int num_cus, hipStream_t s);
 int gemm_f32_variant(int64_t n_rows, int E, int N, int K, int num_cus);
 int gemm_f32_block_m(int variant);
-int gemm_bf16_variant_w8(int64_t n_rows, int E);
+int gemm_bf16_variant_w8(int64_t n_rows, int E, int N, int K);
 int gemm_bf16_variant_w4(int64_t n_rows, int E, int N, int K, int num_cus);
 int gemm_bf16_gate_split(int M, int N, int K, int num_cus);
 
@@ -323,7 +323,7 @@ static int64_t mxfp4_scale_bytes(int64_t rows, int64_t cols) { return (rows / 32
 static int quant_variant(const moe_handle_t *h, int wbits, int64_t n_rows)
 {
     const moe_config_t &c = h->cfg;
-    return wbits == 4 ? gemm_bf16_variant_w4(n_rows, c.E, c.F, c.D, h->num_cus) : gemm_bf16_variant_w8(n_rows, c.E);
+    return wbits == 4 ? gemm_bf16_variant_w4(n_rows, c.E, c.F, c.D, h->num_cus) : gemm_bf16_variant_w8(n_rows, c.E, c.F, c.D);
 }
 
 // Options of the grouped FFN beyond the plain call.
