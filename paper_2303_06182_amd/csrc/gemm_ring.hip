@@ -84,6 +84,8 @@ constexpr int q_tile_bytes(int bq) { return bq == 8 ? BN * 64 : bq == 4 ? BN * 3
 template <int BQ> struct QuantRaw { typedef u32x2 type; };   // a lane's 8 weights
 template <> struct QuantRaw<4> { typedef u32_lds type; };
 
+constexpr int kTurnedK = 2048, kTurnedRows = 512, kTurnedExperts = 256;  // see first_k
+
 struct RingTile {
     int row0, row_end, expert, n0;
 };
@@ -109,10 +111,11 @@ __device__ __forceinline__ int opaque(int v)
 
 }  // namespace
 
-template <bool RELU, bool RAGGED, int BQ = 0>
+template <bool RELU, bool RAGGED, int BQ = 0, bool TURNED = false>
 __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
 {
     constexpr bool Q = BQ != 0, B4 = BQ == 4;
+    static_assert(!TURNED || (!Q && !RAGGED), "turned: bf16 rows of whole K tiles");
     static_assert(!Q || !RAGGED, "8- and 4-bit weights come in whole K tiles");
     constexpr int SLOT = Q ? BM * 64 : SLOT_BYTES;
     constexpr int SLOTS = Q ? Q_SLOTS : NSLOT, AHEAD = Q ? Q_AHEAD : 2;
@@ -193,6 +196,25 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
         pos_next = after;
         return true;
     };
+    // The K tile a tile begins with.  Weight rows of a multiple of 4 KB have the same K tile in the same few memory channels, and the
+    // blocks, which walk K in step, ask those all at once: the tiles of different experts and columns begin at different places and
+    // go round K.  By the expert (Fibonacci hashing: neighbours lie far apart) over the whole of K, and a K tile further with every
+    // column tile, so that those find their common rows in the L2 still.  The row tiles of an expert, which share weights, agree.
+    // FFN in us, from 0 / turned: 64 experts 1024 -> 4096, 32 even rows 239 / 211, 128 rows 281 / 254, 256 rows 340 / 313, skewed (0.5) 373 / 362;
+    // 16 experts 2048 -> 8192, 128 rows 304 / 257; 128 experts, 32 rows 1498 / 1450, 128 rows 1684 / 1648, skewed 1878 / 1823; 128 experts 512 ->
+    // 2048, 128 rows 174 / 159; 12 experts 4096 -> 14336, 256 skewed rows 968 / 939.  Other ways to turn (by a hash of expert and column, two or five
+    // K tiles a column, the expert alone) are behind by up to 9 %.  Rows of other lengths spread by themselves (1536, 3072, 4000, 6144:
+    // within 1 % either way), as do the blocks of quantised weights.  From 512 rows per expert on the weights' time hides behind the
+    // MFMAs and what is left is the rows' lost sharing (128 experts 2048 -> 8192: 384 rows 3005 / 3009, skewed 3123 / 3098, 768 rows 5255 / 5250,
+    // skewed 5574 / 5613, 1024 skewed 7288 / 7317).  With 256 experts and more the blocks' tiles lie far enough
+    // apart (1024 -> 4096, 16 even rows: 192 experts 586 / 557, 256 experts 733 / 733, 400 experts 1210 / 1184, 512 experts 1496 / 1477, skewed 1506 /
+    // 1497; 256 experts 2048 -> 2048 712 / 738; 512 experts 512 -> 2048 409 / 416).  An instance of its own: with the place along K in all of them
+    // full tiles are 0.7 % slower.
+    auto first_k = [&]() __attribute__((always_inline)) -> int {
+        if constexpr (!TURNED) return 0;
+        const uint32_t by_expert = ((uint32_t)nx.expert * 2654435761u >> 16) * (uint32_t)KT >> 16;
+        return (int)((by_expert + (uint32_t)nx.n0 / BN) % (uint32_t)KT);
+    };
     if (p.c_zero_row >= 0 && blockIdx.x == 0) {
         // one all-zero row behind the output rows, for the GEMM that reads C as its A (N is a multiple of 8)
         uint16_t *z = static_cast<uint16_t *>(p.C) + (int64_t)p.c_zero_row * p.ldc;
@@ -211,7 +233,7 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
     auto read_b = [&](int slot, int block) __attribute__((always_inline)) { return *reinterpret_cast<const bf16x8 *>(fragB + slot * SLOT_BYTES + block * 1024); };
 
     // ---- load stream
-    int l_kt = 0;
+    int l_kt = 0, l_k = 0;  // the stream's K tile, and where along K it lies
     bool l_more = true;
     int l_groups = 0;  // row groups of the stream's tile that this wave loads
     int w_slot = 0;    // slot of the first half of the K tile the stream is at
@@ -273,7 +295,7 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
         int slot = w_slot + h;
         if (slot >= SLOTS) slot -= SLOTS;
         if (RAGGED && l_kt * BK + h * 32 + ld_chunk * 8 >= K) voff = kNowhere;
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(buf, (lds_void *)(smem_raw + slot * SLOT + lds_off), 16, voff, l_kt * 128 + h * 64, 0, 0);
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(buf, (lds_void *)(smem_raw + slot * SLOT + lds_off), 16, voff, (TURNED ? l_k : l_kt) * 128 + h * 64, 0, 0);
     };
     auto issue_a = [&](int g, int h) __attribute__((always_inline)) { issue(bufA, a_voff[g], h, (g * NWAVE + wave) * 1024); };
     auto issue_b = [&](int g, int h) __attribute__((always_inline)) { issue(bufB, b_voff[g], h, BM * 64 + (wave * BG + g) * 1024); };
@@ -289,6 +311,7 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
     };
     auto next_k = [&]() __attribute__((always_inline)) {
         ++l_kt;
+        if constexpr (TURNED) l_k = l_k + 1 == KT ? 0 : l_k + 1;
         if constexpr (Q) w_q = w_q + 1 == Q_RING ? 0 : w_q + 1;
         w_slot += 2;
         if (w_slot >= SLOTS) w_slot -= SLOTS;
@@ -297,9 +320,10 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
         l_more = next_tile_pos();
         if (l_more) {
             l_kt = 0;
+            l_k = first_k();
             set_ptrs();
         } else {
-            l_kt = KT - AHEAD;  // past the end: re-read the last K tiles into slots nobody reads
+            l_kt = KT - AHEAD;  // past the end: K tiles again, into slots nobody reads
         }
         // lgkmcnt(0): no scalar load is in flight where this joins the K loop, whose waits then count LDS reads only
         __builtin_amdgcn_s_waitcnt(0xc07f);
@@ -533,6 +557,7 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
 
     // prologue: the stream's first K tiles
     RingTile t = nx;
+    l_k = first_k();
     set_ptrs();
 #pragma unroll 1
     for (int rep = 0; rep < AHEAD; ++rep) {
@@ -574,11 +599,11 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no LDS write may outlive the block
 }
 
-template <bool RELU, bool RAGGED, int BQ = 0>
+template <bool RELU, bool RAGGED, int BQ = 0, bool TURNED = false>
 static int launch_ring_t(const GemmParams &p, hipStream_t s)
 {
     const size_t smem = BQ == 0 ? NSLOT * SLOT_BYTES : Q_SLOTS * BM * 64 + q_ring(BQ) * q_tile_bytes(BQ) + (BQ == 4 ? Q_SCALE_BUFS * Q_SCALES : 0);
-    auto kern = gemm_ring_kernel<RELU, RAGGED, BQ>;
+    auto kern = gemm_ring_kernel<RELU, RAGGED, BQ, TURNED>;
     static std::once_flag once;  // per instantiation, whichever host thread comes first
     static hipError_t setup_rc = hipSuccess;
     std::call_once(once, [&]() {
@@ -618,6 +643,8 @@ int launch_gemm_ring(const GemmParams &p, int wbits, bool relu, hipStream_t s)
     if (wbits == 8) return relu ? launch_ring_t<true, false, 8>(p, s) : launch_ring_t<false, false, 8>(p, s);
     if (wbits == 4) return relu ? launch_ring_t<true, false, 4>(p, s) : launch_ring_t<false, false, 4>(p, s);
     if (p.K % BK != 0) return relu ? launch_ring_t<true, true>(p, s) : launch_ring_t<false, true>(p, s);
+    if (p.K % kTurnedK == 0 && p.M < (int64_t)kTurnedRows * p.num_experts && p.num_experts < kTurnedExperts)
+        return relu ? launch_ring_t<true, false, 0, true>(p, s) : launch_ring_t<false, false, 0, true>(p, s);
     return relu ? launch_ring_t<true, false>(p, s) : launch_ring_t<false, false>(p, s);
 }
 

@@ -122,7 +122,7 @@ struct GemmParams {
     const int32_t *ring_list;    // the ring kernel (gemm_ring.hip): its schedule, see kRingMap
     const int32_t *ring_words;
     int ring_cap_shift;          // 0 for the layer's first GEMM, 8 for the second
-    int num_experts;             // host only: E
+    int num_experts;             // grouped mode: E
     // tail splitting of a grouped GEMM over 256x256 tiles (0 = off): 1 = this launch runs the whole
     // rounds of 256x256 tiles, 2 = this launch runs the tiles of the last, partly filled round as
     // smaller sub-tiles; main_slots = grid size of the launch with tail_mode 1 (both need it)
