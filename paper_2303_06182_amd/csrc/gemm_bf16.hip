@@ -94,6 +94,8 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
     constexpr int BTILE = BN * BROW;                       // one B stage in 16-bit units
     static_assert(!B8 || (BN * 4) % THREADS == 0, "8-bit B tile rows must split evenly over threads");
     static_assert(!B4 || (BN * 2) % THREADS == 0, "4-bit B tile rows must split evenly over threads");
+    // bf16 experts: the K loop may go round K from another place (turned_k)
+    constexpr bool TURNED = GROUPED && KFULL && BQ == 0 && BM < 256;
     static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile must be made of 32x32 blocks");
     static_assert((BM * 8) % THREADS == 0 && (BN * 8) % THREADS == 0, "tile rows must split evenly over threads");
 
@@ -510,8 +512,10 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
         // the accumulators of the largest tile.
         const uint16_t *a_base, *b_base;
         int a_off[A_IT], b_off[B_IT];
+        int k_turn = 0;  // the K tile the loads' tile begins with
         int b_rows = 0;  // NT_SOLE: rows of the expert the loads are at
         auto set_ptrs = [&](const TileInfo &ti) {
+            if constexpr (TURNED) k_turn = p.turned ? __builtin_amdgcn_readfirstlane(turned_k(ti.expert, ti.n0, KT)) : 0;
             if constexpr (NT == NT_SOLE) b_rows = __builtin_amdgcn_readfirstlane(ti.row_end - ti.row_begin);
             // weights of expert e sit in slot b_slot[e] of the weight array when experts are buffered
             const uint16_t *Bg = Bg0 + (int64_t)((GROUPED && p.b_slot) ? uniform_load(p.b_slot + ti.expert) : ti.expert) * p.strideB;
@@ -584,7 +588,13 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
                 }
             }
         };
-        auto issue = [&](int kt, int buf) {
+        auto turn = [&](int kt) {
+            if constexpr (!TURNED) return kt;
+            kt += k_turn;
+            return kt >= KT ? kt - KT : kt;
+        };
+        auto issue = [&](int tile, int buf) {
+            const int kt = turn(tile);
 #pragma unroll
             for (int i = 0; i < A_IT; ++i)
                 __builtin_amdgcn_global_load_lds((const glb_void *)(a_base + (a_off[i] + kt * BK)),
@@ -647,7 +657,7 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
                 return (lane & 7) ^ ((g * 4 + (lane >> 4)) & 7);
             };
             auto gload = [&](int i) -> uint4 {
-                int ko = l_kt * BK;
+                int ko = turn(l_kt) * BK;
                 if (!KFULL && l_kt == KT - 1 && chunk_of(i) >= tail_chunks) ko -= chunk_of(i) * 8;
                 const uint16_t *g = i < A_IT ? a_base + (a_off[i] + ko) : b_base + (b_off[i - A_IT] + ko);
                 return *reinterpret_cast<const uint4 *>(g);
@@ -916,6 +926,12 @@ static int launch_k(const GemmParams &p_in, int num_cus, hipStream_t s, int *mai
     if (m_tiles <= 0 || n_tiles <= 0) return MOE_OK;
     const size_t smem = (size_t)(STAGES == REG_STAGED ? 2 : STAGES) * (BM + (BQ == 8 ? BN / 2 : BQ == 4 ? BN / 4 : BN)) * BK * sizeof(uint16_t) +
                         (BQ == 4 ? 2 * BN * 16 : 0);  // 4-bit weights: two buffers of block scales
+    // FFN in us, K loops from 0 / turned, 32x128 tiles: 128 experts 2048 -> 8192, 2 rows per expert 1357 / 1282, skewed (0.8) 974 / 946; 64
+    // experts 1024 -> 4096, 4 rows 200 / 162, half idle 112 / 103; 16 experts 2048 -> 8192, 8 rows 233 / 196; 256 experts 512 -> 2048, 16 rows
+    // 235 / 203; 64x128: 64 experts 1024 -> 4096, 40 rows 234 / 203; 128x128: 16 experts 2048 -> 8192, 40 rows 266 / 202, 100 rows 276 / 221, 8
+    // experts, 192 rows 195 / 178; from some 256 rows on either way (8 experts, 400 rows 302 / 306, skewed 309 / 304).  With 512 experts 1024 -> 4096
+    // 1385 / 1381, 512 -> 2048 331 / 334.
+    p.turned = GROUPED && p.K % kTurnedK == 0 && p.M < 256ll * p.num_experts && p.num_experts < 384;
     auto kern = gemm_bf16_kernel<BM, BN, WM, WN, OUT_F32, RELU, GROUPED, KFULL, MINB, STAGES, NT, BQ>;
     // per instantiation, once, whichever host thread comes first: the LDS size attribute and the occupancy
     static std::once_flag once;

@@ -84,7 +84,7 @@ constexpr int q_tile_bytes(int bq) { return bq == 8 ? BN * 64 : bq == 4 ? BN * 3
 template <int BQ> struct QuantRaw { typedef u32x2 type; };   // a lane's 8 weights
 template <> struct QuantRaw<4> { typedef u32_lds type; };
 
-constexpr int kTurnedK = 2048, kTurnedRows = 512, kTurnedExperts = 256;  // see first_k
+constexpr int kTurnedRows = 512, kTurnedExperts = 256;  // see first_k
 
 struct RingTile {
     int row0, row_end, expert, n0;
@@ -196,10 +196,7 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
         pos_next = after;
         return true;
     };
-    // The K tile a tile begins with.  Weight rows of a multiple of 4 KB have the same K tile in the same few memory channels, and the
-    // blocks, which walk K in step, ask those all at once: the tiles of different experts and columns begin at different places and
-    // go round K.  By the expert (Fibonacci hashing: neighbours lie far apart) over the whole of K, and a K tile further with every
-    // column tile, so that those find their common rows in the L2 still.  The row tiles of an expert, which share weights, agree.
+    // The K tile a tile begins with: see turned_k.
     // FFN in us, from 0 / turned: 64 experts 1024 -> 4096, 32 even rows 239 / 211, 128 rows 281 / 254, 256 rows 340 / 313, skewed (0.5) 373 / 362;
     // 16 experts 2048 -> 8192, 128 rows 304 / 257; 128 experts, 32 rows 1498 / 1450, 128 rows 1684 / 1648, skewed 1878 / 1823; 128 experts 512 ->
     // 2048, 128 rows 174 / 159; 12 experts 4096 -> 14336, 256 skewed rows 968 / 939.  Other ways to turn (by a hash of expert and column, two or five
@@ -212,8 +209,7 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
     // full tiles are 0.7 % slower.
     auto first_k = [&]() __attribute__((always_inline)) -> int {
         if constexpr (!TURNED) return 0;
-        const uint32_t by_expert = ((uint32_t)nx.expert * 2654435761u >> 16) * (uint32_t)KT >> 16;
-        return (int)((by_expert + (uint32_t)nx.n0 / BN) % (uint32_t)KT);
+        return turned_k(nx.expert, nx.n0, KT);
     };
     if (p.c_zero_row >= 0 && blockIdx.x == 0) {
         // one all-zero row behind the output rows, for the GEMM that reads C as its A (N is a multiple of 8)

@@ -49,6 +49,7 @@ __global__ __launch_bounds__(W * 64, W == 8 ? 4 : 3) void gemm_stream_kernel(Gem
     constexpr int NB = BQ == 0 ? 2 : 1;        // 16-byte weight loads per step and 16 columns
     constexpr int BSTEP = B4 ? 2048 : B8 ? 1024 : 128;  // bytes a step advances in the weights
     constexpr int COLS = 16 * NC;
+    constexpr bool TURNED = BQ == 0 && !RAGGED;
     constexpr int LROW = COLS + 4;             // floats per LDS row of partial sums
     constexpr int NBUF = NC > 2 ? 1 : 2;       // two tiles' worth saves one of the two barriers per tile
     constexpr bool SC4 = B4 && (DP1 == 4 || NC == 4);       // block scales of four steps in one 16-byte load (a wave's steps are a multiple of 4)
@@ -80,6 +81,10 @@ __global__ __launch_bounds__(W * 64, W == 8 ? 4 : 3) void gemm_stream_kernel(Gem
         uniform_load2(p.tile_expert + mt, p.tile_row + mt, expert, row0);
         const int row_end = min(uniform_load(p.offsets + expert + 1), row0 + 32);
         const int slot = p.b_slot ? uniform_load(p.b_slot + expert) : expert;
+        int turn = 0;  // the step of its part of K that a wave begins with
+        if constexpr (TURNED)
+            if (p.turned) turn = (int)((uint32_t)(expert * 5 + n0 / COLS) % (uint32_t)n_steps);
+        (void)turn;
 
         // weights: a base that is the same for every lane (expert, columns, the wave's part of K) + a lane offset
         const uint8_t *bbase;
@@ -149,6 +154,10 @@ __global__ __launch_bounds__(W * 64, W == 8 ? 4 : 3) void gemm_stream_kernel(Gem
                     }
                     __builtin_amdgcn_sched_barrier(0);
                     return;
+                }
+                if constexpr (TURNED) {
+                    s += turn;
+                    if (s >= n_steps) s -= n_steps;
                 }
                 const uint8_t *as = scalar_base(abase + s * (KSTEP * 2));
 #pragma unroll
@@ -330,8 +339,9 @@ __global__ __launch_bounds__(W * 64, W == 8 ? 4 : 3) void gemm_stream_kernel(Gem
 }
 
 template <int BQ, bool RELU, int NC, int W, int DP1, int DP2, bool RAGGED = false>
-static int launch_stream_t(const GemmParams &p, int num_cus, hipStream_t s)
+static int launch_stream_t(const GemmParams &p_in, int num_cus, hipStream_t s)
 {
+    GemmParams p = p_in;
     auto kern = gemm_stream_kernel<BQ, RELU, NC, W, DP1, DP2, RAGGED>;
     static std::once_flag once;
     static int blocks_per_cu = 1;
@@ -346,6 +356,9 @@ static int launch_stream_t(const GemmParams &p, int num_cus, hipStream_t s)
     int64_t grid = (int64_t)num_cus * blocks_per_cu;
     if (grid > tiles) grid = tiles;
     grid = align_up(grid, 8);
+    // FFN in us, a wave's part of K from its beginning / turned: 16 experts 2048 -> 8192, 4 active 57 / 52, 8 active 90 / 86, 16 active 192 / 182; 64
+    // experts 1024 -> 4096 50 / 49; with rows of 4 KB, which the waves cut in parts of 1 KB, either way (128 experts 512 -> 2048, 8 active 21 / 21)
+    p.turned = p.K % (2 * kTurnedK) == 0;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(W * 64), 0, s, p);
     MOE_LAUNCH_CHECK("gemm_stream_kernel");
     return MOE_OK;

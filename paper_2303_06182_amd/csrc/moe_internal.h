@@ -134,6 +134,7 @@ struct GemmParams {
     // c_zero_row >= 0: the launch also writes zeros to that row of C (the next GEMM's a_zero_row).
     int a_zero_row;
     int c_zero_row;
+    bool turned;                 // set by the launch: the K loops of a bf16 grouped GEMM go round K (turned_k)
     const char *name;            // host only: label of the launch for the event profiler (may be NULL)
 };
 
