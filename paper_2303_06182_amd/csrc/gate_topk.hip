@@ -267,6 +267,216 @@ __global__ __launch_bounds__(WAVES * 64) void gate_topk_kernel(GateTopkParams p)
     }
 }
 
+// The same for batches with at most one short tile (32, 64 or 128 rows) per CU, whose time is the latency of the K loop and of the
+// selection.  With one wave for 32 rows and all columns a K tile takes 1 us: 20 loads and 16 MFMAs of a wave, one after the other.
+// Here the column blocks have waves of their own (RG x NI waves of one 32x32 block), which share a K tile's loads; a wave reads a K
+// tile's fragments at once.  A logit is the same sum in the same order.  Then the logits cross LDS and G lanes share a token.
+// us, a wave per 32 rows / this, 2048 dimensions, 128 experts: 600 tokens 29.4 / 12.7, 4096 30.1 / 13.5, 9001 32.7 / 20.9, 16384 29.8 / 24.0,
+// 20000 40.8 / 31.1; 1024 dimensions, 64 experts: 8192 tokens 13.7 / 9.0; 96 experts, 5000 tokens 17.0 / 9.9; 512 dimensions, 64 experts, 16000
+// tokens 10.5 / 8.4; 2048 dimensions, 16 experts, 8000 tokens 14.0 / 12.0.
+template <int RG, int NI, int STAGES>
+__global__ __launch_bounds__(RG *NI * 64) void gate_topk_wide_kernel(GateTopkParams p)
+{
+    constexpr int W = RG * NI, THREADS = W * 64, BM = 32 * RG, BK = 64;
+    constexpr int STAGE = (RG + NI) * 32 * BK;            // one stage in bf16: the rows, then the gate weights
+    constexpr int LOADS = 4 * (RG + NI), LPS = (LOADS + W - 1) / W;  // of 1 KB, and of a wave (the last one again where they do not come out)
+    constexpr int WAITN = (STAGES - 2) * LPS;
+    static_assert(STAGES >= 3 && WAITN < 64, "vmcnt is a 6-bit counter");
+    constexpr int G = NI == 1 ? 2 : NI == 4 ? 8 : 4, V = NI * 32 / G;  // lanes of a token, columns of a lane
+    constexpr int LD = NI * 32 + 4;                                    // floats per row of logits in LDS
+    static_assert(BM * LD * 4 <= STAGES * STAGE * 2, "the logits fit where the stages were");
+
+    extern __shared__ __attribute__((aligned(1024))) uint8_t gt_smem[];
+    uint16_t *stages = reinterpret_cast<uint16_t *>(gt_smem);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), rg = wave / NI, ni = wave % NI;
+    const int row0 = blockIdx.x * BM;
+    const int K = p.K, T = p.T, E = p.E, KT = K / BK;
+
+    // load i of the wave fills 8 rows of 128 bytes; layout, swizzle and the rows past the end as in the kernel above
+    const uint16_t *src[LPS];
+    int dst[LPS];
+#pragma unroll
+    for (int i = 0; i < LPS; ++i) {
+        const int ld = min(wave + i * W, LOADS - 1), r = ld * 8 + (lane >> 3);
+        const int kc = (lane & 7) ^ ((r >> 1) & 7);
+        dst[i] = ld * 8 * BK;
+        src[i] = ld < 4 * RG ? p.x + (int64_t)min(row0 + r, T - 1) * K + kc * 8 : p.wg + (int64_t)min(r - BM, E - 1) * K + kc * 8;
+    }
+    auto issue = [&](int kt, int stage) {
+#pragma unroll
+        for (int i = 0; i < LPS; ++i)
+            __builtin_amdgcn_global_load_lds((const gt_glb_void *)(src[i] + kt * BK), (gt_lds_void *)(stages + stage * STAGE + dst[i]), 16, 0, 0);
+    };
+    auto block_barrier = [&]() {
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    gt_f32x16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    const int frag_row = lane & 31, half = lane >> 5, swz = (lane >> 1) & 7;
+#pragma unroll 1
+    for (int s = 0; s < STAGES - 1; ++s) issue(min(s, KT - 1), s);
+    int cur = 0, nxt = STAGES - 1;
+    for (int kt = 0; kt < KT; ++kt) {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt((WAITN & 15) | ((WAITN >> 4) << 14) | (7 << 4) | (15 << 8));
+        asm volatile("" ::: "memory");
+        block_barrier();  // stage `cur` is complete for every wave; everybody is done reading stage `nxt`
+        const uint16_t *cA = stages + cur * STAGE + (rg * 32 + frag_row) * BK, *cB = stages + cur * STAGE + (BM + ni * 32 + frag_row) * BK;
+        gt_bf16x8 af[BK / 16], bf[BK / 16];  // all reads first: one LDS latency per K tile
+#pragma unroll
+        for (int ks = 0; ks < BK / 16; ++ks) {
+            const int chunkpos = ((ks * 2 + half) ^ swz) << 3;
+            bf[ks] = *reinterpret_cast<const gt_bf16x8 *>(cB + chunkpos);
+            af[ks] = *reinterpret_cast<const gt_bf16x8 *>(cA + chunkpos);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        issue(min(kt + STAGES - 1, KT - 1), nxt);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int ks = 0; ks < BK / 16; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf[ks], af[ks], acc, 0, 0, 0);
+        cur = (cur + 1 == STAGES) ? 0 : cur + 1;
+        nxt = (nxt + 1 == STAGES) ? 0 : nxt + 1;
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // no load may still be writing LDS
+    __syncthreads();
+
+    // ---- the logits: lane -> row frag_row, columns 8 g + 4 half + i of the wave's block
+    float *logits = reinterpret_cast<float *>(gt_smem);
+#pragma unroll
+    for (int g = 0; g < 4; ++g)
+        *reinterpret_cast<float4 *>(logits + (rg * 32 + frag_row) * LD + ni * 32 + 8 * g + 4 * half) =
+            make_float4(acc[4 * g], acc[4 * g + 1], acc[4 * g + 2], acc[4 * g + 3]);
+    __syncthreads();
+    const int sub = tid % G, token = tid / G;  // of the tile
+    const bool mine = token < BM;              // whole waves
+    const int row = row0 + token;
+    const bool live = mine && row < T;
+    auto col_of = [&](int s) { return (s >> 2) * (4 * G) + 4 * sub + (s & 3); };  // ascending with s
+    int sel_e[MOE_MAX_K];
+    if (mine) {
+        float v[V];
+#pragma unroll
+        for (int q = 0; q < V / 4; ++q) {
+            const float4 f = *reinterpret_cast<const float4 *>(logits + token * LD + col_of(4 * q));
+            v[4 * q] = f.x, v[4 * q + 1] = f.y, v[4 * q + 2] = f.z, v[4 * q + 3] = f.w;
+        }
+        if (p.bias) {
+            float off[V];
+#pragma unroll
+            for (int s = 0; s < V; ++s) off[s] = p.bias[min(col_of(s), E - 1)];
+#pragma unroll
+            for (int s = 0; s < V; ++s) v[s] += off[s];
+        }
+        if (p.logits && live) {
+            float *out = p.logits + (int64_t)row * E;
+#pragma unroll
+            for (int q = 0; q < V / 4; ++q) {
+                const int c = col_of(4 * q);
+                if ((E & 3) == 0) {
+                    if (c < E) *reinterpret_cast<float4 *>(out + c) = make_float4(v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        if (c + i < E) out[c + i] = v[4 * q + i];
+                }
+            }
+        }
+        const float NEG_INF = -__builtin_huge_valf();
+        constexpr int NONE = 0x7fffffff;
+        uint32_t taken = 0;  // bit s: slot s already selected, or past the last expert
+#pragma unroll
+        for (int s = 0; s < V; ++s)
+            if (col_of(s) >= E) taken |= 1u << s;
+        float sel_v[MOE_MAX_K];
+#pragma unroll
+        for (int j = 0; j < MOE_MAX_K; ++j) {
+            sel_v[j] = NEG_INF;
+            sel_e[j] = 0;
+            if (j >= p.k) continue;  // uniform over the grid
+            float bv = NEG_INF;
+            int be = NONE;
+#pragma unroll
+            for (int s = 0; s < V; ++s)
+                if (!((taken >> s) & 1u) && (be == NONE || v[s] > bv)) {  // strict: the first (lowest) column keeps a tie
+                    bv = v[s];
+                    be = col_of(s);
+                }
+#pragma unroll
+            for (int off = G / 2; off >= 1; off >>= 1) {
+                const float ov = __shfl_xor(bv, off, 64);
+                const int oe = __shfl_xor(be, off, 64);
+                if (oe != NONE && (be == NONE || ov > bv || (ov == bv && oe < be))) {
+                    bv = ov;
+                    be = oe;
+                }
+            }
+            // the lanes agree for finite inputs; the first one's view keeps the bookkeeping consistent whatever the inputs are
+            bv = __shfl(bv, lane - sub, 64);
+            be = __shfl(be, lane - sub, 64);
+            sel_v[j] = bv;
+            sel_e[j] = be == NONE ? 0 : be;
+            if (be != NONE && (be >> 2) % G == sub) taken |= 1u << (be / (4 * G) * 4 + (be & 3));
+        }
+        const float m = sel_v[0];
+        float denom = 0.f;
+        if (p.renorm) {
+#pragma unroll
+            for (int j = 0; j < MOE_MAX_K; ++j)
+                if (j < p.k) denom += expf(sel_v[j] - m);
+        } else {
+#pragma unroll
+            for (int s = 0; s < V; ++s)
+                if (col_of(s) < E) denom += expf(v[s] - m);
+#pragma unroll
+            for (int off = G / 2; off >= 1; off >>= 1) denom += __shfl_xor(denom, off, 64);
+        }
+        if (live && sub == 0) {
+#pragma unroll
+            for (int j = 0; j < MOE_MAX_K; ++j) {
+                if (j < p.k) {
+                    p.idx[(int64_t)row * p.k + j] = sel_e[j];
+                    p.w[(int64_t)row * p.k + j] = expf(sel_v[j] - m) / denom;
+                }
+            }
+        }
+    }
+    if (p.hist) {
+        int *hist = reinterpret_cast<int *>(gt_smem) + BM * LD;  // behind the logits, which a wave may still read
+        for (int e = tid; e < E; e += THREADS) hist[e] = 0;
+        __syncthreads();
+        if (live && sub == 0) {
+#pragma unroll
+            for (int j = 0; j < MOE_MAX_K; ++j)
+                if (j < p.k) atomicAdd(&hist[sel_e[j]], 1);
+        }
+        __syncthreads();
+        for (int e = tid; e < E; e += THREADS) p.hist[(int64_t)blockIdx.x * E + e] = hist[e];
+    }
+}
+
+template <int RG, int NI, int STAGES>
+static int launch_gate_topk_wide(const GateTopkParams &p, hipStream_t s)
+{
+    const size_t smem = (size_t)STAGES * (RG + NI) * 32 * 64 * sizeof(uint16_t);
+    static_assert((size_t)STAGES * (RG + NI) * 4096 >= 32u * RG * (NI * 32 + 4) * 4 + 128 * 4, "logits and histogram reuse the stages");
+    auto kern = gate_topk_wide_kernel<RG, NI, STAGES>;
+    static std::once_flag once;  // per instantiation
+    static hipError_t attr_rc = hipSuccess;
+    std::call_once(once, [&]() {
+        attr_rc = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+    });
+    MOE_HIP_CHECK(attr_rc);
+    ProfScope ps("gate_topk", s);
+    hipLaunchKernelGGL(kern, dim3((unsigned)ceil_div(p.T, 32 * RG)), dim3(RG * NI * 64), smem, s, p);
+    MOE_LAUNCH_CHECK("gate_topk_wide_kernel");
+    return MOE_OK;
+}
+
 template <int WAVES, int NI, int STAGES>
 static int launch_gate_topk_t(const GateTopkParams &p, hipStream_t s)
 {
@@ -291,17 +501,25 @@ bool gate_topk_fused_ok(int dtype, int T, int E, int K)
     return dtype == MOE_DTYPE_BF16 && T > 0 && E >= 1 && E <= 128 && K >= 64 && K % 64 == 0;
 }
 
+// Groups of 32 rows in a tile of gate_topk_wide_kernel's, 0: not for this kernel
+static int gate_topk_wide(int T, int E, int num_cus)
+{
+    // 128 rows: 20000 tokens, 2048 dimensions, 128 experts 40.8 / 31.1 us, 32768 tokens 38.1 / 39.5; 25000 tokens, 16 experts 14.0 / 13.8
+    return T <= 32 * num_cus ? 1 : T <= 64 * num_cus ? 2 : T <= 96 * num_cus && E > 64 ? 4 : 0;
+}
+
 // Tokens per tile (= tokens per histogram row) the fused kernel uses for T tokens and E experts: the tallest
 // of 256, 128, 64, 32 rows that still gives every CU a tile and whose wave count divides the weight tile's
 // load instructions.
 int gate_topk_tile_tokens(int T, int E, int num_cus)
 {
     const int ni = ceil_div(E, 32);
+    if (gate_topk_wide(T, E, num_cus)) return 32 * gate_topk_wide(T, E, num_cus);
     for (int waves = 8; waves > 1; waves >>= 1) {
         if ((ni * 4) % waves != 0) continue;
         if (ceil_div(T, 32 * waves) >= num_cus) return 32 * waves;
     }
-    return 32;
+    return 64;
 }
 
 int launch_gate_topk(const void *x, const void *wg, const float *gate_bias, int T, int E, int K, int k, int renorm,
@@ -322,6 +540,22 @@ int launch_gate_topk(const void *x, const void *wg, const float *gate_bias, int 
     p.renorm = renorm;
     const int ni = ceil_div(E, 32);
     const int waves = gate_topk_tile_tokens(T, E, num_cus) / 32;
+    // stages: more of them make the start longer and the loop no shorter (4096 tokens above, 4 / 8: 13.5 / 14.2 us; 64 rows, 3 / 6: 22.1 / 20.9)
+    if (const int rg = gate_topk_wide(T, E, num_cus)) {
+        switch (rg * 10 + ni) {
+        case 11: return launch_gate_topk_wide<1, 1, 9>(p, s);
+        case 12: return launch_gate_topk_wide<1, 2, 6>(p, s);
+        case 13: return launch_gate_topk_wide<1, 3, 5>(p, s);
+        case 14: return launch_gate_topk_wide<1, 4, 4>(p, s);
+        case 21: return launch_gate_topk_wide<2, 1, 6>(p, s);
+        case 22: return launch_gate_topk_wide<2, 2, 5>(p, s);
+        case 23: return launch_gate_topk_wide<2, 3, 5>(p, s);
+        case 24: return launch_gate_topk_wide<2, 4, 6>(p, s);
+        case 43: return launch_gate_topk_wide<4, 3, 5>(p, s);
+        case 44: return launch_gate_topk_wide<4, 4, 5>(p, s);
+        default: break;
+        }
+    }
 #define MOE_GT(W, N, S) return launch_gate_topk_t<W, N, S>(p, s)
     switch (waves * 10 + ni) {
     case 84: MOE_GT(8, 4, 3);
@@ -334,10 +568,6 @@ int launch_gate_topk(const void *x, const void *wg, const float *gate_bias, int 
     case 23: MOE_GT(2, 3, 3);
     case 22: MOE_GT(2, 2, 3);
     case 21: MOE_GT(2, 1, 3);
-    case 14: MOE_GT(1, 4, 4);
-    case 13: MOE_GT(1, 3, 4);
-    case 12: MOE_GT(1, 2, 4);
-    case 11: MOE_GT(1, 1, 4);
     default: break;
     }
 #undef MOE_GT
