@@ -1139,6 +1139,10 @@ int gemm_bf16_variant_block_m(int v)
 //    309, 329 / 281 / 302; 16 experts 2048 -> 8192, 48 rows 292 / 291 / 279, 319 / 298 / 285, 310 / 297 / 323; at 64 rows
 //    128x128 has caught up (342 / 320 / 284, 332 / 311 / 309, 342 / 308 / 338).  With 64 panels or fewer it is ahead from 48 on
 //    (16 experts 1024 -> 4096 115 / 108 / 101, 124 / 114 / 102, 120 / 114 / 110).
+//    With 32 panels or fewer the 128-row tiles leave most CUs idle and the calls are still the streaming kernel's: small / 10, even,
+//    skewed (0.8), half idle: 8 experts 512 -> 2048, 48 rows 21 / 32, 21 / 32, 22 / 32, 100 rows 28 / 33, 29 / 33, 28 / 34, 128 rows 28 / 33,
+//    37 / 33, 28 / 34, 160 rows 37 / 34; 4 experts 1024 -> 4096, 100 rows 51 / 59, 51 / 58, 47 / 51, 160 rows 68 / 59; 8 experts 1024 -> 4096, 64
+//    rows 56 / 64, 74 / 70, 52 / 60, 80 rows 73 / 64; 2 experts 4096 -> 14336, 64 rows 170 / 191, 225 / 191, 165 / 190, 80 rows 230 / 193.
 //  * No dimension of 64 and less: 10 is ahead there of 256-row tiles too (9 / 10: 64 experts 64 -> 256, 800 rows 30 / 24; 64 ->
 //    1024 62 / 55; 16 experts 4096 -> 64, 1000 rows 95 / 85; 128 experts 40 -> 512, 1000 rows 82 / 69).  9 is for operands that
 //    8 cannot address (9 / 10: 8 experts 2048 -> 8192, 33750 rows 15550 / 20945; 8 experts 1000 -> 8200, 33000 rows 9183 /
@@ -1158,7 +1162,7 @@ int gemm_bf16_variant(int64_t n_rows, int E, int N, int K, int num_cus)
     if (gemm_ring_ok(n_rows, N, K) && (fills || streams)) return 8;
     if (avg >= 192) return gemm_ring_addresses(n_rows, N, K) ? 10 : 9;
     const int small = avg >= kNtRows ? 4 : avg >= kNtSoleRows ? 5 : 3;
-    if (4 * panels <= num_cus) return avg >= 48 ? 10 : small;
+    if (4 * panels <= num_cus) return avg >= (!whole || 8 * panels > num_cus ? 48 : 16 * panels > num_cus ? 65 : 112) ? 10 : small;
     if (whole && !heavy && avg < 64) return avg >= 34 ? 2 : small;
     return avg >= 30 ? 10 : small;
 }
