@@ -94,8 +94,8 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
     constexpr int BTILE = BN * BROW;                       // one B stage in 16-bit units
     static_assert(!B8 || (BN * 4) % THREADS == 0, "8-bit B tile rows must split evenly over threads");
     static_assert(!B4 || (BN * 2) % THREADS == 0, "4-bit B tile rows must split evenly over threads");
-    // bf16 experts: the K loop may go round K from another place (turned_k)
-    constexpr bool TURNED = GROUPED && KFULL && BQ == 0 && BM < 256;
+    // bf16 and e4m3 experts: the K loop may go round K from another place (turned_k)
+    constexpr bool TURNED = GROUPED && KFULL && !B4 && BM < 256;
     static_assert(WTM % 32 == 0 && WTN % 32 == 0, "wave tile must be made of 32x32 blocks");
     static_assert((BM * 8) % THREADS == 0 && (BN * 8) % THREADS == 0, "tile rows must split evenly over threads");
 
@@ -515,7 +515,7 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
         int k_turn = 0;  // the K tile the loads' tile begins with
         int b_rows = 0;  // NT_SOLE: rows of the expert the loads are at
         auto set_ptrs = [&](const TileInfo &ti) {
-            if constexpr (TURNED) k_turn = p.turned ? __builtin_amdgcn_readfirstlane(turned_k(ti.expert, ti.n0, KT)) : 0;
+            if constexpr (TURNED) k_turn = p.turned ? __builtin_amdgcn_readfirstlane(turned_k(ti.expert, B8 ? ti.n0 / BN & 15 : ti.n0 >> 8 & 31, KT)) : 0;
             if constexpr (NT == NT_SOLE) b_rows = __builtin_amdgcn_readfirstlane(ti.row_end - ti.row_begin);
             // weights of expert e sit in slot b_slot[e] of the weight array when experts are buffered
             const uint16_t *Bg = Bg0 + (int64_t)((GROUPED && p.b_slot) ? uniform_load(p.b_slot + ti.expert) : ti.expert) * p.strideB;
@@ -931,7 +931,11 @@ static int launch_k(const GemmParams &p_in, int num_cus, hipStream_t s, int *mai
     // 235 / 203; 64x128: 64 experts 1024 -> 4096, 40 rows 234 / 203; 128x128: 16 experts 2048 -> 8192, 40 rows 266 / 202, 100 rows 276 / 221, 8
     // experts, 192 rows 195 / 178; from some 256 rows on either way (8 experts, 400 rows 302 / 306, skewed 309 / 304).  With 512 experts 1024 -> 4096
     // 1385 / 1381, 512 -> 2048 331 / 334.
-    p.turned = GROUPED && p.K % kTurnedK == 0 && p.M < 256ll * p.num_experts && p.num_experts < 384;
+    // e4m3, 32x128 tiles: 128 experts 2048 -> 8192, 2 rows 697 / 669, skewed 499 / 489; 64 experts 1024 -> 4096, 4 rows 104 / 92, 16 rows 119 / 105;
+    // 16 experts 2048 -> 8192, 8 rows 125 / 111, 32 rows 138 / 117; 512 experts 1024 -> 4096, 4 rows 718 / 686; 64 rows within 1 %.  Not with few columns
+    // (64 experts 512 -> 2048, whose second GEMM has 512, 4 rows 35.2 / 36.3; 48 experts 1024 -> 1024 27.2 / 27.8).
+    p.turned = GROUPED && (BQ == 8 ? p.K % kTurnedK8 == 0 && p.N >= 2048
+                                   : p.K % kTurnedK == 0 && p.M < 256ll * p.num_experts && p.num_experts < 384);
     auto kern = gemm_bf16_kernel<BM, BN, WM, WN, OUT_F32, RELU, GROUPED, KFULL, MINB, STAGES, NT, BQ>;
     // per instantiation, once, whichever host thread comes first: the LDS size attribute and the occupancy
     static std::once_flag once;

@@ -40,13 +40,14 @@ __device__ __forceinline__ void uniform_load2(const int32_t *pa, const int32_t *
 // The K tile that a tile of an expert's begins with where its K loop goes round K.  Weight rows of a multiple of 4 KB have the same
 // K tile in the same few memory channels, and the blocks, which walk K in step, ask those all at once (a bare read of 256 rows a
 // block, from 0 / from different places: rows of 4 KB 4.9 / 6.3 TB/s, 8 KB 4.7 / 6.3, 16 KB 6.0 / 6.3).  By the expert (Fibonacci
-// hashing: neighbours lie far apart) over the whole of K, and a K tile further with every 256 columns, so that column tiles find
-// their common rows in the L2 still.  An expert's row tiles, which share its weights, agree.
-static constexpr int kTurnedK = 2048;  // rows of a multiple of so many bf16 weights
-__device__ __forceinline__ int turned_k(int expert, int n0, int KT)
+// hashing: neighbours lie far apart) over the whole of K, and a K tile further with every column tile, so that column tiles find
+// their common rows in the L2 still (col: less than KT).  An expert's row tiles, which share its weights, agree.
+// e4m3 weights come in blocks of 1 KB along K, and the 16-row groups of blocks are 16 K bytes apart: the same, four channels at a time.
+static constexpr int kTurnedK = 2048, kTurnedK8 = 1024;  // rows of a multiple of so many bf16, e4m3 weights
+__device__ __forceinline__ int turned_k(int expert, int col, int KT)
 {
     const uint32_t by_expert = ((uint32_t)expert * 2654435761u >> 16) * (uint32_t)KT >> 16;
-    const int k = (int)by_expert + (n0 >> 8 & 31);  // KT is a multiple of 32
+    const int k = (int)by_expert + col;
     return k >= KT ? k - KT : k;
 }
 

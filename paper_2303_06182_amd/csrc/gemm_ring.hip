@@ -209,7 +209,7 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
     // full tiles are 0.7 % slower.
     auto first_k = [&]() __attribute__((always_inline)) -> int {
         if constexpr (!TURNED) return 0;
-        return turned_k(nx.expert, nx.n0, KT);
+        return turned_k(nx.expert, nx.n0 / BN & 31, KT);
     };
     if (p.c_zero_row >= 0 && blockIdx.x == 0) {
         // one all-zero row behind the output rows, for the GEMM that reads C as its A (N is a multiple of 8)

@@ -49,7 +49,7 @@ __global__ __launch_bounds__(W * 64, W == 8 ? 4 : 3) void gemm_stream_kernel(Gem
     constexpr int NB = BQ == 0 ? 2 : 1;        // 16-byte weight loads per step and 16 columns
     constexpr int BSTEP = B4 ? 2048 : B8 ? 1024 : 128;  // bytes a step advances in the weights
     constexpr int COLS = 16 * NC;
-    constexpr bool TURNED = BQ == 0 && !RAGGED;
+    constexpr bool TURNED = !B4 && !RAGGED;
     constexpr int LROW = COLS + 4;             // floats per LDS row of partial sums
     constexpr int NBUF = NC > 2 ? 1 : 2;       // two tiles' worth saves one of the two barriers per tile
     constexpr bool SC4 = B4 && (DP1 == 4 || NC == 4);       // block scales of four steps in one 16-byte load (a wave's steps are a multiple of 4)
@@ -357,8 +357,9 @@ static int launch_stream_t(const GemmParams &p_in, int num_cus, hipStream_t s)
     if (grid > tiles) grid = tiles;
     grid = align_up(grid, 8);
     // FFN in us, a wave's part of K from its beginning / turned: 16 experts 2048 -> 8192, 4 active 57 / 52, 8 active 90 / 86, 16 active 192 / 182; 64
-    // experts 1024 -> 4096 50 / 49; with rows of 4 KB, which the waves cut in parts of 1 KB, either way (128 experts 512 -> 2048, 8 active 21 / 21)
-    p.turned = p.K % (2 * kTurnedK) == 0;
+    // experts 1024 -> 4096 50 / 49; e4m3: 16 experts 2048 -> 8192, 1 row each 119 / 89, 4 active 27 / 24, 64 experts 1024 -> 4096, 1 row each 104 / 90.
+    // With K of 2048 not for few columns (second GEMM of 128 experts 512 -> 2048, 8 active, bf16 20.8 / 21.3; 64 experts, e4m3 29.4 / 30.8).
+    p.turned = p.K % (2 * kTurnedK) == 0 || (p.K % kTurnedK == 0 && p.N >= 2048);
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(W * 64), 0, s, p);
     MOE_LAUNCH_CHECK("gemm_stream_kernel");
     return MOE_OK;
