@@ -84,7 +84,7 @@ constexpr int q_tile_bytes(int bq) { return bq == 8 ? BN * 64 : bq == 4 ? BN * 3
 template <int BQ> struct QuantRaw { typedef u32x2 type; };   // a lane's 8 weights
 template <> struct QuantRaw<4> { typedef u32_lds type; };
 
-constexpr int kTurnedRows = 512, kTurnedExperts = 256;  // see first_k
+constexpr int kTurnedRows = 512, kTurnedRowsHeavy = 320, kTurnedExperts = 256;  // see first_k
 
 struct RingTile {
     int row0, row_end, expert, n0;
@@ -201,9 +201,9 @@ __global__ __launch_bounds__(THREADS, 1) void gemm_ring_kernel(GemmParams p)
     // 16 experts 2048 -> 8192, 128 rows 304 / 257; 128 experts, 32 rows 1498 / 1450, 128 rows 1684 / 1648, skewed 1878 / 1823; 128 experts 512 ->
     // 2048, 128 rows 174 / 159; 12 experts 4096 -> 14336, 256 skewed rows 968 / 939.  Other ways to turn (by a hash of expert and column, two or five
     // K tiles a column, the expert alone) are behind by up to 9 %.  Rows of other lengths spread by themselves (1536, 3072, 4000, 6144:
-    // within 1 % either way), as do the blocks of quantised weights.  From 512 rows per expert on the weights' time hides behind the
-    // MFMAs and what is left is the rows' lost sharing (128 experts 2048 -> 8192: 384 rows 3005 / 3009, skewed 3123 / 3098, 768 rows 5255 / 5250,
-    // skewed 5574 / 5613, 1024 skewed 7288 / 7317).  With 256 experts and more the blocks' tiles lie far enough
+    // within 1 % either way), as do the blocks of quantised weights.  From 512 rows per expert on, 320 with 2^30 weights, the weights'
+    // time hides behind the MFMAs and what is left is the rows' lost sharing (128 experts 2048 -> 8192: 384 rows 3005 / 3009, skewed 3123 / 3098, 768 rows 5255 / 5250,
+    // skewed 5574 / 5613, 1024 skewed 7288 / 7317; 464 rows, layer 3663 / 3691; 64 experts 1024 -> 4096, 384 rows 443 / 433, 512 rows 519 / 515).  With 256 experts and more the blocks' tiles lie far enough
     // apart (1024 -> 4096, 16 even rows: 192 experts 586 / 557, 256 experts 733 / 733, 400 experts 1210 / 1184, 512 experts 1496 / 1477, skewed 1506 /
     // 1497; 256 experts 2048 -> 2048 712 / 738; 512 experts 512 -> 2048 409 / 416).  An instance of its own: with the place along K in all of them
     // full tiles are 0.7 % slower.
@@ -639,7 +639,8 @@ int launch_gemm_ring(const GemmParams &p, int wbits, bool relu, hipStream_t s)
     if (wbits == 8) return relu ? launch_ring_t<true, false, 8>(p, s) : launch_ring_t<false, false, 8>(p, s);
     if (wbits == 4) return relu ? launch_ring_t<true, false, 4>(p, s) : launch_ring_t<false, false, 4>(p, s);
     if (p.K % BK != 0) return relu ? launch_ring_t<true, true>(p, s) : launch_ring_t<false, true>(p, s);
-    if (p.K % kTurnedK == 0 && p.M < (int64_t)kTurnedRows * p.num_experts && p.num_experts < kTurnedExperts)
+    const int64_t turned_rows = (int64_t)p.num_experts * p.N * p.K >= 1ll << 30 ? kTurnedRowsHeavy : kTurnedRows;
+    if (p.K % kTurnedK == 0 && p.M < turned_rows * p.num_experts && p.num_experts < kTurnedExperts)
         return relu ? launch_ring_t<true, false, 0, true>(p, s) : launch_ring_t<false, false, 0, true>(p, s);
     return relu ? launch_ring_t<true, false>(p, s) : launch_ring_t<false, false>(p, s);
 }
