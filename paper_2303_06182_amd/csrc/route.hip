@@ -14,6 +14,48 @@ static constexpr int kThreads = 256;
 static constexpr int kWave = 64;
 static constexpr int kMaxLogitParts = 16;  // slices the top-k kernel can add up (the gate GEMM's split K)
 
+// n logits (whole rows) to LDS, by the whole block.  n_parts > 1: they arrive as n_parts partial sums (the gate GEMM's split K),
+// slice 0 at `logits`, slice i > 0 at parts + (i - 1) * part_stride; they are added in slice order and the sum is also
+// written back to `logits`.  VEC: n, the slices' distance and the pointers allow 16-byte accesses.
+// What bounds it is the latency of a slice another XCD wrote, so all slices of a word are requested before the first is added,
+// by as many threads as there are words.  (The lanes of the selection took their own words here, one group of 16 after the other
+// from more than 64 experts on: a latency each.)
+template <bool VEC>
+__device__ __forceinline__ void stage_logits(float *__restrict__ s_row, float *logits, int n, int n_parts, const float *parts,
+                                             int64_t part_stride)
+{
+    typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+    constexpr int W = VEC ? 4 : 1;
+    for (int i = threadIdx.x * W; i < n; i += blockDim.x * W) {
+        if constexpr (VEC) {
+            f32x4_t f = *reinterpret_cast<const f32x4_t *>(logits + i);
+            if (n_parts > 1) {  // uniform over the grid
+                f32x4_t g[kMaxLogitParts - 1];
+#pragma unroll
+                for (int sp = 1; sp < kMaxLogitParts; ++sp)
+                    g[sp - 1] = sp < n_parts ? *reinterpret_cast<const f32x4_t *>(parts + (sp - 1) * part_stride + i) : f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int sp = 1; sp < kMaxLogitParts; ++sp)
+                    if (sp < n_parts) f += g[sp - 1];
+                *reinterpret_cast<f32x4_t *>(logits + i) = f;
+            }
+            *reinterpret_cast<f32x4_t *>(s_row + i) = f;
+        } else {
+            float f = logits[i];
+            if (n_parts > 1) {
+                float g[kMaxLogitParts - 1];
+#pragma unroll
+                for (int sp = 1; sp < kMaxLogitParts; ++sp) g[sp - 1] = sp < n_parts ? parts[(sp - 1) * part_stride + i] : 0.f;
+#pragma unroll
+                for (int sp = 1; sp < kMaxLogitParts; ++sp)
+                    if (sp < n_parts) f += g[sp - 1];
+                logits[i] = f;
+            }
+            s_row[i] = f;
+        }
+    }
+}
+
 // ------------------------------------------------------------------------------------------------
 // softmax + top-k.  G lanes (a power of two <= 64) share one token; lane `sub` holds logits
 // sub, sub+G, sub+2G, ...  Each of the k rounds takes the largest remaining logit; equal logits
@@ -23,14 +65,11 @@ static constexpr int kMaxLogitParts = 16;  // slices the top-k kernel can add up
 // VEC: lane `sub` instead holds the 16-byte groups sub, sub+G, ... of the row (4 logits each, E a
 // multiple of 4), so every lane has V/4 float4 loads in flight; slot i of the lane is expert
 // (i/4)*4G + 4*sub + i%4, still ascending with i.
-// n_parts > 1: the logits arrive as n_parts partial sums (the gate GEMM's split K): slice 0 at `logits`,
-// slice i > 0 at parts + (i - 1) * part_stride; they are added in slice order and the sum is written
-// back to `logits`.
-// One token per group of G lanes: token t, lane sub of the group.  s_idx (may be NULL): the selection goes there too.
+// One token per group of G lanes: token t, lane sub of the group, its logits at `row`.  s_idx (may be NULL): the selection goes
+// there too.
 template <int G, int V, bool VEC>
-__device__ __forceinline__ void topk_token(int t, bool live, int sub, float *logits, int E, int k, int renorm,
-                                           int32_t *__restrict__ idx, float *__restrict__ w, int n_parts,
-                                           const float *__restrict__ parts, int64_t part_stride, int *s_idx)
+__device__ __forceinline__ void topk_token(int t, bool live, int sub, const float *row, int E, int k, int renorm,
+                                           int32_t *__restrict__ idx, float *__restrict__ w, int *s_idx)
 {
     const float NEG_INF = -__builtin_huge_valf();
     auto expert_of = [&](int i) { return VEC ? (i >> 2) * (4 * G) + 4 * sub + (i & 3) : sub + i * G; };
@@ -41,28 +80,7 @@ __device__ __forceinline__ void topk_token(int t, bool live, int sub, float *log
         for (int q = 0; q < V / 4; ++q) {
             const int e0 = (q * G + sub) * 4;
             float4 f = make_float4(NEG_INF, NEG_INF, NEG_INF, NEG_INF);
-            if (live && e0 < E) {
-                float *src = logits + (int64_t)t * E + e0;
-                f = *reinterpret_cast<const float4 *>(src);
-                if (n_parts > 1) {  // uniform over the grid; all slices are requested before the first is added
-                    float4 g[kMaxLogitParts - 1];
-#pragma unroll
-                    for (int sp = 1; sp < kMaxLogitParts; ++sp)
-                        g[sp - 1] = sp < n_parts ? *reinterpret_cast<const float4 *>(parts + (sp - 1) * part_stride +
-                                                                                     (int64_t)t * E + e0)
-                                                 : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-                    for (int sp = 1; sp < kMaxLogitParts; ++sp) {
-                        if (sp < n_parts) {
-                            f.x += g[sp - 1].x;
-                            f.y += g[sp - 1].y;
-                            f.z += g[sp - 1].z;
-                            f.w += g[sp - 1].w;
-                        }
-                    }
-                    *reinterpret_cast<float4 *>(src) = f;
-                }
-            }
+            if (live && e0 < E) f = *reinterpret_cast<const float4 *>(row + e0);
             v[(4 * q + 0) % V] = f.x;
             v[(4 * q + 1) % V] = f.y;
             v[(4 * q + 2) % V] = f.z;
@@ -72,22 +90,7 @@ __device__ __forceinline__ void topk_token(int t, bool live, int sub, float *log
 #pragma unroll
         for (int i = 0; i < V; ++i) {
             const int e = sub + i * G;
-            v[i] = NEG_INF;
-            if (live && e < E) {
-                float *src = logits + (int64_t)t * E + e;
-                float f = *src;
-                if (n_parts > 1) {
-                    float g[kMaxLogitParts - 1];
-#pragma unroll
-                    for (int sp = 1; sp < kMaxLogitParts; ++sp)
-                        g[sp - 1] = sp < n_parts ? parts[(sp - 1) * part_stride + (int64_t)t * E + e] : 0.f;
-#pragma unroll
-                    for (int sp = 1; sp < kMaxLogitParts; ++sp)
-                        if (sp < n_parts) f += g[sp - 1];
-                    *src = f;
-                }
-                v[i] = f;
-            }
+            v[i] = live && e < E ? row[e] : NEG_INF;
         }
     }
     uint32_t taken = 0;  // bit i: register slot i already selected (or beyond E)
@@ -164,14 +167,26 @@ __device__ __forceinline__ void topk_token(int t, bool live, int sub, float *log
     }
 }
 
-template <int G, int V, bool VEC>
+// PARTS: the logits are the gate GEMM's slices
+template <int G, int V, bool VEC, bool PARTS>
 __global__ __launch_bounds__(kThreads) void topk_kernel(float *logits, int T, int E, int k, int renorm,
                                                         int32_t *__restrict__ idx, float *__restrict__ w,
                                                         int n_parts, const float *__restrict__ parts,
                                                         int64_t part_stride)
 {
-    const int t = blockIdx.x * (kThreads / G) + threadIdx.x / G;
-    topk_token<G, V, VEC>(t, t < T, threadIdx.x % G, logits, E, k, renorm, idx, w, n_parts, parts, part_stride, nullptr);
+    constexpr int TPB = kThreads / G;
+    const int t0 = blockIdx.x * TPB, local = threadIdx.x / G, t = t0 + local;
+    const float *row;
+    if constexpr (PARTS) {
+        __shared__ __align__(16) float s_logits[TPB * G * V];
+        const int64_t at = (int64_t)t0 * E;
+        stage_logits<VEC>(s_logits, logits + at, min(TPB, T - t0) * E, n_parts, parts + at, part_stride);
+        __syncthreads();
+        row = s_logits + local * E;
+    } else {
+        row = logits + (int64_t)t * E;
+    }
+    topk_token<G, V, VEC>(t, t < T, threadIdx.x % G, row, E, k, renorm, idx, w, nullptr);
 }
 
 template <int G, int V, bool VEC>
@@ -180,8 +195,12 @@ static int launch_topk_t(float *logits, int T, int E, int k, int renorm, int32_t
 {
     const int tpb = kThreads / G;
     ProfScope ps("topk", s);
-    hipLaunchKernelGGL((topk_kernel<G, V, VEC>), dim3(ceil_div(T, tpb)), dim3(kThreads), 0, s, logits, T, E, k, renorm,
-                       idx, w, n_parts, parts, part_stride);
+    if (n_parts > 1)
+        hipLaunchKernelGGL((topk_kernel<G, V, VEC, true>), dim3(ceil_div(T, tpb)), dim3(kThreads), 0, s, logits, T, E, k, renorm,
+                           idx, w, n_parts, parts, part_stride);
+    else
+        hipLaunchKernelGGL((topk_kernel<G, V, VEC, false>), dim3(ceil_div(T, tpb)), dim3(kThreads), 0, s, logits, T, E, k, renorm,
+                           idx, w, 1, nullptr, 0);
     MOE_LAUNCH_CHECK("topk_kernel");
     return MOE_OK;
 }
@@ -573,8 +592,8 @@ __global__ __launch_bounds__(kThreads) void route_rank_kernel(const int32_t *__r
 
 // ------------------------------------------------------------------------------------------------
 // Small batches (decoder steps: a few hundred assignments): the three kernels above are then all
-// launch latency, so one block of 1024 threads does the whole job in LDS -- histogram, scan,
-// tile map and ranks -- with one thread per assignment a = t*k + j, in chunks of 1024.  The rank
+// launch latency, so one block of 256 to 1024 threads does the whole job in LDS -- histogram, scan,
+// tile map and ranks -- with one thread per assignment a = t*k + j, in chunks of its size.  The rank
 // of a inside its expert is (assignments of that expert in earlier chunks and waves) + (lanes
 // below it in its wave with the same expert); waves add their counts to the running per-expert
 // totals one after the other, so the order is that of a, as in the kernels above.
@@ -598,10 +617,11 @@ __device__ __forceinline__ void route_small(const int32_t *idx, int n_assign, in
     __shared__ int wave_tot[16];
     const int lane = threadIdx.x % kWave;
     const int wave = threadIdx.x / kWave;
-    hist[threadIdx.x] = 0;  // 1024 threads, at most as many experts
+    const int threads = blockDim.x;
+    hist[threadIdx.x] = 0;  // at least as many threads as experts
     seen[threadIdx.x] = 0;
     __syncthreads();
-    for (int a = threadIdx.x; a < n_assign; a += 1024) atomicAdd(&hist[clamp_expert(idx[a], E)], 1);
+    for (int a = threadIdx.x; a < n_assign; a += threads) atomicAdd(&hist[clamp_expert(idx[a], E)], 1);
     __syncthreads();
     // exclusive scan over the experts, thread e owns expert e: rows in the low half of a word, tiles of the grouped GEMM's M-tile
     // map in the high half (at most kRouteBlockMax of either)
@@ -635,7 +655,7 @@ __device__ __forceinline__ void route_small(const int32_t *idx, int n_assign, in
                 tile_row[ti] = my_off + i * tile_bm;
             }
         }
-        if (threadIdx.x == 1023) num_tiles[0] = min(first + nt, max_m_tiles);
+        if (threadIdx.x == threads - 1) num_tiles[0] = min(first + nt, max_m_tiles);
     } else if (tile_bm > 0) {
         __shared__ RingScratch ring;
         ring_schedule([&](int e) { return hist[e]; }, E, ring_n1, ring_n2, tile_expert, tile_row, max_m_tiles, num_tiles, ring);
@@ -644,7 +664,7 @@ __device__ __forceinline__ void route_small(const int32_t *idx, int n_assign, in
     const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (kWave - lane));
     int nbits = 0;
     while ((1 << nbits) < E) ++nbits;
-    for (int a0 = 0; a0 < n_assign; a0 += 1024) {  // trip count uniform over the block
+    for (int a0 = 0; a0 < n_assign; a0 += threads) {  // trip count uniform over the block
         const int a = a0 + threadIdx.x;
         const bool live = a < n_assign;
         const int e = live ? clamp_expert(idx[a], E) : -1;
@@ -660,7 +680,7 @@ __device__ __forceinline__ void route_small(const int32_t *idx, int n_assign, in
         const bool leader = live && first == lane;
         // the waves take their turns in order; the first lane of every expert group moves the total
         int base = 0;
-        const int live_waves = min(16, (n_assign - a0 + kWave - 1) / kWave);  // uniform over the block
+        const int live_waves = min(threads / kWave, (n_assign - a0 + kWave - 1) / kWave);  // uniform over the block
         for (int w2 = 0; w2 < live_waves; ++w2) {
             if (wave == w2 && leader) {
                 base = seen[e];
@@ -683,16 +703,28 @@ __global__ __launch_bounds__(1024) void route_small_kernel(const int32_t *__rest
                 o.max_m_tiles, o.ring_n1, o.ring_n2);
 }
 
-// Top-k of a decoder step and its routing in one launch: 1024 / G tokens fit the block, their selection stays in LDS.
-// Bound by launch latency: a dependent launch costs about 4.5 us here whatever it does.
+// Threads of the block that routes: as many as it has experts, assignments and other items (at most 1024, in rounds then).
+// Fewer waves start and meet sooner: with it and the logits staged by all threads the launch takes, alone, 8.5 -> 6.2 us for one
+// token over 128 experts (16 slices), 6.5 -> 5.9 over 64.
+static int route_block_threads(int64_t items, int E, int64_t n_assign)
+{
+    const int64_t most = items > n_assign ? (items > E ? items : E) : (n_assign > E ? n_assign : E);
+    return most <= 256 ? 256 : most <= 512 ? 512 : 1024;
+}
+
+// Top-k of a decoder step and its routing in one launch: 1024 / G tokens fit the block, their logits and selection stay in LDS.
+// Bound by latency: a dependent launch costs about 4.5 us here whatever it does.
 template <int G, int V, bool VEC>
 __global__ __launch_bounds__(1024) void route_topk_kernel(float *logits, int T, int E, int k, int renorm, int32_t *__restrict__ idx,
                                                           float *__restrict__ w, int n_parts, const float *__restrict__ parts,
                                                           int64_t part_stride, RouteOut o)
 {
+    __shared__ __align__(16) float s_logits[1024 * V];
     __shared__ int s_idx[kSmallRouteMax];
+    stage_logits<VEC>(s_logits, logits, T * E, n_parts, parts, part_stride);
+    __syncthreads();
     const int t = threadIdx.x / G;
-    topk_token<G, V, VEC>(t, t < T, threadIdx.x % G, logits, E, k, renorm, idx, w, n_parts, parts, part_stride, s_idx);
+    topk_token<G, V, VEC>(t, t < T, threadIdx.x % G, s_logits + t * E, E, k, renorm, idx, w, s_idx);
     __syncthreads();
     route_small(s_idx, T * k, E, k, o.counts, o.offsets, o.dst_row, o.src_tok, o.tile_bm, o.tile_expert, o.tile_row, o.num_tiles,
                 o.max_m_tiles, o.ring_n1, o.ring_n2);
@@ -705,7 +737,9 @@ static int launch_route_topk_t(float *logits, int T, int E, int k, int renorm, i
     if (T > 1024 / G) return MOE_OK;
     *taken = true;
     ProfScope ps("route", s);
-    hipLaunchKernelGGL((route_topk_kernel<G, V, VEC>), dim3(1), dim3(1024), 0, s, logits, T, E, k, renorm, idx, w, n_parts, parts,
+    const int64_t words = (int64_t)T * E / (VEC ? 4 : 1), lanes = (int64_t)T * G;
+    const int threads = route_block_threads(words > lanes ? words : lanes, E, (int64_t)T * k);
+    hipLaunchKernelGGL((route_topk_kernel<G, V, VEC>), dim3(1), dim3(threads), 0, s, logits, T, E, k, renorm, idx, w, n_parts, parts,
                        part_stride, o);
     MOE_LAUNCH_CHECK("route_topk_kernel");
     return MOE_OK;
@@ -717,16 +751,25 @@ int launch_route_topk(float *logits, int T, int E, int k, int renorm, int32_t *i
                       const float *parts, int64_t part_stride, const RouteOut &o, bool *taken)
 {
     *taken = false;
-    if (T < 1 || T > 64 || (int64_t)T * k > kSmallRouteMax || E % 4 != 0 || n_parts > kMaxLogitParts) return MOE_OK;
-#define MOE_ROUTE_TOPK(G, V) launch_route_topk_t<G, V, true>(logits, T, E, k, renorm, idx, w, s, n_parts, parts, part_stride, o, taken)
-    if (E <= 8) return MOE_ROUTE_TOPK(2, 4);
-    if (E <= 16) return MOE_ROUTE_TOPK(4, 4);
-    if (E <= 32) return MOE_ROUTE_TOPK(8, 4);
-    if (E <= 64) return MOE_ROUTE_TOPK(16, 4);
-    if (E <= 128) return MOE_ROUTE_TOPK(16, 8);
-    if (E <= 256) return MOE_ROUTE_TOPK(16, 16);
-    if (E <= 512) return MOE_ROUTE_TOPK(32, 16);
-    return MOE_ROUTE_TOPK(64, 16);
+    if (T < 1 || T > 64 || (int64_t)T * k > kSmallRouteMax || n_parts > kMaxLogitParts) return MOE_OK;
+#define MOE_ROUTE_TOPK(G, V, VEC) launch_route_topk_t<G, V, VEC>(logits, T, E, k, renorm, idx, w, s, n_parts, parts, part_stride, o, taken)
+    if (E % 4 == 0) {
+        if (E <= 8) return MOE_ROUTE_TOPK(2, 4, true);
+        if (E <= 16) return MOE_ROUTE_TOPK(4, 4, true);
+        if (E <= 32) return MOE_ROUTE_TOPK(8, 4, true);
+        if (E <= 64) return MOE_ROUTE_TOPK(16, 4, true);
+        if (E <= 128) return MOE_ROUTE_TOPK(16, 8, true);
+        if (E <= 256) return MOE_ROUTE_TOPK(16, 16, true);
+        if (E <= 512) return MOE_ROUTE_TOPK(32, 16, true);
+        return MOE_ROUTE_TOPK(64, 16, true);
+    }
+    if (E <= 4) return MOE_ROUTE_TOPK(4, 1, false);
+    if (E <= 8) return MOE_ROUTE_TOPK(8, 1, false);
+    if (E <= 16) return MOE_ROUTE_TOPK(16, 1, false);
+    if (E <= 32) return MOE_ROUTE_TOPK(32, 1, false);
+    if (E <= 64) return MOE_ROUTE_TOPK(64, 1, false);
+    if (E <= 128) return MOE_ROUTE_TOPK(64, 2, false);
+    return MOE_OK;
 #undef MOE_ROUTE_TOPK
 }
 
@@ -736,7 +779,7 @@ int launch_route(const int32_t *idx, int T, int E, int k, const RouteOut &o, int
 {
     ProfScope ps("route", s);  // histogram + prefix + rank together
     if ((int64_t)T * k <= (hist_tokens > 0 ? kSmallRouteMax : kRouteBlockMax)) {  // a histogram that is there saves a launch
-        hipLaunchKernelGGL(route_small_kernel, dim3(1), dim3(1024), 0, s, idx, T * k, E, k, o);
+        hipLaunchKernelGGL(route_small_kernel, dim3(1), dim3(route_block_threads(0, E, (int64_t)T * k)), 0, s, idx, T * k, E, k, o);
         MOE_LAUNCH_CHECK("route_small_kernel");
         return MOE_OK;
     }
