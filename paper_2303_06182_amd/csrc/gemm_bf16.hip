@@ -1141,12 +1141,15 @@ int gemm_bf16_variant_block_m(int v)
 //  * With fewer weights 64x128 is the steadiest shape from 34 to 63 rows, 32x128 / 64x128 / 128x128: 128 experts 512 -> 2048,
 //    36 rows 171 / 161 / 162, 173 / 169 / 183, 170 / 164 / 176; 64 experts 1024 -> 4096, 48 rows 314 / 287 / 266, 327 / 280 /
 //    309, 329 / 281 / 302; 16 experts 2048 -> 8192, 48 rows 292 / 291 / 279, 319 / 298 / 285, 310 / 297 / 323; at 64 rows
-//    128x128 has caught up (342 / 320 / 284, 332 / 311 / 309, 342 / 308 / 338).  With 64 panels or fewer it is ahead from 48 on
-//    (16 experts 1024 -> 4096 115 / 108 / 101, 124 / 114 / 102, 120 / 114 / 110).
-//    With 32 panels or fewer the 128-row tiles leave most CUs idle and the calls are still the streaming kernel's: small / 10, even,
-//    skewed (0.8), half idle: 8 experts 512 -> 2048, 48 rows 21 / 32, 21 / 32, 22 / 32, 100 rows 28 / 33, 29 / 33, 28 / 34, 128 rows 28 / 33,
-//    37 / 33, 28 / 34, 160 rows 37 / 34; 4 experts 1024 -> 4096, 100 rows 51 / 59, 51 / 58, 47 / 51, 160 rows 68 / 59; 8 experts 1024 -> 4096, 64
-//    rows 56 / 64, 74 / 70, 52 / 60, 80 rows 73 / 64; 2 experts 4096 -> 14336, 64 rows 170 / 191, 225 / 191, 165 / 190, 80 rows 230 / 193.
+//    128x128 has caught up (342 / 320 / 284, 332 / 311 / 309, 342 / 308 / 338).
+//    With 64 panels or fewer the 64-row tiles have the chip to themselves, as narrow ones with more stages (launch_gemm_bf16), and
+//    take over from the streaming kernel and from 128x128, small / 2 / 10, even, skewed (0.8).  33 to 64 panels, from 8 to 95 rows: 8
+//    experts 2048 -> 8192, 6 rows 98 / 102, 108 / 102; 8 rows 102 / 102, 113 / 102; 18 rows 107 / 100, 144 / 100; 84 rows - / 147 / 148, - / 153 /
+//    173; 100 rows - / 147 / 142, - / 160 / 157; 16 experts 1024 -> 4096, 8 rows 58 / 58, 77 / 58; 32 experts 512 -> 2048, 20 rows 39 / 38, 46 / 44;
+//    80 rows - / 50 / 49, - / 54 / 55.  17 to 32 panels, where the streaming kernel has short rounds while an expert has one of its tiles, from 33 to
+//    128 rows: 8 experts 1024 -> 4096, 28 rows 39 / 44, 56 / 48; 33 rows 56 / 44, 57 / 49; 90 rows 69 / 53 / 68, 76 / 53 / 76; 150 rows - / 62 /
+//    58, - / 67 / 61; 2 experts 4096 -> 14336, 40 rows 168 / 122, 165 / 123.  16 and fewer, from 65 to 191: 8 experts 512 -> 2048, 50 rows 20 / 23, 21 /
+//    24; 65 rows 29 / 24, 29 / 25; 250 rows - / 28 / 32, - / 35 / 35; 4 experts 1024 -> 4096, 80 rows 52 / 41, 51 / 41; 300 rows - / 59 / 56, - / 60 / 56.
 //  * No dimension of 64 and less: 10 is ahead there of 256-row tiles too (9 / 10: 64 experts 64 -> 256, 800 rows 30 / 24; 64 ->
 //    1024 62 / 55; 16 experts 4096 -> 64, 1000 rows 95 / 85; 128 experts 40 -> 512, 1000 rows 82 / 69).  9 is for operands that
 //    8 cannot address (9 / 10: 8 experts 2048 -> 8192, 33750 rows 15550 / 20945; 8 experts 1000 -> 8200, 33000 rows 9183 /
@@ -1166,9 +1169,20 @@ int gemm_bf16_variant(int64_t n_rows, int E, int N, int K, int num_cus)
     if (gemm_ring_ok(n_rows, N, K) && (fills || streams)) return 8;
     if (avg >= 192) return gemm_ring_addresses(n_rows, N, K) ? 10 : 9;
     const int small = avg >= kNtRows ? 4 : avg >= kNtSoleRows ? 5 : 3;
-    if (4 * panels <= num_cus) return avg >= (!whole || 8 * panels > num_cus ? 48 : 16 * panels > num_cus ? 65 : 112) ? 10 : small;
+    if (4 * panels <= num_cus && whole) {
+        if (8 * panels > num_cus) return avg >= 96 ? 10 : avg >= 8 ? 2 : small;
+        return 16 * panels > num_cus ? (avg > 128 ? 10 : avg > 32 ? 2 : small) : (avg > 64 ? 2 : small);
+    }
+    if (4 * panels <= num_cus) return avg >= 48 ? 10 : small;
     if (whole && !heavy && avg < 64) return avg >= 34 ? 2 : small;
     return avg >= 30 ? 10 : small;
+}
+
+// Whether a GEMM has at most so many tiles per CU, as estimated from the mean number of rows per expert times `spread`.
+static bool few_tiles(const GemmParams &p, int block_m, int block_n, double spread, double per_cu, int num_cus)
+{
+    const int64_t rows = (int64_t)(spread * p.M / p.num_experts + 0.999);
+    return (double)(p.num_experts * ((rows + block_m - 1) / block_m)) * ceil_div(p.N, block_n) <= per_cu * num_cus;
 }
 
 int launch_gemm_stream(const GemmParams &p, int wbits, bool relu, int num_cus, hipStream_t s, bool *taken);
@@ -1228,13 +1242,27 @@ int launch_gemm_bf16(const GemmParams &p, bool grouped, int variant, bool out_f3
         q.tail_mode = 2;
         return launch_grouped<128, 128, 2, 2, 2, REG_STAGED>(q, relu, num_cus, s, &main_grid);
     }
-    case 10: return launch_grouped<128, 128, 2, 2, 2, REG_STAGED>(p, relu, num_cus, s);
+    case 10:
+        // At most a tile per CU, also where some experts have half as many rows again: 128x64 tiles, four stages.  FFN in us, 128x128 /
+        // these, even, skewed (0.8): 8 experts 1024 -> 4096, 150 rows 69 / 58, 73 / 61; 4 experts 2048 -> 8192, 150 rows 118 / 101, 126 / 105; 4
+        // experts 1024 -> 4096, 300 rows 67 / 56, 67 / 56; 8 experts 512 -> 2048, 250 rows 37 / 32, 39 / 35.  Without the half: 8 experts 1024 ->
+        // 4096, 240 rows 72 / 61, 82 / 98; 8 experts 2048 -> 8192, 100 rows 141 / 124, 156 / 184.
+        if (p.K % BK == 0 && few_tiles(p, 128, 64, 1.5, 1, num_cus)) return launch_grouped_dtl<128, 64, 2, 2, 2, 4, NT_NONE, 0>(p, relu, num_cus, s);
+        return launch_grouped<128, 128, 2, 2, 2, REG_STAGED>(p, relu, num_cus, s);
     case 2:
         if (p.K % BK != 0) {
             set_error("64x128 tiles need K (%d) to be a multiple of %d", p.K, BK);
             return MOE_ERR_UNSUPPORTED;
         }
-        return launch_grouped_dtl<64, 128, 1, 4, 2, 2, NT_NONE, 0>(p, relu, num_cus, s);
+        // With a tile or two per CU its time is that of the K loop, whose loads are as far ahead as the LDS has stages and which
+        // narrower tiles share among more blocks.  FFN in us, 64x128 in two stages / in three / 64x64 in four, even, skewed (0.8): 8 experts
+        // 2048 -> 8192, 64 rows 160 / 126 / 108, 168 / 132 / 141; 16 experts 1024 -> 4096, 48 rows 91 / 72 / 62, 95 / 76 / 79; 12
+        // experts, 56 rows - / 64 / 55, - / 64 / 58; 4 experts 4096 -> 14336, 40 rows 281 / 209 / 177, 294 / 221 / 237; 16 experts 2048 ->
+        // 8192, 48 rows 225 / 200 / 196, 237 / 242 / 246; with more tiles two stages, of which a CU holds three blocks: 64 experts
+        // 1024 -> 4096, 40 rows 203 / 212, 226 / 231.
+        if (few_tiles(p, 64, 64, 1, 1, num_cus)) return launch_grouped_dtl<64, 64, 2, 2, 2, 4, NT_NONE, 0>(p, relu, num_cus, s);
+        return few_tiles(p, 64, 128, 1, 1.5, num_cus) ? launch_grouped_dtl<64, 128, 1, 4, 2, 3, NT_NONE, 0>(p, relu, num_cus, s)
+                                         : launch_grouped_dtl<64, 128, 1, 4, 2, 2, NT_NONE, 0>(p, relu, num_cus, s);
     case 22: return launch_grouped_dtl<64, 128, 1, 4, 2, 3, NT_NONE, 8>(p, relu, num_cus, s);
     case 23: return launch_grouped_dtl<32, 128, 1, 4, 2, 3, NT_ALL, 8>(p, relu, num_cus, s);
     case 24: return launch_grouped_dtl<32, 128, 1, 4, 2, 3, NT_NONE, 8>(p, relu, num_cus, s);
@@ -1248,7 +1276,10 @@ int launch_gemm_bf16(const GemmParams &p, bool grouped, int variant, bool out_f3
                         : launch_k<32, 128, 1, 4, false, false, true, false, 2, REG_STAGED>(p, num_cus, s, nullptr);
         return variant == 3 ? launch_grouped_dtl<32, 128, 1, 4, 2, 2, NT_ALL, 0>(p, relu, num_cus, s)
                : variant == 5 ? launch_grouped_dtl<32, 128, 1, 4, 2, 2, NT_SOLE, 0>(p, relu, num_cus, s)
-                              : launch_grouped_dtl<32, 128, 1, 4, 2, 2, NT_NONE, 0>(p, relu, num_cus, s);
+               // as the 64-row tiles, two stages / four: 8 experts 2048 -> 8192, 40 rows 158 / 113, 171 / 131; 16 experts 2048 -> 8192, 20
+               // rows 209 / 189, 229 / 236; 16 experts 1024 -> 4096, 36 rows 88 / 66, 95 / 73
+               : few_tiles(p, 32, 128, 1, 1.5, num_cus) ? launch_grouped_dtl<32, 128, 1, 4, 2, 4, NT_NONE, 0>(p, relu, num_cus, s)
+                                           : launch_grouped_dtl<32, 128, 1, 4, 2, 2, NT_NONE, 0>(p, relu, num_cus, s);
     default:
         set_error("unsupported grouped GEMM variant %d", variant);
         return MOE_ERR_UNSUPPORTED;

@@ -1,0 +1,34 @@
+"""Expert GEMMs with a tile or two per CU (few_tiles, gemm_bf16.hip): narrower tiles and more LDS stages.  Row counts around the tiles'
+edges, K of one K tile and of fewer than the stages, K loops that go round K, idle experts, biases; and the choice around its lines."""
+import pytest
+
+from helpers import expert_tile_shape
+from test_gpu_tile_shapes import ragged, run
+
+EDGES = [0, 1, 31, 32, 33, 63, 64, 65]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shape,E,D,F,edges,lo,hi", [
+    ("64x128", 16, 1024, 1088, EDGES, 10, 60),      # three stages in the first GEMM, 64 columns in the second
+    ("64x128", 16, 576, 1088, EDGES, 10, 60), ("64x128", 8, 2048, 2112, EDGES, 0, 0),
+    ("64x128", 16, 64, 256, EDGES + [127, 128, 129, 200], 90, 140), ("64x128", 16, 256, 64, EDGES + [127, 128, 129, 200], 90, 140),
+    ("64x128", 4, 192, 128, [65, 129, 0, 127], 0, 0),
+    ("128x128", 8, 1024, 1024, [0, 1, 127, 128, 129, 257, 255, 256], 0, 0),   # 128x64
+    ("128x128", 8, 1024, 576, [600, 127, 128, 129, 257, 255, 0, 700], 0, 0),
+    ("128x128", 12, 64, 384, EDGES + [600, 900, 700, 1000], 0, 0),
+    ("32x128", 16, 2048, 2112, EDGES[:6], 16, 32)])   # four stages in both GEMMs
+def test_ffn(shape, E, D, F, edges, lo, hi):
+    run(shape, ragged(E, edges, lo, hi, 5) if hi else edges, D, F)
+
+
+@pytest.mark.parametrize("E,D,F,rows,shape", [
+    # 33 to 64 weight panels, 17 to 32, 16 and fewer
+    (8, 2048, 8192, 7, "32x128"), (8, 2048, 8192, 8, "64x128"), (8, 2048, 8192, 95, "64x128"), (8, 2048, 8192, 96, "128x128"),
+    (32, 512, 2048, 20, "64x128"), (8, 1024, 4096, 32, "32x128"), (8, 1024, 4096, 33, "64x128"), (8, 1024, 4096, 128, "64x128"),
+    (8, 1024, 4096, 129, "128x128"), (8, 512, 2048, 64, "32x128"), (8, 512, 2048, 65, "64x128"), (8, 512, 2048, 191, "64x128"),
+    (8, 512, 2048, 192, "128x128"),
+    # K that ends inside a K tile
+    (8, 1000, 4000, 47, "32x128"), (8, 1000, 4000, 48, "128x128")])
+def test_choice(E, D, F, rows, shape):
+    assert expert_tile_shape(E * rows, E, F, D) == shape
