@@ -42,3 +42,22 @@ def test_gate(T, D, E, k, renorm, bias):
     np.testing.assert_array_equal(to_np(r["topk_idx"]), ridx)
     for name, want in zip(("counts", "offsets", "dst_row", "src_tok"), orc.route(ridx, E)):
         np.testing.assert_array_equal(to_np(r[name]), want)
+
+
+@pytest.mark.parametrize("T,D,E,k", [
+    (257, 72, 24, 1), (300, 120, 47, 2), (3001, 1000, 24, 1), (1137, 1496, 47, 2), (8193, 328, 60, 2), (16385, 136, 66, 2),
+    (24577, 200, 128, 2), (24577, 392, 50, 3), (40001, 72, 128, 2), (66000, 104, 7, 2), (300, 2040, 128, 8)])
+def test_k_ends_inside_a_tile(T, D, E, k):
+    test_gate(T, D, E, k, T % 2 == 0, True)
+
+
+def test_nothing_past_k_is_multiplied():
+    """The last row's chunks past K lie behind the arrays, the other rows' in the next row: infinities there must not reach a sum."""
+    T, D, E = 320, 200, 40
+    g = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.empty((T, D), dtype=torch.bfloat16, device="cuda").normal_(0, 1, generator=g)
+    wg = torch.empty((E, D), dtype=torch.bfloat16, device="cuda").normal_(0, 0.1, generator=g)
+    x[1::2, :56] = float("inf")   # what follows an even row
+    logits, _, _ = binding.MoeLayer(T, D, 64, E, 2, "bf16").moe_gate_topk(x, wg)
+    ref = orc.gate_logits(x[::2].cpu(), wg.cpu(), None)
+    assert np.abs(to_np(logits)[::2] - ref).max() <= 2e-6 * np.abs(ref).max() + 1e-7
