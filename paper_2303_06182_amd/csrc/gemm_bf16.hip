@@ -24,7 +24,7 @@
 //    tiles ahead of the MFMAs and are waited for (vmcnt) only at the barrier that ends an
 //    iteration.  Several such blocks share a CU, so one block's load burst and barrier hide
 //    behind another block's MFMAs.
-//  * register-staged (256- and 128-row tiles, one or two blocks per CU; every height for K that ends inside a K tile): measured on gfx950, a
+//  * register-staged (256- and 128-row tiles, one or two blocks per CU; 32-row tiles where K ends inside a K tile): measured on gfx950, a
 //    vector-memory instruction costs the issuing wave 20-30 clocks of MFMA issue and the CU's
 //    address unit 16 clocks, so a K tile's loads issued as one burst stall every wave while the
 //    matrix units idle, and with only two 64 KB stages in LDS they cannot be issued late either.
@@ -67,6 +67,9 @@ static constexpr int REG_STAGED = 0;  // value of the STAGES template argument t
 // that are their expert's only one
 static constexpr int NT_NONE = 0, NT_ALL = 1, NT_SOLE = 2;
 
+// What direct-to-LDS loads take for the 16-byte chunks past the end of K
+__device__ __align__(16) static const uint16_t chunk_of_zeros[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+
 struct TileInfo {
     int row0, row_end, expert, n0;
     int row_begin;  // the expert's first row (NT_SOLE only)
@@ -106,7 +109,7 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
     uint16_t *sA = reinterpret_cast<uint16_t *>(smem_raw);  // [NSTAGE][BM*64]
     uint16_t *sB = sA + NSTAGE * BM * BK;                   // [NSTAGE][BN*64]
     static_assert(NSTAGE >= 2, "at least two LDS stages");
-    static_assert(KFULL || RSTAGE || (STAGES == 2 && !GROUPED), "K that ends inside a K tile: register-staged, or the gate's two-stage loop");
+    static_assert(KFULL || GROUPED || RSTAGE || STAGES == 2, "K that ends inside a K tile: the gate has a two-stage loop of its own");
     static_assert(BQ == 0 || (KFULL && !RSTAGE && GROUPED), "8- and 4-bit weights: grouped direct-to-LDS pipeline, K a multiple of the K tile");
 
     const int tid = threadIdx.x;
@@ -430,7 +433,7 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
     constexpr int STRIP_BYTES = 32 * STRIP_ROW_BYTES;
     constexpr bool STRIP_IN_A = A_IT * 1024 >= STRIP_BYTES;
     constexpr bool STRIP_IN_B = !STRIP_IN_A && B_IT * 1024 >= STRIP_BYTES;
-    constexpr bool LDS_EPILOGUE = !OUT_F32 && (KFULL || RSTAGE) && (STRIP_IN_A || STRIP_IN_B);
+    constexpr bool LDS_EPILOGUE = !OUT_F32 && (KFULL || RSTAGE || GROUPED) && (STRIP_IN_A || STRIP_IN_B);
     auto epilogue_lds = [&](const TileInfo &t, int free_stage) {
         constexpr int CPRW = STRIP_ROW_BYTES / 16;  // chunks per strip row
         constexpr int RPI = 64 / CPRW;              // strip rows one 64-lane access covers
@@ -501,7 +504,7 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
 
     TileInfo t = tile_info(seq);
 
-    if constexpr (KFULL || RSTAGE) {
+    if constexpr (KFULL || RSTAGE || GROUPED) {
         // ---- global -> LDS without registers: one global_load_lds_dwordx4 moves 64 lanes x 16 B =
         // 1 KB = 8 tile rows into LDS, lane L landing at byte 16*L of the instruction's LDS base.
         // The base is fixed per instruction, so the swizzle is applied on the global side: the lane
@@ -595,6 +598,26 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
         };
         auto issue = [&](int tile, int buf) {
             const int kt = turn(tile);
+            if constexpr (!KFULL) {
+                if (kt == KT - 1) {  // uniform: K ends inside this K tile, the lanes whose chunk lies past it load zeros
+                    auto inside = [&](const uint16_t *at, int row) {
+                        return kt * BK + (((lane & 7) ^ (((row + (lane >> 3)) >> 1) & 7)) << 3) < K ? at : chunk_of_zeros;
+                    };
+#pragma unroll
+                    for (int i = 0; i < A_IT; ++i) {
+                        const int r = (wave * A_IT + i) * 8;
+                        __builtin_amdgcn_global_load_lds((const glb_void *)inside(a_base + (a_off[i] + kt * BK), r),
+                                                         (lds_void *)(sA + (buf * BM + r) * BK), 16, 0, 0);
+                    }
+#pragma unroll
+                    for (int i = 0; i < B_IT; ++i) {
+                        const int r = (wave * B_IT + i) * 8;
+                        __builtin_amdgcn_global_load_lds((const glb_void *)inside(b_base + (b_off[i] + kt * BK), r),
+                                                         (lds_void *)(sB + (buf * BN + r) * BK), 16, 0, 0);
+                    }
+                    return;
+                }
+            }
 #pragma unroll
             for (int i = 0; i < A_IT; ++i)
                 __builtin_amdgcn_global_load_lds((const glb_void *)(a_base + (a_off[i] + kt * BK)),
@@ -993,6 +1016,10 @@ static int launch_one(const GemmParams &p, int num_cus, hipStream_t s, int *main
 template <int BM, int BN, int WM, int WN, int MINB, int STAGES, int NT, int BQ>
 static int launch_grouped_dtl(const GemmParams &p, bool relu, int num_cus, hipStream_t s)
 {
+    if constexpr (BQ == 0)
+        if (p.K % BK != 0)
+            return relu ? launch_k<BM, BN, WM, WN, false, true, true, false, MINB, STAGES, NT>(p, num_cus, s, nullptr)
+                        : launch_k<BM, BN, WM, WN, false, false, true, false, MINB, STAGES, NT>(p, num_cus, s, nullptr);
     return relu ? launch_k<BM, BN, WM, WN, false, true, true, true, MINB, STAGES, NT, BQ>(p, num_cus, s, nullptr)
                 : launch_k<BM, BN, WM, WN, false, false, true, true, MINB, STAGES, NT, BQ>(p, num_cus, s, nullptr);
 }
@@ -1154,7 +1181,10 @@ int gemm_bf16_variant_block_m(int v)
 //    1024 62 / 55; 16 experts 4096 -> 64, 1000 rows 95 / 85; 128 experts 40 -> 512, 1000 rows 82 / 69).  9 is for operands that
 //    8 cannot address (9 / 10: 8 experts 2048 -> 8192, 33750 rows 15550 / 20945; 8 experts 1000 -> 8200, 33000 rows 9183 /
 //    16220).
-//  * K that is no multiple of the K tile does not have 64x128: there 128 rows pay from 30 on.
+//  * K that is no multiple of the K tile: with 64 panels and fewer the same lines (small / 2 / 10: 8 experts 1000 -> 4000, 40 rows 53 / 47 / 56,
+//    68 / 60 / 64; 80 rows 71 / 55 / 60, 86 / 59 / 78; 32 experts 496 -> 4984, 30 rows 104 / 82 / 89, 135 / 129 / 138; 5 experts 520 -> 1560, 300 rows
+//    - / 28 / 35), with more 64x128 from 30 to 55 rows (2 / 10: 24 experts 1000 -> 4000, 40 rows 101 / 106, 112 / 125; 47 experts
+//    1496 -> 4504, 48 rows 352 / 356, 403 / 433; 52 experts 840 -> 7120, 60 rows 359 / 362, 447 / 405).
 int gemm_bf16_variant(int64_t n_rows, int E, int N, int K, int num_cus)
 {
     const int64_t avg = E > 0 ? n_rows / E : n_rows;
@@ -1169,12 +1199,12 @@ int gemm_bf16_variant(int64_t n_rows, int E, int N, int K, int num_cus)
     if (gemm_ring_ok(n_rows, N, K) && (fills || streams)) return 8;
     if (avg >= 192) return gemm_ring_addresses(n_rows, N, K) ? 10 : 9;
     const int small = avg >= kNtRows ? 4 : avg >= kNtSoleRows ? 5 : 3;
-    if (4 * panels <= num_cus && whole) {
+    if (4 * panels <= num_cus) {
         if (8 * panels > num_cus) return avg >= 96 ? 10 : avg >= 8 ? 2 : small;
         return 16 * panels > num_cus ? (avg > 128 ? 10 : avg > 32 ? 2 : small) : (avg > 64 ? 2 : small);
     }
-    if (4 * panels <= num_cus) return avg >= 48 ? 10 : small;
     if (whole && !heavy && avg < 64) return avg >= 34 ? 2 : small;
+    if (!whole && avg < 56) return avg >= 30 ? 2 : small;
     return avg >= 30 ? 10 : small;
 }
 
@@ -1247,13 +1277,9 @@ int launch_gemm_bf16(const GemmParams &p, bool grouped, int variant, bool out_f3
         // these, even, skewed (0.8): 8 experts 1024 -> 4096, 150 rows 69 / 58, 73 / 61; 4 experts 2048 -> 8192, 150 rows 118 / 101, 126 / 105; 4
         // experts 1024 -> 4096, 300 rows 67 / 56, 67 / 56; 8 experts 512 -> 2048, 250 rows 37 / 32, 39 / 35.  Without the half: 8 experts 1024 ->
         // 4096, 240 rows 72 / 61, 82 / 98; 8 experts 2048 -> 8192, 100 rows 141 / 124, 156 / 184.
-        if (p.K % BK == 0 && few_tiles(p, 128, 64, 1.5, 1, num_cus)) return launch_grouped_dtl<128, 64, 2, 2, 2, 4, NT_NONE, 0>(p, relu, num_cus, s);
+        if (few_tiles(p, 128, 64, 1.5, 1, num_cus)) return launch_grouped_dtl<128, 64, 2, 2, 2, 4, NT_NONE, 0>(p, relu, num_cus, s);
         return launch_grouped<128, 128, 2, 2, 2, REG_STAGED>(p, relu, num_cus, s);
     case 2:
-        if (p.K % BK != 0) {
-            set_error("64x128 tiles need K (%d) to be a multiple of %d", p.K, BK);
-            return MOE_ERR_UNSUPPORTED;
-        }
         // With a tile or two per CU its time is that of the K loop, whose loads are as far ahead as the LDS has stages and which
         // narrower tiles share among more blocks.  FFN in us, 64x128 in two stages / in three / 64x64 in four, even, skewed (0.8): 8 experts
         // 2048 -> 8192, 64 rows 160 / 126 / 108, 168 / 132 / 141; 16 experts 1024 -> 4096, 48 rows 91 / 72 / 62, 95 / 76 / 79; 12
@@ -1271,11 +1297,14 @@ int launch_gemm_bf16(const GemmParams &p, bool grouped, int variant, bool out_f3
     case 44: return launch_grouped_dtl<32, 256, 1, 4, 2, 3, NT_NONE, 4>(p, relu, num_cus, s);
     case 48: return launch_grouped_dtl<64, 256, 1, 4, 2, 3, NT_NONE, 4>(p, relu, num_cus, s);
     case 3: case 4: case 5:
-        if (p.K % BK != 0)
+        // K that ends inside a K tile: weight rows then begin inside a line, and the loads in flight in registers are as good (47 experts
+        // 1496 -> 4504, 8 and 20 rows 293 / 296, 310 / 314 us register-staged / direct-to-LDS, non-temporal 380, 395), but for
+        // few tiles (24 experts 1000 -> 4000, 16 rows 95 / 89, skewed 103 / 98)
+        if (p.K % BK != 0 && !few_tiles(p, 32, 128, 1, 1.5, num_cus))
             return relu ? launch_k<32, 128, 1, 4, false, true, true, false, 2, REG_STAGED>(p, num_cus, s, nullptr)
                         : launch_k<32, 128, 1, 4, false, false, true, false, 2, REG_STAGED>(p, num_cus, s, nullptr);
-        return variant == 3 ? launch_grouped_dtl<32, 128, 1, 4, 2, 2, NT_ALL, 0>(p, relu, num_cus, s)
-               : variant == 5 ? launch_grouped_dtl<32, 128, 1, 4, 2, 2, NT_SOLE, 0>(p, relu, num_cus, s)
+        return variant == 3 && p.K % BK == 0 ? launch_grouped_dtl<32, 128, 1, 4, 2, 2, NT_ALL, 0>(p, relu, num_cus, s)
+               : variant == 5 && p.K % BK == 0 ? launch_grouped_dtl<32, 128, 1, 4, 2, 2, NT_SOLE, 0>(p, relu, num_cus, s)
                // as the 64-row tiles, two stages / four: 8 experts 2048 -> 8192, 40 rows 158 / 113, 171 / 131; 16 experts 2048 -> 8192, 20
                // rows 209 / 189, 229 / 236; 16 experts 1024 -> 4096, 36 rows 88 / 66, 95 / 73
                : few_tiles(p, 32, 128, 1, 1.5, num_cus) ? launch_grouped_dtl<32, 128, 1, 4, 2, 4, NT_NONE, 0>(p, relu, num_cus, s)

@@ -1,11 +1,14 @@
 """Expert GEMMs with a tile or two per CU (few_tiles, gemm_bf16.hip): narrower tiles and more LDS stages.  Row counts around the tiles'
 edges, K of one K tile and of fewer than the stages, K loops that go round K, idle experts, biases; and the choice around its lines."""
 import pytest
+import torch
 
+from paper_2303_06182_amd import binding
 from helpers import expert_tile_shape
 from test_gpu_tile_shapes import ragged, run
 
 EDGES = [0, 1, 31, 32, 33, 63, 64, 65]
+MORE = [0, 1, 31, 200, 33, 129, 64, 127]
 
 
 @pytest.mark.gpu
@@ -17,9 +20,28 @@ EDGES = [0, 1, 31, 32, 33, 63, 64, 65]
     ("128x128", 8, 1024, 1024, [0, 1, 127, 128, 129, 257, 255, 256], 0, 0),   # 128x64
     ("128x128", 8, 1024, 576, [600, 127, 128, 129, 257, 255, 0, 700], 0, 0),
     ("128x128", 12, 64, 384, EDGES + [600, 900, 700, 1000], 0, 0),
-    ("32x128", 16, 2048, 2112, EDGES[:6], 16, 32)])   # four stages in both GEMMs
+    ("32x128", 16, 2048, 2112, EDGES[:6], 16, 32),   # four stages in both GEMMs
+    # K that ends inside a K tile: 64 columns and four stages, 128 and three, 128 and two, 128x64, 32x128 and four stages
+    ("64x128", 16, 1000, 1096, EDGES, 10, 60), ("64x128", 8, 72, 264, MORE, 0, 0), ("64x128", 8, 200, 1992, MORE, 0, 0),
+    ("64x128", 40, 1000, 1096, EDGES, 40, 50), ("128x128", 8, 1000, 1000, [0, 1, 127, 128, 129, 257, 255, 256], 0, 0),
+    ("32x128", 24, 1000, 1992, EDGES, 6, 20)])
 def test_ffn(shape, E, D, F, edges, lo, hi):
     run(shape, ragged(E, edges, lo, hi, 5) if hi else edges, D, F)
+
+
+@pytest.mark.gpu
+def test_nothing_past_k_is_multiplied():
+    """Every other row of an expert's batch is infinite: what its row's neighbour has behind the end of K."""
+    E, D, F, n = 8, 200, 328, 48
+    g = torch.Generator(device="cuda").manual_seed(9)
+    t = lambda s, std: torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=g)
+    xp, w1, w2 = t((E * n, D), 1.0), t((E, F, D), D ** -0.5), t((E, D, F), F ** -0.5)
+    assert expert_tile_shape(E * n, E, F, D) in ("64x128", "32x128")
+    m = binding.MoeLayer(E * n, D, F, E, 1, "bf16")
+    offsets = torch.arange(0, E * n + 1, n, dtype=torch.int32, device="cuda")
+    want = m.moe_expert_ffn(xp, offsets, w1, w2)
+    xp[1::2] = float("inf")
+    assert torch.equal(m.moe_expert_ffn(xp, offsets, w1, w2)[::2], want[::2])
 
 
 @pytest.mark.parametrize("E,D,F,rows,shape", [
@@ -29,6 +51,7 @@ def test_ffn(shape, E, D, F, edges, lo, hi):
     (8, 1024, 4096, 129, "128x128"), (8, 512, 2048, 64, "32x128"), (8, 512, 2048, 65, "64x128"), (8, 512, 2048, 191, "64x128"),
     (8, 512, 2048, 192, "128x128"),
     # K that ends inside a K tile
-    (8, 1000, 4000, 47, "32x128"), (8, 1000, 4000, 48, "128x128")])
+    (8, 1000, 4000, 32, "32x128"), (8, 1000, 4000, 33, "64x128"), (8, 1000, 4000, 128, "64x128"), (8, 1000, 4000, 129, "128x128"),
+    (24, 1000, 4000, 29, "32x128"), (24, 1000, 4000, 30, "64x128"), (24, 1000, 4000, 55, "64x128"), (24, 1000, 4000, 56, "128x128")])
 def test_choice(E, D, F, rows, shape):
     assert expert_tile_shape(E * rows, E, F, D) == shape
