@@ -222,7 +222,7 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
     // (Kept in registers instead, the refill every 8th K tile made the compiler wait for the load it had
     // just issued -- a full memory latency with the whole operand pipeline drained.)
     uint8_t *sS = reinterpret_cast<uint8_t *>(sB + NSTAGE * BTILE);
-    static_assert(!B4 || BN * 16 == (THREADS / 64) * 1024, "one 1 KB scale load per wave covers the tile's rows");
+    static_assert(!B4 || (BN % 64 == 0 && BN / 64 <= THREADS / 64), "a 1 KB scale load of a wave covers 64 of the tile's columns");
     int c_buf = 0;
     auto compute = [&](int cur, int kt) {
         const uint16_t *cA = sA + cur * BM * BK + (wm * WTM + frag_row) * BK;
@@ -829,8 +829,9 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
         };
         auto issue_scales = [&]() {
             if constexpr (B4) {
-                __builtin_amdgcn_global_load_lds((const glb_void *)(s_lane + s_grp * 512),
-                                                 (lds_void *)(sS + s_buf * (BN * 16) + wave * 1024), 16, 0, 0);
+                if (BN / 64 == THREADS / 64 || __builtin_amdgcn_readfirstlane(wave) < BN / 64)
+                    __builtin_amdgcn_global_load_lds((const glb_void *)(s_lane + s_grp * 512),
+                                                     (lds_void *)(sS + s_buf * (BN * 16) + wave * 1024), 16, 0, 0);
                 s_buf ^= 1;
                 if (++s_grp == s_groups) {  // on to the next tile of this block, if there is one
                     s_grp = 0;
@@ -1294,8 +1295,17 @@ int launch_gemm_bf16(const GemmParams &p, bool grouped, int variant, bool out_f3
     case 24: return launch_grouped_dtl<32, 128, 1, 4, 2, 3, NT_NONE, 8>(p, relu, num_cus, s);
     case 25: return launch_grouped_dtl<32, 128, 1, 4, 2, 3, NT_SOLE, 8>(p, relu, num_cus, s);
     case 43: return launch_grouped_dtl<32, 256, 1, 4, 2, 3, NT_ALL, 4>(p, relu, num_cus, s);
-    case 44: return launch_grouped_dtl<32, 256, 1, 4, 2, 3, NT_NONE, 4>(p, relu, num_cus, s);
-    case 48: return launch_grouped_dtl<64, 256, 1, 4, 2, 3, NT_NONE, 4>(p, relu, num_cus, s);
+    case 44:
+        // At most a tile per CU (64-row tiles: one for every other CU): half the columns, and a stage more.  FFN in us, 256 columns / 128, even,
+        // skewed (0.8): 32 rows: 16 experts 2048 -> 8192, 36 rows 137 / 123, 140 / 126; 64 experts 1024 -> 4096, 20 rows 83 / 77, 94 / 85; 32
+        // experts 2048 -> 8192, 30 rows 157 / 147, 182 / 167; 128 experts 512 -> 2048, 20 rows 50 / 47, 61 / 56; 64 rows: 8 experts 2048 ->
+        // 8192, 100 rows 136 / 121, 136 / 121; 16 experts 1024 -> 4096, 100 rows 78 / 70, 78 / 70; 16 experts 2048 -> 8192, 60 rows 143 / 132,
+        // 159 / 163; a tile per CU: 32 experts 2048 -> 8192, 60 rows 199 / 205, 250 / 260.
+        if (few_tiles(p, 32, 256, 1, 1, num_cus)) return launch_grouped_dtl<32, 128, 1, 4, 2, 4, NT_NONE, 4>(p, relu, num_cus, s);
+        return launch_grouped_dtl<32, 256, 1, 4, 2, 3, NT_NONE, 4>(p, relu, num_cus, s);
+    case 48:
+        if (few_tiles(p, 64, 256, 1, 0.5, num_cus)) return launch_grouped_dtl<64, 128, 2, 2, 2, 4, NT_NONE, 4>(p, relu, num_cus, s);
+        return launch_grouped_dtl<64, 256, 1, 4, 2, 3, NT_NONE, 4>(p, relu, num_cus, s);
     case 3: case 4: case 5:
         // K that ends inside a K tile: weight rows then begin inside a line, and the loads in flight in registers are as good (47 experts
         // 1496 -> 4504, 8 and 20 rows 293 / 296, 310 / 314 us register-staged / direct-to-LDS, non-temporal 380, 395), but for

@@ -1,10 +1,13 @@
 """Expert GEMMs with a tile or two per CU (few_tiles, gemm_bf16.hip): narrower tiles and more LDS stages.  Row counts around the tiles'
 edges, K of one K tile and of fewer than the stages, K loops that go round K, idle experts, biases; and the choice around its lines."""
+import numpy as np
 import pytest
 import torch
 
+from oracle import moe_oracle as orc
 from paper_2303_06182_amd import binding
-from helpers import expert_tile_shape
+from helpers import TOL, expert_tile_shape, norm_max_err, to_np, worst_row_rms_rel_err
+from test_gpu_ring_quant import dequantised, setup
 from test_gpu_tile_shapes import ragged, run
 
 EDGES = [0, 1, 31, 32, 33, 63, 64, 65]
@@ -55,3 +58,26 @@ def test_nothing_past_k_is_multiplied():
     (24, 1000, 4000, 29, "32x128"), (24, 1000, 4000, 30, "64x128"), (24, 1000, 4000, 55, "64x128"), (24, 1000, 4000, 56, "128x128")])
 def test_choice(E, D, F, rows, shape):
     assert expert_tile_shape(E * rows, E, F, D) == shape
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("counts,D,F", [
+    ([0, 1, 31, 32, 33, 63, 64, 65] * 2, 2048, 1984),            # 32x128, K of 32 and 31 K tiles
+    ([0, 1, 127, 128, 129, 257, 63, 300], 1024, 1088), ([64, 0, 150, 129, 190], 192, 320)])   # 64x128; K of 16 and 17, 3 and 5
+def test_mxfp4(counts, D, F):
+    print("mxfp4", counts, D, F, flush=True)
+    E, N = len(counts), sum(counts)
+    t, m, (q1, q2, s1, s2) = setup(4, E, D, F, N)
+    offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
+    for e in (e for e, c in enumerate(counts) if c == 0):   # NaN's place in this format: the largest scale
+        q1[e], q2[e], s1[e], s2[e] = 0x77, 0x77, 254, 254
+    xp, b1, b2 = t((N, D), 1.0), t((E, F), 0.5), t((E, D), 0.5)
+    got = to_np(m.moe_expert_ffn_w4(xp, torch.from_numpy(offsets).cuda(), q1, q2, s1, s2, b1, b2))
+    live = [e for e, c in enumerate(counts) if c]
+    d1, d2 = torch.zeros((E, F, D), dtype=torch.bfloat16), torch.zeros((E, D, F), dtype=torch.bfloat16)
+    d1[live], d2[live] = dequantised(4, q1[live], s1[live], F, D), dequantised(4, q2[live], s2[live], D, F)
+    ref = orc.expert_ffn(xp.cpu(), offsets, d1, d2, b1.cpu(), b2.cpu())
+    assert norm_max_err(got, ref) <= TOL["bf16"]   # h and y are each rounded to bf16 once
+    for e in live:
+        part = slice(int(offsets[e]), int(offsets[e + 1]))
+        assert worst_row_rms_rel_err(got[part], ref[part]) <= 2.0 ** -7
