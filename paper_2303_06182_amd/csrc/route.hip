@@ -5,6 +5,8 @@
 // the occurrences of each expert (Sec. 5.1).  The sort here is a counting sort: its result is the
 // stable argsort (ascending token inside each expert) and costs O(N) instead of O(N log N).
 // Nothing uses atomics on global memory, so the permutation is the same on every run.
+#include <type_traits>
+
 #include "moe_internal.h"
 #include "ring_schedule.h"
 
@@ -66,11 +68,13 @@ __device__ __forceinline__ void stage_logits(float *__restrict__ s_row, float *l
 // multiple of 4), so every lane has V/4 float4 loads in flight; slot i of the lane is expert
 // (i/4)*4G + 4*sub + i%4, still ascending with i.
 // One token per group of G lanes: token t, lane sub of the group, its logits at `row`.  s_idx (may be NULL): the selection goes
-// there too.
-template <int G, int V, bool VEC>
-__device__ __forceinline__ void topk_token(int t, bool live, int sub, const float *row, int E, int k, int renorm,
-                                           int32_t *__restrict__ idx, float *__restrict__ w, int *s_idx)
+// there too.  SLICES (VEC only): the lane adds the slices of its words itself, as stage_logits does; parts: the token's.
+template <int G, int V, bool VEC, bool SLICES = false>
+__device__ __forceinline__ void topk_token(int t, bool live, int sub, std::conditional_t<SLICES, float, const float> *row, int E, int k,
+                                           int renorm, int32_t *__restrict__ idx, float *__restrict__ w, int *s_idx, int n_parts = 1,
+                                           const float *__restrict__ parts = nullptr, int64_t part_stride = 0)
 {
+    static_assert(VEC || !SLICES, "scalar rows are staged");
     const float NEG_INF = -__builtin_huge_valf();
     auto expert_of = [&](int i) { return VEC ? (i >> 2) * (4 * G) + 4 * sub + (i & 3) : sub + i * G; };
 
@@ -80,7 +84,28 @@ __device__ __forceinline__ void topk_token(int t, bool live, int sub, const floa
         for (int q = 0; q < V / 4; ++q) {
             const int e0 = (q * G + sub) * 4;
             float4 f = make_float4(NEG_INF, NEG_INF, NEG_INF, NEG_INF);
-            if (live && e0 < E) f = *reinterpret_cast<const float4 *>(row + e0);
+            if (live && e0 < E) {
+                f = *reinterpret_cast<const float4 *>(row + e0);
+                if constexpr (SLICES) {
+                    if (n_parts > 1) {  // uniform over the grid; all slices are requested before the first is added
+                        float4 g[kMaxLogitParts - 1];
+#pragma unroll
+                        for (int sp = 1; sp < kMaxLogitParts; ++sp)
+                            g[sp - 1] = sp < n_parts ? *reinterpret_cast<const float4 *>(parts + (sp - 1) * part_stride + e0)
+                                                     : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+                        for (int sp = 1; sp < kMaxLogitParts; ++sp) {
+                            if (sp < n_parts) {
+                                f.x += g[sp - 1].x;
+                                f.y += g[sp - 1].y;
+                                f.z += g[sp - 1].z;
+                                f.w += g[sp - 1].w;
+                            }
+                        }
+                        *reinterpret_cast<float4 *>(row + e0) = f;
+                    }
+                }
+            }
             v[(4 * q + 0) % V] = f.x;
             v[(4 * q + 1) % V] = f.y;
             v[(4 * q + 2) % V] = f.z;
@@ -714,17 +739,24 @@ static int route_block_threads(int64_t items, int E, int64_t n_assign)
 
 // Top-k of a decoder step and its routing in one launch: 1024 / G tokens fit the block, their logits and selection stay in LDS.
 // Bound by latency: a dependent launch costs about 4.5 us here whatever it does.
-template <int G, int V, bool VEC>
+// STAGED: batches of at most a word per thread.  With more the lanes add their own slices, whose loads the compiler has in flight
+// together (512 experts 512 -> 2048, 32 tokens, layer 73.5 us staged, 71.0 this way; 128 experts 1024 -> 4096, 52 tokens 60.3 / 59.2).
+template <int G, int V, bool VEC, bool STAGED>
 __global__ __launch_bounds__(1024) void route_topk_kernel(float *logits, int T, int E, int k, int renorm, int32_t *__restrict__ idx,
                                                           float *__restrict__ w, int n_parts, const float *__restrict__ parts,
                                                           int64_t part_stride, RouteOut o)
 {
-    __shared__ __align__(16) float s_logits[1024 * V];
     __shared__ int s_idx[kSmallRouteMax];
-    stage_logits<VEC>(s_logits, logits, T * E, n_parts, parts, part_stride);
-    __syncthreads();
     const int t = threadIdx.x / G;
-    topk_token<G, V, VEC>(t, t < T, threadIdx.x % G, s_logits + t * E, E, k, renorm, idx, w, s_idx);
+    if constexpr (STAGED) {
+        __shared__ __align__(16) float s_logits[1024 * (VEC ? 4 : V)];
+        stage_logits<VEC>(s_logits, logits, T * E, n_parts, parts, part_stride);
+        __syncthreads();
+        topk_token<G, V, VEC>(t, t < T, threadIdx.x % G, s_logits + t * E, E, k, renorm, idx, w, s_idx);
+    } else {
+        const int64_t at = (int64_t)t * E;
+        topk_token<G, V, VEC, true>(t, t < T, threadIdx.x % G, logits + at, E, k, renorm, idx, w, s_idx, n_parts, parts + at, part_stride);
+    }
     __syncthreads();
     route_small(s_idx, T * k, E, k, o.counts, o.offsets, o.dst_row, o.src_tok, o.tile_bm, o.tile_expert, o.tile_row, o.num_tiles,
                 o.max_m_tiles, o.ring_n1, o.ring_n2);
@@ -741,7 +773,15 @@ static int launch_route_topk_t(float *logits, int T, int E, int k, int renorm, i
     ProfScope ps("route", s);
     const int64_t words = (int64_t)T * E / (VEC ? 4 : 1), lanes = (int64_t)T * G;
     const int threads = route_block_threads(words > lanes ? words : lanes, E, (int64_t)T * k);
-    hipLaunchKernelGGL((route_topk_kernel<G, V, VEC>), dim3(1), dim3(threads), 0, s, logits, T, E, k, renorm, idx, w, n_parts, parts,
+    if constexpr (VEC && V > 4) {
+        if (words > 1024) {
+            hipLaunchKernelGGL((route_topk_kernel<G, V, VEC, false>), dim3(1), dim3(threads), 0, s, logits, T, E, k, renorm, idx, w, n_parts,
+                               parts, part_stride, o);
+            MOE_LAUNCH_CHECK("route_topk_kernel");
+            return MOE_OK;
+        }
+    }
+    hipLaunchKernelGGL((route_topk_kernel<G, V, VEC, true>), dim3(1), dim3(threads), 0, s, logits, T, E, k, renorm, idx, w, n_parts, parts,
                        part_stride, o);
     MOE_LAUNCH_CHECK("route_topk_kernel");
     return MOE_OK;
