@@ -57,12 +57,14 @@ def profile_kernel_name(kernel: str):
         if not grouped:
             return "gate_gemm" if (out_f32 or k.startswith("gemm_f32")) else None
         return "expert_gemm1" if relu else "expert_gemm2"
-    if k.startswith("gemm_ring_kernel<"):  # <RELU, RAGGED>
+    if k.startswith("gemm_ring_kernel<"):  # <RELU, RAGGED, weight storage, TURNED>
+        if [a.strip() for a in k[k.index("<") + 1:].rstrip(">").split(",")][2:3] not in ([], ["0"]):
+            return None  # quantised weights
         return "expert_gemm1" if k[k.index("<") + 1:].startswith("true") else "expert_gemm2"
     if k.startswith("gemm_stream_kernel<"):  # <weight storage, RELU, ...>
         args = [a.strip() for a in k[k.index("<") + 1:].rstrip(">").split(",")]
         return None if args[0] != "0" else "expert_gemm1" if args[1] == "true" else "expert_gemm2"
-    for prefix, name in (("gate_topk_kernel", "gate_topk"), ("topk_kernel", "topk"), ("route_", "route"),
+    for prefix, name in (("gate_topk_", "gate_topk"), ("topk_kernel", "topk"), ("route_", "route"),
                          ("dispatch_kernel", "dispatch"), ("combine_kernel", "combine"), ("tile_map_kernel", "tile_map")):
         if k.startswith(prefix):
             return name
