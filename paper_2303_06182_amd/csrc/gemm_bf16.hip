@@ -70,6 +70,13 @@ static constexpr int NT_NONE = 0, NT_ALL = 1, NT_SOLE = 2;
 // What direct-to-LDS loads take for the 16-byte chunks past the end of K
 __device__ __align__(16) static const uint16_t chunk_of_zeros[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 
+// 4-bit weights: whether the block scales of a group of 8 K tiles may still be in flight when it begins, so that the K loop has
+// to wait for them.  They are requested as the group before begins, in front of that K tile's operand loads, and the wait
+// that ends a K tile leaves those of the newest stages - 2 K tiles in flight: stages - 2 K tiles have to pass.  The shortest group
+// is a tile's last one.
+__host__ __device__ constexpr bool scales_in_flight(int KT, int stages) { return ((KT - 1) & 7) + 1 < stages - 2; }
+bool gemm_bf16_scales_in_flight(int KT, int stages) { return scales_in_flight(KT, stages); }
+
 struct TileInfo {
     int row0, row_end, expert, n0;
     int row_begin;  // the expert's first row (NT_SOLE only)
@@ -818,10 +825,12 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
         // One load instruction per wave fills 64 rows x 16 bytes of the buffer: lane L fetches the 16 bytes
         // of row 64 * wave + L (row group 2 * wave + L / 32 of the tile, row L % 32 of that group's 512-byte
         // block).  These loads are older than the operand loads issued after them, and loads complete in
-        // order, so the per-iteration vmcnt wait covers them once two iterations have passed.
+        // order, so the per-iteration vmcnt wait covers them once enough iterations have passed (scales_in_flight).
         int s_seq = seq, s_grp = 0, s_buf = 0;
         const uint8_t *s_lane = nullptr;
         const int s_groups = (KT + 7) >> 3;  // 16-byte scale groups per weight row
+        const bool s_drain = scales_in_flight(KT, STAGES);
+        (void)s_drain;
         auto scale_tile = [&]() {
             const TileInfo ts = tile_info(s_seq);
             const int rg = min((ts.n0 + wave * 64 + (lane >> 5) * 32) >> 5, p.N / 32 - 1);
@@ -857,9 +866,7 @@ __global__ __launch_bounds__(WM *WN * 64, MINB) void gemm_bf16_kernel(GemmParams
             for (int kt = 0; kt < KT; ++kt) {
                 if constexpr (B4) {
                     if ((kt & 7) == 0 && (kt > 0 || seq != (int)(blockIdx.x >> 3))) {  // a new group of 8 K tiles
-                        if (KT < STAGES) {
-                            // groups shorter than the pipeline is deep: the scales requested one group ago
-                            // may not have landed yet
+                        if (s_drain) {
                             asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
                             stage_barrier();
                         }
