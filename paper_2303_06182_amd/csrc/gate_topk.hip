@@ -554,24 +554,28 @@ bool gate_topk_fused_ok(int dtype, int T, int E, int K)
 }
 
 // Groups of 32 rows in a tile of gate_topk_wide_kernel's, 0: not for this kernel
-static int gate_topk_wide(int T, int E, int num_cus)
+static int gate_topk_wide(int T, int E, int K, int num_cus)
 {
+    // One column block and a short K loop: the selection by two lanes a token costs more than the loop gains.  us, a wave per 32 rows / this: 4096
+    // tokens, 32 experts, 64 dimensions 4.8 / 5.6, 256 5.5 / 6.1, 512 6.5 / 6.7, 768 7.5 / 7.3; 16 experts, 256 dimensions 5.5 / 5.8, 512 6.5 /
+    // 6.5; 12000 tokens, 32 experts, 64 dimensions 5.0 / 5.4, 256 5.8 / 5.9
+    if (E <= 32 && K <= (T <= 32 * num_cus ? 512 : 256)) return 0;
     // 128 rows: 20000 tokens, 2048 dimensions, 128 experts 40.8 / 31.1 us, 32768 tokens 38.1 / 39.5; 25000 tokens, 16 experts 14.0 / 13.8
     return T <= 32 * num_cus ? 1 : T <= 64 * num_cus ? 2 : T <= 96 * num_cus && E > 64 ? 4 : 0;
 }
 
-// Tokens per tile (= tokens per histogram row) the fused kernel uses for T tokens and E experts: the tallest
-// of 256, 128, 64, 32 rows that still gives every CU a tile and whose wave count divides the weight tile's
-// load instructions.
-int gate_topk_tile_tokens(int T, int E, int num_cus)
+// Tokens per tile (= tokens per histogram row) the fused kernel uses for T tokens, E experts and K dimensions: the wide kernel's where it
+// runs, else the tallest of 256, 128, 64, 32 rows that still gives every CU a tile and whose wave count divides the weight
+// tile's load instructions (32 rows: only where the wide kernel leaves small batches to it).
+int gate_topk_tile_tokens(int T, int E, int K, int num_cus)
 {
     const int ni = ceil_div(E, 32);
-    if (gate_topk_wide(T, E, num_cus)) return 32 * gate_topk_wide(T, E, num_cus);
+    if (gate_topk_wide(T, E, K, num_cus)) return 32 * gate_topk_wide(T, E, K, num_cus);
     for (int waves = 8; waves > 1; waves >>= 1) {
         if ((ni * 4) % waves != 0) continue;
         if (ceil_div(T, 32 * waves) >= num_cus) return 32 * waves;
     }
-    return 64;
+    return 32;
 }
 
 int launch_gate_topk(const void *x, const void *wg, const float *gate_bias, int T, int E, int K, int k, int renorm,
@@ -591,9 +595,9 @@ int launch_gate_topk(const void *x, const void *wg, const float *gate_bias, int 
     p.k = k;
     p.renorm = renorm;
     const int ni = ceil_div(E, 32);
-    const int waves = gate_topk_tile_tokens(T, E, num_cus) / 32;
+    const int waves = gate_topk_tile_tokens(T, E, K, num_cus) / 32;
     // stages: more of them make the start longer and the loop no shorter (4096 tokens above, 4 / 8: 13.5 / 14.2 us; 64 rows, 3 / 6: 22.1 / 20.9)
-    if (const int rg = gate_topk_wide(T, E, num_cus)) {
+    if (const int rg = gate_topk_wide(T, E, K, num_cus)) {
         switch (rg * 10 + ni) {
         case 11: return launch_gate_topk_wide<1, 1, 9>(p, s);
         case 12: return launch_gate_topk_wide<1, 2, 6>(p, s);
@@ -620,6 +624,7 @@ int launch_gate_topk(const void *x, const void *wg, const float *gate_bias, int 
     case 23: MOE_GT(2, 3, 3);
     case 22: MOE_GT(2, 2, 3);
     case 21: MOE_GT(2, 1, 3);
+    case 11: MOE_GT(1, 1, 4);
     default: break;
     }
 #undef MOE_GT

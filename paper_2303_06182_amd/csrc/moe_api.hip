@@ -281,7 +281,7 @@ static int do_gate_topk(moe_handle_t *h, const void *x, const void *wg, const fl
         const bool want_hist = hist && hist_tokens && route_uses_hist(T, c.k);
         int rc = launch_gate_topk(x, wg, gate_bias, T, c.E, c.D, c.k, c.renormalize, logits_req, idx, w,
                                   want_hist ? hist : nullptr, h->num_cus, s);
-        if (rc == MOE_OK && want_hist) *hist_tokens = gate_topk_tile_tokens(T, c.E, h->num_cus);
+        if (rc == MOE_OK && want_hist) *hist_tokens = gate_topk_tile_tokens(T, c.E, c.D, h->num_cus);
         return rc;
     }
     float *logits = logits_req ? logits_req : logits_ws;
