@@ -68,13 +68,12 @@ __device__ __forceinline__ void stage_logits(float *__restrict__ s_row, float *l
 // multiple of 4), so every lane has V/4 float4 loads in flight; slot i of the lane is expert
 // (i/4)*4G + 4*sub + i%4, still ascending with i.
 // One token per group of G lanes: token t, lane sub of the group, its logits at `row`.  s_idx (may be NULL): the selection goes
-// there too.  SLICES (VEC only): the lane adds the slices of its words itself, as stage_logits does; parts: the token's.
+// there too.  SLICES: the lane adds the slices of its words itself, as stage_logits does; parts: the token's.
 template <int G, int V, bool VEC, bool SLICES = false>
 __device__ __forceinline__ void topk_token(int t, bool live, int sub, std::conditional_t<SLICES, float, const float> *row, int E, int k,
                                            int renorm, int32_t *__restrict__ idx, float *__restrict__ w, int *s_idx, int n_parts = 1,
                                            const float *__restrict__ parts = nullptr, int64_t part_stride = 0)
 {
-    static_assert(VEC || !SLICES, "scalar rows are staged");
     const float NEG_INF = -__builtin_huge_valf();
     auto expert_of = [&](int i) { return VEC ? (i >> 2) * (4 * G) + 4 * sub + (i & 3) : sub + i * G; };
 
@@ -115,7 +114,22 @@ __device__ __forceinline__ void topk_token(int t, bool live, int sub, std::condi
 #pragma unroll
         for (int i = 0; i < V; ++i) {
             const int e = sub + i * G;
-            v[i] = live && e < E ? row[e] : NEG_INF;
+            v[i] = NEG_INF;
+            if (live && e < E) {
+                float f = row[e];
+                if constexpr (SLICES) {
+                    if (n_parts > 1) {
+                        float g[kMaxLogitParts - 1];
+#pragma unroll
+                        for (int sp = 1; sp < kMaxLogitParts; ++sp) g[sp - 1] = sp < n_parts ? parts[(sp - 1) * part_stride + e] : 0.f;
+#pragma unroll
+                        for (int sp = 1; sp < kMaxLogitParts; ++sp)
+                            if (sp < n_parts) f += g[sp - 1];
+                        row[e] = f;
+                    }
+                }
+                v[i] = f;
+            }
         }
     }
     uint32_t taken = 0;  // bit i: register slot i already selected (or beyond E)
@@ -192,8 +206,15 @@ __device__ __forceinline__ void topk_token(int t, bool live, int sub, std::condi
     }
 }
 
-// PARTS: the logits are the gate GEMM's slices
-template <int G, int V, bool VEC, bool PARTS>
+// Where the logits are the gate GEMM's slices, who adds them: all threads into LDS, or the lanes of the selection.
+// Staged, the slices of a word are one thread's; the lanes have the loads of all their words under way at once, and no barrier.
+// Gate and top-k in us, lanes / staged: 200 tokens, 127 experts, 4 slices 9.2 / 9.7, 8 slices 9.7 / 10.1, 16 slices 11.8 / 10.7; 250 experts 10.6 / 11.1,
+// 11.5 / 11.9, 14.5 / 13.7 (one token 21.7 / 21.1 a layer call); 32 experts 7.6 / 7.9, 7.9 / 8.2, 8.2 / 8.4; 256 experts 11.8 / 11.7, 12.9 / 12.7, 15.2 / 14.7.
+enum { PARTS_NONE, PARTS_LANES, PARTS_STAGED };
+template <int G, int V, bool VEC>
+static bool topk_stages(int T, int n_parts) { return n_parts > 8 || (VEC && V >= 8) || T <= 2; }
+
+template <int G, int V, bool VEC, int PARTS>
 __global__ __launch_bounds__(kThreads) void topk_kernel(float *logits, int T, int E, int k, int renorm,
                                                         int32_t *__restrict__ idx, float *__restrict__ w,
                                                         int n_parts, const float *__restrict__ parts,
@@ -201,17 +222,18 @@ __global__ __launch_bounds__(kThreads) void topk_kernel(float *logits, int T, in
 {
     constexpr int TPB = kThreads / G;
     const int t0 = blockIdx.x * TPB, local = threadIdx.x / G, t = t0 + local;
-    const float *row;
-    if constexpr (PARTS) {
+    if constexpr (PARTS == PARTS_STAGED) {
         __shared__ __align__(16) float s_logits[TPB * G * V];
         const int64_t at = (int64_t)t0 * E;
         stage_logits<VEC>(s_logits, logits + at, min(TPB, T - t0) * E, n_parts, parts + at, part_stride);
         __syncthreads();
-        row = s_logits + local * E;
+        topk_token<G, V, VEC>(t, t < T, threadIdx.x % G, s_logits + local * E, E, k, renorm, idx, w, nullptr);
+    } else if constexpr (PARTS == PARTS_LANES) {
+        const int64_t at = (int64_t)t * E;
+        topk_token<G, V, VEC, true>(t, t < T, threadIdx.x % G, logits + at, E, k, renorm, idx, w, nullptr, n_parts, parts + at, part_stride);
     } else {
-        row = logits + (int64_t)t * E;
+        topk_token<G, V, VEC>(t, t < T, threadIdx.x % G, logits + (int64_t)t * E, E, k, renorm, idx, w, nullptr);
     }
-    topk_token<G, V, VEC>(t, t < T, threadIdx.x % G, row, E, k, renorm, idx, w, nullptr);
 }
 
 template <int G, int V, bool VEC>
@@ -220,12 +242,9 @@ static int launch_topk_t(float *logits, int T, int E, int k, int renorm, int32_t
 {
     const int tpb = kThreads / G;
     ProfScope ps("topk", s);
-    if (n_parts > 1)
-        hipLaunchKernelGGL((topk_kernel<G, V, VEC, true>), dim3(ceil_div(T, tpb)), dim3(kThreads), 0, s, logits, T, E, k, renorm,
-                           idx, w, n_parts, parts, part_stride);
-    else
-        hipLaunchKernelGGL((topk_kernel<G, V, VEC, false>), dim3(ceil_div(T, tpb)), dim3(kThreads), 0, s, logits, T, E, k, renorm,
-                           idx, w, 1, nullptr, 0);
+    const auto kern = n_parts <= 1 ? topk_kernel<G, V, VEC, PARTS_NONE>
+                      : topk_stages<G, V, VEC>(T, n_parts) ? topk_kernel<G, V, VEC, PARTS_STAGED> : topk_kernel<G, V, VEC, PARTS_LANES>;
+    hipLaunchKernelGGL(kern, dim3(ceil_div(T, tpb)), dim3(kThreads), 0, s, logits, T, E, k, renorm, idx, w, n_parts, parts, part_stride);
     MOE_LAUNCH_CHECK("topk_kernel");
     return MOE_OK;
 }
