@@ -758,8 +758,9 @@ static int route_block_threads(int64_t items, int E, int64_t n_assign)
 
 // Top-k of a decoder step and its routing in one launch: 1024 / G tokens fit the block, their logits and selection stay in LDS.
 // Bound by latency: a dependent launch costs about 4.5 us here whatever it does.
-// STAGED: batches of at most a word per thread.  With more the lanes add their own slices, whose loads the compiler has in flight
-// together (512 experts 512 -> 2048, 32 tokens, layer 73.5 us staged, 71.0 this way; 128 experts 1024 -> 4096, 52 tokens 60.3 / 59.2).
+// STAGED: lanes with several words each (V > 4), and batches of at most a word per thread.  Else the lanes add their own slices, whose
+// loads the compiler has in flight together.  Layer in us, lanes / staged: 512 experts 512 -> 2048, 32 tokens 71.0 / 73.5; 128 experts 1024 ->
+// 4096, 52 tokens 59.2 / 60.3; 64 experts 1024 -> 64, 64 tokens 24.2 / 25.0, 2048 -> 64 28.6 / 29.4.
 template <int G, int V, bool VEC, bool STAGED>
 __global__ __launch_bounds__(1024) void route_topk_kernel(float *logits, int T, int E, int k, int renorm, int32_t *__restrict__ idx,
                                                           float *__restrict__ w, int n_parts, const float *__restrict__ parts,
@@ -792,17 +793,19 @@ static int launch_route_topk_t(float *logits, int T, int E, int k, int renorm, i
     ProfScope ps("route", s);
     const int64_t words = (int64_t)T * E / (VEC ? 4 : 1), lanes = (int64_t)T * G;
     const int threads = route_block_threads(words > lanes ? words : lanes, E, (int64_t)T * k);
-    if constexpr (VEC && V > 4) {
-        if (words > 1024) {
+    if constexpr (VEC) {
+        if (V <= 4 || words > 1024) {
             hipLaunchKernelGGL((route_topk_kernel<G, V, VEC, false>), dim3(1), dim3(threads), 0, s, logits, T, E, k, renorm, idx, w, n_parts,
                                parts, part_stride, o);
             MOE_LAUNCH_CHECK("route_topk_kernel");
             return MOE_OK;
         }
     }
-    hipLaunchKernelGGL((route_topk_kernel<G, V, VEC, true>), dim3(1), dim3(threads), 0, s, logits, T, E, k, renorm, idx, w, n_parts, parts,
-                       part_stride, o);
-    MOE_LAUNCH_CHECK("route_topk_kernel");
+    if constexpr (!VEC || V > 4) {
+        hipLaunchKernelGGL((route_topk_kernel<G, V, VEC, true>), dim3(1), dim3(threads), 0, s, logits, T, E, k, renorm, idx, w, n_parts, parts,
+                           part_stride, o);
+        MOE_LAUNCH_CHECK("route_topk_kernel");
+    }
     return MOE_OK;
 }
 
