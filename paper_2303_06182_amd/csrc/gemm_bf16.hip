@@ -1044,6 +1044,8 @@ static int launch_grouped_dtl(const GemmParams &p, bool relu, int num_cus, hipSt
 static constexpr int kNtRows = 8, kNtSoleRows = 2;
 // Weights of one GEMM (all experts) from which on its time is that of streaming them
 static constexpr int64_t kHeavyWeights = 1ll << 29;
+// ... and below which it is that of its launch and of one tile
+static constexpr int64_t kLightWeights = 3ll << 23;
 
 // Quantised weights on tiles cut to an expert's rows (28: e4m3, 49: mxfp4; gemm_ring.hip), which take a tile's weights once for up to
 // 256 rows where the small tiles take them, and widen them, once for 64: from so many rows per expert on, and so much
@@ -1178,21 +1180,30 @@ int gemm_bf16_variant_block_m(int v)
 //    309, 329 / 281 / 302; 16 experts 2048 -> 8192, 48 rows 292 / 291 / 279, 319 / 298 / 285, 310 / 297 / 323; at 64 rows
 //    128x128 has caught up (342 / 320 / 284, 332 / 311 / 309, 342 / 308 / 338).
 //    With 64 panels or fewer the 64-row tiles have the chip to themselves, as narrow ones with more stages (launch_gemm_bf16), and
-//    take over from the streaming kernel and from 128x128, small / 2 / 10, even, skewed (0.8).  33 to 64 panels, from 8 to 95 rows: 8
+//    take over from the streaming kernel and from 128x128, small / 2 / 10, even, skewed (0.8).  33 to 64 panels, from 8 to 95 rows (they
+//    lose where half of the experts are idle and the others even, which the host does not see: 16 experts 1024 -> 4096, 8 rows 37 / 42, 16 rows
+//    42 / 43; 4 experts 4096 -> 14336, 8 rows 108 / 119): 8
 //    experts 2048 -> 8192, 6 rows 98 / 102, 108 / 102; 8 rows 102 / 102, 113 / 102; 18 rows 107 / 100, 144 / 100; 84 rows - / 147 / 148, - / 153 /
 //    173; 100 rows - / 147 / 142, - / 160 / 157; 16 experts 1024 -> 4096, 8 rows 58 / 58, 77 / 58; 32 experts 512 -> 2048, 20 rows 39 / 38, 46 / 44;
 //    80 rows - / 50 / 49, - / 54 / 55.  17 to 32 panels, where the streaming kernel has short rounds while an expert has one of its tiles, from 33 to
 //    128 rows: 8 experts 1024 -> 4096, 28 rows 39 / 44, 56 / 48; 33 rows 56 / 44, 57 / 49; 90 rows 69 / 53 / 68, 76 / 53 / 76; 150 rows - / 62 /
 //    58, - / 67 / 61; 2 experts 4096 -> 14336, 40 rows 168 / 122, 165 / 123.  16 and fewer, from 65 to 191: 8 experts 512 -> 2048, 50 rows 20 / 23, 21 /
 //    24; 65 rows 29 / 24, 29 / 25; 250 rows - / 28 / 32, - / 35 / 35; 4 experts 1024 -> 4096, 80 rows 52 / 41, 51 / 41; 300 rows - / 59 / 56, - / 60 / 56.
+//    33 to 64 panels of few weights: from 17 rows (small / 2, mean over even, skewed and half idle batches: 100 experts 128 -> 512, 8 rows 12.5 /
+//    13.4, 24 rows 14.3 / 13.9; 64 experts 192 -> 768, 8 rows 15.5 / 16.8; 40 experts 320 -> 1280, 12 rows, half idle 15.5 / 17.7, 24 rows 25 / 22), with
+//    a dimension of 64 from 48 (250 experts 64 -> 512, 24 rows 17.8 / 18.2, skewed 18.7 / 20.1; 48 rows - / 21 / 25).
 //  * No dimension of 64 and less: 10 is ahead there of 256-row tiles too (9 / 10: 64 experts 64 -> 256, 800 rows 30 / 24; 64 ->
 //    1024 62 / 55; 16 experts 4096 -> 64, 1000 rows 95 / 85; 128 experts 40 -> 512, 1000 rows 82 / 69).  9 is for operands that
 //    8 cannot address (9 / 10: 8 experts 2048 -> 8192, 33750 rows 15550 / 20945; 8 experts 1000 -> 8200, 33000 rows 9183 /
 //    16220).
 //  * K that is no multiple of the K tile: with 64 panels and fewer the same lines (small / 2 / 10: 8 experts 1000 -> 4000, 40 rows 53 / 47 / 56,
 //    68 / 60 / 64; 80 rows 71 / 55 / 60, 86 / 59 / 78; 32 experts 496 -> 4984, 30 rows 104 / 82 / 89, 135 / 129 / 138; 5 experts 520 -> 1560, 300 rows
-//    - / 28 / 35), with more 64x128 from 30 to 55 rows (2 / 10: 24 experts 1000 -> 4000, 40 rows 101 / 106, 112 / 125; 47 experts
-//    1496 -> 4504, 48 rows 352 / 356, 403 / 433; 52 experts 840 -> 7120, 60 rows 359 / 362, 447 / 405).
+//    - / 28 / 35) but for two, 2 / 10, mean and worst of even, random, skewed and half idle batches against 128x128 in registers: 33 to 47 panels from
+//    60 rows 10 (17 experts 680 -> 5896, 64 rows 1.00, 1.18 / 0.83, 0.85; 6 experts 2040 -> 6000, 72 rows 0.93, 1.00 / 0.88, 0.89), 17 to 32 panels from 120
+//    (8 experts 1000 -> 4000, 0.97, 1.15 / 0.91, 0.92; 16 experts 400 -> 4400, 128 rows 0.94, 1.08 / 0.87, 0.89).  With up to 96 panels, 128 of few
+//    weights, 64x128 from 30 to 49 rows (24 experts 1000 -> 4000, 36 rows 0.93, 1.02, 48 rows 0.97, 1.05, 50 rows 1.01, 1.25; 36 experts 520 -> 2000,
+//    48 rows 0.92, 0.95; 130 experts 200 -> 600, 30 rows 0.88, 0.93); with more the 128-row tiles throughout (36 rows: 28 experts 1000 -> 3000 1.05, 1.25; 47
+//    experts 1496 -> 4504 1.01, 1.10; 52 experts 840 -> 7120 1.03, 1.29; 60 experts 1000 -> 2000 1.01, 1.24; 40 experts 1960 -> 3000 1.04, 1.17).
 int gemm_bf16_variant(int64_t n_rows, int E, int N, int K, int num_cus)
 {
     const int64_t avg = E > 0 ? n_rows / E : n_rows;
@@ -1204,15 +1215,17 @@ int gemm_bf16_variant(int64_t n_rows, int E, int N, int K, int num_cus)
     const bool fills = width <= 768 ? avg >= 192 && tiles >= 144 && (N > K ? N : K) >= 1024
                                     : tiles >= 96 && avg >= (tiles < 112 ? 120 : 116);
     const bool streams = heavy && avg >= kNtRows && panels >= 2 * (int64_t)num_cus;
+    const bool light = (int64_t)E * N * K < kLightWeights;
     if (gemm_ring_ok(n_rows, N, K) && (fills || streams)) return 8;
     if (avg >= 192) return gemm_ring_addresses(n_rows, N, K) ? 10 : 9;
     const int small = avg >= kNtRows ? 4 : avg >= kNtSoleRows ? 5 : 3;
     if (4 * panels <= num_cus) {
-        if (8 * panels > num_cus) return avg >= 96 ? 10 : avg >= 8 ? 2 : small;
-        return 16 * panels > num_cus ? (avg > 128 ? 10 : avg > 32 ? 2 : small) : (avg > 64 ? 2 : small);
+        const int from = width <= 64 ? 48 : light ? 17 : 8;
+        if (8 * panels > num_cus) return avg >= (whole || 16 * panels >= 3 * num_cus ? 96 : 60) ? 10 : avg >= from ? 2 : small;
+        return 16 * panels > num_cus ? (avg > (whole || light ? 128 : 119) ? 10 : avg > 32 ? 2 : small) : (avg > 64 ? 2 : small);
     }
     if (whole && !heavy && avg < 64) return avg >= 34 ? 2 : small;
-    if (!whole && avg < 56) return avg >= 30 ? 2 : small;
+    if (!whole && avg < 50 && (light ? 2 * panels <= num_cus : 8 * panels <= 3 * num_cus)) return avg >= 30 ? 2 : small;
     return avg >= 30 ? 10 : small;
 }
 
@@ -1293,8 +1306,10 @@ int launch_gemm_bf16(const GemmParams &p, bool grouped, int variant, bool out_f3
         // 2048 -> 8192, 64 rows 160 / 126 / 108, 168 / 132 / 141; 16 experts 1024 -> 4096, 48 rows 91 / 72 / 62, 95 / 76 / 79; 12
         // experts, 56 rows - / 64 / 55, - / 64 / 58; 4 experts 4096 -> 14336, 40 rows 281 / 209 / 177, 294 / 221 / 237; 16 experts 2048 ->
         // 8192, 48 rows 225 / 200 / 196, 237 / 242 / 246; with more tiles two stages, of which a CU holds three blocks: 64 experts
-        // 1024 -> 4096, 40 rows 203 / 212, 226 / 231.
-        if (few_tiles(p, 64, 64, 1, 1, num_cus)) return launch_grouped_dtl<64, 64, 2, 2, 2, 4, NT_NONE, 0>(p, relu, num_cus, s);
+        // 1024 -> 4096, 40 rows 203 / 212, 226 / 231.  Up to 16 rows per expert 64x64 also with more tiles: most of a tile's rows are padding
+        // then, and it is the weights' way that counts (64x128 in three stages / 64x64, half of the experts idle, 16 experts 1024 -> 4096, 8 rows 46 /
+        // 42; 4 experts 4096 -> 14336 136 / 119; even 6 experts 2040 -> 6000, 12 rows 92 / 88).
+        if (few_tiles(p, 64, 64, 1, 1, num_cus) || p.M <= 16ll * p.num_experts) return launch_grouped_dtl<64, 64, 2, 2, 2, 4, NT_NONE, 0>(p, relu, num_cus, s);
         return few_tiles(p, 64, 128, 1, 1.5, num_cus) ? launch_grouped_dtl<64, 128, 1, 4, 2, 3, NT_NONE, 0>(p, relu, num_cus, s)
                                          : launch_grouped_dtl<64, 128, 1, 4, 2, 2, NT_NONE, 0>(p, relu, num_cus, s);
     case 22: return launch_grouped_dtl<64, 128, 1, 4, 2, 3, NT_NONE, 8>(p, relu, num_cus, s);
@@ -1307,11 +1322,12 @@ int launch_gemm_bf16(const GemmParams &p, bool grouped, int variant, bool out_f3
         // skewed (0.8): 32 rows: 16 experts 2048 -> 8192, 36 rows 137 / 123, 140 / 126; 64 experts 1024 -> 4096, 20 rows 83 / 77, 94 / 85; 32
         // experts 2048 -> 8192, 30 rows 157 / 147, 182 / 167; 128 experts 512 -> 2048, 20 rows 50 / 47, 61 / 56; 64 rows: 8 experts 2048 ->
         // 8192, 100 rows 136 / 121, 136 / 121; 16 experts 1024 -> 4096, 100 rows 78 / 70, 78 / 70; 16 experts 2048 -> 8192, 60 rows 143 / 132,
-        // 159 / 163; a tile per CU: 32 experts 2048 -> 8192, 60 rows 199 / 205, 250 / 260.
+        // 159 / 163; a tile per CU: 32 experts 2048 -> 8192, 60 rows 199 / 205, 250 / 260.  64-row tiles counted with 1.15 times the rows: near a
+        // whole tile some experts have two (layer, random gate: 16 experts 2048 -> 8192, 60 rows 178 / 182, 32 experts 512 -> 2048, 128 rows 71 / 74).
         if (few_tiles(p, 32, 256, 1, 1, num_cus)) return launch_grouped_dtl<32, 128, 1, 4, 2, 4, NT_NONE, 4>(p, relu, num_cus, s);
         return launch_grouped_dtl<32, 256, 1, 4, 2, 3, NT_NONE, 4>(p, relu, num_cus, s);
     case 48:
-        if (few_tiles(p, 64, 256, 1, 0.5, num_cus)) return launch_grouped_dtl<64, 128, 2, 2, 2, 4, NT_NONE, 4>(p, relu, num_cus, s);
+        if (few_tiles(p, 64, 256, 1.15, 0.5, num_cus)) return launch_grouped_dtl<64, 128, 2, 2, 2, 4, NT_NONE, 4>(p, relu, num_cus, s);
         return launch_grouped_dtl<64, 256, 1, 4, 2, 3, NT_NONE, 4>(p, relu, num_cus, s);
     case 3: case 4: case 5:
         // K that ends inside a K tile: weight rows then begin inside a line, and the loads in flight in registers are as good (47 experts
@@ -1323,8 +1339,9 @@ int launch_gemm_bf16(const GemmParams &p, bool grouped, int variant, bool out_f3
         return variant == 3 && p.K % BK == 0 ? launch_grouped_dtl<32, 128, 1, 4, 2, 2, NT_ALL, 0>(p, relu, num_cus, s)
                : variant == 5 && p.K % BK == 0 ? launch_grouped_dtl<32, 128, 1, 4, 2, 2, NT_SOLE, 0>(p, relu, num_cus, s)
                // as the 64-row tiles, two stages / four: 8 experts 2048 -> 8192, 40 rows 158 / 113, 171 / 131; 16 experts 2048 -> 8192, 20
-               // rows 209 / 189, 229 / 236; 16 experts 1024 -> 4096, 36 rows 88 / 66, 95 / 73
-               : few_tiles(p, 32, 128, 1, 1.5, num_cus) ? launch_grouped_dtl<32, 128, 1, 4, 2, 4, NT_NONE, 0>(p, relu, num_cus, s)
+               // rows 209 / 189, 229 / 236; 16 experts 1024 -> 4096, 36 rows 88 / 66, 95 / 73.  Not with a K tile or three (64 experts 192 -> 768, 12
+               // rows 17.0 / 17.5)
+               : few_tiles(p, 32, 128, 1, 1.5, num_cus) && p.K >= 4 * BK ? launch_grouped_dtl<32, 128, 1, 4, 2, 4, NT_NONE, 0>(p, relu, num_cus, s)
                                            : launch_grouped_dtl<32, 128, 1, 4, 2, 2, NT_NONE, 0>(p, relu, num_cus, s);
     default:
         set_error("unsupported grouped GEMM variant %d", variant);

@@ -54,8 +54,12 @@ def test_nothing_past_k_is_multiplied():
     (8, 1024, 4096, 129, "128x128"), (8, 512, 2048, 64, "32x128"), (8, 512, 2048, 65, "64x128"), (8, 512, 2048, 191, "64x128"),
     (8, 512, 2048, 192, "128x128"),
     # K that ends inside a K tile
-    (8, 1000, 4000, 32, "32x128"), (8, 1000, 4000, 33, "64x128"), (8, 1000, 4000, 128, "64x128"), (8, 1000, 4000, 129, "128x128"),
-    (24, 1000, 4000, 29, "32x128"), (24, 1000, 4000, 30, "64x128"), (24, 1000, 4000, 55, "64x128"), (24, 1000, 4000, 56, "128x128")])
+    (8, 1000, 4000, 32, "32x128"), (8, 1000, 4000, 33, "64x128"), (8, 1000, 4000, 119, "64x128"), (8, 1000, 4000, 120, "128x128"),
+    (24, 1000, 4000, 29, "32x128"), (24, 1000, 4000, 30, "64x128"), (24, 1000, 4000, 49, "64x128"), (24, 1000, 4000, 50, "128x128"),
+    (17, 680, 5896, 59, "64x128"), (17, 680, 5896, 60, "128x128"), (32, 496, 4984, 95, "64x128"), (47, 1496, 4504, 29, "32x128"),
+    (47, 1496, 4504, 30, "128x128"), (130, 200, 600, 49, "64x128"),
+    # few weights, a dimension of 64
+    (100, 128, 512, 16, "32x128"), (100, 128, 512, 17, "64x128"), (250, 64, 512, 47, "32x128"), (250, 64, 512, 48, "64x128")])
 def test_choice(E, D, F, rows, shape):
     assert expert_tile_shape(E * rows, E, F, D) == shape
 
