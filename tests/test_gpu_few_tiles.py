@@ -26,7 +26,7 @@ MORE = [0, 1, 31, 200, 33, 129, 64, 127]
     ("32x128", 16, 2048, 2112, EDGES[:6], 16, 32),   # four stages in both GEMMs
     # K that ends inside a K tile: 64 columns and four stages, 128 and three, 128 and two, 128x64, 32x128 and four stages
     ("64x128", 16, 1000, 1096, EDGES, 10, 60), ("64x128", 8, 72, 264, MORE, 0, 0), ("64x128", 8, 200, 1992, MORE, 0, 0),
-    ("64x128", 40, 1000, 1096, EDGES, 40, 50), ("128x128", 8, 1000, 1000, [0, 1, 127, 128, 129, 257, 255, 256], 0, 0),
+    ("64x128", 24, 1000, 4000, EDGES, 40, 50), ("128x128", 8, 1000, 1000, [0, 1, 127, 128, 129, 257, 255, 256], 0, 0),
     ("32x128", 24, 1000, 1992, EDGES, 6, 20)])
 def test_ffn(shape, E, D, F, edges, lo, hi):
     run(shape, ragged(E, edges, lo, hi, 5) if hi else edges, D, F)

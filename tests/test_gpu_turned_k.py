@@ -20,7 +20,7 @@ EDGES = [0, 1, 31, 32, 33, 0, 63, 64, 65, 127, 128, 129]
     ("cut to rows", 40, 2048, 1096, 120, 260),    # the first GEMM turns: 32 K tiles
     ("cut to rows", 40, 1096, 4096, 120, 260),    # the second one: 64
     ("128x128", 14, 2048, 776, 350, 360), ("128x128", 14, 776, 2048, 350, 360),   # 96 rows in the mean: fewer are 64x128's
-    ("64x128", 14, 2048, 776, 100, 120),
+    ("64x128", 14, 2048, 776, 60, 70),
     ("64x128", 80, 2048, 320, 25, 50), ("64x128", 80, 320, 4096, 25, 50),
     ("32x128", 120, 2048, 320, 5, 15), ("32x128", 120, 320, 2048, 5, 15)])
 def test_tiles(shape, E, D, F, lo, hi):
