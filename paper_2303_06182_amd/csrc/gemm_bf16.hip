@@ -952,6 +952,10 @@ template <int BM, int BN, int WM, int WN, bool OUT_F32, bool RELU, bool GROUPED,
 static int launch_k(const GemmParams &p_in, int num_cus, hipStream_t s, int *main_grid)
 {
     GemmParams p = p_in;
+    if (p.chosen) {
+        *p.chosen = BM * 10000 + BN * 10 + STAGES;
+        return MOE_OK;
+    }
     const int n_tiles = ceil_div(p.N, BN);
     const int m_tiles = GROUPED ? p.max_m_tiles : ceil_div(p.M, BM);
     if (m_tiles <= 0 || n_tiles <= 0) return MOE_OK;

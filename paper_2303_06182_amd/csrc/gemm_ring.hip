@@ -632,6 +632,10 @@ bool gemm_ring_quant_ok(int64_t n_rows, int N, int K)
 // wbits: storage of the weights, 8 or 4, else bf16
 int launch_gemm_ring(const GemmParams &p, int wbits, bool relu, hipStream_t s)
 {
+    if (p.chosen) {
+        *p.chosen = kChosenRing;
+        return MOE_OK;
+    }
     if (wbits && p.K < kRingQuantK) {
         set_error("cut tiles over quantised weights need K (%d) of %d at least", p.K, kRingQuantK);
         return MOE_ERR_UNSUPPORTED;

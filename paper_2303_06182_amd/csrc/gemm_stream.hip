@@ -342,6 +342,10 @@ template <int BQ, bool RELU, int NC, int W, int DP1, int DP2, bool RAGGED = fals
 static int launch_stream_t(const GemmParams &p_in, int num_cus, hipStream_t s)
 {
     GemmParams p = p_in;
+    if (p.chosen) {
+        *p.chosen = kChosenStream + 16 * NC;
+        return MOE_OK;
+    }
     auto kern = gemm_stream_kernel<BQ, RELU, NC, W, DP1, DP2, RAGGED>;
     static std::once_flag once;
     static int blocks_per_cu = 1;

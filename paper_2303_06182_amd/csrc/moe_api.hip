@@ -326,6 +326,24 @@ static int quant_variant(const moe_handle_t *h, int wbits, int64_t n_rows)
     return wbits == 4 ? gemm_bf16_variant_w4(n_rows, c.E, c.F, c.D, h->num_cus) : gemm_bf16_variant_w8(n_rows, c.E, c.F, c.D);
 }
 
+// The kernel that an expert GEMM over weights of wbits (16: bf16) bits runs on, N columns and a contraction of K (GemmParams::chosen).
+int expert_gemm_choice(int wbits, int64_t n_rows, int E, int N, int K, int num_cus)
+{
+    const int v = wbits == 4   ? gemm_bf16_variant_w4(n_rows, E, N, K, num_cus)
+                  : wbits == 8 ? gemm_bf16_variant_w8(n_rows, E, N, K)
+                               : gemm_bf16_variant(n_rows, E, N, K, num_cus);
+    int chosen = 0;
+    GemmParams p;
+    memset(&p, 0, sizeof(p));
+    p.M = (int)n_rows;
+    p.N = N;
+    p.K = p.lda = p.ldb = K;
+    p.num_experts = E;
+    p.max_m_tiles = map_tiles_max(n_rows, E, gemm_bf16_variant_block_m(v));
+    p.chosen = &chosen;
+    return launch_gemm_bf16(p, true, v, false, true, num_cus, nullptr) == MOE_OK ? chosen : -1;
+}
+
 // Options of the grouped FFN beyond the plain call.
 struct FfnExtra {
     // xp is the token array and row r of the experts' input is its row a_rows[r] (dispatch fused

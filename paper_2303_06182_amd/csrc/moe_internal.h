@@ -134,8 +134,10 @@ struct GemmParams {
     // c_zero_row >= 0: the launch also writes zeros to that row of C (the next GEMM's a_zero_row).
     int a_zero_row;
     int c_zero_row;
-    bool turned;                 // set by the launch: the K loops of a bf16 grouped GEMM go round K (turned_k)
+    bool turned;                 // set by the launch: the K loops of a grouped GEMM over bf16 or e4m3 weights go round K (turned_k)
     const char *name;            // host only: label of the launch for the event profiler (may be NULL)
+    int *chosen;                 // host only, grouped bf16 kernels: not NULL: launch nothing, say here which kernel it would be
+                                 // (rows * 10000 + columns * 10 + LDS stages of its tiles; kChosenRing, kChosenStream + columns)
 };
 
 // Tile shape (an opaque variant id) the grouped GEMM uses for n_rows rows over E experts, N output columns
@@ -165,6 +167,7 @@ int launch_tile_map(const int32_t *offsets, int E, int block_m, int32_t *tile_ex
 // unit of it that the former ends in front of (expert << kRingCutShift | unit; MOE_MAX_E as expert: none); kRingCap + x, the
 // greatest tile height in units (bits 0 .. 7 first, 8 .. 15 second GEMM) and, as bit kRingShared, that all XCDs have the same
 // list and each takes an eighth of its output tiles.
+static constexpr int kChosenRing = 1, kChosenStream = 1000;
 static constexpr int kRingMap = 1 << 30;  // tile height that stands for it
 static constexpr int kRingFirst = 8, kRingLast = 16, kRingCut = 24, kRingCap = 33, kRingShared = 16;
 

@@ -9,7 +9,7 @@ import torch
 from oracle import expert_cache as ec
 from oracle import moe_oracle as orc
 from paper_2303_06182_amd import binding, workloads as wl
-from helpers import expert_tile_shape, TOL, norm_max_err, to_np
+from helpers import expert_kernels, expert_tile_shape, norm_max_err, to_np, TOL
 
 pytestmark = pytest.mark.gpu
 
@@ -150,4 +150,32 @@ def test_buffered_quantised_weights_equal_the_resident_call(dev, wbits):
         st = cache.stats()
         assert (st["hits"], st["misses"]) == (sim["hits"], sim["misses"])
         assert st["bytes_copied"] == sim["misses"] * expert_bytes
+        del cache
+
+
+@pytest.mark.parametrize("wbits", [8, 4])
+def test_buffered_quantised_ring(dev, wbits):
+    """Enough rows for the tiles cut to the experts' rows, in stages of three experts: weights by slot, scales by expert, a schedule per
+    stage.  Bit for bit the resident call."""
+    w = wl.CONFIGS["mt_encoder"].scaled(name="buf_ring_q%d" % wbits, T=8000, D=832, F=1088, E=12)
+    assert expert_kernels(wbits, w.T * w.k, w.E, w.F, w.D) == ("ring", "ring")
+    inp = wl.make_inputs(w, with_ffn_bias=True)
+    g = {k: (None if v is None else v.cuda()) for k, v in inp.items()}
+    layer = binding.MoeLayer(w.T, w.D, w.F, w.E, w.k, w.dtype)
+    quantise, fwd = (layer.moe_quantize_e4m3, layer.moe_layer_forward_w8) if wbits == 8 else (layer.moe_quantize_mxfp4, layer.moe_layer_forward_w4)
+    g["w1"][::2] *= 23.0   # experts with different scales
+    (q1, s1), (q2, s2) = quantise(g["w1"]), quantise(g["w2"])
+    hq1, hq2 = q1.cpu().pin_memory(), q2.cpu().pin_memory()
+    xs = [g["x"], g["x"].flip(0)[:7777].contiguous()]
+    ref = [fwd(x, g["wg"], q1, q2, s1, s2, g["gate_bias"], g["b1"], g["b2"]) for x in xs]
+    torch.cuda.synchronize()
+    q1.fill_(0x7F), q2.fill_(0x7F)   # the cache must not read these
+    for slots in (3, 12):
+        say("buffered ring q%d" % wbits, "slots", slots)
+        cache = binding.ExpertCache(layer, slots, hq1, hq2, wbits, s1, s2)
+        for x, want in zip(xs, ref):
+            y = cache.moe_layer_forward_buffered(x, g["wg"], g["gate_bias"], g["b1"], g["b2"])
+            torch.cuda.synchronize()
+            assert torch.equal(y, want)
+        assert slots == w.E or cache.stats()["stages"] > len(xs)
         del cache

@@ -1,12 +1,13 @@
 """Expert GEMMs with a tile or two per CU (few_tiles, gemm_bf16.hip): narrower tiles and more LDS stages.  Row counts around the tiles'
-edges, K of one K tile and of fewer than the stages, K loops that go round K, idle experts, biases; and the choice around its lines."""
+edges, K of one K tile and of fewer than the stages, K loops that go round K, idle experts, biases; and the choice around its lines.
+Every case asks the library which kernels its two GEMMs run on."""
 import numpy as np
 import pytest
 import torch
 
 from oracle import moe_oracle as orc
 from paper_2303_06182_amd import binding
-from helpers import TOL, expert_tile_shape, norm_max_err, to_np, worst_row_rms_rel_err
+from helpers import TOL, expert_kernels, expert_tile_shape, norm_max_err, to_np, worst_row_rms_rel_err
 from test_gpu_ring_quant import dequantised, setup
 from test_gpu_tile_shapes import ragged, run
 
@@ -15,21 +16,27 @@ MORE = [0, 1, 31, 200, 33, 129, 64, 127]
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("shape,E,D,F,edges,lo,hi", [
-    ("64x128", 16, 1024, 1088, EDGES, 10, 60),      # three stages in the first GEMM, 64 columns in the second
-    ("64x128", 16, 576, 1088, EDGES, 10, 60), ("64x128", 8, 2048, 2112, EDGES, 0, 0),
-    ("64x128", 16, 64, 256, EDGES + [127, 128, 129, 200], 90, 140), ("64x128", 16, 256, 64, EDGES + [127, 128, 129, 200], 90, 140),
-    ("64x128", 4, 192, 128, [65, 129, 0, 127], 0, 0),
-    ("128x128", 8, 1024, 1024, [0, 1, 127, 128, 129, 257, 255, 256], 0, 0),   # 128x64
-    ("128x128", 8, 1024, 576, [600, 127, 128, 129, 257, 255, 0, 700], 0, 0),
-    ("128x128", 12, 64, 384, EDGES + [600, 900, 700, 1000], 0, 0),
-    ("32x128", 16, 2048, 2112, EDGES[:6], 16, 32),   # four stages in both GEMMs
-    # K that ends inside a K tile: 64 columns and four stages, 128 and three, 128 and two, 128x64, 32x128 and four stages
-    ("64x128", 16, 1000, 1096, EDGES, 10, 60), ("64x128", 8, 72, 264, MORE, 0, 0), ("64x128", 8, 200, 1992, MORE, 0, 0),
-    ("64x128", 24, 1000, 4000, EDGES, 40, 50), ("128x128", 8, 1000, 1000, [0, 1, 127, 128, 129, 257, 255, 256], 0, 0),
-    ("32x128", 24, 1000, 1992, EDGES, 6, 20)])
-def test_ffn(shape, E, D, F, edges, lo, hi):
-    run(shape, ragged(E, edges, lo, hi, 5) if hi else edges, D, F)
+@pytest.mark.parametrize("shape,E,D,F,edges,lo,hi,kernels", [
+    ("64x128", 16, 1024, 1088, EDGES, 10, 60, "64x128x3 64x64x4"), ("64x128", 16, 576, 1088, EDGES, 10, 60, "64x128x3 64x64x4"),
+    ("64x128", 8, 2048, 2112, EDGES, 0, 0, "64x128x3 64x64x4"), ("64x128", 8, 2048, 2112, [0, 1, 5, 33, 20, 4, 2, 63], 0, 0, "64x64x4 64x64x4"),
+    ("64x128", 16, 64, 256, EDGES + [127, 128, 129, 200], 90, 140, "64x64x4 64x64x4"),
+    ("64x128", 16, 256, 64, EDGES + [127, 128, 129, 200], 90, 140, "64x64x4 64x64x4"),
+    ("64x128", 4, 192, 128, [65, 129, 0, 127], 0, 0, "64x64x4 64x64x4"),
+    ("128x128", 8, 1024, 1024, [0, 1, 127, 128, 129, 257, 255, 256], 0, 0, "128x64x4 128x64x4"),
+    ("128x128", 8, 1024, 576, [600, 127, 128, 129, 257, 255, 0, 700], 0, 0, "128x128 128x128"),
+    ("128x128", 12, 64, 384, EDGES + [600, 900, 700, 1000], 0, 0, "128x128 128x64x4"),
+    ("32x128", 16, 2048, 2112, EDGES[:6], 16, 32, "32x128x4 32x128x4"),
+    # K of fewer K tiles than stages
+    ("32x128", 40, 192, 768, EDGES[:6], 6, 14, "32x128x2 stream32"),
+    # K that ends inside a K tile
+    ("64x128", 16, 1000, 1096, EDGES, 10, 60, "64x128x3 64x64x4"), ("64x128", 8, 72, 264, MORE, 0, 0, "64x64x4 64x64x4"),
+    ("64x128", 8, 200, 1992, MORE, 0, 0, "64x128x3 64x64x4"), ("64x128", 24, 1000, 4000, EDGES, 40, 50, "64x128x2 64x128x3"),
+    ("128x128", 8, 1000, 1000, [0, 1, 127, 128, 129, 257, 255, 256], 0, 0, "128x64x4 128x64x4"),
+    ("128x128", 40, 1000, 1096, EDGES, 40, 50, "128x128 128x128"), ("32x128", 24, 1000, 1992, EDGES, 6, 20, "32x128x4 32x128x4")])
+def test_ffn(shape, E, D, F, edges, lo, hi, kernels):
+    counts = ragged(E, edges, lo, hi, 5) if hi else edges
+    assert " ".join(expert_kernels(16, sum(counts), E, F, D)) == kernels
+    run(shape, counts, D, F)
 
 
 @pytest.mark.gpu
@@ -65,12 +72,14 @@ def test_choice(E, D, F, rows, shape):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("counts,D,F", [
-    ([0, 1, 31, 32, 33, 63, 64, 65] * 2, 2048, 1984),            # 32x128, K of 32 and 31 K tiles
-    ([0, 1, 127, 128, 129, 257, 63, 300], 1024, 1088), ([64, 0, 150, 129, 190], 192, 320)])   # 64x128; K of 16 and 17, 3 and 5
-def test_mxfp4(counts, D, F):
+@pytest.mark.parametrize("counts,D,F,kernel", [
+    ([0, 1, 31, 32, 33, 63, 64, 65] * 2, 2048, 1984, "32x128x4"),   # K of 32 and 31 K tiles
+    # K of 16 and 17 K tiles, 3 and 5
+    ([0, 1, 127, 128, 129, 257, 63, 300], 1024, 1088, "64x128x4"), ([64, 0, 150, 129, 190], 192, 320, "64x128x4")])
+def test_mxfp4(counts, D, F, kernel):
     print("mxfp4", counts, D, F, flush=True)
     E, N = len(counts), sum(counts)
+    assert expert_kernels(4, N, E, F, D) == (kernel, kernel)
     t, m, (q1, q2, s1, s2) = setup(4, E, D, F, N)
     offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
     for e in (e for e, c in enumerate(counts) if c == 0):   # NaN's place in this format: the largest scale

@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 import torch
 
-from helpers import TOL, norm_max_err, to_np, worst_row_rms_rel_err
+from helpers import TOL, expert_kernels, norm_max_err, to_np, worst_row_rms_rel_err
 from oracle import moe_oracle as orc
 from oracle import quant_e4m3
 from paper_2303_06182_amd import binding
@@ -29,16 +29,19 @@ def test_tiles(shape, E, D, F, lo, hi):
 
 @pytest.mark.parametrize("D,F", [(4096, 544), (544, 8192)])   # the streaming kernel: 4096 and 8192 in parts of a wave each
 def test_streams(D, F):
-    run("32x128", [0, 1, 3, 0, 16, 17, 2, 33], D, F)
+    counts = [0, 1, 3, 0, 16, 17, 2, 33]
+    assert "stream16" in expert_kernels(16, sum(counts), len(counts), F, D)
+    run("32x128", counts, D, F)
 
 
-@pytest.mark.parametrize("counts,D,F", [
-    ([0, 1, 31, 33, 64, 0, 17, 40], 1024, 2112),                       # the first GEMM turns: 16 K tiles
-    ([20, 0, 33, 1, 32, 15, 40, 31, 30, 29] * 3, 2048, 1024),          # the second one: N = 2048 and K = 1024
-    ([0, 1, 0, 3, 16, 2], 2048, 2112), ([1, 0, 17, 2], 4096, 576)])    # the streaming kernel
-def test_e4m3(counts, D, F):
+@pytest.mark.parametrize("counts,D,F,kernel", [
+    ([0, 1, 31, 33, 64, 0, 17, 40], 1024, 2112, "32x128x3"),                     # the first GEMM turns: 16 K tiles
+    ([20, 0, 33, 1, 32, 15, 40, 31, 30, 29] * 3, 2048, 1024, "32x128x3"),        # the second one: N = 2048 and K = 1024
+    ([0, 1, 0, 3, 16, 2], 2048, 2112, "stream32"), ([1, 0, 17, 2], 4096, 576, "stream16")])
+def test_e4m3(counts, D, F, kernel):
     print("e4m3", len(counts), D, F, flush=True)
     E, N = len(counts), sum(counts)
+    assert kernel in expert_kernels(8, N, E, F, D)
     offsets = np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)
     g = torch.Generator(device="cuda").manual_seed(8)
     t = lambda s, std: torch.empty(s, dtype=torch.bfloat16, device="cuda").normal_(0.0, std, generator=g)
