@@ -27,14 +27,10 @@
 // tiles ahead, only the gate weights staged -- measured the same cold and 20 % slower warm, and was dropped.)
 #include <mutex>
 
+#include "gemm_bf16_dev.h"
 #include "moe_internal.h"
 
 namespace moe355 {
-
-typedef __attribute__((ext_vector_type(8))) __bf16 gt_bf16x8;
-typedef __attribute__((ext_vector_type(16))) float gt_f32x16;
-typedef __attribute__((address_space(3))) void gt_lds_void;
-typedef __attribute__((address_space(1))) void gt_glb_void;
 
 struct GateTopkParams {
     const uint16_t *x;    // [T, K] bf16
@@ -47,17 +43,13 @@ struct GateTopkParams {
     int T, E, K, k, renorm;
 };
 
-// What lanes load for the chunks of the last K tile that lie past K: either operand is then zero there, whatever the other holds.
-// (By address and not with a mask behind the LDS read: the K loop stays as it is.)  Gate and
-// selection in us, a two-stage GEMM, top-k and histogram kernels / this: 3001 tokens, 1000 dimensions, 24 experts 23.9 / 10.4; 1137 tokens, 1496
+// Where the lane's chunk of K tile kt of row `row` of a tile is, at = that of K tile 0.  Gate and selection in us where K ends inside a
+// K tile, a two-stage GEMM, top-k and histogram kernels / this: 3001 tokens, 1000 dimensions, 24 experts 23.9 / 10.4; 1137 tokens, 1496
 // dimensions, 47 experts 31.2 / 13.2.
-__device__ __align__(16) static const uint16_t gt_zeros[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-
-// Where the lane's chunk of K tile kt of row `row` of a tile is, at = that of K tile 0
 __device__ __forceinline__ const uint16_t *gt_inside(const uint16_t *at, int row, int kt, int K)
 {
     const int kc = (threadIdx.x & 7) ^ ((row >> 1) & 7);
-    return kt * 64 + kc * 8 < K ? at + kt * 64 : gt_zeros;
+    return kt * 64 + kc * 8 < K ? at + kt * 64 : chunk_of_zeros;
 }
 
 // RAGGED: K ends inside a K tile.  (An instance of its own: with the question in the K loop whole K tiles cost 3 to 5 % more, 20000 tokens, 2048
@@ -110,25 +102,25 @@ __global__ __launch_bounds__(WAVES * 64) void gate_topk_kernel(GateTopkParams p)
 #pragma unroll
             for (int i = 0; i < A_IT; ++i) {
                 const int r = (wave * A_IT + i) * 8;
-                __builtin_amdgcn_global_load_lds((const gt_glb_void *)gt_inside(a_ptr[i], r + (lane >> 3), kt, K),
-                                                 (gt_lds_void *)(sA + buf * BM * BK + r * BK), 16, 0, 0);
+                __builtin_amdgcn_global_load_lds((const glb_void *)gt_inside(a_ptr[i], r + (lane >> 3), kt, K),
+                                                 (lds_void *)(sA + buf * BM * BK + r * BK), 16, 0, 0);
             }
 #pragma unroll
             for (int i = 0; i < B_IT; ++i) {
                 const int r = (wave * B_IT + i) * 8;
-                __builtin_amdgcn_global_load_lds((const gt_glb_void *)gt_inside(b_ptr[i], r + (lane >> 3), kt, K),
-                                                 (gt_lds_void *)(sB + buf * BN * BK + r * BK), 16, 0, 0);
+                __builtin_amdgcn_global_load_lds((const glb_void *)gt_inside(b_ptr[i], r + (lane >> 3), kt, K),
+                                                 (lds_void *)(sB + buf * BN * BK + r * BK), 16, 0, 0);
             }
             return;
         }
 #pragma unroll
         for (int i = 0; i < A_IT; ++i)
-            __builtin_amdgcn_global_load_lds((const gt_glb_void *)(a_ptr[i] + kt * BK),
-                                             (gt_lds_void *)(sA + buf * BM * BK + (wave * A_IT + i) * 8 * BK), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((const glb_void *)(a_ptr[i] + kt * BK),
+                                             (lds_void *)(sA + buf * BM * BK + (wave * A_IT + i) * 8 * BK), 16, 0, 0);
 #pragma unroll
         for (int i = 0; i < B_IT; ++i)
-            __builtin_amdgcn_global_load_lds((const gt_glb_void *)(b_ptr[i] + kt * BK),
-                                             (gt_lds_void *)(sB + buf * BN * BK + (wave * B_IT + i) * 8 * BK), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((const glb_void *)(b_ptr[i] + kt * BK),
+                                             (lds_void *)(sB + buf * BN * BK + (wave * B_IT + i) * 8 * BK), 16, 0, 0);
     };
     // "at most STAGES - 2 stages' loads of this wave outstanding": the K tile needed next has landed.  Every
     // iteration issues the same number of loads (past the end it re-reads the last K tile into a stage nobody
@@ -148,7 +140,7 @@ __global__ __launch_bounds__(WAVES * 64) void gate_topk_kernel(GateTopkParams p)
         __builtin_amdgcn_sched_barrier(0);
     };
 
-    gt_f32x16 acc[NI];
+    f32x16 acc[NI];
 #pragma unroll
     for (int ni = 0; ni < NI; ++ni)
 #pragma unroll
@@ -170,10 +162,10 @@ __global__ __launch_bounds__(WAVES * 64) void gate_topk_kernel(GateTopkParams p)
 #pragma unroll
         for (int ks = 0; ks < BK / 16; ++ks) {
             const int chunkpos = ((ks * 2 + half) ^ swz) << 3;
-            const gt_bf16x8 af = *reinterpret_cast<const gt_bf16x8 *>(cA + chunkpos);
+            const bf16x8 af = *reinterpret_cast<const bf16x8 *>(cA + chunkpos);
 #pragma unroll
             for (int ni = 0; ni < NI; ++ni) {
-                const gt_bf16x8 bf = *reinterpret_cast<const gt_bf16x8 *>(cB + ni * 32 * BK + chunkpos);
+                const bf16x8 bf = *reinterpret_cast<const bf16x8 *>(cB + ni * 32 * BK + chunkpos);
                 acc[ni] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bf, af, acc[ni], 0, 0, 0);
             }
         }
@@ -337,13 +329,13 @@ __global__ __launch_bounds__(RG *NI * 64) void gate_topk_wide_kernel(GateTopkPar
         if (RAGGED && (kt + 1) * BK > K) {  // uniform: K ends inside this K tile
 #pragma unroll
             for (int i = 0; i < LPS; ++i)
-                __builtin_amdgcn_global_load_lds((const gt_glb_void *)gt_inside(src[i], min(wave + i * W, LOADS - 1) * 8 + (lane >> 3), kt, K),
-                                                 (gt_lds_void *)(stages + stage * STAGE + dst[i]), 16, 0, 0);
+                __builtin_amdgcn_global_load_lds((const glb_void *)gt_inside(src[i], min(wave + i * W, LOADS - 1) * 8 + (lane >> 3), kt, K),
+                                                 (lds_void *)(stages + stage * STAGE + dst[i]), 16, 0, 0);
             return;
         }
 #pragma unroll
         for (int i = 0; i < LPS; ++i)
-            __builtin_amdgcn_global_load_lds((const gt_glb_void *)(src[i] + kt * BK), (gt_lds_void *)(stages + stage * STAGE + dst[i]), 16, 0, 0);
+            __builtin_amdgcn_global_load_lds((const glb_void *)(src[i] + kt * BK), (lds_void *)(stages + stage * STAGE + dst[i]), 16, 0, 0);
     };
     auto block_barrier = [&]() {
         __builtin_amdgcn_sched_barrier(0);
@@ -351,7 +343,7 @@ __global__ __launch_bounds__(RG *NI * 64) void gate_topk_wide_kernel(GateTopkPar
         asm volatile("" ::: "memory");
         __builtin_amdgcn_sched_barrier(0);
     };
-    gt_f32x16 acc;
+    f32x16 acc;
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
     const int frag_row = lane & 31, half = lane >> 5, swz = (lane >> 1) & 7;
@@ -364,12 +356,12 @@ __global__ __launch_bounds__(RG *NI * 64) void gate_topk_wide_kernel(GateTopkPar
         asm volatile("" ::: "memory");
         block_barrier();  // stage `cur` is complete for every wave; everybody is done reading stage `nxt`
         const uint16_t *cA = stages + cur * STAGE + (rg * 32 + frag_row) * BK, *cB = stages + cur * STAGE + (BM + ni * 32 + frag_row) * BK;
-        gt_bf16x8 af[BK / 16], bf[BK / 16];  // all reads first: one LDS latency per K tile
+        bf16x8 af[BK / 16], bf[BK / 16];  // all reads first: one LDS latency per K tile
 #pragma unroll
         for (int ks = 0; ks < BK / 16; ++ks) {
             const int chunkpos = ((ks * 2 + half) ^ swz) << 3;
-            bf[ks] = *reinterpret_cast<const gt_bf16x8 *>(cB + chunkpos);
-            af[ks] = *reinterpret_cast<const gt_bf16x8 *>(cA + chunkpos);
+            bf[ks] = *reinterpret_cast<const bf16x8 *>(cB + chunkpos);
+            af[ks] = *reinterpret_cast<const bf16x8 *>(cA + chunkpos);
         }
         __builtin_amdgcn_sched_barrier(0);
         issue(min(kt + STAGES - 1, KT - 1), nxt);

@@ -19,12 +19,12 @@
 // ds_read_b128 against 6 clk with an (r & 7) swizzle).
 //
 // Two K pipelines, chosen per tile shape (template argument STAGES); tiles cut to an expert's rows are gemm_ring.hip's:
-//  * direct-to-LDS, whole K tiles (small tiles, the gate): STAGES LDS stages; K tiles go straight from global
-//    memory into LDS (global_load_lds_dwordx4, no register staging), the loads run STAGES-1 K
+//  * direct-to-LDS (small tiles; the gate's with whole K tiles): STAGES LDS stages; K tiles go straight from global
+//    memory into LDS (global_load_lds_dwordx4, no register staging; zeros for what lies past K), the loads run STAGES-1 K
 //    tiles ahead of the MFMAs and are waited for (vmcnt) only at the barrier that ends an
 //    iteration.  Several such blocks share a CU, so one block's load burst and barrier hide
 //    behind another block's MFMAs.
-//  * register-staged (256- and 128-row tiles, one or two blocks per CU; 32-row tiles where K ends inside a K tile): measured on gfx950, a
+//  * register-staged (256- and 128-row tiles, one or two blocks per CU; 32-row tiles where K ends inside a K tile, but for few tiles): measured on gfx950, a
 //    vector-memory instruction costs the issuing wave 20-30 clocks of MFMA issue and the CU's
 //    address unit 16 clocks, so a K tile's loads issued as one burst stall every wave while the
 //    matrix units idle, and with only two 64 KB stages in LDS they cannot be issued late either.
@@ -66,9 +66,6 @@ static constexpr int REG_STAGED = 0;  // value of the STAGES template argument t
 // cache policy of the direct-to-LDS weight loads (template argument NT): plain, non-temporal, or non-temporal for the tiles
 // that are their expert's only one
 static constexpr int NT_NONE = 0, NT_ALL = 1, NT_SOLE = 2;
-
-// What direct-to-LDS loads take for the 16-byte chunks past the end of K
-__device__ __align__(16) static const uint16_t chunk_of_zeros[8] = {0, 0, 0, 0, 0, 0, 0, 0};
 
 // 4-bit weights: whether the block scales of a group of 8 K tiles may still be in flight when it begins, so that the K loop has
 // to wait for them.  They are requested as the group before begins, in front of that K tile's operand loads, and the wait
@@ -1023,15 +1020,18 @@ static int launch_one(const GemmParams &p, int num_cus, hipStream_t s, int *main
                : launch_k<BM, BN, WM, WN, OUT_F32, RELU, GROUPED, false, MINB, STAGES == REG_STAGED ? REG_STAGED : 2>(p, num_cus, s, main_grid);
 }
 
-// grouped GEMM on the direct-to-LDS pipeline, bf16 (BQ = 0), 8-bit (8) or 4-bit (4) weights (K a multiple of the K tile:
-// checked by the caller)
+// grouped GEMM on the direct-to-LDS pipeline, bf16 (BQ = 0), 8-bit (8) or 4-bit (4) weights.  K that ends inside a K tile: bf16 only, and
+// not for 32-row tiles in two stages, which are register-staged there.
 template <int BM, int BN, int WM, int WN, int MINB, int STAGES, int NT, int BQ>
 static int launch_grouped_dtl(const GemmParams &p, bool relu, int num_cus, hipStream_t s)
 {
-    if constexpr (BQ == 0)
-        if (p.K % BK != 0)
+    if (p.K % BK != 0) {
+        if constexpr (BQ == 0 && (BM > 32 || STAGES > 2))
             return relu ? launch_k<BM, BN, WM, WN, false, true, true, false, MINB, STAGES, NT>(p, num_cus, s, nullptr)
                         : launch_k<BM, BN, WM, WN, false, false, true, false, MINB, STAGES, NT>(p, num_cus, s, nullptr);
+        set_error("%dx%d tiles need K (%d) to be a multiple of %d", BM, BN, p.K, BK);
+        return MOE_ERR_UNSUPPORTED;
+    }
     return relu ? launch_k<BM, BN, WM, WN, false, true, true, true, MINB, STAGES, NT, BQ>(p, num_cus, s, nullptr)
                 : launch_k<BM, BN, WM, WN, false, false, true, true, MINB, STAGES, NT, BQ>(p, num_cus, s, nullptr);
 }
@@ -1333,20 +1333,21 @@ int launch_gemm_bf16(const GemmParams &p, bool grouped, int variant, bool out_f3
     case 48:
         if (few_tiles(p, 64, 256, 1.15, 0.5, num_cus)) return launch_grouped_dtl<64, 128, 2, 2, 2, 4, NT_NONE, 4>(p, relu, num_cus, s);
         return launch_grouped_dtl<64, 256, 1, 4, 2, 3, NT_NONE, 4>(p, relu, num_cus, s);
-    case 3: case 4: case 5:
+    case 3: case 4: case 5: {
+        // as the 64-row tiles, two stages / four: 8 experts 2048 -> 8192, 40 rows 158 / 113, 171 / 131; 16 experts 2048 -> 8192, 20 rows 209 / 189, 229 /
+        // 236; 16 experts 1024 -> 4096, 36 rows 88 / 66, 95 / 73.  Not with a K tile or three (64 experts 192 -> 768, 12 rows 17.0 / 17.5).
+        const bool deep = few_tiles(p, 32, 128, 1, 1.5, num_cus) && p.K >= 4 * BK;
         // K that ends inside a K tile: weight rows then begin inside a line, and the loads in flight in registers are as good (47 experts
         // 1496 -> 4504, 8 and 20 rows 293 / 296, 310 / 314 us register-staged / direct-to-LDS, non-temporal 380, 395), but for
         // few tiles (24 experts 1000 -> 4000, 16 rows 95 / 89, skewed 103 / 98)
-        if (p.K % BK != 0 && !few_tiles(p, 32, 128, 1, 1.5, num_cus))
+        if (p.K % BK != 0 && !deep)
             return relu ? launch_k<32, 128, 1, 4, false, true, true, false, 2, REG_STAGED>(p, num_cus, s, nullptr)
                         : launch_k<32, 128, 1, 4, false, false, true, false, 2, REG_STAGED>(p, num_cus, s, nullptr);
         return variant == 3 && p.K % BK == 0 ? launch_grouped_dtl<32, 128, 1, 4, 2, 2, NT_ALL, 0>(p, relu, num_cus, s)
                : variant == 5 && p.K % BK == 0 ? launch_grouped_dtl<32, 128, 1, 4, 2, 2, NT_SOLE, 0>(p, relu, num_cus, s)
-               // as the 64-row tiles, two stages / four: 8 experts 2048 -> 8192, 40 rows 158 / 113, 171 / 131; 16 experts 2048 -> 8192, 20
-               // rows 209 / 189, 229 / 236; 16 experts 1024 -> 4096, 36 rows 88 / 66, 95 / 73.  Not with a K tile or three (64 experts 192 -> 768, 12
-               // rows 17.0 / 17.5)
-               : few_tiles(p, 32, 128, 1, 1.5, num_cus) && p.K >= 4 * BK ? launch_grouped_dtl<32, 128, 1, 4, 2, 4, NT_NONE, 0>(p, relu, num_cus, s)
-                                           : launch_grouped_dtl<32, 128, 1, 4, 2, 2, NT_NONE, 0>(p, relu, num_cus, s);
+               : deep                          ? launch_grouped_dtl<32, 128, 1, 4, 2, 4, NT_NONE, 0>(p, relu, num_cus, s)
+                                               : launch_grouped_dtl<32, 128, 1, 4, 2, 2, NT_NONE, 0>(p, relu, num_cus, s);
+    }
     default:
         set_error("unsupported grouped GEMM variant %d", variant);
         return MOE_ERR_UNSUPPORTED;

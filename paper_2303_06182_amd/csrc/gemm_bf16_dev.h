@@ -17,6 +17,10 @@ typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(1))) void glb_void;
 
+// What direct-to-LDS loads take for the 16-byte chunks of the last K tile that lie past K: either operand is then zero there, whatever
+// the other holds.  (By address and not with a mask behind the LDS read: the K loop stays as it is.)
+__device__ __align__(16) static const uint16_t chunk_of_zeros[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+
 // One 32-bit word at an address that is the same for every lane of the wave, through the scalar data path
 // (read only).  The compiler issues such loads as vector loads here (it cannot prove that the kernel's own
 // stores leave the tile map alone), and a vector load's result can only be waited for together with every
