@@ -16,46 +16,37 @@ static constexpr int kThreads = 256;
 static constexpr int kWave = 64;
 static constexpr int kMaxLogitParts = 16;  // slices the top-k kernel can add up (the gate GEMM's split K)
 
-// n logits (whole rows) to LDS, by the whole block.  n_parts > 1: they arrive as n_parts partial sums (the gate GEMM's split K),
-// slice 0 at `logits`, slice i > 0 at parts + (i - 1) * part_stride; they are added in slice order and the sum is also
-// written back to `logits`.  VEC: n, the slices' distance and the pointers allow 16-byte accesses.
-// What bounds it is the latency of a slice another XCD wrote, so all slices of a word are requested before the first is added,
-// by as many threads as there are words.  (The lanes of the selection took their own words here, one group of 16 after the other
-// from more than 64 experts on: a latency each.)
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+
+// A word (one or four logits) that arrives as n_parts partial sums (the gate GEMM's split K), slice 0 at `at`, slice i > 0 at parts +
+// (i - 1) * part_stride: added in slice order, the sum is also written back to `at`.  What bounds it is the latency of a slice another
+// XCD wrote, so all slices are requested before the first is added.
+template <typename W>
+__device__ __forceinline__ W add_slices(float *at, int n_parts, const float *parts, int64_t part_stride)
+{
+    W f = *reinterpret_cast<const W *>(at);
+    if (n_parts > 1) {  // uniform over the grid
+        W g[kMaxLogitParts - 1];
+#pragma unroll
+        for (int sp = 1; sp < kMaxLogitParts; ++sp) g[sp - 1] = sp < n_parts ? *reinterpret_cast<const W *>(parts + (sp - 1) * part_stride) : W{};
+#pragma unroll
+        for (int sp = 1; sp < kMaxLogitParts; ++sp)
+            if (sp < n_parts) f += g[sp - 1];
+        *reinterpret_cast<W *>(at) = f;
+    }
+    return f;
+}
+
+// n logits (whole rows) to LDS, by the whole block, a word per thread and round.  VEC: n, the slices' distance and the pointers allow
+// 16-byte accesses.
 template <bool VEC>
 __device__ __forceinline__ void stage_logits(float *__restrict__ s_row, float *logits, int n, int n_parts, const float *parts,
                                              int64_t part_stride)
 {
-    typedef __attribute__((ext_vector_type(4))) float f32x4_t;
-    constexpr int W = VEC ? 4 : 1;
-    for (int i = threadIdx.x * W; i < n; i += blockDim.x * W) {
-        if constexpr (VEC) {
-            f32x4_t f = *reinterpret_cast<const f32x4_t *>(logits + i);
-            if (n_parts > 1) {  // uniform over the grid
-                f32x4_t g[kMaxLogitParts - 1];
-#pragma unroll
-                for (int sp = 1; sp < kMaxLogitParts; ++sp)
-                    g[sp - 1] = sp < n_parts ? *reinterpret_cast<const f32x4_t *>(parts + (sp - 1) * part_stride + i) : f32x4_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-                for (int sp = 1; sp < kMaxLogitParts; ++sp)
-                    if (sp < n_parts) f += g[sp - 1];
-                *reinterpret_cast<f32x4_t *>(logits + i) = f;
-            }
-            *reinterpret_cast<f32x4_t *>(s_row + i) = f;
-        } else {
-            float f = logits[i];
-            if (n_parts > 1) {
-                float g[kMaxLogitParts - 1];
-#pragma unroll
-                for (int sp = 1; sp < kMaxLogitParts; ++sp) g[sp - 1] = sp < n_parts ? parts[(sp - 1) * part_stride + i] : 0.f;
-#pragma unroll
-                for (int sp = 1; sp < kMaxLogitParts; ++sp)
-                    if (sp < n_parts) f += g[sp - 1];
-                logits[i] = f;
-            }
-            s_row[i] = f;
-        }
-    }
+    typedef std::conditional_t<VEC, f32x4_t, float> W;
+    constexpr int N = sizeof(W) / sizeof(float);
+    for (int i = threadIdx.x * N; i < n; i += blockDim.x * N)
+        *reinterpret_cast<W *>(s_row + i) = add_slices<W>(logits + i, n_parts, parts + i, part_stride);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -68,7 +59,7 @@ __device__ __forceinline__ void stage_logits(float *__restrict__ s_row, float *l
 // multiple of 4), so every lane has V/4 float4 loads in flight; slot i of the lane is expert
 // (i/4)*4G + 4*sub + i%4, still ascending with i.
 // One token per group of G lanes: token t, lane sub of the group, its logits at `row`.  s_idx (may be NULL): the selection goes
-// there too.  SLICES: the lane adds the slices of its words itself, as stage_logits does; parts: the token's.
+// there too.  SLICES: the lane adds the slices of its words itself; parts: the token's.
 template <int G, int V, bool VEC, bool SLICES = false>
 __device__ __forceinline__ void topk_token(int t, bool live, int sub, std::conditional_t<SLICES, float, const float> *row, int E, int k,
                                            int renorm, int32_t *__restrict__ idx, float *__restrict__ w, int *s_idx, int n_parts = 1,
@@ -82,33 +73,15 @@ __device__ __forceinline__ void topk_token(int t, bool live, int sub, std::condi
 #pragma unroll
         for (int q = 0; q < V / 4; ++q) {
             const int e0 = (q * G + sub) * 4;
-            float4 f = make_float4(NEG_INF, NEG_INF, NEG_INF, NEG_INF);
+            f32x4_t f = {NEG_INF, NEG_INF, NEG_INF, NEG_INF};
             if (live && e0 < E) {
-                f = *reinterpret_cast<const float4 *>(row + e0);
-                if constexpr (SLICES) {
-                    if (n_parts > 1) {  // uniform over the grid; all slices are requested before the first is added
-                        float4 g[kMaxLogitParts - 1];
-#pragma unroll
-                        for (int sp = 1; sp < kMaxLogitParts; ++sp)
-                            g[sp - 1] = sp < n_parts ? *reinterpret_cast<const float4 *>(parts + (sp - 1) * part_stride + e0)
-                                                     : make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-                        for (int sp = 1; sp < kMaxLogitParts; ++sp) {
-                            if (sp < n_parts) {
-                                f.x += g[sp - 1].x;
-                                f.y += g[sp - 1].y;
-                                f.z += g[sp - 1].z;
-                                f.w += g[sp - 1].w;
-                            }
-                        }
-                        *reinterpret_cast<float4 *>(row + e0) = f;
-                    }
-                }
+                if constexpr (SLICES)
+                    f = add_slices<f32x4_t>(row + e0, n_parts, parts + e0, part_stride);
+                else
+                    f = *reinterpret_cast<const f32x4_t *>(row + e0);
             }
-            v[(4 * q + 0) % V] = f.x;
-            v[(4 * q + 1) % V] = f.y;
-            v[(4 * q + 2) % V] = f.z;
-            v[(4 * q + 3) % V] = f.w;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[(4 * q + i) % V] = f[i];
         }
     } else {
 #pragma unroll
@@ -116,19 +89,10 @@ __device__ __forceinline__ void topk_token(int t, bool live, int sub, std::condi
             const int e = sub + i * G;
             v[i] = NEG_INF;
             if (live && e < E) {
-                float f = row[e];
-                if constexpr (SLICES) {
-                    if (n_parts > 1) {
-                        float g[kMaxLogitParts - 1];
-#pragma unroll
-                        for (int sp = 1; sp < kMaxLogitParts; ++sp) g[sp - 1] = sp < n_parts ? parts[(sp - 1) * part_stride + e] : 0.f;
-#pragma unroll
-                        for (int sp = 1; sp < kMaxLogitParts; ++sp)
-                            if (sp < n_parts) f += g[sp - 1];
-                        row[e] = f;
-                    }
-                }
-                v[i] = f;
+                if constexpr (SLICES)
+                    v[i] = add_slices<float>(row + e, n_parts, parts + e, part_stride);
+                else
+                    v[i] = row[e];
             }
         }
     }
