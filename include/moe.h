@@ -136,7 +136,7 @@ int32_t moe_capacity(int32_t T, int32_t E, int32_t k, double cf, int32_t convent
  *   topk_w[t,j] = gate weight of slot j (see moe_config_t.renormalize), fp32
  * x [T,D] elem, wg [E,D] elem, gate_bias [E] fp32 or NULL.  logits_out [T,E] fp32 may
  * be NULL only if `workspace` is given (kernels that need the logits in memory keep them
- * there; for bf16, E <= 128, D a multiple of 64 and more than 256 tokens the decision is
+ * there; for bf16, E <= 128, D of 64 and more, and more than 256 tokens the decision is
  * taken in the gate GEMM's epilogue and the logits are written only where logits_out asks
  * for them).  workspace may be NULL when logits_out is given.  T = 0 is a no-op. */
 int moe_gate_topk(moe_handle_t *h, const void *x, const void *wg, const float *gate_bias,

@@ -293,9 +293,9 @@ __global__ __launch_bounds__(WAVES * 64) void gate_topk_kernel(GateTopkParams p)
 // selection.  With one wave for 32 rows and all columns a K tile takes 1 us: 20 loads and 16 MFMAs of a wave, one after the other.
 // Here the column blocks have waves of their own (RG x NI waves of one 32x32 block), which share a K tile's loads; a wave reads a K
 // tile's fragments at once.  A logit is the same sum in the same order.  Then the logits cross LDS and G lanes share a token.
-// us, a wave per 32 rows / this, 2048 dimensions, 128 experts: 600 tokens 29.4 / 12.7, 4096 30.1 / 13.5, 9001 32.7 / 20.9, 16384 29.8 / 24.0,
-// 20000 40.8 / 31.1; 1024 dimensions, 64 experts: 8192 tokens 13.7 / 9.0; 96 experts, 5000 tokens 17.0 / 9.9; 512 dimensions, 64 experts, 16000
-// tokens 10.5 / 8.4; 2048 dimensions, 16 experts, 8000 tokens 14.0 / 12.0.
+// us, launches on the same inputs, a wave per 32 rows / this, 2048 dimensions, 128 experts: 512 tokens 29.9 / 11.9, 4096 30.0 / 12.5, 8192 30.3 / 13.8,
+// 12000 30.9 / 17.3, 16384 28.5 / 19.7, 20000 35.9 / 23.2; 1024 dimensions, 64 experts: 8192 tokens 12.9 / 8.5; 96 experts, 4096 tokens 17.1 / 9.5;
+// 512 dimensions, 64 experts, 16384 tokens 9.7 / 7.8; 2048 dimensions, 16 experts, 8192 tokens 12.9 / 10.7.
 template <int RG, int NI, int STAGES, bool RAGGED>
 __global__ __launch_bounds__(RG *NI * 64) void gate_topk_wide_kernel(GateTopkParams p)
 {
@@ -552,7 +552,7 @@ static int gate_topk_wide(int T, int E, int K, int num_cus)
     // tokens, 32 experts, 64 dimensions 4.8 / 5.6, 256 5.5 / 6.1, 512 6.5 / 6.7, 768 7.5 / 7.3; 16 experts, 256 dimensions 5.5 / 5.8, 512 6.5 /
     // 6.5; 12000 tokens, 32 experts, 64 dimensions 5.0 / 5.4, 256 5.8 / 5.9
     if (E <= 32 && K <= (T <= 32 * num_cus ? 512 : 256)) return 0;
-    // 128 rows: 20000 tokens, 2048 dimensions, 128 experts 40.8 / 31.1 us, 32768 tokens 38.1 / 39.5; 25000 tokens, 16 experts 14.0 / 13.8
+    // 128 rows: 20000 tokens, 2048 dimensions, 128 experts 35.9 / 23.2 us, 24576 36.6 / 25.8; with 64 experts and fewer they are no faster
     return T <= 32 * num_cus ? 1 : T <= 64 * num_cus ? 2 : T <= 96 * num_cus && E > 64 ? 4 : 0;
 }
 
@@ -588,7 +588,7 @@ int launch_gate_topk(const void *x, const void *wg, const float *gate_bias, int 
     p.renorm = renorm;
     const int ni = ceil_div(E, 32);
     const int waves = gate_topk_tile_tokens(T, E, K, num_cus) / 32;
-    // stages: more of them make the start longer and the loop no shorter (4096 tokens above, 4 / 8: 13.5 / 14.2 us; 64 rows, 3 / 6: 22.1 / 20.9)
+    // stages: more of them make the start longer and the loop no shorter (4096 tokens over 128 experts, 4 / 8: 13.5 / 14.2 us; 64 rows, 3 / 6: 22.1 / 20.9)
     if (const int rg = gate_topk_wide(T, E, K, num_cus)) {
         switch (rg * 10 + ni) {
         case 11: return launch_gate_topk_wide<1, 1, 9>(p, s);

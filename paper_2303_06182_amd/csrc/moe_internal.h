@@ -194,7 +194,7 @@ int launch_route_topk(float *logits, int T, int E, int k, int renorm, int32_t *i
                       const float *parts, int64_t part_stride, const RouteOut &o, bool *taken);
 
 // Gate GEMM with softmax / top-k and the per-tile expert histogram in its epilogue (gate_topk.hip); bf16, E <= 128,
-// K at least 64.  logits and hist may be NULL.  hist gets one row per gate_topk_tile_tokens() tokens.
+// K at least 64 and a multiple of 8 (16-byte loads).  logits and hist may be NULL.  hist gets one row per gate_topk_tile_tokens() tokens.
 bool gate_topk_fused_ok(int dtype, int T, int E, int K);
 int gate_topk_tile_tokens(int T, int E, int K, int num_cus);
 int launch_gate_topk(const void *x, const void *wg, const float *gate_bias, int T, int E, int K, int k, int renorm,
