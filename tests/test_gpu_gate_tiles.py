@@ -16,7 +16,10 @@ pytestmark = pytest.mark.gpu
     (257, 64, 1, 1, True, False), (300, 64, 32, 2, True, True), (289, 128, 33, 3, False, True), (1000, 320, 64, 8, True, False),
     (8192, 192, 65, 2, False, False), (500, 1024, 97, 2, True, True), (320, 576, 128, 8, False, True),
     (8193, 64, 7, 2, True, True), (8200, 192, 50, 1, False, False), (12001, 128, 96, 2, True, True), (16384, 320, 126, 2, False, True),
-    (16385, 64, 66, 2, True, True), (16500, 192, 100, 4, False, False), (24576, 128, 128, 2, True, True), (24577, 128, 128, 2, True, True)])
+    (16385, 64, 66, 2, True, True), (16500, 192, 100, 4, False, False), (24576, 128, 128, 2, True, True), (24577, 128, 128, 2, True, True),
+    # 32 experts and fewer: a wave per 32 rows up to 512 dimensions, 256 from 32 rows per CU on
+    (300, 512, 32, 2, True, True), (8192, 512, 31, 8, False, False), (300, 576, 32, 2, True, False), (8193, 256, 32, 2, False, True),
+    (8193, 320, 32, 2, True, True), (16384, 256, 5, 1, True, False), (16385, 256, 32, 2, True, True)])
 def test_gate(T, D, E, k, renorm, bias):
     print("gate", T, D, E, k, flush=True)
     g = torch.Generator(device="cuda").manual_seed(T + E)
@@ -46,7 +49,8 @@ def test_gate(T, D, E, k, renorm, bias):
 
 @pytest.mark.parametrize("T,D,E,k", [
     (257, 72, 24, 1), (300, 120, 47, 2), (3001, 1000, 24, 1), (1137, 1496, 47, 2), (8193, 328, 60, 2), (16385, 136, 66, 2),
-    (24577, 200, 128, 2), (24577, 392, 50, 3), (40001, 72, 128, 2), (66000, 104, 7, 2), (300, 2040, 128, 8)])
+    (24577, 200, 128, 2), (24577, 392, 50, 3), (40001, 72, 128, 2), (66000, 104, 7, 2), (300, 2040, 128, 8), (301, 504, 32, 2), (301, 520, 32, 2),
+    (9000, 264, 30, 2)])
 def test_k_ends_inside_a_tile(T, D, E, k):
     test_gate(T, D, E, k, T % 2 == 0, True)
 

@@ -15,7 +15,10 @@ pytestmark = pytest.mark.gpu
     (1, 2048, 128, 2), (16, 2048, 128, 2), (17, 1024, 128, 2), (64, 2048, 128, 4), (65, 2048, 128, 2), (64, 1024, 8, 8), (1, 128, 4, 1),
     (33, 2048, 512, 2), (32, 2048, 512, 4), (16, 2048, 1024, 8), (17, 1024, 1000, 2), (64, 512, 256, 2), (3, 64, 64, 2), (200, 2048, 512, 3),
     (1, 872, 7, 2), (64, 512, 7, 2), (64, 2048, 3, 3), (64, 512, 15, 2), (32, 1024, 31, 4), (33, 1024, 31, 4), (16, 2048, 63, 2),
-    (17, 2048, 63, 2), (16, 512, 127, 8), (5, 128, 33, 1), (9, 1024, 250, 2), (100, 1024, 50, 2), (4, 512, 255, 2)])
+    (17, 2048, 63, 2), (16, 512, 127, 8), (5, 128, 33, 1), (9, 1024, 250, 2), (100, 1024, 50, 2), (4, 512, 255, 2),
+    # slices added by the lanes and by all threads, batches of more than a block
+    (65, 512, 8, 2), (256, 1024, 32, 4), (200, 1024, 64, 2), (201, 2048, 64, 2), (130, 512, 96, 2), (2, 1024, 250, 2), (3, 1024, 250, 2),
+    (129, 512, 127, 2), (129, 2048, 127, 2), (66, 1024, 510, 8)])
 def test_decoder_step(T, D, E, k):
     print("route_topk", T, D, E, k, flush=True)
     g = torch.Generator(device="cuda").manual_seed(T * 1000 + E)
